@@ -123,7 +123,9 @@ int odp_digest_buffers(const void* const* ptrs, const uint64_t* sizes, size_t n,
 int odp_digest_buffers_noalloc(const void* const* ptrs, const uint64_t* sizes, size_t n, uint64_t* out,
                                odp_stream_t stream);
 
-/* Per-buffer digest: the plain form, one kernel launch per buffer.
+/* Digest from host descriptors: the plain form. A workgroup per 256 KiB of each
+ * buffer, without a work plan; consecutive buffers of a call share a launch (up
+ * to 128 of at most 1 GiB each), a call over one buffer is one launch.
  *   host_ptrs   HOST, n entries: device start address of buffer i.
  *   host_sizes  HOST, n entries: byte length of buffer i.
  *   out         DEVICE, n entries: receives D64(buffer i).

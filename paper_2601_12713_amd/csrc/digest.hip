@@ -6,7 +6,7 @@
 // coalesced 128-bit nontemporal loads, and leaf digests are combined into
 // level-1 node digests (64 leaves, 256 KiB) inside the workgroup or wavefront.
 //
-// Plain form (one launch per buffer): one workgroup per level-1 node; the
+// Plain form (host descriptors, up to 128 buffers a launch): one workgroup per level-1 node; the
 // upper levels are finished by whichever workgroup completes the last level-1
 // node (one atomic ticket per buffer up to 1 GiB, one per node above that).
 //
@@ -588,11 +588,12 @@ __device__ __forceinline__ void run_node(Smem<kSlabOne>& sm, const uint8_t* buf,
 }
 
 // ---------------------------------------------------------------------------
-// Plain form: one launch per buffer, one workgroup per level-1 node.
+// Plain form: one workgroup per level-1 node (or per buffer of at most one
+// leaf), one launch per buffer or per group of buffers.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void digest_one_kernel(const uint8_t* p, uint64_t size, uint64_t* out,
-                                                             uint64_t* tree, uint32_t* tk) {
-  __shared__ Smem<kSlabOne> sm;
+// Workgroup `node` of one buffer.
+__device__ __forceinline__ void digest_block(Smem<kSlabOne>& sm, const uint8_t* p, uint64_t size, uint64_t node,
+                                             uint64_t* out, uint64_t* tree, uint32_t* tk) {
   if (size <= kLeaf) {
     const int t = threadIdx.x;
     if ((reinterpret_cast<uintptr_t>(p) & 15) == 0) {
@@ -616,7 +617,44 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     }
     return;
   }
-  run_node(sm, p, size, blockIdx.x, out, tree, tk);
+  run_node(sm, p, size, node, out, tree, tk);
+}
+
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void digest_one_kernel(const uint8_t* p, uint64_t size, uint64_t* out,
+                                                             uint64_t* tree, uint32_t* tk) {
+  __shared__ Smem<kSlabOne> sm;
+  digest_block(sm, p, size, blockIdx.x, out, tree, tk);
+}
+
+// Up to kManyMax buffers of at most kOneTicketNodes level-1 nodes each in one
+// launch, their descriptors in the kernel arguments (nothing is staged, and a
+// captured launch keeps its own copy). A launch of one small buffer is bound
+// by latency (about 10 us for 64 KiB, one workgroup on 256 CUs) and launches
+// of one stream run one after another, so the buffers of a call share one:
+// 64 buffers of 4-256 KiB took 648 us as 64 launches and take 15 us as one.
+// The kernel arguments may hold 4 KiB; 128 descriptors take 2.5 KiB.
+// Each workgroup finds its buffer from the first workgroups of all buffers,
+// two per lane and one ballot each; a buffer's tree slots are numbered like
+// its workgroups, and it has a ticket of its own.
+constexpr uint32_t kManyMax = 128;
+struct ManyArgs {
+  const uint8_t* ptr[kManyMax];
+  uint64_t size[kManyMax];
+  uint32_t first[kManyMax];  // first workgroup of each buffer; kManyEnd past the last buffer
+  uint64_t* out;
+  uint64_t* tree;
+  uint32_t* tk;
+};
+constexpr uint32_t kManyEnd = 0xFFFFFFFFu;
+static_assert(kManyMax == 128 && sizeof(ManyArgs) <= 4096, "two descriptors per lane; kernel argument limit");
+
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void digest_many_kernel(ManyArgs A) {
+  __shared__ Smem<kSlabOne> sm;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t f0 = A.first[lane], f1 = A.first[lane + 64];
+  const uint32_t b = uniform((uint32_t)(__popcll(__ballot(f0 <= blockIdx.x)) + __popcll(__ballot(f1 <= blockIdx.x)) - 1));
+  const uint32_t first = A.first[b];
+  digest_block(sm, A.ptr[b], A.size[b], blockIdx.x - first, A.out + b, A.tree + first, A.tk + b);
 }
 
 // ---------------------------------------------------------------------------
@@ -1270,10 +1308,13 @@ extern "C" int odp_digest_buffers(const void* const* ptrs, const uint64_t* sizes
 }
 
 namespace odp {
-// Tree and ticket slots of the per-buffer form (grow-only; tickets zeroed).
+// Tree and ticket slots of the per-buffer form (grow-only; tickets zeroed). At
+// least kPlainSlots tree slots, one per workgroup of a launch over several
+// buffers: 4 GiB of data, far past the point where a longer launch gains.
+constexpr uint64_t kPlainSlots = 16384;
 int plain_reserve_slots(Workspace* ws, uint64_t need_tree, uint64_t need_tk) {
   if (need_tree <= ws->p_cap_tree && need_tk <= ws->p_cap_tk && ws->p_tickets.ptr) return ODP_OK;
-  const uint64_t tr = std::max<uint64_t>(need_tree, 1024), tk = std::max<uint64_t>(need_tk, 256);
+  const uint64_t tr = std::max<uint64_t>(need_tree, kPlainSlots), tk = std::max<uint64_t>(need_tk, 256);
   int e;
   if ((e = ws->p_tree.ensure(tr * 8)) || (e = ws->p_tickets.ensure(tk * 4))) return e;
   ODP_HIP(hipMemset(ws->p_tickets.ptr, 0, tk * 4));
@@ -1285,7 +1326,7 @@ int plain_reserve_slots(Workspace* ws, uint64_t need_tree, uint64_t need_tk) {
 uint64_t digest_plain_workspace_bytes(uint64_t max_bytes) {
   uint64_t tr = 0, tk = 0;
   if (max_bytes > kLeaf) tree_need(ceil_div(ceil_div(max_bytes, kLeaf), kFanIn), tr, tk);
-  return std::max<uint64_t>(tr, 1024) * 8 + std::max<uint64_t>(tk, 256) * 4;
+  return std::max<uint64_t>(tr, kPlainSlots) * 8 + std::max<uint64_t>(tk, 256) * 4;
 }
 
 int digest_plain_reserve(Workspace* ws, uint64_t max_bytes) {
@@ -1460,11 +1501,39 @@ extern "C" int odp_digest_buffers_plain(const void* const* host_ptrs, const uint
   }
   uint64_t* tree = static_cast<uint64_t*>(ws->p_tree.ptr);
   uint32_t* tk = static_cast<uint32_t*>(ws->p_tickets.ptr);
-  for (size_t i = 0; i < n; ++i) {
+  auto nodes = [&](size_t i) {
     const uint64_t s = host_sizes[i];
-    const unsigned grid = s <= kLeaf ? 1u : (unsigned)ceil_div(ceil_div(s, kLeaf), kFanIn);
-    hipLaunchKernelGGL(digest_one_kernel, dim3(grid), dim3(kThreads), 0, stream,
-                       static_cast<const uint8_t*>(host_ptrs[i]), s, out + i, tree, tk);
+    return s <= kLeaf ? uint64_t(1) : ceil_div(ceil_div(s, kLeaf), kFanIn);
+  };
+  // Consecutive buffers share a launch while their descriptors fit its
+  // arguments and their workgroups the tree slots; a buffer above 1 GiB (whose
+  // levels take tickets of their own) and a buffer alone take the one-buffer
+  // kernel, which has no descriptor to look up.
+  for (size_t i = 0; i < n;) {
+    ManyArgs A;
+    uint32_t k = 0;
+    uint64_t blocks = 0;
+    while (i + k < n && k < kManyMax) {
+      const uint64_t nk = nodes(i + k);
+      if (nk > kOneTicketNodes || blocks + nk > ws->p_cap_tree) break;
+      A.ptr[k] = static_cast<const uint8_t*>(host_ptrs[i + k]);
+      A.size[k] = host_sizes[i + k];
+      A.first[k] = (uint32_t)blocks;
+      blocks += nk;
+      ++k;
+    }
+    if (k <= 1) {
+      hipLaunchKernelGGL(digest_one_kernel, dim3((unsigned)nodes(i)), dim3(kThreads), 0, stream,
+                         static_cast<const uint8_t*>(host_ptrs[i]), host_sizes[i], out + i, tree, tk);
+      ++i;
+      continue;
+    }
+    for (uint32_t q = k; q < kManyMax; ++q) A.first[q] = kManyEnd;
+    A.out = out + i;
+    A.tree = tree;
+    A.tk = tk;
+    hipLaunchKernelGGL(digest_many_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, A);
+    i += k;
   }
-  return check_hip(hipGetLastError(), "digest_one launch");
+  return check_hip(hipGetLastError(), "digest launch");
 }

@@ -131,7 +131,7 @@ def digest_buffers_noalloc(ptrs, sizes, out, stream=None):
 
 
 def digest_buffers_plain(host_ptrs, host_sizes, out, stream=None):
-    """Per-buffer launches. host_ptrs, host_sizes: sequences of ints (device addresses, bytes)."""
+    """Digest from host descriptors (up to 128 buffers a launch). host_ptrs, host_sizes: sequences of ints (device addresses, bytes)."""
     n = len(host_sizes)
     hp = np.ascontiguousarray(np.asarray(host_ptrs, dtype=np.uint64))
     hs = np.ascontiguousarray(np.asarray(host_sizes, dtype=np.uint64))
