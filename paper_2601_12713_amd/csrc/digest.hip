@@ -76,7 +76,12 @@ __host__ __device__ inline void tree_need(uint64_t n1, uint64_t& tree_slots, uin
   }
 }
 
-typedef __attribute__((address_space(1))) const u32x4 gu32x4;
+// A 128-bit global or buffer load needs a 4-byte aligned address only.
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+typedef __attribute__((address_space(1))) const u32x4_a4 gu32x4;
+
+__device__ __forceinline__ bool aligned16(const uint8_t* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+__device__ __forceinline__ bool aligned4(const uint8_t* p) { return (reinterpret_cast<uintptr_t>(p) & 3) == 0; }
 
 __device__ __forceinline__ u32x4 ld_global_nt(const uint8_t* p) {
   return __builtin_nontemporal_load(reinterpret_cast<gu32x4*>(reinterpret_cast<uintptr_t>(p)));
@@ -117,7 +122,10 @@ __device__ __forceinline__ uint64_t finish_row(uint64_t acc, const RowDesc& hrow
 }
 
 // Fast path as one stage of a wavefront's continuous stream of items: 16
-// whole, 16-byte aligned leaves at leaf_base + r*4096 (leaf_base wave-uniform).
+// whole leaves at leaf_base + r*4096 (leaf_base wave-uniform, 4-byte aligned:
+// every load lies inside the leaves, so no more is asked of the address than
+// the instruction does, and sections of arrays of 4- and 8-byte elements take
+// this path too).
 // Each step stages 64*NL bytes of every leaf (512 bytes, 8 KiB per wavefront,
 // in the per-buffer kernel; 256 in the batched one) through the wavefront's
 // LDS slab with NL 128-bit nontemporal loads per lane; load k
@@ -137,15 +145,28 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_rsrc(const uint8_t* base)
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), (short)0, -1, 0x00020000);
 }
 
+// Loads of one step. Leaves that start on a 128-byte line are streamed past the
+// caches: no step touches another's lines. Otherwise the last line of each
+// row's step is the first of its next one, and streamed it is fetched from
+// memory twice (1.5 times the bytes with 256-byte steps), so these loads go
+// through the L2. 2,000 sections of fp64 arrays (2.2 GB): 521 us streamed, 437
+// cached; the same buffers on line boundaries: 412 streamed, 444 cached. (Only
+// the second 128 bytes of the step cached: 449.)
 template <int NL>
 __device__ __forceinline__ void fast_load(u32x4 (&R)[NL], const uint8_t* base, uint32_t step_off) {
+  constexpr int kStream = 2;  // nontemporal
   const int lane = threadIdx.x & 63;
   const __amdgpu_buffer_rsrc_t rs = wave_rsrc(base);
   const uint32_t o = (uint32_t)(lane >> 3) * kLeaf + (uint32_t)(lane & 7) * 16;
+  auto voff = [&](int k) { return (int)(o + (uint32_t)(8 * (k & 1)) * kLeaf + (uint32_t)(k >> 1) * 128); };
+  if ((reinterpret_cast<uintptr_t>(base) & 127) == 0) {
 #pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const uint32_t vo = o + (uint32_t)(8 * (k & 1)) * kLeaf + (uint32_t)(k >> 1) * 128;
-    R[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vo, (int)step_off, 2 /* nt */));
+    for (int k = 0; k < NL; ++k)
+      R[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff(k), (int)step_off, kStream));
+  } else {
+#pragma unroll
+    for (int k = 0; k < NL; ++k)
+      R[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff(k), (int)step_off, 0));
   }
 }
 
@@ -209,10 +230,10 @@ __device__ __forceinline__ uint64_t hash_wave_leaves_pipe(const uint8_t* leaf_ba
 }
 
 // General path: 16 rows of any length (<= 4096) and presence. When every
-// present row is 16-byte aligned, rows are staged through LDS like the fast
+// present row is 4-byte aligned, rows are staged through LDS like the fast
 // path (same lane mapping, two steps in flight) with loads predicated on each
-// row's length; a 16-byte load that crosses a row's end stays inside the
-// row's last 16-byte granule, so inside the same page. Otherwise every lane
+// row's length: a 16-byte load that would cross the row's end is left out, as
+// no whole 32-byte stripe has bytes in it. Otherwise every lane
 // reads its words straight from memory at any alignment, eight stripes per
 // batch of independent loads. Returns the row digest in lane 4r.
 // A 16-byte granule that row loads past a row's end read instead.
@@ -221,8 +242,8 @@ __device__ __align__(16) uint8_t g_no_row[16];
 // In the per-buffer kernel every lane issues every load of the step, without
 // a branch: a load under a branch makes the compiler wait for all loads in
 // flight at the next stage, which serialised the two steps kept in flight (a
-// partial node of 2-16 leaves took 9.8 us per launch). An offset at or past
-// the row's end (or an absent row) reads g_no_row instead; those bytes are
+// partial node of 2-16 leaves took 9.8 us per launch). A load that would pass
+// the row's end (or of an absent row) reads g_no_row instead; those bytes are
 // staged but never folded. The batched kernel keeps predicated loads: the
 // address selects cost it a register spill.
 template <int kSlab>
@@ -234,9 +255,9 @@ __device__ __forceinline__ void rows_load(u32x4 (&R)[kSlab / 64], const RowDesc&
     const RowDesc& d = (k & 1) ? rb : ra;
     const uint32_t o = step_off + (uint32_t)(k >> 1) * 128 + lc;
     if constexpr (kSlab == kSlabOne) {
-      R[k] = ld_global_nt(o < d.len ? d.base + o : g_no_row);
+      R[k] = ld_global_nt(o + 16 <= d.len ? d.base + o : g_no_row);
     } else {
-      if (o < d.len) R[k] = ld_global_nt(d.base + o);
+      if (o + 16 <= d.len) R[k] = ld_global_nt(d.base + o);
     }
   }
 }
@@ -287,7 +308,7 @@ __device__ __forceinline__ uint64_t hash_wave_rows(const RowDesc* rows, uint8_t*
   constexpr int kStride = kSlab + kPad;
   const int lane = threadIdx.x & 63;
   const RowDesc mine = rows[lane & 15];
-  const bool aligned = !mine.present || ((reinterpret_cast<uintptr_t>(mine.base) & 15) == 0);
+  const bool aligned = !mine.present || aligned4(mine.base);
   const bool all_aligned = __all(aligned);
   uint32_t mlen = mine.present ? mine.len : 0u;
 #pragma unroll
@@ -522,14 +543,13 @@ __device__ __forceinline__ void run_node(Smem<kSlabOne>& sm, const uint8_t* buf,
   const uint32_t nl = (uint32_t)min<uint64_t>(kFanIn, nleaves - first);
   // leaves [first + 16w, first + 16w + 16) belong to this wavefront
   const uint64_t wfirst = first + (uint64_t)w * kRowsPerWave;
-  const bool wave_full = ((reinterpret_cast<uintptr_t>(buf) & 15) == 0) &&
-                         (wfirst + kRowsPerWave) * kLeaf <= size;
+  const bool wave_full = aligned4(buf) && (wfirst + kRowsPerWave) * kLeaf <= size;
   // The buffer's last leaf, when shorter than a leaf (and the buffer 16-byte
   // aligned), is hashed on its own by hash_one_leaf, so that every row the
   // wavefronts fold is a whole leaf and folds without per-round predicates:
   // wavefront 3 takes it when it holds no leaves of this node, else the
   // wavefront that owns it, after its rows.
-  const bool has_short = ((reinterpret_cast<uintptr_t>(buf) & 15) == 0) && (size % kLeaf) != 0 && node == n1 - 1;
+  const bool has_short = aligned16(buf) && (size % kLeaf) != 0 && node == n1 - 1;
   const uint32_t short_row = (uint32_t)(nleaves - 1 - first);  // its index in the node
   const int short_wave = !has_short ? -1 : nl <= 3 * kRowsPerWave ? 3 : (int)(short_row / kRowsPerWave);
   uint64_t h;
@@ -596,7 +616,7 @@ __device__ __forceinline__ void digest_block(Smem<kSlabOne>& sm, const uint8_t* 
                                              uint64_t* out, uint64_t* tree, uint32_t* tk) {
   if (size <= kLeaf) {
     const int t = threadIdx.x;
-    if ((reinterpret_cast<uintptr_t>(p) & 15) == 0) {
+    if (aligned16(p)) {
       if (t < 64) {
         const uint64_t h = hash_one_leaf(p, (uint32_t)size, sm.slab[0]);
         if (t == 0) *out = h;
@@ -884,8 +904,6 @@ struct BatchArgs {
   uint32_t chunk;    // items per claim
 };
 
-__device__ __forceinline__ bool aligned16(const uint8_t* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
 // The work record of queue item `item` (node items only; zeros otherwise).
 __device__ __forceinline__ NodeRec load_rec(const BatchArgs& A, uint32_t item, uint64_t n_node) {
   NodeRec r;
@@ -897,11 +915,11 @@ __device__ __forceinline__ NodeRec load_rec(const BatchArgs& A, uint32_t item, u
   return r;
 }
 
-// First leaf of wavefront w's rows in a node when they are 16 whole, 16-byte
+// First leaf of wavefront w's rows in a node when they are 16 whole, 4-byte
 // aligned leaves (the fast path), else null.
 __device__ __forceinline__ const uint8_t* fast_rows(const uint8_t* base, uint32_t len, int w) {
   const uint32_t end = (uint32_t)(w + 1) * kRowsPerWave * kLeaf;
-  return aligned16(base) && end <= len ? base + (uint32_t)w * kRowsPerWave * kLeaf : nullptr;
+  return aligned4(base) && end <= len ? base + (uint32_t)w * kRowsPerWave * kLeaf : nullptr;
 }
 
 // Persistent batched digest. Workgroups take the items in chunks of

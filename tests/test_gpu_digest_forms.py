@@ -57,3 +57,22 @@ def test_host_descriptors_captured(odp):
         g.replay()
         torch.cuda.synchronize()
         assert out.cpu().numpy().view(np.uint64).tolist() == want
+
+
+@pytest.mark.parametrize("shift", [1, 2, 3, 4, 6, 8, 12, 15])
+def test_array_sections(odp, shift):
+    """Buffers that start inside an allocation: 4-byte aligned ones are staged
+    like whole allocations, the rest word by word; every path edge in each form."""
+    rng = np.random.default_rng(shift)
+    host, dev, ptrs = host_views(rng, EDGES, [shift] * len(EDGES))
+    want = [oracle.d64(h) for h in host]
+    n = len(EDGES)
+    out = torch.full((n,), -1, dtype=torch.int64, device="cuda")
+    dp = torch.tensor(np.array(ptrs, dtype=np.uint64).view(np.int64), device="cuda")
+    ds = torch.tensor(np.array(EDGES, dtype=np.int64), device="cuda")
+    for form in (lambda: odp.digest_buffers(dp, ds, out), lambda: odp.digest_buffers_noalloc(dp, ds, out),
+                 lambda: odp.digest_buffers_plain(ptrs, EDGES, out),
+                 lambda: [odp.digest_buffers_plain(ptrs[i:i + 1], EDGES[i:i + 1], out[i:]) for i in range(n)]):
+        out.fill_(-1)
+        form()
+        assert out.cpu().numpy().view(np.uint64).tolist() == want
