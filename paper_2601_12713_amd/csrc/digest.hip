@@ -1326,13 +1326,15 @@ extern "C" int odp_digest_buffers(const void* const* ptrs, const uint64_t* sizes
 }
 
 namespace odp {
-// Tree and ticket slots of the per-buffer form (grow-only; tickets zeroed). At
-// least kPlainSlots tree slots, one per workgroup of a launch over several
-// buffers: 4 GiB of data, far past the point where a longer launch gains.
-constexpr uint64_t kPlainSlots = 16384;
+// Tree and ticket slots of the per-buffer form (grow-only; tickets zeroed). A
+// caller's first call takes kPlainSlots tree slots, one per workgroup of a
+// launch over several buffers: 4 GiB of data, far past the point where a
+// longer launch gains. A server's streams keep to the slots its budget counts
+// (launches over several buffers are cut to what there is).
+constexpr uint64_t kPlainSlots = 16384, kPlainMinSlots = 1024;
 int plain_reserve_slots(Workspace* ws, uint64_t need_tree, uint64_t need_tk) {
   if (need_tree <= ws->p_cap_tree && need_tk <= ws->p_cap_tk && ws->p_tickets.ptr) return ODP_OK;
-  const uint64_t tr = std::max<uint64_t>(need_tree, kPlainSlots), tk = std::max<uint64_t>(need_tk, 256);
+  const uint64_t tr = std::max<uint64_t>(need_tree, kPlainMinSlots), tk = std::max<uint64_t>(need_tk, 256);
   int e;
   if ((e = ws->p_tree.ensure(tr * 8)) || (e = ws->p_tickets.ensure(tk * 4))) return e;
   ODP_HIP(hipMemset(ws->p_tickets.ptr, 0, tk * 4));
@@ -1344,7 +1346,7 @@ int plain_reserve_slots(Workspace* ws, uint64_t need_tree, uint64_t need_tk) {
 uint64_t digest_plain_workspace_bytes(uint64_t max_bytes) {
   uint64_t tr = 0, tk = 0;
   if (max_bytes > kLeaf) tree_need(ceil_div(ceil_div(max_bytes, kLeaf), kFanIn), tr, tk);
-  return std::max<uint64_t>(tr, kPlainSlots) * 8 + std::max<uint64_t>(tk, 256) * 4;
+  return std::max<uint64_t>(tr, kPlainMinSlots) * 8 + std::max<uint64_t>(tk, 256) * 4;
 }
 
 int digest_plain_reserve(Workspace* ws, uint64_t max_bytes) {
@@ -1514,7 +1516,7 @@ extern "C" int odp_digest_buffers_plain(const void* const* host_ptrs, const uint
   if (!ws) return err;
   if (need_tree > ws->p_cap_tree || need_tk > ws->p_cap_tk || !ws->p_tickets.ptr) {
     ODP_HIP(hipStreamSynchronize(stream));
-    int e = plain_reserve_slots(ws, need_tree, need_tk);
+    int e = plain_reserve_slots(ws, std::max(need_tree, kPlainSlots), need_tk);
     if (e) return e;
   }
   uint64_t* tree = static_cast<uint64_t*>(ws->p_tree.ptr);
