@@ -105,17 +105,27 @@ __device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* p) {
 }
 
 // Finishes the XXH64 of one row from its four lane accumulators; the result
-// is valid in lane 4r (accumulator 0) of row r.
+// is valid in lane 4r (accumulator 0) of row r. The remainder past the last
+// whole stripe (up to 31 bytes) is read as one word per lane, all four at once:
+// read byte by byte between the serial steps, each step of a ragged row waited
+// for its own memory round trip (20,000 ragged buffers, 8e9 bytes: 1,252 ->
+// 1,243 us; 4,096 of 1 B-16 KiB: 48.8 -> 48.2 us).
 __device__ __forceinline__ uint64_t finish_row(uint64_t acc, const RowDesc& hrow) {
   const int a = threadIdx.x & 3;
+  const uint32_t nstripes = hrow.present ? hrow.len >> 5 : 0u;
+  const uint32_t rem = hrow.present ? hrow.len & 31 : 0u;
+  uint64_t x = 0, x0 = 0, x1 = 0, x2 = 0, x3 = 0;
+  if (rem) {
+    if (rem > (uint32_t)a * 8) x = load64_part(hrow.base + nstripes * 32 + a * 8, rem - a * 8);
+    xx_gather4(x, x0, x1, x2, x3);
+  }
   uint64_t v1, v2, v3, v4;
   xx_gather4(acc, v1, v2, v3, v4);
   uint64_t h = 0;
   if (a == 0 && hrow.present) {
-    const uint32_t nstripes = hrow.len >> 5;
     h = nstripes ? xx_converge(v1, v2, v3, v4) : kP5;
     h += hrow.len;
-    h = xx_tail_bytes(h, hrow.base + nstripes * 32, hrow.len - nstripes * 32);
+    if (rem) h = xx_tail_words(h, x0, x1, x2, x3, rem);
     h = xx_avalanche(h);
   }
   return h;

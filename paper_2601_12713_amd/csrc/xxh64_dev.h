@@ -76,29 +76,31 @@ __device__ __forceinline__ uint64_t load64_any(const uint8_t* p) {
   return (lo >> sh) | (hi << (64 - sh));
 }
 
-// The remainder steps over rem (< 32) bytes at p (any alignment, byte reads).
-__device__ __forceinline__ uint64_t xx_tail_bytes(uint64_t h, const uint8_t* p, uint32_t rem) {
-  while (rem >= 8) {
-    uint64_t w = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) w |= uint64_t(p[i]) << (8 * i);
-    h = xx_step8(h, w);
-    p += 8;
-    rem -= 8;
+// Little-endian first min(avail, 8) bytes at p (any address, avail > 0); the
+// bytes above them are undefined. Only 8-byte granules that hold some of
+// [p, p + avail) are read.
+__device__ __forceinline__ uint64_t load64_part(const uint8_t* p, uint32_t avail) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+  const uint64_t* q = reinterpret_cast<const uint64_t*>(a & ~uintptr_t(7));
+  const uint32_t o = uint32_t(a & 7);
+  uint64_t v = q[0] >> (8 * o);
+  if (o + (avail < 8 ? avail : 8) > 8) v |= q[1] << (64 - 8 * o);  // o > 0 here
+  return v;
+}
+
+// The remainder steps over the rem (1..31) bytes held in four words.
+__device__ __forceinline__ uint64_t xx_tail_words(uint64_t h, uint64_t x0, uint64_t x1, uint64_t x2, uint64_t x3,
+                                                  uint32_t rem) {
+  const uint32_t n8 = rem >> 3;
+  if (n8 > 0) h = xx_step8(h, x0);
+  if (n8 > 1) h = xx_step8(h, x1);
+  if (n8 > 2) h = xx_step8(h, x2);
+  uint64_t x = n8 == 0 ? x0 : n8 == 1 ? x1 : n8 == 2 ? x2 : x3;
+  if (rem & 4) {
+    h = xx_step4(h, (uint32_t)x);
+    x >>= 32;
   }
-  if (rem >= 4) {
-    uint32_t w = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w |= uint32_t(p[i]) << (8 * i);
-    h = xx_step4(h, w);
-    p += 4;
-    rem -= 4;
-  }
-  while (rem > 0) {
-    h = xx_step1(h, *p);
-    ++p;
-    --rem;
-  }
+  for (uint32_t r = rem & 3; r > 0; --r, x >>= 8) h = xx_step1(h, (uint8_t)x);
   return h;
 }
 
