@@ -76,3 +76,31 @@ def test_array_sections(odp, shift):
         out.fill_(-1)
         form()
         assert out.cpu().numpy().view(np.uint64).tolist() == want
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 8191, 8192, 8193])
+@pytest.mark.parametrize("split", [0, 65536])
+def test_plan_sizes(odp, n, split):
+    """Both sides of the one-launch plan's limits, with and without medium
+    nodes; calls with new arguments launch directly, repeats replay a graph."""
+    keep = odp.get_tuning()
+    odp.set_tuning(split_bytes=split)
+    try:
+        calls = []
+        for seed in (n, n + 1):
+            rng = np.random.default_rng(seed)
+            sizes = rng.integers(0, 6000, size=n)
+            some = rng.choice(n, size=min(n, 40), replace=False)
+            sizes[some] = [EDGES[i % len(EDGES)] for i in range(some.size)]
+            host, dev, ptrs = host_views(rng, [int(s) for s in sizes], [0] * n)
+            dp = torch.tensor(np.array(ptrs, dtype=np.uint64).view(np.int64), device="cuda")
+            ds = torch.tensor(sizes.astype(np.int64), device="cuda")
+            calls.append((dp, ds, torch.empty(n, dtype=torch.int64, device="cuda"), oracle.d64_many(host), dev))
+        for k in (0, 1, 0, 0, 0, 1, 1):
+            dp, ds, out, want, _ = calls[k]
+            out.fill_(-1)
+            odp.digest_buffers(dp, ds, out)
+            assert (out.cpu().numpy().view(np.uint64) == want).all()
+        assert odp.device_status() == odp.ODP_OK
+    finally:
+        odp.set_tuning(**keep)
