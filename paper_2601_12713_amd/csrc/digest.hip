@@ -708,6 +708,7 @@ struct PlanArgs {
   DigestCtl* ctl;
   uint64_t cap_items, cap_tree, cap_tk;
   uint64_t cap_nodes;   // level-1 nodes of buffers above one leaf, at most (the fixed array's limit)
+  uint32_t grid;        // workgroups of the last launch (the tree's)
 };
 
 constexpr int kPlanThreads = 256;
@@ -805,6 +806,14 @@ __device__ void finalize_plan(const PlanArgs& A, const uint64_t carry[kQ]) {
   c->tk_total = carry[3];
   c->head = 0;
   c->overflow = plan_overflow(A, carry) ? 1u : 0u;
+  // When every item can have a workgroup of its own, nothing is claimed and
+  // nothing is carried from item to item: the digest kernel then hashes each
+  // node like the per-buffer kernel (more loads in flight, levels above done
+  // by the last node's workgroup). Small buffers then go one per wavefront if
+  // there are workgroups enough, else 64 per workgroup.
+  c->few = carry[4] || c->overflow ? 0u
+           : carry[0] + ceil_div(carry[1], kWaves) <= A.grid ? (uint32_t)kWaves
+           : carry[0] + ceil_div(carry[1], kRows) <= A.grid  ? (uint32_t)kRows : 0u;
 }
 
 __global__ __launch_bounds__(kPlanThreads) void plan_count_kernel(PlanArgs A) {
@@ -1052,6 +1061,7 @@ __device__ __forceinline__ const uint8_t* fast_rows(const uint8_t* base, uint32_
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void digest_batched_kernel(BatchArgs A) {
   __shared__ Smem<kSlabBatch> sm;
   const DigestCtl* c = A.ctl;
+  if (c->few) return;
   if (c->overflow) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < A.n; i += (uint64_t)gridDim.x * blockDim.x)
       A.out[i] = 0;
@@ -1166,12 +1176,66 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   }
 }
 
+// A plan with at most one item per workgroup (DigestCtl::few rows per group of
+// small buffers): level-1 nodes as in the per-buffer kernel, upper levels
+// included. It runs in the tree kernel's launch, which such a plan leaves idle:
+// inside the persistent kernel its registers pushed that one's loop into 40
+// bytes of spills (20,000 buffers, 8e9 bytes: 1,230 -> 1,243 us).
+__device__ __forceinline__ void run_few(const BatchArgs& A, Smem<kSlabOne>& sm, uint32_t few, uint64_t n_node, uint64_t n_small) {
+  const int t = threadIdx.x, w = uniform(t >> 6), lane = t & 63;
+  const uint32_t item = blockIdx.x;
+  if (item < n_node) {
+    const uint32_t i = uniform(A.rec[item].buf);
+    run_node(sm, static_cast<const uint8_t*>(A.ptrs[i]), A.sizes[i], item - A.node_off[i], A.out + i,
+             A.tree + A.tree_off[i], A.tickets + A.tk_off[i]);
+    return;
+  }
+  const uint64_t q0 = (item - n_node) * few;
+  if (few == kWaves) {
+    const uint64_t q = q0 + w;
+    if (q >= n_small) return;
+    const uint32_t i = uniform(A.small_list[q]);
+    const uint8_t* p = static_cast<const uint8_t*>(A.ptrs[i]);
+    const uint32_t len = (uint32_t)A.sizes[i];
+    uint64_t h;
+    if (aligned16(p)) {
+      h = hash_one_leaf(p, len, sm.slab[w]);
+    } else {
+      RowDesc* rows = sm.rows + w * kRowsPerWave;
+      if (lane < kRowsPerWave) rows[lane] = lane == 0 ? RowDesc{p, len, 1u} : RowDesc{p, 0u, 0u};
+      wave_fence();
+      h = hash_wave_rows<kSlabOne>(rows, sm.slab[w]);
+    }
+    if (lane == 0) A.out[i] = h;
+    return;
+  }
+  RowDesc* rows = sm.rows + w * kRowsPerWave;
+  uint32_t* outidx = sm.outidx + w * kRowsPerWave;
+  if (lane < kRowsPerWave) {
+    const uint64_t q = q0 + w * kRowsPerWave + lane;
+    const bool present = q < n_small;
+    const uint32_t i = present ? A.small_list[q] : 0u;
+    rows[lane] = RowDesc{present ? static_cast<const uint8_t*>(A.ptrs[i]) : nullptr, present ? (uint32_t)A.sizes[i] : 0u,
+                         (uint32_t)present};
+    outidx[lane] = i;
+  }
+  wave_fence();
+  const uint64_t h = hash_wave_rows<kSlabOne>(rows, sm.slab[w]);
+  if ((lane & 3) == 0 && rows[lane >> 2].present) A.out[outidx[lane >> 2]] = h;
+}
+
 // Levels 2 and up of every buffer with more than one level-1 node: one
 // wavefront per level-2 node hashes its (up to 64) level-1 digests, then
-// climbs with tickets like the per-buffer form.
-__global__ __launch_bounds__(kThreads) void digest_tree_kernel(BatchArgs A) {
+// climbs with tickets like the per-buffer form. Or, for a plan of few items,
+// all of it (run_few).
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void digest_tree_kernel(BatchArgs A) {
+  __shared__ Smem<kSlabOne> sm;
   const DigestCtl* c = A.ctl;
   if (c->overflow) return;
+  if (c->few) {
+    run_few(A, sm, c->few, c->n_node_items, c->n_small);
+    return;
+  }
   const uint64_t n_node = c->n_node_items;
   const int lane = threadIdx.x & 63;
   const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
@@ -1346,11 +1410,16 @@ static int enqueue_batched(const BatchedSpace& S, const void* const* ptrs, const
   auto sized = [&](uint64_t full, uint64_t per) {
     return (unsigned)(item_hint ? std::max<uint64_t>(1, std::min<uint64_t>(full, ceil_div(item_hint, per))) : full);
   };
+  // the last launch holds a plan of few items (one a workgroup) or the tree
+  const unsigned grid_last = sized(cus * 4, 1);
+  P.grid = grid_last;
   if (n <= kPlanOneMax) {
     // few workgroups: each repeats the scan, and writes its share of the items
     const dim3 grid(sized(32, kPlanOneThreads));
     if (n <= (uint64_t)kPlanOneThreads)
       hipLaunchKernelGGL(plan_one_kernel<1>, grid, dim3(kPlanOneThreads), 0, stream, P, S.item_buf);
+    else if (n <= 4ull * kPlanOneThreads)
+      hipLaunchKernelGGL(plan_one_kernel<4>, grid, dim3(kPlanOneThreads), 0, stream, P, S.item_buf);
     else
       hipLaunchKernelGGL(plan_one_kernel<8>, grid, dim3(kPlanOneThreads), 0, stream, P, S.item_buf);
   } else {
@@ -1377,9 +1446,8 @@ static int enqueue_batched(const BatchedSpace& S, const void* const* ptrs, const
   B.ctl = P.ctl;
   B.status = S.status;
   B.chunk = std::max<uint32_t>(1, tuning().chunk_nodes);
-  const uint64_t bpc = tuning().blocks_per_cu;
-  hipLaunchKernelGGL(digest_batched_kernel, dim3(sized(cus * bpc, 1)), dim3(kThreads), 0, stream, B);
-  hipLaunchKernelGGL(digest_tree_kernel, dim3(sized(cus * 4, 64 * kWaves)), dim3(kThreads), 0, stream, B);
+  hipLaunchKernelGGL(digest_batched_kernel, dim3(sized(cus * tuning().blocks_per_cu, 1)), dim3(kThreads), 0, stream, B);
+  hipLaunchKernelGGL(digest_tree_kernel, dim3(grid_last), dim3(kThreads), 0, stream, B);
   return check_hip(hipGetLastError(), "digest launch");
 }
 

@@ -43,6 +43,7 @@ struct DigestCtl {
   uint64_t n_med;         // level-1 nodes small enough for one wavefront
   uint32_t head;          // work-queue head
   uint32_t overflow;      // 1 when the plan did not fit the workspace
+  uint32_t few;           // nonzero: an item per workgroup at most, with this many small buffers in a group
 };
 
 struct Workspace {
