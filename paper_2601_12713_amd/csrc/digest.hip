@@ -1240,10 +1240,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const int lane = threadIdx.x & 63;
   const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
   const uint64_t nwaves = (uint64_t)gridDim.x * kWaves;
-  for (uint64_t base = wave * 64; base < n_node; base += nwaves * 64) {
+  // A wavefront takes its level-2 nodes one after another, so it looks at as
+  // few node items as cover them all (64 at most, one per lane): 10,400 items
+  // 17.5 -> 7.8 us against always 64.
+  const uint64_t per = min<uint64_t>(64, ceil_div(n_node, nwaves));
+  for (uint64_t base = wave * per; base < n_node; base += nwaves * per) {
     const uint64_t k = base + lane;
     bool first = false;
-    if (k < n_node) {
+    if ((uint64_t)lane < per && k < n_node) {
       const uint32_t b = A.item_buf[k];
       const uint64_t node = k - A.node_off[b];
       const uint64_t n1 = ceil_div(ceil_div(A.sizes[b], kLeaf), kFanIn);
@@ -1265,10 +1269,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   }
   // a level-2 node whose only child is a buffer's last node, hashed as a medium node
   const uint64_t n_med = c->n_med;
-  for (uint64_t base = wave * 64; base < n_med; base += nwaves * 64) {
+  const uint64_t mper = min<uint64_t>(64, ceil_div(n_med, nwaves));
+  for (uint64_t base = wave * mper; base < n_med; base += nwaves * mper) {
     const uint64_t j = base + lane;
     bool alone = false;
-    if (j < n_med) {
+    if ((uint64_t)lane < mper && j < n_med) {
       const uint32_t b = A.med_rec[j].buf;
       const uint64_t n1 = ceil_div(ceil_div(A.sizes[b], kLeaf), kFanIn);
       alone = n1 > 1 && (n1 - 1) % kFanIn == 0;
