@@ -64,6 +64,8 @@ constexpr int kWaveCnt = 3 + kEp;
 constexpr uint32_t kPackLimit = 1u << 24;
 constexpr uint32_t kIdxMask = kPackLimit - 1;
 constexpr uint32_t kNone = 0xFFFFFFFFu;
+// Logs up to kWalkMax records are analysed by walks over all of them (below).
+constexpr uint32_t kWalkMax = 4096;
 
 // C_COPYIN: a transfer that writes device memory (H2D or D2D, dst_dev >= 0),
 // the records the unused-transfer rule looks at.
@@ -102,6 +104,7 @@ struct AnaCtl {
   // transfers flagged DD or RT_RX; pairs flagged RA or UA; transfers flagged
   // UT only
   uint64_t elim_tx, elim_pairs, elim_ut;
+  uint32_t wticket;                   // logs analysed by walks: workgroups done
 };
 constexpr int kNumMasks = 8;
 
@@ -3120,6 +3123,40 @@ __device__ __forceinline__ unsigned long long tiny_red(int k, unsigned long long
   return (k == TA_BAD || k == TA_TMIN) ? min(a, b) : k == TA_TMAX ? max(a, b) : a + b;
 }
 
+// The report of a whole log from its reduced accumulators.
+__device__ void acc_report(const unsigned long long* t, uint32_t n, odp_report* rep) {
+  rep->n_events = n;
+  rep->n_invalid = t[TA_INV];
+  rep->n_transfers = t[TA_TX];
+  rep->n_kernels = t[TA_K];
+  rep->n_alloc_pairs = t[TA_PAIRS];
+  rep->n_unpaired_alloc = t[TA_UNP_A];
+  rep->n_unpaired_delete = t[TA_UNP_D];
+  rep->dd_events = t[TA_DD];
+  rep->dd_groups = t[TA_DD_GRP];
+  rep->dd_members = t[TA_DD] + t[TA_DD_GRP];
+  rep->dd_bytes = t[TA_DD_B];
+  rep->dd_time_ns = t[TA_DD_T];
+  rep->rt_pairs = t[TA_RT_TX];
+  rep->rt_rx_events = t[TA_RT_RX];
+  rep->rt_bytes = t[TA_RT_B];
+  rep->rt_time_ns = t[TA_RT_T];
+  rep->ra_events = t[TA_RA];
+  rep->ra_groups = t[TA_RA_GRP];
+  rep->ra_members = t[TA_RA] + t[TA_RA_GRP];
+  rep->ra_bytes = t[TA_RA_B];
+  rep->ra_time_ns = t[TA_RA_T];
+  rep->ua_events = t[TA_UA];
+  rep->ua_bytes = t[TA_UA_B];
+  rep->ua_time_ns = t[TA_UA_T];
+  rep->ut_events = t[TA_UT];
+  rep->ut_bytes = t[TA_UT_B];
+  rep->ut_time_ns = t[TA_UT_T];
+  write_estimate(rep, t[TA_INV] < n, t[TA_TMIN], t[TA_TMAX], t[TA_ELIM]);
+  rep->first_bad_event = (uint32_t)t[TA_BAD];
+  rep->status = t[TA_BAD] != kNone ? 1 : 0;
+}
+
 __global__ __launch_bounds__(kTinyMax) void analyze_tiny_kernel(const odp_event* __restrict__ ev, uint32_t n,
                                                                uint8_t* __restrict__ flags, odp_report* __restrict__ rep) {
   __shared__ TinyLds L;
@@ -3334,38 +3371,315 @@ __global__ __launch_bounds__(kTinyMax) void analyze_tiny_kernel(const odp_event*
   }
   __syncthreads();
   if (i == 0) {
-    const unsigned long long* t = L.acc[0];
-    rep->n_events = n;
-    rep->n_invalid = t[TA_INV];
-    rep->n_transfers = t[TA_TX];
-    rep->n_kernels = t[TA_K];
-    rep->n_alloc_pairs = t[TA_PAIRS];
-    rep->n_unpaired_alloc = t[TA_UNP_A];
-    rep->n_unpaired_delete = t[TA_UNP_D];
-    rep->dd_events = t[TA_DD];
-    rep->dd_groups = t[TA_DD_GRP];
-    rep->dd_members = t[TA_DD] + t[TA_DD_GRP];
-    rep->dd_bytes = t[TA_DD_B];
-    rep->dd_time_ns = t[TA_DD_T];
-    rep->rt_pairs = t[TA_RT_TX];
-    rep->rt_rx_events = t[TA_RT_RX];
-    rep->rt_bytes = t[TA_RT_B];
-    rep->rt_time_ns = t[TA_RT_T];
-    rep->ra_events = t[TA_RA];
-    rep->ra_groups = t[TA_RA_GRP];
-    rep->ra_members = t[TA_RA] + t[TA_RA_GRP];
-    rep->ra_bytes = t[TA_RA_B];
-    rep->ra_time_ns = t[TA_RA_T];
-    rep->ua_events = t[TA_UA];
-    rep->ua_bytes = t[TA_UA_B];
-    rep->ua_time_ns = t[TA_UA_T];
-    rep->ut_events = t[TA_UT];
-    rep->ut_bytes = t[TA_UT_B];
-    rep->ut_time_ns = t[TA_UT_T];
-    write_estimate(rep, t[TA_INV] < n, t[TA_TMIN], t[TA_TMAX], t[TA_ELIM]);
-    rep->first_bad_event = (uint32_t)t[TA_BAD];
-    rep->status = t[TA_BAD] != kNone ? 1 : 0;
+    acc_report(L.acc[0], n, rep);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Logs of kTinyMax + 1 .. kWalkMax records: every rule evaluated as its
+// definition here too, by all workgroups. What a record needs to know about
+// the others is a maximum, a minimum, an OR or a count over them, so the
+// others may be looked at in any order and by several lanes: a workgroup
+// stages the whole log's keys in LDS and takes 16 records, each with 64 lanes
+// that walk every 64th record; the partial results meet in LDS. Two launches on
+// one stream:
+//   walk   DD, RT, the next copy and UT, pairing and UA
+//   pairs  RA over the paired ALLOCs; the report by the last workgroup
+// instead of the sorting pipeline's 26 (up to 2,048 records) or 79, each bound
+// by its latency. The work grows with n^2, and 4,096 records fill the LDS:
+// 1,000 records 145 -> 21 us, 4,000 records 224 -> 40 us.
+// ---------------------------------------------------------------------------
+constexpr int kWalkT = 1024;
+constexpr uint32_t kWalkRec = 16;                     // records per workgroup
+constexpr uint32_t kWalkSub = kWalkT / kWalkRec;      // lanes per record
+constexpr uint32_t kUnusedBit = 0x80000000u;          // in pair[]: no kernel meets the pair's window
+constexpr uint32_t kNoGroup = 0xFFFFFFFFu;
+
+struct WalkKeys {
+  unsigned long long k1, k2;  // transfers: digest, source address; ALLOC/DELETE: -, device address; KERNELs: start, end
+};
+struct WalkCode {
+  uint32_t m;  // 0 rejected; else bit 3, bit 0 transfer, bit 1 KERNEL, bit 2 DELETE, src_dev + 1 << 8; dst_dev + 1 << 12
+  uint32_t g;  // with k2, the group of copies into one place or of one device address; 0 for other records
+};
+
+struct WalkArgs {
+  const odp_event* ev;
+  uint32_t n;
+  uint8_t* flags;
+  odp_report* rep;
+  uint32_t* pair;            // per record: an ALLOC's DELETE (| kUnusedBit), else kNone
+  unsigned long long* sums;  // [2 * workgroups][kWalkAcc] accumulators of the walk's and the pairs' workgroups
+  AnaCtl* ctl;               // wticket
+};
+constexpr uint32_t kWalkAcc = 32;
+
+__device__ __forceinline__ unsigned long long acc_identity(int k) {
+  return k == TA_BAD ? (unsigned long long)kNone : k == TA_TMIN ? ~0ull : 0ull;
+}
+
+__global__ __launch_bounds__(kWalkT) void walk_kernel(WalkArgs A) {
+  __shared__ WalkKeys s_key[kWalkMax];
+  __shared__ WalkCode s_code[kWalkMax];
+  __shared__ uint16_t s_k[kWalkMax];  // the KERNEL records, in any order
+  __shared__ uint32_t s_nk;
+  __shared__ uint32_t s_fl[kWalkRec], s_rx[kWalkRec], s_next[kWalkRec], s_prev[kWalkRec], s_cnt[kWalkRec];
+  __shared__ unsigned long long s_lo[kWalkRec], s_hi[kWalkRec];
+  __shared__ unsigned long long s_acc[kWalkAcc][kWalkRec];
+  const odp_event* __restrict__ ev = A.ev;
+  const uint32_t n = A.n, t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (blockIdx.x == 0 && t == 0) A.ctl->wticket = 0;
+  if (t == 0) s_nk = 0;
+  if (t < kWalkRec) {
+    s_fl[t] = s_rx[t] = s_prev[t] = s_cnt[t] = 0;
+    s_next[t] = kNone;
+  }
+  if (t < kWalkAcc * kWalkRec) s_acc[t / kWalkRec][t % kWalkRec] = acc_identity((int)(t / kWalkRec));
+  __syncthreads();
+  // every record's keys and codes
+  for (uint32_t j = t; j < n; j += kWalkT) {
+    const odp_event e = ev[j];
+    const uint64_t before = j ? ev[j - 1].t_start : 0;
+    const bool tx = e.op == ODP_H2D || e.op == ODP_D2H || e.op == ODP_D2D;
+    const bool valid = e.op >= ODP_ALLOC && e.op <= ODP_KERNEL && e.t_end >= e.t_start && e.t_start >= before &&
+                       dev_ok(e.dst_dev) && (!tx || dev_ok(e.src_dev));
+    const bool kern = valid && e.op == ODP_KERNEL, ad = valid && !tx && !kern;
+    const bool copyin = valid && tx && e.op != ODP_D2H && e.dst_dev >= 0;
+    const uint32_t sd = tx ? (uint32_t)(e.src_dev + 1) : 0u, dd = (uint32_t)(e.dst_dev + 1);
+    s_key[j] = kern ? WalkKeys{e.t_start, e.t_end} : WalkKeys{e.digest, ad ? e.dst_addr : e.src_addr};
+    s_code[j] = WalkCode{!valid ? 0u : 8u | (tx ? 1u : 0u) | (kern ? 2u : 0u) | (e.op == ODP_DELETE ? 4u : 0u) | sd << 8 | dd << 12,
+                         copyin ? 1u | sd << 8 | dd << 12 : ad ? 2u | dd << 12 : 0u};
+    const uint64_t bk = __ballot(kern);
+    if (bk) {
+      uint32_t q = 0;
+      if (lane == (uint32_t)__builtin_ctzll(bk)) q = atomicAdd(&s_nk, (uint32_t)__popcll(bk));
+      q = (uint32_t)__shfl((int)q, __builtin_ctzll(bk), 64) + (uint32_t)__popcll(bk & lanemask_lt());
+      if (kern) s_k[q] = (uint16_t)j;
+    }
+  }
+  __syncthreads();
+  const uint32_t r = lane % kWalkRec, sub = w * (64 / kWalkRec) + lane / kWalkRec, i = blockIdx.x * kWalkRec + r;
+  const bool in = i < n;
+  const WalkKeys ki = in ? s_key[i] : WalkKeys{0, 0};
+  const WalkCode ci = in ? s_code[i] : WalkCode{0, 0};
+  const bool tx = ci.m & 1;
+  const uint32_t sr = (ci.m >> 8) & 15, ds = (ci.m >> 12) & 15, gi = ci.g ? ci.g : kNoGroup;
+  // rx: 1 + 2 * (latest earlier transfer of the pair) + whether it went the
+  // other way; prev, next: the nearest records of i's group (prev plus 1)
+  uint32_t fl = 0, rx = 0, next = kNone, prev = 0;
+#pragma unroll 4
+  for (uint32_t j = sub; j < n; j += kWalkSub) {
+    const WalkKeys kj = s_key[j];
+    const WalkCode cj = s_code[j];
+    if (kj.k1 == ki.k1 && tx && (cj.m & 1)) {
+      const uint32_t sj = (cj.m >> 8) & 15, dj = (cj.m >> 12) & 15;
+      if (j < i) {
+        fl |= dj == ds ? 1u : 0u;
+        if (sr != ds && ((sj == sr && dj == ds) || (sj == ds && dj == sr))) rx = 1 + 2 * j + (sj == ds ? 1u : 0u);
+      } else if (j > i) {
+        fl |= (dj == ds ? 2u : 0u) | (sr != ds && sj == ds && dj == sr ? 4u : 0u);
+      }
+    }
+    if (kj.k2 == ki.k2 && cj.g == gi) {
+      if (j < i) prev = 1 + j;
+      if (j > i) next = min(next, j);
+    }
+  }
+  if (fl) atomicOr(&s_fl[r], fl);
+  if (rx) atomicMax(&s_rx[r], rx);
+  if (next != kNone) atomicMin(&s_next[r], next);
+  if (prev) atomicMax(&s_prev[r], prev);
+  __syncthreads();
+  // The window the device's kernels are counted over: of a copy into the
+  // device, or of the pair that an ALLOC opens.
+  const bool del = ci.m & 4, ad = (ci.g & 3) == 2, copyin = (ci.g & 3) == 1;
+  const uint32_t nx = s_next[r];
+  const bool alloc_paired = ad && !del && nx != kNone && (s_code[nx == kNone ? 0 : nx].m & 4);
+  odp_event e{};
+  if (t < kWalkRec && in) {
+    e = ev[i];
+    s_lo[r] = e.t_start;
+    s_hi[r] = alloc_paired ? ev[nx].t_end : nx == kNone ? ~0ull : ev[nx].t_start;
+  }
+  __syncthreads();
+  // kernels on the device that start by the window's end, less those that end
+  // before it opens
+  if (copyin || alloc_paired) {
+    const uint64_t lo = s_lo[r], hi = s_hi[r];
+    const uint32_t nk = s_nk;
+    uint32_t cnt = 0;
+#pragma unroll 2
+    for (uint32_t q = sub; q < nk; q += kWalkSub) {
+      const uint32_t j = s_k[q];
+      const WalkKeys kj = s_key[j];
+      if (((s_code[j].m >> 12) & 15) == ds) cnt += (kj.k1 <= hi ? 1u : 0u) - (kj.k2 < lo ? 1u : 0u);
+    }
+    if (cnt) atomicAdd(&s_cnt[r], cnt);
+  }
+  __syncthreads();
+  if (t < kWalkRec && in) {
+    const bool unread = s_cnt[r] == 0;
+    const unsigned long long d = e.t_end - e.t_start;
+    uint8_t f = 0;
+    uint32_t pr = kNone;
+    if (!ci.m) {
+      f = ODP_F_INVALID;
+      s_acc[TA_INV][r] = 1;
+      s_acc[TA_BAD][r] = i;
+    } else {
+      s_acc[TA_TMIN][r] = e.t_start;
+      s_acc[TA_TMAX][r] = e.t_end;
+    }
+    if (tx) {
+      s_acc[TA_TX][r] = 1;
+      const uint32_t x = s_fl[r];
+      if (x & 1) {
+        f |= ODP_F_DD;
+        s_acc[TA_DD][r] = 1;
+        s_acc[TA_DD_B][r] = e.bytes;
+        s_acc[TA_DD_T][r] = d;
+      } else {
+        s_acc[TA_DD_GRP][r] = (x >> 1) & 1;
+      }
+      if (x & 4) {
+        f |= ODP_F_RT_TX;
+        s_acc[TA_RT_TX][r] = 1;
+      }
+      if (s_rx[r] && ((s_rx[r] - 1) & 1)) {
+        f |= ODP_F_RT_RX;
+        s_acc[TA_RT_RX][r] = 1;
+        s_acc[TA_RT_B][r] = e.bytes;
+        s_acc[TA_RT_T][r] = d;
+      }
+      if (copyin && unread) {
+        f |= ODP_F_UT;
+        s_acc[TA_UT][r] = 1;
+        s_acc[TA_UT_B][r] = e.bytes;
+        s_acc[TA_UT_T][r] = d;
+      }
+      if (f & (ODP_F_DD | ODP_F_RT_RX | ODP_F_UT)) s_acc[TA_ELIM][r] = d;
+    } else if (ci.m & 2) {
+      s_acc[TA_K][r] = 1;
+    } else if (ad && del) {
+      const uint32_t pv = s_prev[r];
+      const bool paired = pv && !(s_code[pv ? pv - 1 : 0].m & 4);
+      f = paired ? ODP_F_PAIRED : 0;
+      s_acc[TA_UNP_D][r] = !paired;
+    } else if (ad) {
+      s_acc[TA_UNP_A][r] = !alloc_paired;
+      if (alloc_paired) pr = nx | (unread ? kUnusedBit : 0u);
+    }
+    A.flags[i] = f;  // (a paired ALLOC's flags follow in the pairs kernel)
+    A.pair[i] = pr;
+  }
+  __syncthreads();
+  if (t < kWalkAcc) {
+    unsigned long long v = s_acc[t][0];
+    for (uint32_t x = 1; x < kWalkRec; ++x) v = tiny_red((int)t, v, s_acc[t][x]);
+    A.sums[(size_t)blockIdx.x * kWalkAcc + t] = v;
+  }
+}
+
+// One workgroup per 64 records, for the paired ALLOCs among them; the walked
+// records are spread over its wavefronts. The last workgroup to finish folds
+// all sums into the report.
+constexpr uint32_t kWalkPairRec = 64;
+__global__ __launch_bounds__(kWalkT) void walk_pairs_kernel(WalkArgs A, uint32_t walk_blocks) {
+  __shared__ uint32_t s_list[kWalkMax];  // the paired ALLOCs of the log, in any order
+  __shared__ uint32_t s_n, s_fl[kWalkPairRec], s_last;
+  __shared__ unsigned long long s_part[kWalkT / kWalkAcc][kWalkAcc];
+  const odp_event* __restrict__ ev = A.ev;
+  const uint32_t n = A.n, t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const uint32_t i = blockIdx.x * kWalkPairRec + lane;
+  const uint32_t pr = i < n ? A.pair[i] : kNone;
+  unsigned long long* own = A.sums + (size_t)(walk_blocks + blockIdx.x) * kWalkAcc;
+  unsigned long long a[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const bool any = __ballot(pr != kNone) != 0;  // the same 64 records in every wavefront
+  if (any) {
+    if (t == 0) s_n = 0;
+    if (t < kWalkPairRec) s_fl[t] = 0;
+    __syncthreads();
+    for (uint32_t j = t; j < n; j += kWalkT) {
+      const uint64_t b = __ballot(A.pair[j] != kNone);
+      if (!b) continue;
+      uint32_t q = 0;
+      if (lane == (uint32_t)__builtin_ctzll(b)) q = atomicAdd(&s_n, (uint32_t)__popcll(b));
+      q = (uint32_t)__shfl((int)q, __builtin_ctzll(b), 64) + (uint32_t)__popcll(b & lanemask_lt());
+      if ((b >> lane) & 1) s_list[q] = j;
+    }
+    odp_event e{};
+    if (pr != kNone) e = ev[i];
+    __syncthreads();
+    const uint32_t np = s_n;
+    uint32_t fl = 0;  // 1: an earlier paired ALLOC of the key, 2: a later one
+    // 64 listed ALLOCs at a time, one per lane, handed round by lane reads
+    for (uint32_t q0 = w * 64; q0 < np; q0 += kWalkT) {
+      const bool ok = q0 + lane < np;
+      const uint32_t jl = ok ? s_list[q0 + lane] : 0u;
+      const uint64_t hl = ok ? ev[jl].src_addr : 0ull, bl = ok ? ev[jl].bytes : 0ull;
+      const int dl = ok ? ev[jl].dst_dev : -2;
+      const int m = (int)min(64u, np - q0);
+      for (int x = 0; x < m; ++x) {
+        const uint32_t j = lane32(jl, x);
+        if (lane64(hl, x) == e.src_addr && lane64(bl, x) == e.bytes && (int)lane32((uint32_t)dl, x) == e.dst_dev)
+          fl |= j < i ? 1u : j > i ? 2u : 0u;
+      }
+    }
+    if (fl && pr != kNone) atomicOr(&s_fl[lane], fl);
+    __syncthreads();
+    if (t < 64 && pr != kNone) {
+      const odp_event& ed = ev[pr & ~kUnusedBit];
+      const unsigned long long d = (e.t_end - e.t_start) + (ed.t_end - ed.t_start);
+      uint8_t f = ODP_F_PAIRED;
+      a[0] = 1;
+      if (s_fl[lane] & 1) {
+        f |= ODP_F_RA;
+        a[1] = 1;
+        a[3] = e.bytes;
+        a[4] = d;
+      } else {
+        a[2] = s_fl[lane] >> 1;
+      }
+      if (pr & kUnusedBit) {
+        f |= ODP_F_UA;
+        a[5] = 1;
+        a[6] = e.bytes;
+        a[7] = d;
+      }
+      if (f & (ODP_F_RA | ODP_F_UA)) a[8] = d;
+      A.flags[i] = f;
+    }
+  }
+  if (t < 64) {
+    // this workgroup's sums, and after them its ticket
+    constexpr int kAcc[9] = {TA_PAIRS, TA_RA, TA_RA_GRP, TA_RA_B, TA_RA_T, TA_UA, TA_UA_B, TA_UA_T, TA_ELIM};
+    unsigned long long mine = acc_identity((int)lane);
+    if (any) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        const unsigned long long v = wave_sum(a[k]);
+        if ((int)lane == kAcc[k]) mine = v;
+      }
+    }
+    if (lane < kWalkAcc) __hip_atomic_store(own + lane, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (t == 0)
+      s_last = __hip_atomic_fetch_add(&A.ctl->wticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  const uint32_t k = t % kWalkAcc, part = t / kWalkAcc;
+  unsigned long long v = acc_identity((int)k);
+  for (uint32_t b = part; b < walk_blocks + gridDim.x; b += kWalkT / kWalkAcc)
+    v = tiny_red((int)k, v, __hip_atomic_load(A.sums + (size_t)b * kWalkAcc + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  s_part[part][k] = v;
+  __syncthreads();
+  if (t < kWalkAcc) {
+    for (uint32_t x = 1; x < kWalkT / kWalkAcc; ++x) v = tiny_red((int)t, v, s_part[x][t]);
+    s_part[0][t] = v;
+  }
+  __syncthreads();
+  if (t == 0) acc_report(s_part[0], n, A.rep);
 }
 
 // Digest passes to run before the first local fix, for n records (at most n
@@ -3581,6 +3895,26 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   return check_hip(hipGetLastError(), "odp_analyze_trace launch");
 }
 
+// The analysis of kTinyMax < n <= kWalkMax records, in arrays of the same workspace.
+static int enqueue_walks(Workspace* ws, const odp_event* events, size_t n, uint8_t* out_flags, odp_report* out_report,
+                         hipStream_t stream) {
+  const Views v = views(ws);
+  WalkArgs A;
+  A.ev = events;
+  A.n = (uint32_t)n;
+  A.flags = out_flags;
+  A.rep = out_report;
+  A.pair = v.bv[0];
+  A.sums = v.skey[0];
+  A.ctl = v.ctl;
+  const uint32_t blocks = ceil_div32(n, kWalkRec), pblocks = ceil_div32(n, kWalkPairRec);
+  // (the workspace holds at least 4,096 records with 2 * kSubsetJobs sort key words each)
+  static_assert((kWalkMax / kWalkRec + kWalkMax / kWalkPairRec) * kWalkAcc <= 2 * kSubsetJobs * 4096, "sums fit the sort keys");
+  hipLaunchKernelGGL(walk_kernel, dim3(blocks), dim3(kWalkT), 0, stream, A);
+  hipLaunchKernelGGL(walk_pairs_kernel, dim3(pblocks), dim3(kWalkT), 0, stream, A, blocks);
+  return check_hip(hipGetLastError(), "odp_analyze_trace launch");
+}
+
 extern "C" int odp_analyze_trace(const odp_event* events, size_t n, uint8_t* out_flags, odp_report* out_report,
                                  odp_stream_t stream_) {
   hipStream_t stream = static_cast<hipStream_t>(stream_);
@@ -3605,6 +3939,7 @@ extern "C" int odp_analyze_trace(const odp_event* events, size_t n, uint8_t* out
     int e = analyze_reserve(ws, n);
     if (e) return e;
   }
+  if (n <= kWalkMax) return enqueue_walks(ws, events, n, out_flags, out_report, stream);
   if (capturing) return enqueue_analysis(ws, events, n, out_flags, out_report, stream);
   // The sequence is some fifty launches on two streams; a call repeated with
   // the same arguments replays it as one graph instead (the first repeat

@@ -1,0 +1,91 @@
+"""The analysis at the log lengths where its form changes, against the oracle:
+every flag and every report field, bit-exact."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2601_12713_amd import workloads as W
+
+from gpu_helpers import analyze_gpu, compare
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def random_log(seed, n, devices=3, digests=40, places=12, invalid=0.0, kernels=0.12, allocs=0.25, tie=0.3, long_kernels=False):
+    """A random log with few keys (every rule fires), ties, and records out of order when invalid > 0."""
+    rng = np.random.default_rng(seed)
+    ev = W.empty_events(n)
+    u = rng.random(n)
+    op = np.where(u < kernels, W.KERNEL, np.where(u < kernels + allocs, rng.choice([W.ALLOC, W.DELETE], size=n),
+                                                  rng.choice([W.H2D, W.D2H, W.D2D], size=n)))
+    ev["op"] = op
+    ev["digest"] = rng.integers(0, digests, size=n).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
+    ev["src_dev"], ev["dst_dev"] = rng.integers(-1, devices, size=n), rng.integers(-1, devices, size=n)
+    ev["src_addr"] = W.HOST_BASE + rng.integers(0, places, size=n) * 4096
+    ev["dst_addr"] = W.DEV_BASE + rng.integers(0, places, size=n) * 4096
+    ev["bytes"] = rng.choice([64, 128], size=n)
+    ev["t_start"] = np.cumsum(rng.integers(0, 10, size=n) * (rng.random(n) >= tie)) + 50
+    ev["t_end"] = ev["t_start"] + rng.integers(0, 400 if long_kernels else 8, size=n)
+    bad = rng.random(n) < invalid
+    back = bad & (rng.random(n) < 0.5)  # before its predecessor: what follows may start earlier than what was
+    ev["t_start"][back] -= rng.integers(1, 50, size=int(back.sum())).astype(np.uint64)
+    ev["op"][bad & ~back] = 9
+    return ev
+
+
+def check(odp, ev):
+    fr, rr = oracle.analyze(ev)
+    fg, rg = analyze_gpu(odp, ev)
+    compare(fg, rg, fr, rr)
+    return fg, rg
+
+
+@pytest.mark.parametrize("n", [512, 513, 640, 1023, 1024, 1025, 2047, 3001])
+@pytest.mark.parametrize("invalid", [0.0, 0.02])
+def test_walked_logs(odp, n, invalid):
+    check(odp, random_log(n, n, invalid=invalid))
+    check(odp, random_log(n + 1, n, devices=10, digests=n, places=n, invalid=invalid, long_kernels=True))
+    check(odp, random_log(n + 2, n, devices=1, digests=2, places=1, invalid=invalid, kernels=0.002))
+
+
+@pytest.mark.parametrize("kind", ["no kernels", "kernels only", "allocations only", "all rejected", "one digest"])
+def test_walked_one_class(odp, kind):
+    n = 3000
+    ev = random_log(7, n, kernels=1.0 if kind == "kernels only" else 0.0 if kind == "no kernels" else 0.1,
+                    allocs=1.0 if kind == "allocations only" else 0.2, digests=1 if kind == "one digest" else 40)
+    if kind == "allocations only":
+        ev["op"] = np.where(np.arange(n) % 3 == 0, W.ALLOC, W.DELETE)
+    if kind == "all rejected":
+        ev["op"] = 0
+    check(odp, ev)
+
+
+@pytest.mark.parametrize("n", [4095, 4096, 4097])
+def test_last_walked_length(odp, n):
+    check(odp, random_log(n, n, digests=n // 4, places=300, invalid=0.001))
+
+
+def test_walked_calls_alternate(odp):
+    """Calls on one stream share the workspace: logs of other lengths between, under capture and replayed."""
+    logs = [random_log(100 + k, m) for k, m in enumerate((600, 4000, 3000, 30000))]
+    want = [oracle.analyze(ev) for ev in logs]
+    for k in (0, 1, 3, 2, 0, 3, 1):
+        fg, rg = analyze_gpu(odp, logs[k])
+        compare(fg, rg, *want[k])
+    s = torch.cuda.Stream()
+    odp.reserve(max_events=4000, stream=s)
+    ev = logs[1]
+    d_ev = torch.from_numpy(ev.view(np.uint8).reshape(-1).copy()).to("cuda")
+    d_fl = torch.zeros(len(ev), dtype=torch.uint8, device="cuda")
+    d_rep = torch.zeros(odp.REPORT_BYTES, dtype=torch.uint8, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        odp.analyze_trace(d_ev, d_fl, d_rep, stream=s, n=len(ev))
+    for _ in range(3):
+        d_fl.fill_(0xAA)
+        g.replay()
+        torch.cuda.synchronize()
+        compare(d_fl.cpu().numpy(), odp.report_to_dict(d_rep.cpu().numpy()), *want[1])
+        odp.analyze_trace(d_ev, d_fl, d_rep, n=len(ev))
