@@ -100,7 +100,8 @@ def traffic_from_profile(name, sources):
 
 DIGEST_SOURCES = ["paper_2601_12713_amd/csrc/digest.hip", "paper_2601_12713_amd/csrc/xxh64_dev.h",
                   "paper_2601_12713_amd/csrc/internal.h"]
-ANALYSIS_SOURCES = ["paper_2601_12713_amd/csrc/analyze.hip", "paper_2601_12713_amd/csrc/internal.h"]
+ANALYSIS_SOURCES = ["paper_2601_12713_amd/csrc/analyze.hip", "paper_2601_12713_amd/csrc/analyze_mid.h",
+                    "paper_2601_12713_amd/csrc/internal.h"]
 
 
 def host_info():

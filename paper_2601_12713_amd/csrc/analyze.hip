@@ -230,6 +230,7 @@ enum Slot : uint32_t {
   S_DD_EVENTS, S_DD_GROUPS, S_DD_BYTES, S_DD_TIME, S_RT_PAIRS, S_RT_RX, S_RT_BYTES, S_RT_TIME, S_ELIM_TX,
   S_RA_EVENTS, S_RA_GROUPS, S_RA_BYTES, S_RA_TIME, S_UA_EVENTS, S_UA_BYTES, S_UA_TIME, S_ELIM_PAIRS,
   S_UT_EVENTS, S_UT_BYTES, S_UT_TIME, S_ELIM_UT,
+  S_PAIRS, S_UNP_ALLOC,
   kSlots
 };
 
@@ -250,17 +251,17 @@ __device__ __forceinline__ unsigned long long red2(unsigned long long a, unsigne
   return a > b ? a : b;
 }
 
-// Reduces v over the block; thread 0 stores the result to *dst.
-template <RedOp OP>
+// Reduces v over the block (NT threads); thread 0 stores the result to *dst.
+template <RedOp OP, int NT = kT>
 __device__ void block_store(unsigned long long* dst, unsigned long long v) {
-  __shared__ unsigned long long sh[kT / 64];
+  __shared__ unsigned long long sh[NT / 64];
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v = red2<OP>(v, __shfl_xor(v, o, 64));
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     unsigned long long r = sh[0];
-    for (int w = 1; w < kT / 64; ++w) r = red2<OP>(r, sh[w]);
+    for (int w = 1; w < NT / 64; ++w) r = red2<OP>(r, sh[w]);
     *dst = r;
   }
   __syncthreads();
@@ -561,7 +562,7 @@ __device__ bool scan_quantity(T* base, T* ct, uint32_t stride, uint32_t nw, uint
   return *flag != 0;
 }
 
-__global__ __launch_bounds__(1024) void wave_scan_kernel(WaveScan S, uint32_t nchunk, AnaCtl* ctl) {
+__device__ void wave_scan_body(const WaveScan& S, uint32_t nchunk, AnaCtl* ctl) {
   __shared__ unsigned long long wt[16];
   __shared__ uint32_t flag;
   const uint32_t q = blockIdx.x / nchunk, c = blockIdx.x % nchunk;
@@ -586,6 +587,10 @@ __global__ __launch_bounds__(1024) void wave_scan_kernel(WaveScan S, uint32_t nc
     ctl->kd_total[d] = (uint32_t)tot[3 + d];
     b += (uint32_t)tot[3 + d];
   }
+}
+
+__global__ __launch_bounds__(1024) void wave_scan_kernel(WaveScan S, uint32_t nchunk, AnaCtl* ctl) {
+  wave_scan_body(S, nchunk, ctl);
 }
 
 struct SubsetOut {
@@ -615,6 +620,14 @@ struct SubsetOut {
   uint32_t* k_vals_e;
 };
 
+// Hash of a key of two words (group tables, places of copies).
+__device__ __forceinline__ uint32_t near_hash(uint64_t a, uint64_t b) {
+  uint64_t h = (a ^ (b << 48) ^ (b >> 16)) * 0x9E3779B97F4A7C15ull;
+  h ^= h >> 32;
+  h *= 0xBF58476D1CE4E5B9ull;
+  return (uint32_t)(h >> 32);
+}
+
 // Ordered compaction of the ALLOC/DELETE, KERNEL and copy-in records. Wavefront w
 // takes its 1,024 records in 16 coalesced rounds of 64 (lane l: record
 // wb + 64r + l); a ballot per round gives each matching lane its rank, so the
@@ -622,14 +635,19 @@ struct SubsetOut {
 // records of a round are read together. Each copy-in also gets the number of
 // KERNEL records on its receiving device logged before it: the device's count
 // before the wavefront (scanned) plus the kernels of earlier rounds and lanes.
-__global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* __restrict__ ev, const uint8_t* __restrict__ cls,
-                                                            uint32_t n, WaveScan W, SubsetOut S, Parts parts) {
+// ROUNDS rounds per wavefront. MID (logs of up to kMidMax records): no sort
+// words, values and masks are written, but each ALLOC/DELETE's host address and
+// bytes, and the kernels' ends in their per-device lists.
+template <int ROUNDS, bool MID>
+__device__ void subset_scatter_body(const odp_event* __restrict__ ev, const uint8_t* __restrict__ cls, uint32_t n,
+                                    const WaveScan& W, const SubsetOut& S, const Parts& parts, uint64_t* ad_host,
+                                    uint64_t* ad_bytes, uint64_t* kd_te) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint32_t wid = blockIdx.x * (kT / 64) + w;
-  const uint32_t wb = wid * kWaveElems;
-  uint8_t c[kRounds];
+  const uint32_t wb = wid * (ROUNDS * 64);
+  uint8_t c[ROUNDS];
 #pragma unroll
-  for (int r = 0; r < kRounds; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t i = wb + r * 64 + lane;
     c[r] = i < n ? cls[i] : C_INVALID;
   }
@@ -648,8 +666,9 @@ __global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* __r
   unsigned long long o_dev = 0, a_dev = ~0ull, o_addr = 0, a_addr = ~0ull, o_ks = 0, a_ks = ~0ull, o_ke = 0,
                      a_ke = ~0ull, o_kd = 0, a_kd = ~0ull, o_ua = 0, a_ua = ~0ull, o_uc = 0, a_uc = ~0ull;
   const uint64_t lt = lanemask_lt();
-#pragma unroll 4
-  for (int r = 0; r < kRounds; ++r) {
+  constexpr int kUnroll = ROUNDS < 4 ? ROUNDS : 4;
+#pragma unroll kUnroll
+  for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t i = wb + r * 64 + lane;
     const bool is_ad = c[r] == C_ALLOCDEL, is_k = c[r] == C_KERNEL, is_ut = c[r] == C_COPYIN;
     const uint64_t bad = __ballot(is_ad), bk = __ballot(is_k), bu = __ballot(is_ut);
@@ -696,7 +715,7 @@ __global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* __r
       S.ut_w_addr[q] = sa;
       S.ut_w_code[q] = code;
       S.ut_ts[q] = e.t_start;
-      S.ut_vals[q] = q;
+      S.ut_vals[q] = MID ? near_hash(sa, code) : q;  // MID: a hash of the place
       S.ut_kc[q] = kc;
       S.ut_km[q] = km;
       o_ua |= sa;
@@ -710,7 +729,12 @@ __global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* __r
       S.ad_op[q] = e.op;
       S.ad_w_dev[q] = dv;
       S.ad_w_addr[q] = ad;
-      S.ad_vals[q] = q;
+      if constexpr (MID) {
+        ad_host[q] = e.src_addr;
+        ad_bytes[q] = e.bytes;
+      } else {
+        S.ad_vals[q] = q;
+      }
       S.ad_alloc_partner[q] = kNone;
       S.ad_kc[q] = kc;
       S.ad_km[q] = km;
@@ -721,16 +745,19 @@ __global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* __r
     } else if (is_k) {
       const uint32_t q = q1 + (uint32_t)__popcll(bk & lt);
       const uint64_t dv = (uint64_t)(e.dst_dev + 1);
-      S.k_idx[q] = i;
-      S.k_w_start[q] = e.t_start;
+      if constexpr (!MID) {
+        S.k_idx[q] = i;
+        S.k_w_start[q] = e.t_start;
+        S.k_w_end[q] = e.t_end;
+        S.k_w_dev[q] = dv;
+        S.k_vals_s[q] = q;
+        S.k_vals_e[q] = q;
+      }
       // this kernel's place among its device's kernels in log order
       const uint32_t kp = S.ctl->kd_base[dc] + kc;
       S.kd_ts[kp] = e.t_start;
       S.kd_idx[kp] = i;
-      S.k_w_end[q] = e.t_end;
-      S.k_w_dev[q] = dv;
-      S.k_vals_s[q] = q;
-      S.k_vals_e[q] = q;
+      if constexpr (MID) kd_te[kp] = e.t_end;
       o_ks |= e.t_start;
       a_ks &= e.t_start;
       o_ke |= e.t_end;
@@ -742,6 +769,7 @@ __global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* __r
     q1 += (uint32_t)__popcll(bk);
     q2 += (uint32_t)__popcll(bu);
   }
+  if constexpr (MID) return;
   // (identity values where a lane saw no such record)
   block_store<R_OR>(parts.at(S_AD_DEV_OR), o_dev);
   block_store<R_AND>(parts.at(S_AD_DEV_AND), a_dev);
@@ -759,11 +787,15 @@ __global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* __r
   block_store<R_AND>(parts.at(S_UT_CODE_AND), a_uc);
 }
 
+__global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* ev, const uint8_t* cls, uint32_t n, WaveScan W,
+                                                            SubsetOut S, Parts parts) {
+  subset_scatter_body<kRounds, false>(ev, cls, n, W, S, parts, nullptr, nullptr, nullptr);
+}
+
 // One block per slot: reduces the blocks' partials of slots [first, first +
 // gridDim.x) into the control block and the report.
-__global__ __launch_bounds__(kT) void reduce_parts_kernel(Parts parts, uint32_t nb, uint32_t first, AnaCtl* ctl,
-                                                          odp_report* rep) {
-  const uint32_t slot = first + blockIdx.x;
+template <int NT>
+__device__ void reduce_slot(const Parts& parts, uint32_t nb, uint32_t slot, AnaCtl* ctl, odp_report* rep) {
   const unsigned long long* p = parts.p + (size_t)slot * parts.stride;
   int op = R_ADD;
   switch (slot) {
@@ -776,7 +808,7 @@ __global__ __launch_bounds__(kT) void reduce_parts_kernel(Parts parts, uint32_t 
     default: break;
   }
   unsigned long long v = op == R_AND || op == R_MIN ? ~0ull : 0ull;
-  for (uint32_t b = threadIdx.x; b < nb; b += kT) {
+  for (uint32_t b = threadIdx.x; b < nb; b += NT) {
     const unsigned long long x = p[b];
     v = op == R_ADD ? v + x : op == R_OR ? (v | x) : op == R_AND ? (v & x) : op == R_MIN ? min(v, x) : max(v, x);
   }
@@ -785,11 +817,11 @@ __global__ __launch_bounds__(kT) void reduce_parts_kernel(Parts parts, uint32_t 
     const unsigned long long x = __shfl_xor(v, o, 64);
     v = op == R_ADD ? v + x : op == R_OR ? (v | x) : op == R_AND ? (v & x) : op == R_MIN ? min(v, x) : max(v, x);
   }
-  __shared__ unsigned long long sh[kT / 64];
+  __shared__ unsigned long long sh[NT / 64];
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x != 0) return;
-  for (int t = 1; t < kT / 64; ++t) {
+  for (int t = 1; t < NT / 64; ++t) {
     const unsigned long long x = sh[t];
     v = op == R_ADD ? v + x : op == R_OR ? (v | x) : op == R_AND ? (v & x) : op == R_MIN ? min(v, x) : max(v, x);
   }
@@ -843,6 +875,11 @@ __global__ __launch_bounds__(kT) void reduce_parts_kernel(Parts parts, uint32_t 
     case S_ELIM_UT: ctl->elim_ut = v; break;
     default: break;
   }
+}
+
+__global__ __launch_bounds__(kT) void reduce_parts_kernel(Parts parts, uint32_t nb, uint32_t first, AnaCtl* ctl,
+                                                          odp_report* rep) {
+  reduce_slot<kT>(parts, nb, first + blockIdx.x, ctl, rep);
 }
 
 // ---------------------------------------------------------------------------
@@ -1262,101 +1299,6 @@ __global__ __launch_bounds__(kST) void sort_scatter_kernel(JobSet J, uint32_t p)
   } while (next_tile(J, s, tile, n));
 }
 
-// Small logs: every pass of a job in one workgroup, keys and values held in
-// LDS (ping-pong), one launch per sort instead of three per pass. Used when
-// the log has at most kSmallMax records (so every job has at most that many
-// elements). The result lands in keys/vals[npasses & 1], as with the passes.
-constexpr uint32_t kSmallMax = 2048;
-constexpr int kQT = 512;                         // threads
-constexpr int kQW = kQT / 64;                    // wavefronts
-constexpr int kQElems = kSmallMax / kQW;         // elements per wavefront (256)
-constexpr int kQRounds = kQElems / 64;           // rounds of 64 per wavefront
-
-__global__ __launch_bounds__(kQT) void sort_small_kernel(JobSet J) {
-  const SortJob& s = J.jobs[blockIdx.x];
-  const uint32_t n = *s.n_ptr;
-  const uint32_t np = s.npasses;
-  __shared__ unsigned long long lk[2][kSmallMax];
-  __shared__ uint32_t lv[2][kSmallMax];
-  __shared__ uint32_t wcnt[kQW][256];
-  __shared__ uint32_t base[256];
-  __shared__ uint32_t wsum[4];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (uint32_t i = threadIdx.x; i < n; i += kQT) {
-    lk[0][i] = s.keys[0][i];
-    lv[0][i] = s.vals[0][i];
-  }
-  __syncthreads();
-  uint32_t cur = 0;
-  for (uint32_t p = 0; p < np; ++p) {
-    for (int x = 0; x < 256; x += 64) wcnt[w][x + lane] = 0;
-    __syncthreads();
-    const uint32_t shift = s.ps[p];
-    const bool gather = s.pg[p] != 0;
-    const uint64_t* word = s.words[s.pw[p]];
-    uint32_t dg[kQRounds], rk[kQRounds];
-    unsigned long long ky[kQRounds];
-#pragma unroll
-    for (int r = 0; r < kQRounds; ++r) {
-      const uint32_t i = w * kQElems + r * 64 + lane;
-      const bool in = i < n;
-      ky[r] = in ? (gather ? word[lv[cur][i]] : lk[cur][i]) : 0ull;
-      const uint32_t d = in ? (uint32_t)(ky[r] >> shift) & 0xFF : 0u;
-      uint64_t peers = __ballot(in);
-#pragma unroll
-      for (int bit = 0; bit < 8; ++bit) {
-        const uint64_t bb = __ballot((d >> bit) & 1);
-        peers &= ((d >> bit) & 1) ? bb : ~bb;
-      }
-      const uint32_t before = in ? wcnt[w][d] : 0;
-      dg[r] = d;
-      rk[r] = before + (uint32_t)__popcll(peers & lanemask_lt());
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      if (in && (peers >> lane) == 1ull) wcnt[w][d] = before + (uint32_t)__popcll(peers);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
-    __syncthreads();
-    if (threadIdx.x < 256) {
-      const uint32_t d = threadIdx.x;
-      uint32_t c = 0;
-      for (int x = 0; x < kQW; ++x) {
-        const uint32_t t = wcnt[x][d];
-        wcnt[x][d] = c;
-        c += t;
-      }
-      uint32_t xs = c;
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(xs, o, 64);
-        if (lane >= o) xs += y;
-      }
-      if (lane == 63) wsum[w] = xs;
-      base[d] = xs - c;
-    }
-    __syncthreads();
-    if (threadIdx.x < 256) {
-      uint32_t pre = 0;
-      for (int q = 0; q < w; ++q) pre += wsum[q];
-      base[threadIdx.x] += pre;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kQRounds; ++r) {
-      const uint32_t i = w * kQElems + r * 64 + lane;
-      if (i < n) {
-        const uint32_t pos = base[dg[r]] + wcnt[w][dg[r]] + rk[r];
-        lk[cur ^ 1][pos] = ky[r];
-        lv[cur ^ 1][pos] = lv[cur][i];
-      }
-    }
-    __syncthreads();
-    cur ^= 1;
-  }
-  for (uint32_t i = threadIdx.x; i < n; i += kQT) {
-    s.keys[np & 1][i] = lk[cur][i];
-    s.vals[np & 1][i] = lv[cur][i];
-  }
-}
-
 // ---------------------------------------------------------------------------
 // 4. Duplicate and round-trip transfers: segmented scans per digest group.
 //
@@ -1576,7 +1518,6 @@ __device__ __forceinline__ BS<1> get_b<1>(const uint32_t* w) {
 struct DDArgs {
   const odp_event* ev;
   uint32_t n;          // records of the log (values are packed when n < kPackLimit)
-  uint32_t small;      // 1: the digest job was sorted in one workgroup (every record kept)
   const uint8_t* aux;
   const SortJob* job;  // the digest job (keys/vals in buffer npasses & 1)
   const AnaCtl* ctl;
@@ -1585,6 +1526,7 @@ struct DDArgs {
   uint8_t* flags;
   odp_report* rep;
   Parts parts;
+  const uint8_t* uth;  // per record: 1 for an unused transfer (logs of up to kMidMax records; else null)
 };
 
 
@@ -1665,47 +1607,48 @@ __device__ __forceinline__ void wave_bscan(uint32_t& f, BS<MODE>& v) {
 __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Elements of the digest job's sorted order the scans read.
-__device__ __forceinline__ uint32_t dd_len(const DDArgs& A) { return A.small ? A.n : sorted_len(*A.job); }
+__device__ __forceinline__ uint32_t dd_len(const DDArgs& A) { return sorted_len(*A.job); }
 
 // All 16 rounds of a wavefront at once: keys and values (coalesced), then
 // the endpoint codes gathered by value, all loads in flight together. Values
 // and codes go to the wavefront's LDS rows; bit r of heads / tails says
 // whether this lane's element of round r starts / ends its digest group.
 // n: the sorted elements; packed: codes in the values' top byte.
+template <int ROUNDS>
 __device__ __forceinline__ void load_wave(const unsigned long long* k, const uint32_t* v, const uint8_t* aux,
                                           uint32_t n, bool packed, uint32_t wb, uint32_t* s_val, uint8_t* s_code,
                                           uint32_t& heads, uint32_t& tails) {
   const int lane = threadIdx.x & 63;
-  unsigned long long key[kRounds];
-  uint32_t val[kRounds];
+  unsigned long long key[ROUNDS];
+  uint32_t val[ROUNDS];
 #pragma unroll
-  for (int r = 0; r < kRounds; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t j = wb + r * 64 + lane;
     key[r] = j < n ? k[j] : 0ull;
     val[r] = j < n ? v[j] : 0u;
   }
   const unsigned long long before = (lane == 0 && wb > 0 && wb < n) ? k[wb - 1] : 0ull;
-  const unsigned long long after = (lane == 63 && wb + kWaveElems < n) ? k[wb + kWaveElems] : 0ull;
-  uint8_t a[kRounds];
+  const unsigned long long after = (lane == 63 && wb + (ROUNDS * 64) < n) ? k[wb + (ROUNDS * 64)] : 0ull;
+  uint8_t a[ROUNDS];
   if (packed) {
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
+    for (int r = 0; r < ROUNDS; ++r) {
       a[r] = wb + r * 64 + lane < n ? (uint8_t)(val[r] >> 24) : kNotTransfer;
       val[r] &= kIdxMask;
     }
   } else {
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) a[r] = wb + r * 64 + lane < n ? aux[val[r]] : kNotTransfer;
+    for (int r = 0; r < ROUNDS; ++r) a[r] = wb + r * 64 + lane < n ? aux[val[r]] : kNotTransfer;
   }
   heads = tails = 0;
 #pragma unroll
-  for (int r = 0; r < kRounds; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t j = wb + r * 64 + lane;
     const bool in = j < n;
     unsigned long long prev = __shfl_up(key[r], 1, 64);
     unsigned long long next = __shfl_down(key[r], 1, 64);
     const unsigned long long last_before = r > 0 ? __shfl(key[r > 0 ? r - 1 : 0], 63, 64) : before;
-    const unsigned long long first_after = r + 1 < kRounds ? __shfl(key[r + 1 < kRounds ? r + 1 : r], 0, 64) : after;
+    const unsigned long long first_after = r + 1 < ROUNDS ? __shfl(key[r + 1 < ROUNDS ? r + 1 : r], 0, 64) : after;
     if (lane == 0) prev = last_before;
     if (lane == 63) next = first_after;
     heads |= (uint32_t)(in && (j == 0 || prev != key[r])) << r;
@@ -1737,7 +1680,7 @@ __device__ __forceinline__ void load_round(const unsigned long long* k, const ui
 // group end, so rounds are read from each end only until such a boundary
 // turns up (one round each for typical groups; all 16 for a group that
 // spans the wavefront).
-template <int MODE>
+template <int MODE, int ROUNDS>
 __device__ void ddrt_agg_body(const DDArgs& A) {
   using S = St<MODE>;
   const SortJob& s = *A.job;
@@ -1746,14 +1689,14 @@ __device__ void ddrt_agg_body(const DDArgs& A) {
   const uint32_t* v = s.vals[buf];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint32_t wid = blockIdx.x * (kT / 64) + w;
-  const uint32_t wb = wid * kWaveElems;
+  const uint32_t wb = wid * (ROUNDS * 64);
   const uint32_t ns = dd_len(A);
   const bool packed = A.n < kPackLimit;
   uint32_t cf = 0, cb = 0;
   FS<MODE> fv = S::fid();
   BS<MODE> bv = S::bid();
 #pragma unroll 1
-  for (int r = kRounds - 1; r >= 0; --r) {
+  for (int r = ROUNDS - 1; r >= 0; --r) {
     uint8_t a;
     bool head, tail;
     load_round(k, v, A.aux, ns, packed, wb + r * 64 + lane, a, head, tail);
@@ -1769,7 +1712,7 @@ __device__ void ddrt_agg_body(const DDArgs& A) {
     }
   }
 #pragma unroll 1
-  for (int r = 0; r < kRounds; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     uint8_t a;
     bool head, tail;
     load_round(k, v, A.aux, ns, packed, wb + r * 64 + lane, a, head, tail);
@@ -1793,8 +1736,9 @@ __device__ void ddrt_agg_body(const DDArgs& A) {
   }
 }
 
+template <int ROUNDS>
 __global__ __launch_bounds__(kT) void ddrt_agg_kernel(DDArgs A) {
-  if (A.ctl->max_ep < 4) ddrt_agg_body<0>(A); else ddrt_agg_body<1>(A);
+  if (A.ctl->max_ep < 4) ddrt_agg_body<0, ROUNDS>(A); else ddrt_agg_body<1, ROUNDS>(A);
 }
 
 // Carries between wavefronts (one block of 1,024 threads): the forward
@@ -1919,8 +1863,12 @@ __global__ __launch_bounds__(kCT) void ddrt_carry_kernel(DDArgs A, uint32_t nw) 
   if (A.ctl->max_ep < 4) ddrt_carry_body<0>(A, nw); else ddrt_carry_body<1>(A, nw);
 }
 
-template <int MODE>
-__device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[kWaveElems], uint8_t (*s_code)[kWaveElems]) {
+// ROUNDS: rounds of 64 elements per wavefront. MID: the carries come from the
+// wavefronts' aggregates themselves, 64 at a time back to the latest group
+// start (and on to the next group end) instead of from the carry kernel, and
+// the unused-transfer results are merged here (A.uth).
+template <int MODE, int ROUNDS, bool MID>
+__device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64], uint8_t (*s_code)[ROUNDS * 64]) {
   using S = St<MODE>;
   const SortJob& s = *A.job;
   const uint32_t buf = s.npasses & 1;
@@ -1928,14 +1876,48 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[kWaveElems], 
   const uint32_t* v = s.vals[buf];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint32_t wid = blockIdx.x * (kT / 64) + w;
-  const uint32_t wb = wid * kWaveElems;
+  const uint32_t wb = wid * (ROUNDS * 64);
   // per round: value and endpoint code (LDS), start/end flags and forward results (bits)
   uint32_t heads, tails, fres = 0;
   const uint32_t ns = dd_len(A);
-  load_wave(k, v, A.aux, ns, A.n < kPackLimit, wb, s_val[w], s_code[w], heads, tails);
-  FS<MODE> carry = get_f<MODE>(A.carry[wid].fs);
+  load_wave<ROUNDS>(k, v, A.aux, ns, A.n < kPackLimit, wb, s_val[w], s_code[w], heads, tails);
+  FS<MODE> carry = S::fid();
+  BS<MODE> bcarry = S::bid();
+  uint32_t unread = 0;  // bit r: this lane's element of round r is an unused transfer
+  if constexpr (MID) {
+    for (int r = 0; r < ROUNDS; ++r)
+      if (wb + r * 64 + lane < ns) unread |= (uint32_t)A.uth[s_val[w][r * 64 + lane]] << r;
+    for (int e = (int)wid - 1; e >= 0; e -= 64) {
+      const int q = e - 63 + lane;
+      uint32_t f = 0;
+      FS<MODE> x = S::fid();
+      if (q >= 0) {
+        f = A.agg[q].ff;
+        x = get_f<MODE>(A.agg[q].fs);
+      }
+      wave_fscan<MODE>(f, x);
+      carry = S::fop(S::lane(x, 63), carry);
+      if (lane32(f, 63)) break;
+    }
+    const int nw = (int)(gridDim.x * (kT / 64));
+    for (int e = (int)wid + 1; e < nw; e += 64) {
+      const int q = e + lane;
+      uint32_t g = 0;
+      BS<MODE> y = S::bid();
+      if (q < nw) {
+        g = A.agg[q].bf;
+        y = get_b<MODE>(A.agg[q].bs);
+      }
+      wave_bscan<MODE>(g, y);
+      bcarry = S::bop(bcarry, S::lane(y, 0));
+      if (lane32(g, 0)) break;
+    }
+  } else {
+    carry = get_f<MODE>(A.carry[wid].fs);
+    bcarry = get_b<MODE>(A.carry[wid].bs);
+  }
 #pragma unroll 1
-  for (int r = 0; r < kRounds; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     const uint8_t a = s_code[w][r * 64 + lane];
     const bool head = (heads >> r) & 1;
     uint32_t f = head;
@@ -1955,10 +1937,10 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[kWaveElems], 
     const FS<MODE> x63 = S::shfl(x, 63);
     carry = f63 ? x63 : S::fop(carry, x63);
   }
-  BS<MODE> bcarry = get_b<MODE>(A.carry[wid].bs);
+  unsigned long long c_ut = 0, b_ut = 0, t_ut = 0;
   unsigned long long c_dd = 0, c_grp = 0, c_tx = 0, c_rx = 0, b_dd = 0, t_dd = 0, b_rx = 0, t_rx = 0, t_el = 0;
 #pragma unroll 1
-  for (int r = kRounds - 1; r >= 0; --r) {
+  for (int r = ROUNDS - 1; r >= 0; --r) {
     const uint32_t j = wb + r * 64 + lane;
     const uint8_t a = s_code[w][r * 64 + lane];
     const bool tail = (tails >> r) & 1;
@@ -1975,6 +1957,7 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[kWaveElems], 
       if (fres & (1u << (2 * r))) res |= ODP_F_DD;
       if (fres & (2u << (2 * r))) res |= ODP_F_RT_RX;
       if (sr != d && S::tx(ex, sr, d)) res |= ODP_F_RT_TX;
+      if (MID && ((unread >> r) & 1)) res |= ODP_F_UT;
       c_grp += !(res & ODP_F_DD) && S::has_dst(ex, d);
       c_dd += (res & ODP_F_DD) != 0;
       c_tx += (res & ODP_F_RT_TX) != 0;
@@ -1990,23 +1973,24 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[kWaveElems], 
     bcarry = g0 ? y0 : S::bop(y0, bcarry);
   }
   // bytes and durations of the flagged records, four rounds of gathers in flight at a time
+  constexpr int kG = ROUNDS < 4 ? ROUNDS : 4;
   wave_lds_fence();
 #pragma unroll 1
-  for (int r0 = 0; r0 < kRounds; r0 += 4) {
-    uint64_t eb[4], ed[4];
-    uint8_t rs[4];
+  for (int r0 = 0; r0 < ROUNDS; r0 += kG) {
+    uint64_t eb[kG], ed[kG];
+    uint8_t rs[kG];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < kG; ++q) {
       rs[q] = s_code[w][(r0 + q) * 64 + lane];
       eb[q] = ed[q] = 0;
-      if (rs[q] & (ODP_F_DD | ODP_F_RT_RX)) {
+      if (rs[q] & (ODP_F_DD | ODP_F_RT_RX | (MID ? ODP_F_UT : 0))) {
         const odp_event& e = A.ev[s_val[w][(r0 + q) * 64 + lane]];
         eb[q] = e.bytes;
         ed[q] = e.t_end - e.t_start;
       }
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < kG; ++q) {
       t_el += ed[q];  // removable once, whether DD, RT_RX or both
       if (rs[q] & ODP_F_DD) {
         b_dd += eb[q];
@@ -2015,6 +1999,11 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[kWaveElems], 
       if (rs[q] & ODP_F_RT_RX) {
         b_rx += eb[q];
         t_rx += ed[q];
+      }
+      if (MID && (rs[q] & ODP_F_UT)) {
+        ++c_ut;
+        b_ut += eb[q];
+        t_ut += ed[q];
       }
     }
   }
@@ -2027,12 +2016,19 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[kWaveElems], 
   block_store<R_ADD>(A.parts.at(S_RT_BYTES), b_rx);
   block_store<R_ADD>(A.parts.at(S_RT_TIME), t_rx);
   block_store<R_ADD>(A.parts.at(S_ELIM_TX), t_el);
+  if constexpr (MID) {
+    block_store<R_ADD>(A.parts.at(S_UT_EVENTS), c_ut);
+    block_store<R_ADD>(A.parts.at(S_UT_BYTES), b_ut);
+    block_store<R_ADD>(A.parts.at(S_UT_TIME), t_ut);
+  }
 }
 
+template <int ROUNDS, bool MID>
 __global__ __launch_bounds__(kT) void ddrt_final_kernel(DDArgs A) {
-  __shared__ uint32_t s_val[kT / 64][kWaveElems];
-  __shared__ uint8_t s_code[kT / 64][kWaveElems];
-  if (A.ctl->max_ep < 4) ddrt_final_body<0>(A, s_val, s_code); else ddrt_final_body<1>(A, s_val, s_code);
+  __shared__ uint32_t s_val[kT / 64][ROUNDS * 64];
+  __shared__ uint8_t s_code[kT / 64][ROUNDS * 64];
+  if (A.ctl->max_ep < 4) ddrt_final_body<0, ROUNDS, MID>(A, s_val, s_code);
+  else ddrt_final_body<1, ROUNDS, MID>(A, s_val, s_code);
 }
 
 // ---------------------------------------------------------------------------
@@ -2663,7 +2659,6 @@ struct Alg2Args {
   const SortJob* job;        // the digest job (keys/vals in buffer npasses & 1)
   const uint8_t* aux;
   uint32_t n;                // records of the log
-  uint32_t small;            // 1: the digest job was sorted in one workgroup (every record kept)
   uint32_t* rx;              // [n] partner record, or kNone
   unsigned long long* npairs;
 };
@@ -2704,7 +2699,7 @@ __global__ __launch_bounds__(kT) void alg2_kernel(Alg2Args A) {
   const unsigned long long* k = s.keys[s.npasses & 1];
   const uint32_t* v = s.vals[s.npasses & 1];
   uint32_t* lists = s.vals[(s.npasses + 1) & 1];
-  const uint32_t n = A.small ? A.n : sorted_len(s), lane = threadIdx.x & 63;
+  const uint32_t n = sorted_len(s), lane = threadIdx.x & 63;
   const uint64_t lt = lanemask_lt();
   const uint32_t c0 = (blockIdx.x * kT + threadIdx.x) / 64 * 64;
   if (c0 >= n) return;
@@ -2817,12 +2812,14 @@ __global__ __launch_bounds__(kT) void alg2_kernel(Alg2Args A) {
   if (lane == 0 && pairs) atomicAdd(A.npairs, (unsigned long long)pairs);
 }
 
+#include "analyze_mid.h"
+
 // ---------------------------------------------------------------------------
 // Workspace layout.
 // ---------------------------------------------------------------------------
 enum Buf {
   B_CTL, B_JOBS, B_CLS, B_AUX, B_BKEY0, B_BKEY1, B_BVAL0, B_BVAL1, B_TILECNT, B_AD, B_K, B_PR, B_HIST,
-  B_TOTALS, B_SEG, B_SKEY, B_PARTS, B_UT, B_WSCAN
+  B_TOTALS, B_SEG, B_SKEY, B_PARTS, B_UT, B_WSCAN, B_MID
 };
 
 // Jobs 1..4 (the subsets) are sorted together in the same launches.
@@ -2868,7 +2865,47 @@ struct Views {
   WaveAgg* carry;
   unsigned long long* skey[2 * (kNumJobs - 1)];  // key ping-pong of the subset jobs
   Parts parts;                  // per-block partials of the grid-wide reductions
+  MidView mid;
 };
+
+// Arrays of the analysis of up to kMidMax records, for a workspace of cap
+// records; with base == null only their size is computed.
+size_t mid_views(MidView& m, char* base, size_t cap) {
+  const size_t c = (std::min<size_t>(cap, kMidMax) + kMidTile - 1) / kMidTile * kMidTile;
+  const size_t slots = (size_t)pair_table_mask((uint32_t)c) + 1, waves = c / kClsWave, blocks = c / kClsT;
+  char* p = base;
+  m.gid0 = carve<uint32_t>(p, c);
+  m.gid1 = carve<uint32_t>(p, c);
+  p = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(p) + 15) & ~uintptr_t(15));
+  m.dtab = carve<uint32_t>(p, slots);
+  m.h0 = carve<uint32_t>(p, c / kMidTile * kMidDigits);
+  m.h1 = carve<uint32_t>(p, c / kMidTile * kMidDigits);
+  m.uth = carve<uint8_t>(p, c);
+  m.ad_host = carve<uint64_t>(p, c);
+  m.ad_bytes = carve<uint64_t>(p, c);
+  m.kd_te = carve<uint64_t>(p, c);
+  m.node1 = carve<KernNode>(p, c / 64);
+  m.node2 = carve<KernNode>(p, c / 4096 + 1);
+  for (NearTable* t : {&m.ad, &m.ut}) {
+    p = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(p) + 15) & ~uintptr_t(15));  // read four slots at once
+    t->owner = carve<uint32_t>(p, slots);
+    t->bits = carve<unsigned long long>(p, slots * kChunkWords);
+    t->ckey = carve<uint32_t>(p, slots);
+    t->cfirst = carve<uint32_t>(p, slots);
+    t->clast = carve<uint32_t>(p, slots);
+    t->gid = carve<uint32_t>(p, c + 8) + 4;
+  }
+  const size_t nchunk = waves / kScanChunk + 1;
+  m.wscan.cnt = carve<uint32_t>(p, waves * kWaveCnt);
+  m.wscan.kmax = carve<uint64_t>(p, waves * kEp);
+  m.wscan.ccnt = carve<uint32_t>(p, nchunk * kWaveCnt);
+  m.wscan.cmax = carve<uint64_t>(p, nchunk * kEp);
+  m.wscan.nw = 0;
+  m.agg = carve<WaveAgg>(p, waves);
+  m.parts.p = carve<unsigned long long>(p, kSlots * blocks);
+  m.parts.stride = (uint32_t)blocks;
+  return (size_t)(p - base);
+}
 
 Views views(Workspace* ws) {
   Views v;
@@ -2948,6 +2985,7 @@ Views views(Workspace* ws) {
   for (int i = 0; i < 2 * (kNumJobs - 1); ++i) v.skey[i] = carve<unsigned long long>(pkey, cap);
   v.parts.p = static_cast<unsigned long long*>(b[B_PARTS].ptr);
   v.parts.stride = v.ntc;
+  mid_views(v.mid, static_cast<char*>(b[B_MID].ptr), cap);
   return v;
 }
 
@@ -3047,7 +3085,8 @@ int analyze_reserve(Workspace* ws, size_t max_events) {
   const uint32_t nt = ceil_div32(cap, kTile);
   DevBuf* b = ws->a_bufs;
   int e;
-  if ((e = b[B_CTL].ensure(sizeof(AnaCtl))) || (e = b[B_JOBS].ensure(sizeof(SortJob) * kNumJobs)) ||
+  MidView sized;
+  if ((e = b[B_MID].ensure(mid_views(sized, nullptr, cap) + 64)) || (e = b[B_CTL].ensure(sizeof(AnaCtl))) || (e = b[B_JOBS].ensure(sizeof(SortJob) * kNumJobs)) ||
       (e = b[B_CLS].ensure(cap)) || (e = b[B_AUX].ensure(cap)) || (e = b[B_BKEY0].ensure(cap * 8)) ||
       (e = b[B_BKEY1].ensure(cap * 8)) || (e = b[B_BVAL0].ensure(cap * 4)) || (e = b[B_BVAL1].ensure(cap * 4)) ||
       (e = b[B_TILECNT].ensure((size_t)nt * 4 * (2 + kWaveCnt * (kT / 64)))) ||
@@ -3696,12 +3735,119 @@ uint32_t first_digest_passes(size_t n) {
 
 using namespace odp;
 
-// The launch sequence of one analysis (of more than kTinyMax records unless
-// the literal Algorithm 2 pairs are asked for too, in alg2_rx / alg2_np), in
-// the workspace `ws` (reserved for n), enqueued on `stream`.
+// The launch sequence of one analysis of 1 .. kMidMax records.
+static int enqueue_mid(Workspace* ws, const odp_event* events, size_t n, uint8_t* out_flags, odp_report* out_report,
+                       hipStream_t stream, uint32_t* alg2_rx, unsigned long long* alg2_np) {
+  const Views v = views(ws);
+  const MidView& m = v.mid;
+  const uint32_t nn = (uint32_t)n, tiles = ceil_div32(n, kMidTile), blocks = ceil_div32(n, kT * kMidRounds),
+                 cblocks = ceil_div32(n, kClsT * kClsRounds);
+  AnaCtl* ctl = v.ctl;
+  // digest table: at most half full; its slot numbers split into two digits
+  uint32_t tb = 10;
+  while ((1ull << tb) < 2 * n) ++tb;
+  const uint32_t bits = (tb + 1) / 2;
+  static_assert(kMidMax <= 1u << 18 && kMidDigits >= 1u << 10, "two digits cover the table");
+
+  if (alg2_rx)
+    hipLaunchKernelGGL(alg2_fill_kernel, dim3(ceil_div32(n, kT)), dim3(kT), 0, stream, alg2_rx, nn, alg2_np);
+  hipLaunchKernelGGL(mid_clear_kernel, dim3(std::max<uint32_t>(1, (1u << tb) / (4 * kMidT))), dim3(kMidT), 0, stream, m.dtab,
+                     1u << tb, m.h0, tiles << bits, ctl, nn);
+  MidClassify C;
+  C.ev = events;
+  C.n = nn;
+  C.flags = out_flags;
+  C.cls = v.cls;
+  C.uth = m.uth;
+  C.gid = m.gid0;
+  C.val = v.bv[0];
+  C.wave_cnt = m.wscan.cnt;
+  C.wave_kmax = m.wscan.kmax;
+  C.dtab = m.dtab;
+  C.dmask = (1u << tb) - 1;
+  C.hist = m.h0;
+  C.bits = bits;
+  C.parts = m.parts;
+  hipLaunchKernelGGL(mid_classify_kernel, dim3(cblocks), dim3(kClsT), 0, stream, C);
+  WaveScan W = m.wscan;
+  W.nw = cblocks * (kClsT / 64);
+  const uint32_t nchunk = ceil_div32(W.nw, kScanChunk);
+  hipLaunchKernelGGL(mid_scan_kernel, dim3(nchunk * kScanQ + kMidSums), dim3(kMidT), 0, stream, W, nchunk, ctl, m.parts,
+                     cblocks, out_report, v.jobs + kJobBig);
+
+  // Fork: as in the pipeline for longer logs.
+  hipStream_t side = ws->a_side;
+  ODP_HIP(hipEventRecord(ws->a_fork, stream));
+  ODP_HIP(hipStreamWaitEvent(side, ws->a_fork, 0));
+  MidSide A;
+  A.ev = events;
+  A.cls = v.cls;
+  A.n = nn;
+  A.W = W;
+  A.S = v.S;
+  A.M = m;
+  A.T = v.pt;
+  A.flags = out_flags;
+  A.ctl = ctl;
+  UtArgs& U = A.U;
+  U = UtArgs{};
+  U.ev = events;
+  U.n_ut = &ctl->n_ut;
+  U.ut_idx = v.S.ut_idx;
+  U.ut_w_addr = v.S.ut_w_addr;
+  U.ut_w_code = v.S.ut_w_code;
+  U.ut_ts = v.S.ut_ts;
+  U.ut_kc = v.S.ut_kc;
+  U.ut_km = v.S.ut_km;
+  U.ut_hit = v.ut_hit;
+  U.kd_ts = v.S.kd_ts;
+  U.kd_idx = v.S.kd_idx;
+  U.ctl = ctl;
+  // (in turn: the host enqueues about as fast as the device runs)
+  hipLaunchKernelGGL(mid_subset_kernel, dim3(cblocks), dim3(kT), 0, side, A);
+  hipLaunchKernelGGL(mid_scatter_kernel, dim3(tiles), dim3(kMidT), 0, stream, 0u, nn, ctl, bits, m.h0, m.gid0, v.bv[0], m.gid1,
+                     nullptr, v.bv[1]);
+  hipLaunchKernelGGL(mid_link_kernel, dim3(2 * blocks), dim3(kT), 0, side, A);
+  hipLaunchKernelGGL(mid_hist_kernel, dim3(tiles), dim3(kMidT), 0, stream, ctl, bits, m.gid1, m.h1);
+  hipLaunchKernelGGL(mid_pair_kernel, dim3(blocks), dim3(kT), 0, side, A);
+  hipLaunchKernelGGL(mid_scatter_kernel, dim3(tiles), dim3(kMidT), 0, stream, 1u, nn, ctl, bits, m.h1, m.gid1, v.bv[1], nullptr,
+                     v.bk[0], v.bv[0]);
+  hipLaunchKernelGGL(mid_ra_ua_kernel, dim3(blocks), dim3(kT), 0, side, A);
+  ODP_HIP(hipEventRecord(ws->a_join, side));
+  DDArgs D{};
+  D.ev = events;
+  D.n = nn;
+  D.aux = v.aux;
+  D.job = v.jobs + kJobBig;
+  D.ctl = ctl;
+  D.agg = m.agg;
+  D.flags = out_flags;
+  D.rep = out_report;
+  D.parts = m.parts;
+  D.uth = m.uth;
+  hipLaunchKernelGGL(ddrt_agg_kernel<kMidRounds>, dim3(blocks), dim3(kT), 0, stream, D);
+  if (alg2_rx) {
+    Alg2Args G{};
+    G.job = v.jobs + kJobBig;
+    G.aux = v.aux;
+    G.n = nn;
+    G.rx = alg2_rx;
+    G.npairs = alg2_np;
+    hipLaunchKernelGGL(alg2_kernel, dim3(ceil_div32(n, kT)), dim3(kT), 0, stream, G);
+  }
+  ODP_HIP(hipStreamWaitEvent(stream, ws->a_join, 0));
+  hipLaunchKernelGGL((ddrt_final_kernel<kMidRounds, true>), dim3(blocks), dim3(kT), 0, stream, D);
+  hipLaunchKernelGGL(mid_finish_kernel, dim3(1), dim3(kMidT), 0, stream, m.parts, blocks, blocks, nn, ctl, out_report);
+  return check_hip(hipGetLastError(), "odp_analyze_trace launch");
+}
+
+// The launch sequence of one analysis (with the literal Algorithm 2 pairs when
+// alg2_rx / alg2_np are given), in the workspace `ws` (reserved for n), enqueued
+// on `stream`.
 static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, uint8_t* out_flags,
                             odp_report* out_report, hipStream_t stream, uint32_t* alg2_rx = nullptr,
                             unsigned long long* alg2_np = nullptr) {
+  if (n > 0 && n <= kMidMax) return enqueue_mid(ws, events, n, out_flags, out_report, stream, alg2_rx, alg2_np);
   const Views v = views(ws);
   const uint32_t nn = (uint32_t)n;
   const uint32_t nt = n ? ceil_div32(n, kTile) : 1;  // tiles of this call
@@ -3737,7 +3883,6 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   ODP_HIP(hipEventRecord(ws->a_fork, stream));
   ODP_HIP(hipStreamWaitEvent(side, ws->a_fork, 0));
 
-  const bool small = n <= kSmallMax;  // every job then has at most kSmallMax elements
   // The allocation path on the side stream, enqueued first (it waits only
   // for the classification), then the digest path on the caller's stream.
   WaveScan WS = v.wscan;
@@ -3775,14 +3920,10 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   const uint32_t side_blocks = std::min<uint32_t>(nt, (uint32_t)cus * 2);
   const JobSet Js{v.jobs + kJobAd, kSubsetJobs, side_blocks};
   hipLaunchKernelGGL(sort_plan_kernel, dim3(1), dim3(64), 0, side, Js, 0u);
-  if (small) {
-    hipLaunchKernelGGL(sort_small_kernel, dim3(Js.njobs), dim3(kQT), 0, side, Js);
-  } else {
-    for (uint32_t p = 0; p < 9; ++p) {
-      hipLaunchKernelGGL(sort_hist_kernel, dim3(Js.njobs * side_blocks), dim3(kT), 0, side, Js, p);
-      hipLaunchKernelGGL(sort_scan_kernel, dim3(256 * Js.njobs), dim3(kT), 0, side, Js, p);
-      hipLaunchKernelGGL(sort_scatter_kernel, dim3(Js.njobs * side_blocks), dim3(kST), 0, side, Js, p);
-    }
+  for (uint32_t p = 0; p < 9; ++p) {
+    hipLaunchKernelGGL(sort_hist_kernel, dim3(Js.njobs * side_blocks), dim3(kT), 0, side, Js, p);
+    hipLaunchKernelGGL(sort_scan_kernel, dim3(256 * Js.njobs), dim3(kT), 0, side, Js, p);
+    hipLaunchKernelGGL(sort_scatter_kernel, dim3(Js.njobs * side_blocks), dim3(kST), 0, side, Js, p);
   }
   // Pairing and the pair list.
   PairArgs P;
@@ -3840,27 +3981,22 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   // Records by digest (up to 8 passes), then duplicates and round trips, on
   // the caller's stream.
   const JobSet Jb{v.jobs + kJobBig, 1, nt};
-  const uint32_t kfirst = small ? 0u : first_digest_passes(n);
+  const uint32_t kfirst = first_digest_passes(n);
   const uint32_t nft = (uint32_t)((n + kFixTile - 1) / kFixTile);  // tiles of the local fix
   // the digest histograms take two tiles per block on long logs (measured a
   // little faster than one: the per-block start-up is amortised)
   const JobSet Jh{v.jobs + kJobBig, 1, nt > 4u * (uint32_t)cus ? (nt + 1) / 2 : nt};
   hipLaunchKernelGGL(sort_plan_kernel, dim3(1), dim3(64), 0, stream, Jb, kfirst);
-  if (small) {
-    hipLaunchKernelGGL(sort_small_kernel, dim3(Jb.njobs), dim3(kQT), 0, stream, Jb);
-  } else {
-    for (uint32_t p = 0; p < 8; ++p) {
-      if (kfirst && p == kfirst) hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, p);
-      hipLaunchKernelGGL(sort_hist_kernel, dim3(Jh.stride), dim3(kT), 0, stream, Jh, p);
-      hipLaunchKernelGGL(sort_scan_kernel, dim3(256), dim3(kT), 0, stream, Jb, p);
-      hipLaunchKernelGGL(sort_scatter_kernel, dim3(nt), dim3(kST), 0, stream, Jb, p);
-    }
-    if (kfirst) hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, kFixFinal);
+  for (uint32_t p = 0; p < 8; ++p) {
+    if (p == kfirst) hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, p);
+    hipLaunchKernelGGL(sort_hist_kernel, dim3(Jh.stride), dim3(kT), 0, stream, Jh, p);
+    hipLaunchKernelGGL(sort_scan_kernel, dim3(256), dim3(kT), 0, stream, Jb, p);
+    hipLaunchKernelGGL(sort_scatter_kernel, dim3(nt), dim3(kST), 0, stream, Jb, p);
   }
+  hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, kFixFinal);
   DDArgs D;
   D.ev = events;
   D.n = nn;
-  D.small = small;
   D.aux = v.aux;
   D.job = v.jobs + kJobBig;
   D.ctl = ctl;
@@ -3869,9 +4005,10 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   D.flags = out_flags;
   D.rep = out_report;
   D.parts = v.parts;
-  hipLaunchKernelGGL(ddrt_agg_kernel, dim3(nt), dim3(kT), 0, stream, D);
+  D.uth = nullptr;
+  hipLaunchKernelGGL(ddrt_agg_kernel<kRounds>, dim3(nt), dim3(kT), 0, stream, D);
   hipLaunchKernelGGL(ddrt_carry_kernel, dim3(1), dim3(kCT), 0, stream, D, nt * (kT / 64));
-  hipLaunchKernelGGL(ddrt_final_kernel, dim3(nt), dim3(kT), 0, stream, D);
+  hipLaunchKernelGGL((ddrt_final_kernel<kRounds, false>), dim3(nt), dim3(kT), 0, stream, D);
   hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_ELIM_TX + 1 - S_DD_EVENTS), dim3(kT), 0, stream, v.parts, nt,
                      (uint32_t)S_DD_EVENTS, ctl, out_report);
   if (alg2_rx) {
@@ -3879,7 +4016,6 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
     G.job = v.jobs + kJobBig;
     G.aux = v.aux;
     G.n = nn;
-    G.small = small;
     G.rx = alg2_rx;
     G.npairs = alg2_np;
     hipLaunchKernelGGL(alg2_kernel, dim3(ceil_div32(n, kT)), dim3(kT), 0, stream, G);

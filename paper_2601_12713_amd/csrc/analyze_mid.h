@@ -1,0 +1,818 @@
+// Logs of kTinyMax / kWalkMax + 1 .. kMidMax records (part of analyze.hip).
+//
+// Such a log is bound by the number and the latency of its launches, not by its
+// bytes: the 79 launches of the pipeline for longer logs took 290 us for 100,000
+// records, whose bytes take 2. Random accesses to tables that stay in the caches
+// are cheap here (25 G compare-and-swaps a second), so the groups come from hash
+// tables, and 13 launches remain, the longest chain 9: 113 us. (At 10.7 million
+// records the same tables would cost 0.4 ms per access to each record, more
+// than the sort passes; 262,144 records, the last here: 150 us against 330.)
+//
+//   clear     the digest table, the call's counters
+//   classify  as in the pipeline; each transfer also finds its digest's slot in
+//             the table: its group number, exact, so the sort that follows
+//             needs two passes over the group number and no fix-up
+//   scan      wavefront counts and the classification's sums
+//   digest path: two scatters (each sums the tile histograms it needs itself),
+//             group aggregates, DD/RT (carries looked up, not scanned)
+//   other path: subsets; unused transfers and the groups of ALLOC/DELETE
+//             records; pairing and RA table; RA/UA. The nearest record of a
+//             group comes from the group's table entries per chunk of 2,048
+//             records (NearTable) instead of a sort
+//   finish    all sums into the report
+#pragma once
+
+constexpr uint32_t kMidMax = 262144;
+constexpr int kMidT = 1024, kMidRounds = 2;
+constexpr uint32_t kMidTile = kMidT * kMidRounds;           // records (elements) per workgroup
+constexpr uint32_t kMidWave = 64 * kMidRounds;              // ... per wavefront
+constexpr uint32_t kMidDigits = 1024;                       // at most, per pass
+constexpr uint32_t kChunkBits = 11;                         // positions per chunk of a NearTable: 2,048
+constexpr uint32_t kChunkWords = (kMidMax >> kChunkBits) / 64;
+static_assert((kMidMax >> kChunkBits) % 64 == 0 && kChunkWords == 2, "a chunk is one bit of two words");
+
+// Groups of equal keys over a list of positions (0 .. m - 1, m <= kMidMax),
+// and the nearest earlier or later position of a group. A position's group is
+// the slot of its key in an open-addressing table. Per group, a bit for each
+// chunk of positions that holds it; per (group, chunk), the first and the last
+// such position. Within a chunk the neighbour is searched from the position
+// itself, only when the chunk's first (last) says that there is one.
+struct NearTable {
+  uint32_t* owner;           // group table (below)
+  unsigned long long* bits;  // [slots][kChunkWords]
+  uint32_t *ckey, *cfirst, *clast;  // 0 empty, else (group << 7 | chunk) + 1; complement of the first; last + 1
+  uint32_t* gid;             // per position; four words of padding before and after
+};
+
+// (grid-stride over the workgroups of the launch)
+__device__ __forceinline__ void near_clear(const NearTable& T, uint32_t m, uint32_t start, uint32_t step) {
+  const uint32_t slots = pair_table_mask(m) + 1;
+  for (uint32_t i = start; i < slots; i += step) {
+    T.owner[i] = T.ckey[i] = T.cfirst[i] = T.clast[i] = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kChunkWords; ++w) T.bits[(size_t)i * kChunkWords + w] = 0;
+  }
+}
+
+// Group tables: a slot is 0 or holds its owner (the index that claimed it, plus
+// one) and a tag of the owner's hash, so a slot of another key is told apart
+// without reading that key. Four slots are read at once. A slot read as empty
+// may be stale, which costs the compare-and-swap only; owners never change.
+constexpr uint32_t kOwnerBits = 19;
+static_assert(kMidMax < 1u << kOwnerBits, "owners fit");
+struct Probe {
+  uint32_t bucket, pos, tag;  // first slot of the bucket, next slot in it, tag in place
+  uint32_t need;              // 1 while the group is not known; then the group is bucket + pos
+};
+__device__ __forceinline__ Probe probe_start(uint32_t hash, uint32_t mask, bool need) {
+  return Probe{hash & mask & ~3u, 0, (hash >> kOwnerBits) << kOwnerBits, need};
+}
+__device__ __forceinline__ void probe_next(Probe& p, uint32_t mask) {
+  if (++p.pos == 4) {
+    p.pos = 0;
+    p.bucket = (p.bucket + 4) & mask;
+  }
+}
+// One step over the bucket's words: claims the first empty slot for owner own
+// (then the group is known: returns 0), or returns the owner + 1 to compare
+// with, or 0 with p moved on to the next bucket.
+__device__ __forceinline__ uint32_t probe_step(Probe& p, const uint4& v, uint32_t* table, uint32_t mask, uint32_t own) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t hit = 4, o = 0;
+#pragma unroll
+  for (int k = 3; k >= 0; --k)
+    if ((uint32_t)k >= p.pos && (w[k] == 0 || (w[k] >> kOwnerBits) << kOwnerBits == p.tag)) {
+      hit = (uint32_t)k;
+      o = w[k];
+    }
+  if (hit == 4) {
+    p.bucket = (p.bucket + 4) & mask;
+    p.pos = 0;
+    return 0;
+  }
+  p.pos = hit;
+  if (o == 0) {
+    o = atomicCAS(table + p.bucket + hit, 0u, p.tag | (own + 1));
+    if (o == 0) {
+      p.need = 0;
+      return 0;
+    }
+    if ((o >> kOwnerBits) << kOwnerBits != p.tag) {  // taken meanwhile, by another key
+      probe_next(p, mask);
+      return 0;
+    }
+  }
+  return o & ((1u << kOwnerBits) - 1);
+}
+
+// Position q's group, by key words a (64 bits) and b (small) of every position.
+// All lanes of a wavefront call it and leave it together.
+__device__ __forceinline__ uint32_t near_group(const NearTable& T, uint32_t mask, uint32_t q, bool in, const uint64_t* a,
+                                               const uint64_t* b) {
+  const uint64_t ka = in ? a[q] : 0ull, kb = in ? b[q] : 0ull;
+  Probe p = probe_start(near_hash(ka, kb), mask, in);
+  while (__ballot(p.need)) {
+    if (!p.need) continue;
+    const uint32_t o = probe_step(p, *reinterpret_cast<const uint4*>(T.owner + p.bucket), T.owner, mask, q);
+    if (o) {
+      if (a[o - 1] == ka && b[o - 1] == kb) p.need = 0; else probe_next(p, mask);
+    }
+  }
+  return p.bucket + p.pos;
+}
+
+__device__ __forceinline__ uint32_t near_slot(const NearTable& T, uint32_t mask, uint32_t g, uint32_t chunk, bool insert) {
+  const uint32_t key = (g << 7 | chunk) + 1;
+  uint32_t h = near_hash(key, 0) & mask;
+  for (;;) {
+    uint32_t o = T.ckey[h];
+    if (o == 0 && insert) o = atomicCAS(T.ckey + h, 0u, key);
+    if (o == 0 || o == key) break;
+    h = (h + 1) & mask;
+  }
+  return h;
+}
+
+// Enters 64 consecutive positions q (one per lane, from a multiple of 64;
+// lanes with in == false take no part). A position followed (preceded) by its
+// group within four lanes leaves the last (first) to that one: hot groups would
+// otherwise send every lane's update to one word.
+__device__ __forceinline__ void near_insert(const NearTable& T, uint32_t m, uint32_t q, bool in, const uint64_t* a,
+                                            const uint64_t* b) {
+  const uint32_t mask = pair_table_mask(m), lane = threadIdx.x & 63;
+  const uint32_t gq = near_group(T, mask, q, in, a, b), g = in ? gq : kNone;
+  if (in) T.gid[q] = g;
+  bool first = in, last = in;
+#pragma unroll
+  for (int o = 1; o <= 4; ++o) {
+    const uint32_t up = (uint32_t)__shfl_up((int)g, o, 64), dn = (uint32_t)__shfl_down((int)g, o, 64);
+    if ((int)lane >= o && up == g) first = false;
+    if ((int)lane + o < 64 && dn == g) last = false;
+  }
+  if (!(first || last)) return;
+  const uint32_t c = q >> kChunkBits;
+  unsigned long long* w = T.bits + (size_t)g * kChunkWords + (c >> 6);
+  if (!((*w >> (c & 63)) & 1)) atomicOr(w, 1ull << (c & 63));
+  const uint32_t h = near_slot(T, mask, g, c, true);
+  if (first && T.cfirst[h] < ~q) atomicMax(T.cfirst + h, ~q);
+  if (last && T.clast[h] < q + 1) atomicMax(T.clast + h, q + 1);
+}
+
+// The nearest earlier (later) position of q's group, or kNone.
+__device__ __forceinline__ uint32_t near_prev(const NearTable& T, uint32_t mask, uint32_t q) {
+  const uint32_t g = T.gid[q], c = q >> kChunkBits;
+  if (~T.cfirst[near_slot(T, mask, g, c, false)] < q) {
+    // four at a time (the list is padded by four in front)
+    for (const uint32_t* p = T.gid + q;; p -= 4) {
+      const uint32_t x[4] = {p[-1], p[-2], p[-3], p[-4]};
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (x[k] == g) return (uint32_t)(p - T.gid) - 1 - k;
+    }
+  }
+  for (int w = (int)(c >> 6); w >= 0; --w) {
+    unsigned long long b = T.bits[(size_t)g * kChunkWords + w];
+    if (w == (int)(c >> 6)) b &= (1ull << (c & 63)) - 1;
+    if (b) return T.clast[near_slot(T, mask, g, (uint32_t)w * 64 + 63 - (uint32_t)__builtin_clzll(b), false)] - 1;
+  }
+  return kNone;
+}
+__device__ __forceinline__ uint32_t near_next(const NearTable& T, uint32_t mask, uint32_t q) {
+  const uint32_t g = T.gid[q], c = q >> kChunkBits;
+  if (T.clast[near_slot(T, mask, g, c, false)] - 1 > q) {
+    for (const uint32_t* p = T.gid + q;; p += 4) {  // (and behind)
+      const uint32_t x[4] = {p[1], p[2], p[3], p[4]};
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (x[k] == g) return (uint32_t)(p - T.gid) + 1 + k;
+    }
+  }
+  for (uint32_t w = c >> 6; w < kChunkWords; ++w) {
+    unsigned long long b = T.bits[(size_t)g * kChunkWords + w];
+    if (w == c >> 6) b &= (c & 63) == 63 ? 0ull : ~0ull << ((c & 63) + 1);
+    if (b) return ~T.cfirst[near_slot(T, mask, g, w * 64 + (uint32_t)__builtin_ctzll(b), false)];
+  }
+  return kNone;
+}
+
+// Extremes of the starts and ends of 64 (and of 4,096) consecutive kernels of
+// the per-device lists, for logs that are not chronological.
+struct KernNode {
+  uint64_t smin, smax, emin, emax;
+};
+
+struct MidView {
+  uint32_t *gid0, *gid1;   // digest group of each record (kNone: no transfer); of each element after the first pass
+  uint32_t* dtab;          // digest table: 1 + the record that claimed the slot
+  uint32_t *h0, *h1;       // [tiles][digits] of the two passes
+  uint8_t* uth;            // per record: 1 for an unused transfer
+  uint64_t *ad_host, *ad_bytes;  // per ALLOC/DELETE: host address, bytes
+  uint64_t* kd_te;         // per kernel of the per-device lists: end
+  KernNode *node1, *node2; // per 64, per 4,096 of them
+  NearTable ad, ut;
+  WaveScan wscan;
+  WaveAgg* agg;
+  Parts parts;
+};
+
+// ---------------------------------------------------------------------------
+// Digest path.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kMidT) void mid_clear_kernel(uint32_t* dtab, uint32_t slots, uint32_t* hist, uint32_t nhist,
+                                                          AnaCtl* ctl, uint32_t n) {
+  const uint32_t t = blockIdx.x * kMidT + threadIdx.x;
+  for (uint32_t i = t; i < slots; i += gridDim.x * kMidT) dtab[i] = 0;
+  for (uint32_t i = t; i < nhist; i += gridDim.x * kMidT) hist[i] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < kScanQ) ctl->scan_tq[threadIdx.x] = 0;
+  if (t == 0) {
+    ctl->n = n;
+    ctl->ut_need_sort = ctl->scan_ticket = 0;
+  }
+}
+
+struct MidClassify {
+  const odp_event* ev;
+  uint32_t n;
+  uint8_t *flags, *cls, *uth;
+  uint32_t *gid, *val;
+  uint32_t* wave_cnt;
+  uint64_t* wave_kmax;
+  uint32_t *dtab, dmask;
+  uint32_t* hist;
+  uint32_t bits;
+  Parts parts;
+};
+
+// 256 threads and one record each: a workgroup's time is a chain of memory
+// round trips (record, table, compare-and-swap), so the log is spread over as
+// many compute units as there are (100,000 records: 30 us with workgroups of
+// 2,048 records, 18 us with 256). The first pass's tile histograms are summed by
+// atomics then (kMidTile / 256 workgroups each).
+constexpr int kClsT = 256, kClsRounds = 1;
+constexpr uint32_t kClsWave = 64 * kClsRounds;
+__global__ __launch_bounds__(kClsT) void mid_classify_kernel(MidClassify A) {
+  constexpr int kW = kClsT / 64, R = kClsRounds;
+  __shared__ uint32_t s_kdev[kW][kEp];
+  __shared__ unsigned long long s_kmax[kW][kEp];
+  __shared__ uint32_t s_h[kMidDigits];
+  const odp_event* __restrict__ ev = A.ev;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t n = A.n, wid = blockIdx.x * kW + w, wb = wid * kClsWave;
+  for (uint32_t d = threadIdx.x; d < (1u << A.bits); d += kClsT) s_h[d] = 0;
+  if (lane < kEp) {
+    s_kdev[w][lane] = 0;
+    s_kmax[w][lane] = 0;
+  }
+  __syncthreads();
+  odp_event e[R];
+  uint64_t before[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = wb + r * 64 + lane;
+    before[r] = 0;
+    if (i < n) {
+      e[r] = ev[i];
+      if (i) before[r] = ev[i - 1].t_start;
+    }
+  }
+  unsigned long long n_inv = 0, n_tx = 0, n_k = 0, tmin = ~0ull, tmax = 0;
+  uint32_t bad = kNone, mep = 0, c_ad = 0, c_k = 0, c_ut = 0;
+  uint32_t code[R];
+  Probe pr[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = wb + r * 64 + lane;
+    uint8_t c = C_INVALID;
+    code[r] = kNotTransfer;
+    pr[r] = Probe{0, 0, 0, 0};
+    if (i < n) {
+      const odp_event& x = e[r];
+      const bool is_tx = x.op == ODP_H2D || x.op == ODP_D2H || x.op == ODP_D2D;
+      const bool valid = x.op >= ODP_ALLOC && x.op <= ODP_KERNEL && x.t_end >= x.t_start && x.t_start >= before[r] &&
+                         dev_ok(x.dst_dev) && (!is_tx || dev_ok(x.src_dev));
+      if (valid) {
+        tmin = min(tmin, (unsigned long long)x.t_start);
+        tmax = max(tmax, (unsigned long long)x.t_end);
+        if (is_tx) {
+          c = x.op != ODP_D2H && x.dst_dev >= 0 ? C_COPYIN : C_TRANSFER;
+          code[r] = (uint32_t)(x.src_dev + 1) << 4 | (uint32_t)(x.dst_dev + 1);
+          mep = max(mep, (uint32_t)max(x.src_dev + 1, x.dst_dev + 1));
+          pr[r] = probe_start(near_hash(x.digest, 0), A.dmask, true);
+          ++n_tx;
+        } else if (x.op == ODP_KERNEL) {
+          c = C_KERNEL;
+          ++n_k;
+          atomicAdd(&s_kdev[w][x.dst_dev + 1], 1u);
+          atomicMax(&s_kmax[w][x.dst_dev + 1], (unsigned long long)x.t_end);
+        } else {
+          c = C_ALLOCDEL;
+        }
+      } else {
+        ++n_inv;
+        bad = min(bad, i);
+      }
+      A.flags[i] = valid ? 0 : ODP_F_INVALID;
+      A.cls[i] = c;
+      A.uth[i] = 0;
+    }
+    c_ad += (uint32_t)__popcll(__ballot(c == C_ALLOCDEL));
+    c_k += (uint32_t)__popcll(__ballot(c == C_KERNEL));
+    c_ut += (uint32_t)__popcll(__ballot(c == C_COPYIN));
+  }
+  // Digest groups: both rounds' probes in flight together. The loop runs while
+  // any lane of the wavefront probes, so all lanes leave it together.
+  for (;;) {
+    uint32_t any = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) any |= pr[r].need;
+    if (!__ballot(any)) break;
+    uint4 v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (pr[r].need) v[r] = *reinterpret_cast<const uint4*>(A.dtab + pr[r].bucket);
+    uint32_t o[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) o[r] = pr[r].need ? probe_step(pr[r], v[r], A.dtab, A.dmask, wb + r * 64 + lane) : 0u;
+    uint64_t od[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) od[r] = o[r] ? ev[o[r] - 1].digest : 0ull;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (o[r]) {
+        if (od[r] == e[r].digest) pr[r].need = 0; else probe_next(pr[r], A.dmask);
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = wb + r * 64 + lane;
+    if (i < n) {
+      const bool tx = code[r] != kNotTransfer;
+      const uint32_t g = pr[r].bucket + pr[r].pos;
+      A.gid[i] = tx ? g : kNone;
+      A.val[i] = i | code[r] << 24;
+      if (tx) atomicAdd(&s_h[g & ((1u << A.bits) - 1)], 1u);
+    }
+  }
+  if (lane == 0) {
+    A.wave_cnt[kWaveCnt * wid] = c_ad;
+    A.wave_cnt[kWaveCnt * wid + 1] = c_k;
+    A.wave_cnt[kWaveCnt * wid + 2] = c_ut;
+  }
+  __syncthreads();
+  const uint32_t tile = blockIdx.x / (kMidTile / (kClsT * kClsRounds));
+  for (uint32_t d = threadIdx.x; d < (1u << A.bits); d += kClsT)
+    if (s_h[d]) atomicAdd(A.hist + ((size_t)tile << A.bits | d), s_h[d]);
+  if (lane < kEp) {
+    A.wave_cnt[kWaveCnt * wid + 3 + lane] = s_kdev[w][lane];
+    A.wave_kmax[kEp * wid + lane] = s_kmax[w][lane];
+  }
+  block_store<R_ADD, kClsT>(A.parts.at(S_N_INVALID), n_inv);
+  block_store<R_ADD, kClsT>(A.parts.at(S_N_TRANSFERS), n_tx);
+  block_store<R_ADD, kClsT>(A.parts.at(S_N_KERNELS), n_k);
+  block_store<R_MIN, kClsT>(A.parts.at(S_FIRST_BAD), bad);
+  block_store<R_MAX, kClsT>(A.parts.at(S_MAX_EP), mep);
+  block_store<R_MIN, kClsT>(A.parts.at(S_TMIN), tmin);
+  block_store<R_MAX, kClsT>(A.parts.at(S_TMAX), tmax);
+}
+
+// The wavefront scans and, in further workgroups, the classification's sums.
+constexpr uint32_t kMidSums = 7;
+__global__ __launch_bounds__(kMidT) void mid_scan_kernel(WaveScan S, uint32_t nchunk, AnaCtl* ctl, Parts parts, uint32_t nb,
+                                                         odp_report* rep, SortJob* big) {
+  if (blockIdx.x < nchunk * kScanQ) {
+    wave_scan_body(S, nchunk, ctl);
+    return;
+  }
+  constexpr uint32_t kSlot[kMidSums] = {S_N_INVALID, S_N_TRANSFERS, S_N_KERNELS, S_FIRST_BAD, S_MAX_EP, S_TMIN, S_TMAX};
+  const uint32_t k = blockIdx.x - nchunk * kScanQ;
+  reduce_slot<kMidT>(parts, nb, kSlot[k], ctl, rep);
+  if (k == 0 && threadIdx.x == 0) big->npasses = 2;  // the sorted order ends in keys[0], vals[0]
+}
+
+// One pass of the stable sort by group number: a tile of kMidTile elements per
+// workgroup. Digit d of all tiles is summed by thread d, which gives the
+// global start of the digit and of this tile's share of it without a scan
+// launch between (128 tiles at most).
+__global__ __launch_bounds__(kMidT) void mid_scatter_kernel(uint32_t pass, uint32_t n, const AnaCtl* ctl, uint32_t bits,
+                                                            const uint32_t* __restrict__ hist,
+                                                            const uint32_t* __restrict__ gid,
+                                                            const uint32_t* __restrict__ val, uint32_t* gid_out,
+                                                            unsigned long long* key_out, uint32_t* val_out) {
+  constexpr int kW = kMidT / 64, R = kMidRounds;
+  __shared__ uint32_t s_cnt[kW * kMidDigits];
+  __shared__ uint32_t s_wt[16];
+  const uint32_t nel = pass == 0 ? n : ctl->n_tx, tb = blockIdx.x * kMidTile;
+  if (tb >= nel) return;
+  const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6, nd = 1u << bits, shift = pass * bits;
+  const uint32_t tiles = (nel + kMidTile - 1) / kMidTile;
+  uint32_t g[R], v[R], rk[R], dg[R], in[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t j = tb + w * kMidWave + r * 64 + lane;
+    g[r] = j < nel ? gid[j] : kNone;
+    v[r] = j < nel ? val[j] : 0u;
+    in[r] = g[r] != kNone;
+    dg[r] = in[r] ? (g[r] >> shift) & (nd - 1) : 0u;
+  }
+  uint32_t earlier = 0, all = 0;
+  if (t < nd) {
+#pragma unroll 8
+    for (uint32_t x = 0; x < tiles; ++x) {
+      const uint32_t c = hist[(size_t)x << bits | t];
+      earlier += x < blockIdx.x ? c : 0u;
+      all += c;
+    }
+  }
+  for (uint32_t x = t; x < kW * nd; x += kMidT) s_cnt[x] = 0;
+  __syncthreads();
+  uint32_t* const mine = s_cnt + w * nd;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    uint64_t peers = __ballot(in[r]);
+    for (uint32_t b = 0; b < bits; ++b) {
+      const bool bit = (dg[r] >> b) & 1;
+      const uint64_t m = __ballot(bit);
+      peers &= bit ? m : ~m;
+    }
+    const uint32_t before = in[r] ? mine[dg[r]] : 0u;
+    rk[r] = before + (uint32_t)__popcll(peers & lanemask_lt());
+    wave_lds_fence();
+    if (in[r] && (peers >> lane) == 1ull) mine[dg[r]] = before + (uint32_t)__popcll(peers);
+    wave_lds_fence();
+  }
+  uint32_t total;
+  const uint32_t start = block_xscan<uint32_t, false>(all, s_wt, total);  // (its barriers order s_cnt too)
+  if (t < nd) {
+    uint32_t run = start + earlier;
+    for (int x = 0; x < kW; ++x) {
+      const uint32_t c = s_cnt[x * nd + t];
+      s_cnt[x * nd + t] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (!in[r]) continue;
+    const uint32_t p = mine[dg[r]] + rk[r];
+    if (pass == 0) gid_out[p] = g[r]; else key_out[p] = g[r];
+    val_out[p] = v[r];
+  }
+}
+
+__global__ __launch_bounds__(kMidT) void mid_hist_kernel(const AnaCtl* ctl, uint32_t bits, const uint32_t* __restrict__ gid,
+                                                         uint32_t* __restrict__ hist) {
+  __shared__ uint32_t s_h[kMidDigits];
+  const uint32_t nel = ctl->n_tx, tb = blockIdx.x * kMidTile, t = threadIdx.x, nd = 1u << bits;
+  if (tb >= nel) return;
+  s_h[t] = 0;
+  uint32_t g[kMidRounds];
+#pragma unroll
+  for (int r = 0; r < kMidRounds; ++r) {
+    const uint32_t j = tb + r * kMidT + t;
+    g[r] = j < nel ? gid[j] : kNone;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kMidRounds; ++r)
+    if (g[r] != kNone) atomicAdd(&s_h[(g[r] >> bits) & (nd - 1)], 1u);
+  __syncthreads();
+  if (t < nd) hist[(size_t)blockIdx.x << bits | t] = s_h[t];
+}
+
+// ---------------------------------------------------------------------------
+// Allocation and unused-transfer path.
+// ---------------------------------------------------------------------------
+struct MidSide {
+  const odp_event* ev;
+  const uint8_t* cls;
+  uint32_t n;
+  WaveScan W;
+  SubsetOut S;
+  MidView M;
+  PairTable T;
+  UtArgs U;
+  uint8_t* flags;
+  AnaCtl* ctl;
+};
+
+// Ordered compaction of the subsets (as subset_scatter_kernel, a round per
+// wavefront), and the clearing of the tables that the next launches fill.
+__global__ __launch_bounds__(kT) void mid_subset_kernel(MidSide A) {
+  const AnaCtl* c = A.ctl;
+  {
+    const uint32_t start = blockIdx.x * kT + threadIdx.x, step = gridDim.x * kT;
+    near_clear(A.M.ad, c->n_ad, start, step);
+    near_clear(A.M.ut, c->n_ut, start, step);
+    const uint32_t slots = pair_table_mask(c->n_ad / 2) + 1;
+    for (uint32_t i = start; i < slots; i += step) {
+      A.T.owner[i] = 0;
+      A.T.first[i] = kNone;
+      A.T.multi[i] = 0;
+    }
+  }
+  subset_scatter_body<kClsRounds, true>(A.ev, A.cls, A.n, A.W, A.S, Parts{}, A.M.ad_host, A.M.ad_bytes, A.M.kd_te);
+}
+
+// Unused transfers by the forward search, and the groups of the ALLOC/DELETE
+// records.
+// The forward search of ut_scan_body over a longer stretch: the staged copies
+// are hashes of their places, compared in full when equal. A log whose devices
+// each run a kernel every few hundred copies needs no group table for its
+// copies then (with 64 copies ahead, 200,000 records on three devices did: the
+// table's insertion and lookups took 340 us).
+constexpr uint32_t kMidWindow = 1024;
+__device__ void mid_ut_scan(const MidSide& A, uint32_t block, uint32_t nblocks) {
+  const UtArgs& U = A.U;
+  const uint32_t n = *U.n_ut;
+  if (U.ctl->first_bad != kNone) {
+    if (n && block == 0 && threadIdx.x == 0) U.ctl->ut_need_sort = 1;
+    return;
+  }
+  constexpr uint32_t kStage = kT + kMidWindow;
+  __shared__ uint32_t s_ix[kStage], s_h[kStage + 8];  // (read eight at a time)
+  for (uint32_t b0 = block * kT; b0 < n; b0 += nblocks * kT) {
+    // s_*[x] holds copy-in b0 + 1 + x (index kNone past the last)
+    for (uint32_t x = threadIdx.x; x < kStage; x += kT) {
+      const uint32_t r = b0 + 1 + x;
+      s_ix[x] = r < n ? U.ut_idx[r] : kNone;
+      s_h[x] = r < n ? A.S.ut_vals[r] : 0u;
+    }
+    __syncthreads();
+    const uint32_t q = b0 + threadIdx.x;
+    if (q < n) {
+      const uint64_t code = U.ut_w_code[q], ts = U.ut_ts[q];
+      const uint32_t d = (uint32_t)(code & 15), k = U.ut_kc[q], total = U.ctl->kd_total[d];
+      uint8_t hit = 0;  // a kernel is still running
+      if (!(k > 0 && U.ut_km[q] >= ts)) {
+        if (k == total) {
+          hit = 1;  // no kernel follows
+        } else {
+          const uint32_t kp = U.ctl->kd_base[d] + k, kidx = U.kd_idx[kp], h = A.S.ut_vals[q];
+          const uint64_t sk = U.kd_ts[kp], addr = U.ut_w_addr[q];
+          // end: the staged copies logged before the kernel, kMidWindow of them at most
+          uint32_t x = threadIdx.x, end = x, top = x + kMidWindow;
+          while (end < top) {
+            const uint32_t mid = (end + top) / 2;
+            if (s_ix[mid] > kidx) top = mid; else end = mid + 1;
+          }
+          if (end == threadIdx.x + kMidWindow) hit = 2;  // undecided unless the next copy is among them
+          for (; x < end; x += 8) {
+            uint32_t eq = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) eq |= (s_h[x + k] == h ? 1u : 0u) << k;
+            if (end - x < 8) eq &= (1u << (end - x)) - 1;
+            while (eq) {
+              const uint32_t c = b0 + 1 + x + (uint32_t)__builtin_ctz(eq);
+              if (U.ut_w_addr[c] == addr && U.ut_w_code[c] == code) {
+                hit = U.ut_ts[c] < sk ? 1 : 0;  // the next copy of the place
+                break;
+              }
+              eq &= eq - 1;
+            }
+            if (eq) break;
+          }
+        }
+      }
+      U.ut_hit[q] = hit;
+      if (hit == 1) A.M.uth[U.ut_idx[q]] = 1;
+      if (hit == 2) U.ctl->ut_need_sort = 1;
+    }
+    __syncthreads();
+  }
+}
+
+// Half of the workgroups each: both are chains of memory round trips.
+__global__ __launch_bounds__(kT) void mid_link_kernel(MidSide A) {
+  const uint32_t half = gridDim.x / 2;
+  if (blockIdx.x >= half) {
+    mid_ut_scan(A, blockIdx.x - half, half);
+    return;
+  }
+  const uint32_t m = A.ctl->n_ad, lane = threadIdx.x & 63;
+  for (uint32_t b = (blockIdx.x * kT + threadIdx.x) / 64 * 64; b < m; b += half * kT)
+    near_insert(A.M.ad, m, b + lane, b + lane < m, A.S.ad_w_addr, A.S.ad_w_dev);
+}
+
+// Inserts the paired ALLOC at position k into the RA table.
+__device__ __forceinline__ void mid_ra_insert(const MidSide& A, uint32_t tmask, uint32_t k) {
+  const uint64_t ha = A.M.ad_host[k], dv = A.S.ad_w_dev[k], by = A.M.ad_bytes[k];
+  uint32_t t = pair_hash(ha, dv, by) & tmask;
+  for (;; t = (t + 1) & tmask) {
+    uint32_t o = A.T.owner[t];
+    if (o == 0) o = atomicCAS(A.T.owner + t, 0u, k + 1);
+    if (o == 0) break;  // claimed
+    if (same_pair_key(A.M.ad_host, A.S.ad_w_dev, A.M.ad_bytes, o - 1, k)) {  // joined
+      if (A.T.multi[t] == 0) A.T.multi[t] = 1;
+      break;
+    }
+  }
+  if (k < A.T.first[t]) atomicMin(A.T.first + t, k);
+  A.T.slot[k] = t;
+}
+
+// Pairing (a DELETE with its predecessor of the same device address, when that
+// is an ALLOC) and the RA table; when the forward search left copies open, the
+// groups of the copies' places; in a log that is not chronological, the
+// extremes of the kernel lists.
+__global__ __launch_bounds__(kT) void mid_pair_kernel(MidSide A) {
+  const AnaCtl* c = A.ctl;
+  const uint32_t m = c->n_ad, mask = pair_table_mask(m), tmask = pair_table_mask(m / 2);
+  for (uint32_t q = blockIdx.x * kT + threadIdx.x; q < m; q += gridDim.x * kT) {
+    if (A.S.ad_op[q] != ODP_DELETE) continue;
+    const uint32_t p = near_prev(A.M.ad, mask, q);
+    if (p == kNone || A.S.ad_op[p] != ODP_ALLOC) continue;
+    A.S.ad_alloc_partner[p] = q;
+    A.flags[A.S.ad_idx[q]] = ODP_F_PAIRED;
+    mid_ra_insert(A, tmask, p);
+  }
+  const uint32_t lane = threadIdx.x & 63;
+  if (c->ut_need_sort) {
+    const uint32_t u = c->n_ut;
+    for (uint32_t b = (blockIdx.x * kT + threadIdx.x) / 64 * 64; b < u; b += gridDim.x * kT)
+      near_insert(A.M.ut, u, b + lane, b + lane < u, A.S.ut_w_addr, A.S.ut_w_code);
+  }
+  if (c->first_bad != kNone) {
+    // a wavefront per 4,096 kernels
+    const uint32_t k = c->n_k;
+    for (uint32_t b = (blockIdx.x * kT + threadIdx.x) / 64; b < (k + 4095) / 4096; b += gridDim.x * (kT / 64)) {
+      KernNode all{~0ull, 0, ~0ull, 0};
+      for (uint32_t x = 0; x < 64 && b * 4096 + x * 64 < k; ++x) {
+        const uint32_t q = b * 4096 + x * 64 + lane;
+        KernNode d{q < k ? A.S.kd_ts[q] : ~0ull, q < k ? A.S.kd_ts[q] : 0ull, q < k ? A.M.kd_te[q] : ~0ull,
+                   q < k ? A.M.kd_te[q] : 0ull};
+        for (int o = 32; o >= 1; o >>= 1) {
+          d.smin = min(d.smin, __shfl_xor(d.smin, o, 64));
+          d.smax = max(d.smax, __shfl_xor(d.smax, o, 64));
+          d.emin = min(d.emin, __shfl_xor(d.emin, o, 64));
+          d.emax = max(d.emax, __shfl_xor(d.emax, o, 64));
+        }
+        if (lane == 0) A.M.node1[b * 64 + x] = d;
+        all.smin = min(all.smin, d.smin);
+        all.smax = max(all.smax, d.smax);
+        all.emin = min(all.emin, d.emin);
+        all.emax = max(all.emax, d.emax);
+      }
+      if (lane == 0) A.M.node2[b] = all;
+    }
+  }
+}
+
+// Kernels of device code dev that start by hi, less those that end before lo
+// (modulo 2^32): the count form, in any kernel order. Whole nodes on one side
+// of both bounds count at once.
+__device__ __forceinline__ uint32_t mid_kernels_meeting(const MidSide& A, uint32_t dev, uint64_t lo, uint64_t hi) {
+  uint32_t cnt = 0, p = A.ctl->kd_base[dev];
+  const uint32_t end = p + A.ctl->kd_total[dev];
+  while (p < end) {
+    uint32_t len = 1;
+    KernNode d;
+    if ((p & 4095) == 0 && p + 4096 <= end) {
+      d = A.M.node2[p >> 12];
+      len = 4096;
+    }
+    if (len == 1 || !((d.smax <= hi || d.smin > hi) && (d.emax < lo || d.emin >= lo))) {
+      len = 1;
+      if ((p & 63) == 0 && p + 64 <= end) {
+        d = A.M.node1[p >> 6];
+        len = 64;
+      }
+      if (len == 1 || !((d.smax <= hi || d.smin > hi) && (d.emax < lo || d.emin >= lo))) {
+        len = 1;
+        d.smax = A.S.kd_ts[p];
+        d.emax = A.M.kd_te[p];
+      }
+    }
+    cnt += (d.smax <= hi ? len : 0u) - (d.emax < lo ? len : 0u);
+    p += len;
+  }
+  return cnt;
+}
+
+// Flags and sums of the ALLOC/DELETE records, and the copies that the forward
+// search left open.
+__global__ __launch_bounds__(kT) void mid_ra_ua_kernel(MidSide A) {
+  const AnaCtl* ctl = A.ctl;
+  const odp_event* __restrict__ ev = A.ev;
+  const bool chrono = ctl->first_bad == kNone;
+  const uint32_t m = ctl->n_ad;
+  unsigned long long c_pair = 0, c_unp = 0, c_ra = 0, c_grp = 0, b_ra = 0, t_ra = 0, c_ua = 0, b_ua = 0, t_ua = 0, t_el = 0;
+  for (uint32_t q = blockIdx.x * kT + threadIdx.x; q < m; q += gridDim.x * kT) {
+    if (A.S.ad_op[q] != ODP_ALLOC) continue;
+    const uint32_t p = A.S.ad_alloc_partner[q];
+    if (p == kNone) {
+      ++c_unp;
+      continue;
+    }
+    ++c_pair;
+    const uint32_t t = A.T.slot[q], ai = A.S.ad_idx[q];
+    const odp_event &a = ev[ai], &d = ev[A.S.ad_idx[p]];
+    const uint64_t dur = (a.t_end - a.t_start) + (d.t_end - d.t_start);
+    const bool head = A.T.first[t] == q;
+    uint8_t f = ODP_F_PAIRED;
+    if (!head) {
+      f |= ODP_F_RA;
+      ++c_ra;
+      b_ra += a.bytes;
+      t_ra += dur;
+    }
+    c_grp += head && A.T.multi[t] != 0;
+    const uint32_t dev = (uint32_t)A.S.ad_w_dev[q];
+    bool used;
+    if (chrono) {
+      const uint32_t ka = A.S.ad_kc[q], kd = A.S.ad_kc[p];
+      used = (ka > 0 && A.S.ad_km[q] >= a.t_start) || kd != ka ||
+             (kd < ctl->kd_total[dev] && A.S.kd_ts[ctl->kd_base[dev] + kd] <= d.t_end);
+    } else {
+      used = mid_kernels_meeting(A, dev, a.t_start, d.t_end) != 0;
+    }
+    if (!used) {
+      f |= ODP_F_UA;
+      ++c_ua;
+      b_ua += a.bytes;
+      t_ua += dur;
+    }
+    if (f & (ODP_F_RA | ODP_F_UA)) t_el += dur;
+    A.flags[ai] = f;
+  }
+  if (ctl->ut_need_sort) {
+    const uint32_t n = ctl->n_ut, mask = pair_table_mask(n);
+    for (uint32_t q = blockIdx.x * kT + threadIdx.x; q < n; q += gridDim.x * kT) {
+      if (chrono && A.U.ut_hit[q] != 2) continue;
+      const uint32_t dev = (uint32_t)(A.S.ut_w_code[q] & 15), nq = near_next(A.M.ut, mask, q);
+      const uint64_t ts = A.S.ut_ts[q];
+      bool read;
+      if (chrono) {
+        const uint32_t k = A.S.ut_kc[q], cnt = ctl->kd_total[dev];
+        read = k > 0 && A.S.ut_km[q] >= ts;
+        if (!read && nq != kNone) {
+          const uint32_t kn = A.S.ut_kc[nq];
+          read = kn != k || (kn < cnt && A.S.kd_ts[ctl->kd_base[dev] + kn] == A.S.ut_ts[nq]);
+        } else if (!read) {
+          read = k != cnt;
+        }
+      } else {
+        read = mid_kernels_meeting(A, dev, ts, nq != kNone ? A.S.ut_ts[nq] : ~0ull) != 0;
+      }
+      if (!read) A.M.uth[A.S.ut_idx[q]] = 1;
+    }
+  }
+  block_store<R_ADD>(A.M.parts.at(S_PAIRS), c_pair);
+  block_store<R_ADD>(A.M.parts.at(S_UNP_ALLOC), c_unp);
+  block_store<R_ADD>(A.M.parts.at(S_RA_EVENTS), c_ra);
+  block_store<R_ADD>(A.M.parts.at(S_RA_GROUPS), c_grp);
+  block_store<R_ADD>(A.M.parts.at(S_RA_BYTES), b_ra);
+  block_store<R_ADD>(A.M.parts.at(S_RA_TIME), t_ra);
+  block_store<R_ADD>(A.M.parts.at(S_UA_EVENTS), c_ua);
+  block_store<R_ADD>(A.M.parts.at(S_UA_BYTES), b_ua);
+  block_store<R_ADD>(A.M.parts.at(S_UA_TIME), t_ua);
+  block_store<R_ADD>(A.M.parts.at(S_ELIM_PAIRS), t_el);
+}
+
+// ---------------------------------------------------------------------------
+// All sums into the report, by one workgroup: nd partials of the digest path's
+// last launch, na of the allocation path's.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kMidT) void mid_finish_kernel(Parts parts, uint32_t nd, uint32_t na, uint32_t n, AnaCtl* ctl,
+                                                           odp_report* rep) {
+  __shared__ unsigned long long s_sum[kSlots];
+  const uint32_t lane = threadIdx.x & 63;
+  for (uint32_t k = S_DD_EVENTS + (threadIdx.x >> 6); k < kSlots; k += kMidT / 64) {
+    const bool digest = k <= S_ELIM_TX || (k >= S_UT_EVENTS && k <= S_UT_TIME);
+    const uint32_t nb = k == S_ELIM_UT ? 0u : digest ? nd : na;  // (the digest path counts a transfer's time once)
+    unsigned long long v = 0;
+    for (uint32_t b = lane; b < nb; b += 64) v += parts.p[(size_t)k * parts.stride + b];
+    v = wave_sum(v);
+    if (lane == 0) s_sum[k] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const unsigned long long* s = s_sum;
+  rep->n_events = n;
+  rep->n_alloc_pairs = s[S_PAIRS];
+  rep->n_unpaired_alloc = s[S_UNP_ALLOC];
+  rep->n_unpaired_delete = ctl->n_ad - s[S_UNP_ALLOC] - 2 * s[S_PAIRS];
+  rep->dd_events = s[S_DD_EVENTS];
+  rep->dd_groups = s[S_DD_GROUPS];
+  rep->dd_members = s[S_DD_EVENTS] + s[S_DD_GROUPS];
+  rep->dd_bytes = s[S_DD_BYTES];
+  rep->dd_time_ns = s[S_DD_TIME];
+  rep->rt_pairs = s[S_RT_PAIRS];
+  rep->rt_rx_events = s[S_RT_RX];
+  rep->rt_bytes = s[S_RT_BYTES];
+  rep->rt_time_ns = s[S_RT_TIME];
+  rep->ra_events = s[S_RA_EVENTS];
+  rep->ra_groups = s[S_RA_GROUPS];
+  rep->ra_members = s[S_RA_EVENTS] + s[S_RA_GROUPS];
+  rep->ra_bytes = s[S_RA_BYTES];
+  rep->ra_time_ns = s[S_RA_TIME];
+  rep->ua_events = s[S_UA_EVENTS];
+  rep->ua_bytes = s[S_UA_BYTES];
+  rep->ua_time_ns = s[S_UA_TIME];
+  rep->ut_events = s[S_UT_EVENTS];
+  rep->ut_bytes = s[S_UT_BYTES];
+  rep->ut_time_ns = s[S_UT_TIME];
+  rep->first_bad_event = ctl->first_bad;
+  rep->status = ctl->first_bad != kNone ? 1 : 0;
+  write_estimate(rep, n > rep->n_invalid, ctl->t_min, ctl->t_max, s[S_ELIM_TX] + s[S_ELIM_PAIRS]);
+}

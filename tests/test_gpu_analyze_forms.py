@@ -89,3 +89,61 @@ def test_walked_calls_alternate(odp):
         torch.cuda.synchronize()
         compare(d_fl.cpu().numpy(), odp.report_to_dict(d_rep.cpu().numpy()), *want[1])
         odp.analyze_trace(d_ev, d_fl, d_rep, n=len(ev))
+
+
+@pytest.mark.parametrize("n", [4097, 6143, 6144, 6145, 16385, 50000])
+@pytest.mark.parametrize("invalid", [0.0, 0.01])
+def test_table_logs(odp, n, invalid):
+    """Groups in hash tables: few hot keys, as many keys as records, long
+    stretches without kernels, all endpoints."""
+    check(odp, random_log(n, n, invalid=invalid))
+    check(odp, random_log(n + 1, n, devices=10, digests=n, places=n, invalid=invalid, long_kernels=True))
+    check(odp, random_log(n + 2, n, devices=1, digests=3, places=1, invalid=invalid, kernels=0.0005))
+    check(odp, random_log(n + 3, n, devices=2, digests=500, places=3000, invalid=invalid, kernels=0.6, allocs=0.3))
+    check(odp, random_log(n + 4, n, devices=1, digests=n // 3, places=400, invalid=invalid, kernels=0.001, allocs=0.9))
+
+
+def test_table_log_one_digest(odp):
+    """One group over every workgroup: the carries are looked up past 64 wavefronts."""
+    n = 40000
+    ev = random_log(3, n, digests=1, kernels=0.01, allocs=0.01)
+    check(odp, ev)
+    ev["op"] = W.H2D  # one direction, one receiver
+    ev["src_dev"], ev["dst_dev"] = -1, 0
+    check(odp, ev)
+    ev["op"][:-1] = W.D2H  # the return leg is the last record
+    ev["src_dev"][:-1], ev["dst_dev"][:-1] = 0, -1
+    check(odp, ev)
+
+
+@pytest.mark.parametrize("n", [262143, 262144, 262145])
+def test_last_table_length(odp, n):
+    check(odp, random_log(n, n, devices=4, digests=n // 8, places=2000, invalid=0.0))
+    check(odp, random_log(n, n, devices=4, digests=n // 8, places=2000, invalid=0.0005))
+
+
+def test_keys_that_collide_in_the_tables(odp):
+    """Digests and addresses that are multiples of large powers of two."""
+    n = 9000
+    ev = random_log(11, n, digests=n, places=n, kernels=0.02)
+    k = np.arange(n, dtype=np.uint64)
+    ev["digest"] = (k % 3000) << np.uint64(40)
+    ev["src_addr"] = (k % 700) << np.uint64(33)
+    ev["dst_addr"] = (k % 900) << np.uint64(50)
+    check(odp, ev)
+
+
+@pytest.mark.parametrize("kind", ["random", "out of order", "shared low bytes", "one digest", "few kernels", "all ones"])
+def test_sorted_logs(odp, kind):
+    """The sorting pipeline, just above the last table length."""
+    n = 262145 + 4096 + 7
+    ev = random_log(n, n, devices=3, digests=n // 8, places=2000, invalid=0.001 if kind == "out of order" else 0.0,
+                    kernels=0.0002 if kind == "few kernels" else 0.1, long_kernels=kind == "out of order")
+    k = np.arange(n, dtype=np.uint64)
+    if kind == "shared low bytes":  # long runs of equal low bytes holding several digests
+        ev["digest"] = (k % 5) << np.uint64(48) | (k % 7) << np.uint64(40) | (k % 3000) // np.uint64(1000)
+    if kind == "one digest":
+        ev["digest"] = 77
+    if kind == "all ones":
+        ev["digest"] = np.where(k % 3 == 0, np.uint64(2**64 - 1), k // np.uint64(4) << np.uint64(8) | np.uint64(255))
+    check(odp, ev)
