@@ -187,7 +187,105 @@ enum : uint8_t { K_INVALID = 0, K_TRANSFER = 1, K_ALLOCDEL = 2, K_KERNEL = 3 };
 
 __device__ __forceinline__ uint64_t tx_key(int s, int d) { return kMark | ((uint64_t)(s + 1) << 8) | (uint64_t)(d + 1); }
 
+// The tick's records by group, each group's in tick order, so that a record
+// looks for its predecessors and successors of the tick among its own group
+// instead of among all records: walks over all of a tick of 1,024 records took
+// 960 us, almost all of the kernel; the kernel takes 109 now. Groups are the slots of an LDS
+// hash table (exact: a slot's owner has the same key), and two stable 6-bit
+// passes order the records by slot. Ticks of at most kWalkTick records are
+// their own only group: there the walk is shorter than the sort.
+constexpr uint32_t kWalkTick = 64;
+constexpr uint32_t kGroupSlots = 2 * kTickMax;
+struct GroupLds {
+  uint32_t owner[kGroupSlots];
+  uint32_t tag[kTickMax];
+  uint32_t cnt[kTickMax];   // [digit][wavefront]
+  uint32_t perm[kTickMax];
+  uint32_t wsum[kTickMax / 64];
+};
+struct GroupList {
+  uint16_t ord[kTickMax];                           // records by group
+  uint16_t start[kGroupSlots], end[kGroupSlots];    // a slot's range in ord
+};
+
+// The range [lo, hi) of L.ord that holds the group of record t (key[t], tag;
+// records with active == false are in no group). All threads of the workgroup
+// call it; L is complete after the next barrier.
+__device__ void group_tick(GroupLds& G, GroupList& L, const uint64_t* key, uint32_t tag, bool active, uint32_t m,
+                           uint32_t& lo, uint32_t& hi) {
+  const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (m <= kWalkTick) {
+    L.ord[t] = (uint16_t)t;
+    lo = 0;
+    hi = m;
+    return;
+  }
+  constexpr uint32_t kFree = 0xFFFFFFFFu;
+  G.tag[t] = tag;
+  G.owner[t] = G.owner[t + kTickMax] = kFree;
+  __syncthreads();
+  uint32_t slot = kGroupSlots;  // no group: behind all others
+  if (active) {
+    slot = (uint32_t)(mix64(key[t], tag, 0) >> 20) & (kGroupSlots - 1);
+    for (;;) {
+      const uint32_t o = atomicCAS(&G.owner[slot], kFree, t);
+      if (o == kFree || (key[o] == key[t] && G.tag[o] == tag)) break;
+      slot = (slot + 1) & (kGroupSlots - 1);
+    }
+  }
+  uint32_t v = slot << 16 | t;
+  const uint64_t lt = lane ? ~0ull >> (64 - lane) : 0ull;
+  for (uint32_t shift = 16; shift <= 22; shift += 6) {  // slots take 12 bits
+    const uint32_t d = (v >> shift) & 63;
+    uint64_t peers = ~0ull;
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+      const bool bit = (d >> b) & 1;
+      const uint64_t x = __ballot(bit);
+      peers &= bit ? x : ~x;
+    }
+    G.cnt[t] = 0;
+    __syncthreads();
+    if ((peers >> lane) == 1ull) G.cnt[d * (kTickMax / 64) + w] = (uint32_t)__popcll(peers);
+    __syncthreads();
+    // exclusive sums over (digit, wavefront)
+    const uint32_t c = G.cnt[t];
+    uint32_t x = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if ((int)lane >= o) x += y;
+    }
+    if (lane == 63) G.wsum[w] = x;
+    __syncthreads();
+    uint32_t before = 0;
+    for (uint32_t q = 0; q < w; ++q) before += G.wsum[q];
+    G.cnt[t] = before + x - c;
+    __syncthreads();
+    G.perm[G.cnt[d * (kTickMax / 64) + w] + (uint32_t)__popcll(peers & lt)] = v;
+    __syncthreads();
+    v = G.perm[t];
+  }
+  const uint32_t g = v >> 16;
+  L.ord[t] = (uint16_t)v;
+  if (g < kGroupSlots) {
+    if (t == 0 || G.perm[t - 1] >> 16 != g) L.start[g] = (uint16_t)t;
+    if (t + 1 == kTickMax || G.perm[t + 1] >> 16 != g) L.end[g] = (uint16_t)(t + 1);
+  }
+  __syncthreads();
+  lo = hi = 0;
+  if (active) {
+    lo = L.start[slot];
+    hi = L.end[slot];
+  }
+}
+
 __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
+  __shared__ GroupLds s_group;
+  __shared__ GroupList s_main, s_place;  // transfers by digest, ALLOC/DELETE by device address; copies by place
+  __shared__ uint64_t s_key[kTickMax];
+  __shared__ uint64_t s_kmask[kDev][kTickMax / 64];  // the tick's KERNEL records per device code
+  __shared__ uint64_t s_pmask[kTickMax / 64];        // its DELETEs that pair
   __shared__ uint64_t s_dig[kTickMax];
   __shared__ uint64_t s_addr[kTickMax];   // dst_addr (ALLOC/DELETE: device address)
   __shared__ uint64_t s_saddr[kTickMax];  // src_addr (copies: source; ALLOC: host address)
@@ -206,7 +304,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
   const bool in = t < A.m;
   const uint64_t id = A.base_id + t;
   ServeState* st = A.st;
-  odp_event e;
+  odp_event e{};
   if (t < kDev) s_kc0[t] = st->kcount[t];
   if (t == 0) {
     s_pend_n = st->pend_n;
@@ -242,41 +340,64 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
   const bool tick_invalid = __syncthreads_or(in && kind == K_INVALID);
   const bool windows_on = !st->any_invalid && !tick_invalid;
   // Kernels on my device logged before me (earlier ticks and earlier in this one).
+  const uint32_t lane = t & 63, wave = t >> 6;
+  const uint64_t lt = lane ? ~0ull >> (64 - lane) : 0ull;
+  for (int dv = 0; dv < kDev; ++dv) {
+    const uint64_t b = __ballot(kind == K_KERNEL && e.dst_dev + 1 == dv);
+    if (lane == 0) s_kmask[dv][wave] = b;
+  }
+  // My groups in the tick.
+  const bool copyin_me = kind == K_TRANSFER && e.op != ODP_D2H && e.dst_dev >= 0;
+  uint32_t g0, g1, p0, p1;
+  s_key[t] = kind == K_TRANSFER ? e.digest : kind == K_ALLOCDEL ? e.dst_addr : 0ull;
+  group_tick(s_group, s_main, s_key, kind == K_TRANSFER ? 1u : 2u | (uint32_t)(uint16_t)(e.dst_dev + 1) << 8,
+             kind == K_TRANSFER || kind == K_ALLOCDEL, A.m, g0, g1);
+  group_tick(s_group, s_place, s_saddr, (uint32_t)(uint16_t)e.src_dev << 16 | (uint16_t)e.dst_dev, copyin_me, A.m, p0, p1);
+  __syncthreads();
   uint32_t kc_me = 0;
   if (in && kind != K_INVALID) {
-    const int dv = e.dst_dev;
-    uint32_t c = 0;
-    for (uint32_t u = 0; u < t; ++u) c += s_kind[u] == K_KERNEL && s_dst[u] == dv;
-    kc_me = s_kc0[dv + 1] + c;
+    const uint64_t* km = s_kmask[e.dst_dev + 1];
+    uint32_t c = (uint32_t)__popcll(km[wave] & lt);
+    for (uint32_t x = 0; x < wave; ++x) c += (uint32_t)__popcll(km[x]);
+    kc_me = s_kc0[e.dst_dev + 1] + c;
   }
   // Phase 1: predecessors inside the tick, else the state of earlier ticks.
   uint8_t f = kind == K_INVALID && in ? ODP_F_INVALID : 0;
-  int dd_first = -1, rx_pred = -1, rx_last = 1, ad_pred = -1, ad_last = 1;
-  bool tx_first = true, tx_last = true, ut_last = true, is_copyin = false;
+  // What the walks find is kept in integers, not booleans: lanes leave them at
+  // different trips (hipcc has lost booleans set in such loops).
+  enum : uint32_t { kRxLater = 1, kTxEarlier = 2, kTxLater = 4, kUtLater = 8, kAdLater = 16, kSentBack = 32 };
+  uint32_t seen = 0;
+  int dd_first = -1, rx_pred = -1, ad_pred = -1;
+  bool is_copyin = false;
   int ut_prev = -1;
   uint64_t ut_prev_id = kNone64;  // the copy this one closes (its next copy is this one)
   if (kind == K_TRANSFER) {
     const uint64_t h = e.digest;
     const int s = e.src_dev, d = e.dst_dev;
     const int lo = min(s, d), hi = max(s, d);
-    is_copyin = e.op != ODP_D2H && d >= 0;
-    bool sent_back = false;
-    for (uint32_t u = 0; u < A.m; ++u) {
-      if (s_kind[u] != K_TRANSFER) continue;
-      if (is_copyin && u != t && s_op[u] != ODP_D2H && s_dst[u] == d && s_src[u] == s && s_saddr[u] == e.src_addr) {
-        if (u < t) ut_prev = (int)u; else ut_last = false;
+    is_copyin = copyin_me;
+    if (is_copyin) {
+      for (uint32_t q = p0; q < p1; ++q) {
+        const uint32_t u = s_place.ord[q];
+        if (u != t && s_kind[u] == K_TRANSFER && s_op[u] != ODP_D2H && s_dst[u] == d && s_src[u] == s &&
+            s_saddr[u] == e.src_addr) {
+          if (u < t) ut_prev = (int)u; else seen |= kUtLater;
+        }
       }
-      if (s_dig[u] != h) continue;
+    }
+    for (uint32_t q = g0; q < g1; ++q) {
+      const uint32_t u = s_main.ord[q];
+      if (s_kind[u] != K_TRANSFER || s_dig[u] != h) continue;
       const int su = s_src[u], du = s_dst[u];
       const bool same_pair = s != d && su != du && min(su, du) == lo && max(su, du) == hi;
       if (u < t) {
         if (du == d && dd_first < 0) dd_first = (int)u;
         if (same_pair) rx_pred = (int)u;
-        if (su == s && du == d) tx_first = false;
+        if (su == s && du == d) seen |= kTxEarlier;
       } else if (u > t) {
-        if (same_pair) rx_last = 0;
-        if (s != d && su == d && du == s) sent_back = true;
-        if (su == s && du == d) tx_last = false;
+        if (same_pair) seen |= kRxLater;
+        if (s != d && su == d && du == s) seen |= kSentBack;
+        if (su == s && du == d) seen |= kTxLater;
       }
     }
     if (dd_first >= 0) {
@@ -294,11 +415,11 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
       }
       const int mydir = s == lo ? 1 : 0;
       if (pdir >= 0 && pdir != mydir) f |= ODP_F_RT_RX;
-      if (sent_back) f |= ODP_F_RT_TX;
+      if (seen & kSentBack) f |= ODP_F_RT_TX;
       // The first transfer of my ordered pair in this tick takes the list of
       // earlier ticks' transfers that went the other way and marks them all:
       // it carries their data back.
-      if (tx_first) {
+      if (!(seen & kTxEarlier)) {
         Slot* sl = tfind(A.t_tx, h, tx_key(d, s));
         if (sl) {
           uint64_t head = atomicExch(reinterpret_cast<unsigned long long*>(&sl->v1), 0ull);
@@ -309,7 +430,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
           }
         }
       }
-      s_unmarked[t] = !sent_back;
+      s_unmarked[t] = !(seen & kSentBack);
     }
     if (is_copyin) {
       if (ut_prev >= 0) {
@@ -322,10 +443,11 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
   } else if (kind == K_ALLOCDEL) {
     const uint64_t a = e.dst_addr;
     const int d = e.dst_dev;
-    for (uint32_t u = 0; u < A.m; ++u) {
+    for (uint32_t q = g0; q < g1; ++q) {
+      const uint32_t u = s_main.ord[q];
       if (s_kind[u] != K_ALLOCDEL || s_addr[u] != a || s_dst[u] != d) continue;
       if (u < t) ad_pred = (int)u;
-      else if (u > t) ad_last = 0;
+      else if (u > t) seen |= kAdLater;
     }
     uint8_t pop = 0;
     uint64_t pid = 0;
@@ -349,6 +471,10 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     known_or(A.known, id, f);
     A.kc_at[id] = kc_me;
   }
+  {
+    const uint64_t b = __ballot(kind == K_ALLOCDEL && s_pid[t] != kNone64);
+    if (lane == 0) s_pmask[wave] = b;
+  }
   __syncthreads();
   // Phase 2: state updates, one thread per key.
   const uint32_t tag = A.tag;
@@ -360,7 +486,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
       Slot* sl = tupsert(A.t_dd, h, kMark | (uint64_t)(d + 1), 0, tag, 0, &ins);
       if (!sl) st->overflow = 1;
     }
-    if (s != d && rx_last) {
+    if (s != d && !(seen & kRxLater)) {
       const int lo = min(s, d), hi = max(s, d);
       Slot* sl = tupsert(A.t_rx, h, kMark | ((uint64_t)(lo + 1) << 8) | (uint64_t)(hi + 1), 0, tag, 0, &ins);
       if (sl) sl->v0 = s == lo ? 1u : 0u;
@@ -370,10 +496,13 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     // the pair's last transfer of the tick swaps the newest unmarked one in as
     // the head; each links to the next older unmarked one of the tick, the
     // oldest to the old head (phase 2b).
-    if (s != d && tx_last) {
+    if (s != d && !(seen & kTxLater)) {
       int newest = -1;
-      for (uint32_t u = 0; u <= t; ++u)
-        if (s_kind[u] == K_TRANSFER && s_unmarked[u] && s_dig[u] == h && s_src[u] == s && s_dst[u] == d) newest = (int)u;
+      for (uint32_t q = g0; q < g1; ++q) {
+        const uint32_t u = s_main.ord[q];
+        if (u <= t && s_kind[u] == K_TRANSFER && s_unmarked[u] && s_dig[u] == h && s_src[u] == s && s_dst[u] == d)
+          newest = (int)u;
+      }
       s_xchg[t] = 0;
       if (newest >= 0) {
         Slot* sl = tupsert(A.t_tx, h, tx_key(s, d), 0, tag, 0, &ins);
@@ -381,7 +510,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
         else st->overflow = 1;
       }
     }
-    if (is_copyin && ut_last) {
+    if (is_copyin && !(seen & kUtLater)) {
       Slot* sl = tupsert(A.t_ut, e.src_addr, tx_key(s, d), 0, tag, 0, &ins);
       if (sl) sl->v1 = id + 1;  // open: no later copy of this place yet
       else st->overflow = 1;
@@ -399,7 +528,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
       A.pend[st->pend_cur][atomicAdd(&s_pend_n, 1u)] = p;
     }
   } else if (kind == K_ALLOCDEL) {
-    if (ad_last) {
+    if (!(seen & kAdLater)) {
       Slot* sl = tupsert(A.t_ad, e.dst_addr, kMark | (uint64_t)(e.dst_dev + 1), 0, tag, 0, &ins);
       if (sl) {
         sl->v0 = e.op;
@@ -417,21 +546,24 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
       const uint64_t pid = s_pid[t];
       const odp_event& a = A.log[pid];
       const uint64_t k0 = a.src_addr, k1 = kMark | (uint64_t)(a.dst_dev + 1), k2 = a.bytes;
-      bool first = true;
+      uint32_t earlier = 0;
       uint64_t tick_min = pid;
-      for (uint32_t u = 0; u < A.m; ++u) {
-        if (u == t || s_pid[u] == kNone64) continue;
-        const odp_event& b = A.log[s_pid[u]];
-        if (b.src_addr == k0 && b.dst_dev == a.dst_dev && b.bytes == k2) {
-          if (u < t) first = false;
-          tick_min = min(tick_min, s_pid[u]);
+      for (uint32_t x = 0; x < kTickMax / 64; ++x) {
+        for (uint64_t pm = s_pmask[x]; pm; pm &= pm - 1) {
+          const uint32_t u = x * 64 + (uint32_t)__builtin_ctzll(pm);
+          if (u == t) continue;
+          const odp_event& b = A.log[s_pid[u]];
+          if (b.src_addr == k0 && b.dst_dev == a.dst_dev && b.bytes == k2) {
+            if (u < t) earlier = 1;
+            tick_min = min(tick_min, s_pid[u]);
+          }
         }
       }
       const Slot* found = tfind(A.t_ra, k0, k1, k2);
       const uint64_t before = found ? found->v1 : kNone64;
       if (pid > min(before, tick_min)) known_or(A.known, pid, ODP_F_RA);
-      if (first && before != kNone64 && before > tick_min) known_or(A.known, before, ODP_F_RA);
-      if (first) s_xchg[t] = tick_min;
+      if (!earlier && before != kNone64 && before > tick_min) known_or(A.known, before, ODP_F_RA);
+      if (!earlier) s_xchg[t] = tick_min;
       // unused allocation: the window [ALLOC start, DELETE end]
       if (windows_on) {
         Pending p;
@@ -450,8 +582,9 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     const uint64_t row = (uint64_t)(dv + 1) * A.cap;
     const uint32_t k0 = s_kc0[dv + 1];
     uint64_t mx = k0 ? A.kmaxend[row + k0 - 1] : 0;
-    for (uint32_t u = 0; u <= t; ++u)
-      if (s_kind[u] == K_KERNEL && s_dst[u] == dv) mx = max(mx, s_te[u]);
+    for (uint32_t x = 0; x <= wave; ++x)
+      for (uint64_t km = s_kmask[dv + 1][x] & (x < wave ? ~0ull : lt | 1ull << lane); km; km &= km - 1)
+        mx = max(mx, s_te[x * 64 + (uint32_t)__builtin_ctzll(km)]);
     A.kstart[row + kc_me] = e.t_start;
     A.kmaxend[row + kc_me] = mx;
   }
@@ -467,7 +600,8 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     const uint64_t h = e.digest;
     const int s = e.src_dev, d = e.dst_dev;
     int older = -1, last = -1;
-    for (uint32_t u = 0; u < A.m; ++u) {
+    for (uint32_t q = g0; q < g1; ++q) {
+      const uint32_t u = s_main.ord[q];
       if (!(s_kind[u] == K_TRANSFER && s_dig[u] == h && s_src[u] == s && s_dst[u] == d)) continue;
       if (u < t && s_unmarked[u]) older = (int)u;
       last = (int)u;  // the pair's last transfer of the tick took the old head
@@ -476,7 +610,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
   }
   if (t < kDev) {
     uint32_t c = 0;
-    for (uint32_t u = 0; u < A.m; ++u) c += s_kind[u] == K_KERNEL && s_dst[u] == (int)t - 1;
+    for (uint32_t x = 0; x < kTickMax / 64; ++x) c += (uint32_t)__popcll(s_kmask[t][x]);
     s_kc1[t] = s_kc0[t] + c;
   }
   __syncthreads();

@@ -1,0 +1,32 @@
+"""Served ticks on both sides of the length from which a tick's records are
+grouped instead of walked: flags known before the drain, and drained, against
+the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+from gpu_helpers import compare
+from test_gpu_analyze_forms import random_log
+from test_gpu_serve import check_known
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("max_tick", [63, 64, 65, 192, 1023, 1024])
+@pytest.mark.parametrize("kind", ["few keys", "many keys", "one key", "rejected"])
+def test_tick_lengths(odp, max_tick, kind):
+    n = 3 * max_tick + 17
+    few = kind == "few keys"
+    ev = random_log(max_tick, n, devices=10 if kind == "many keys" else 2, digests=1 if kind == "one key" else 20 if few else n,
+                    places=1 if kind == "one key" else 6 if few else n // 2, invalid=0.03 if kind == "rejected" else 0.0)
+    srv = odp.Server(max_events=n, budget_bytes=64 << 20, max_tick=max_tick)
+    zero = np.zeros(n, dtype=np.uint64)
+    _, stats = srv.run(ev, zero, zero, zero)
+    known, fl, rep = srv.drain()
+    srv.close()
+    fo, ro = oracle.analyze(ev)
+    compare(fl, rep, fo, ro)
+    check_known(known, fo, ev)
+    assert stats["max_tick"] <= max_tick
