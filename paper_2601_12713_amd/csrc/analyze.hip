@@ -83,6 +83,7 @@ struct WordMask {
 struct AnaCtl {
   uint32_t n;           // records
   uint32_t n_tx;        // valid transfers (the digest sort keeps only these after its first pass)
+  uint32_t n_cand;      // ... that may share their digest with another (only these after its second)
   uint32_t n_ad;        // ALLOC/DELETE records
   uint32_t n_k;         // KERNEL records
   uint32_t n_pairs;     // paired allocations
@@ -147,11 +148,17 @@ struct SortJob {
   const uint32_t* n_after0;
   const uint8_t* aux;
   uint32_t drop0;
+  // The digest job's second pass keeps only the elements that may share their
+  // key with another one (cand, per element of the first pass's order, from
+  // sort_filter_kernel); the passes after it sort *n_after1 elements. Null:
+  // no filter.
+  uint8_t* cand;
+  uint32_t* n_after1;
 };
 
 // Elements of job s that pass p reads.
 __device__ __forceinline__ uint32_t pass_len(const SortJob& s, uint32_t p) {
-  return (p > 0 && s.n_after0) ? *s.n_after0 : *s.n_ptr;
+  return p > 1 && s.n_after1 ? *s.n_after1 : p > 0 && s.n_after0 ? *s.n_after0 : *s.n_ptr;
 }
 // Elements in the job's sorted order once its passes have run (all of them
 // when none ran).
@@ -160,6 +167,13 @@ __device__ __forceinline__ uint32_t sorted_len(const SortJob& s) { return pass_l
 __device__ __forceinline__ bool keep0(const SortJob& s, uint32_t val) {
   const uint8_t a = *s.n_ptr < kPackLimit ? (uint8_t)(val >> 24) : s.aux[val];
   return a != kNotTransfer;
+}
+// Whether pass p drops elements, and whether it keeps element j of value val.
+__device__ __forceinline__ bool drops(const SortJob& s, uint32_t p) {
+  return (p == 0 && s.drop0) || (p == 1 && s.cand != nullptr);
+}
+__device__ __forceinline__ bool keep(const SortJob& s, uint32_t p, uint32_t j, uint32_t val) {
+  return p == 0 ? keep0(s, val) : s.cand[j] != 0;
 }
 constexpr uint32_t kNoWord = 0xFFFFFFFFu;
 
@@ -281,7 +295,7 @@ __global__ void init_kernel(AnaCtl* ctl, odp_report* rep, uint32_t* totals, uint
     rep->status = 0;
     rep->first_bad_event = kNone;
     ctl->n = n;
-    ctl->n_ad = ctl->n_k = ctl->n_pairs = ctl->n_ut = ctl->n_tx = 0;
+    ctl->n_ad = ctl->n_k = ctl->n_pairs = ctl->n_ut = ctl->n_tx = ctl->n_cand = 0;
     ctl->first_bad = kNone;
     ctl->max_ep = 0;
     ctl->t_min = ~0ull;
@@ -318,7 +332,8 @@ __global__ __launch_bounds__(kT) void classify_kernel(const odp_event* __restric
                                                       uint8_t* __restrict__ cls, uint8_t* __restrict__ aux,
                                                       unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
                                                       uint32_t* __restrict__ wave_cnt, uint64_t* __restrict__ wave_kmax,
-                                                      uint32_t* __restrict__ hist0, uint32_t ntc, Parts parts) {
+                                                      uint32_t* __restrict__ hist0, uint32_t ntc, uint8_t* __restrict__ cand,
+                                                      Parts parts) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint32_t wid = blockIdx.x * (kT / 64) + w;
   const uint32_t wb = wid * kWaveElems;
@@ -383,6 +398,7 @@ __global__ __launch_bounds__(kT) void classify_kernel(const odp_event* __restric
       flags[i] = valid ? 0 : ODP_F_INVALID;
       cls[i] = c;
       aux[i] = a;
+      if (cand) cand[i] = 1;
       keys[i] = key;
       if (c == C_TRANSFER || c == C_COPYIN) atomicAdd(&s_h0[key & 0xFF], 1u);
       vals[i] = n < kPackLimit ? i | ((uint32_t)a << 24) : i;
@@ -887,10 +903,13 @@ __global__ __launch_bounds__(kT) void reduce_parts_kernel(Parts parts, uint32_t 
 // ---------------------------------------------------------------------------
 // first_passes: when nonzero, the passes after that many are deferred to the
 // local fix (digest job only).
-__global__ void sort_plan_kernel(JobSet J, uint32_t first_passes) {
+// cand, n_after1: the filter's arrays for the job, or null to run without it.
+__global__ void sort_plan_kernel(JobSet J, uint32_t first_passes, uint8_t* cand, uint32_t* n_after1) {
   const uint32_t j = threadIdx.x;
   if (j >= J.njobs) return;
   SortJob& s = J.jobs[j];
+  s.cand = cand;
+  s.n_after1 = n_after1;
   uint32_t np = 0;
   const uint32_t skip = (s.first_bad && *s.first_bad == kNone) ? s.mono_word : kNoWord;
   const uint32_t nwords = (s.run_flag && *s.run_flag == 0) ? 0u : s.nwords;
@@ -951,7 +970,7 @@ __global__ __launch_bounds__(kT) void sort_fix_kernel(SortJob* job, uint32_t p) 
   if (threadIdx.x == 0) s_np = __hip_atomic_load(&s.npasses, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   const uint32_t np = s_np;
-  const uint32_t n = pass_len(s, 1);  // the sorted elements (the fix runs after a pass)
+  const uint32_t n = pass_len(s, s.np_first);  // the sorted elements
   const uint32_t nft = (n + kFixTile - 1) / kFixTile;
   if (p == kFixFinal) {
     if (np != s.np_first || np >= s.np_full) return;
@@ -1103,11 +1122,11 @@ __global__ __launch_bounds__(kT) void sort_hist_kernel(JobSet J, uint32_t p) {
   const uint32_t b = tile * kTile;
   uint32_t d[kItems];
   const uint32_t shift = s->ps[p];
-  const bool drop = p == 0 && s->drop0;
+  const bool drop = drops(*s, p);
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
     const uint32_t j = b + r * kT + threadIdx.x;
-    const bool in = j < n && (!drop || keep0(*s, s->vals[src][j]));
+    const bool in = j < n && (!drop || keep(*s, p, j, p == 0 ? s->vals[src][j] : 0u));
     d[r] = in ? (uint32_t)(key_of(*s, p, src, j) >> shift) & 0xFF : 256u;
   }
 #pragma unroll
@@ -1152,7 +1171,10 @@ __global__ __launch_bounds__(kT) void sort_scan_kernel(JobSet J, uint32_t p) {
     row[t] = before;
     before += c;
   }
-  if (threadIdx.x == kT - 1) s.totals[p * 256 + d] = before;
+  if (threadIdx.x == kT - 1) {
+    s.totals[p * 256 + d] = before;
+    if (p == 1 && s.n_after1 && before) atomicAdd(s.n_after1, before);
+  }
 }
 
 // Stable scatter, 512 threads per tile (twice the wavefronts of the other
@@ -1177,7 +1199,7 @@ __global__ __launch_bounds__(kST) void sort_scatter_kernel(JobSet J, uint32_t p)
   __shared__ uint32_t ws[4], wt[4];
   __shared__ uint32_t s_kept;       // elements of this tile the pass writes
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const bool drop = p == 0 && s->drop0;
+  const bool drop = drops(*s, p);
   do {
   for (int x = 0; x < 256; x += 64) wcnt[w][x + lane] = 0;
   __syncthreads();
@@ -1208,7 +1230,7 @@ __global__ __launch_bounds__(kST) void sort_scatter_kernel(JobSet J, uint32_t p)
 #pragma unroll
   for (int r = 0; r < kSRounds; ++r) {
     const uint32_t j = wb + r * 64 + lane;
-    inmask |= (uint32_t)(j < n && (!drop || keep0(*s, vl[r]))) << r;
+    inmask |= (uint32_t)(j < n && (!drop || keep(*s, p, j, vl[r]))) << r;
   }
 #pragma unroll
   for (int r = 0; r < kSRounds; ++r) {
@@ -1297,6 +1319,83 @@ __global__ __launch_bounds__(kST) void sort_scatter_kernel(JobSet J, uint32_t p)
   }
   __syncthreads();
   } while (next_tile(J, s, tile, n));
+}
+
+// Between the digest job's first two passes: marks the transfers that may share
+// their digest with another one. A transfer whose digest no other carries is no
+// duplicate, no round trip and no group, and in a log where most content is
+// moved once (8.1 of the 9.8 million transfers of the trace workload) those are
+// most of the elements that the later passes, the fix and the scans would carry.
+// Equal digests lie in one digit's range of the first pass's order: a workgroup
+// takes a range and keeps two bits per hash of a digest in LDS, "occurs" and
+// "occurs again". Two digests that share a hash are only kept for nothing (7% of
+// the single ones at 38,500 per range and 2^19 hashes). A range of more than
+// kFilterMax elements (one digest moved again and again, or more than 33
+// million transfers) keeps all of its elements, as the classification marked
+// them: there are few single digests in it to drop, or too many for the bits.
+// Bound by the read of the keys and the LDS atomics: 30 us for the 9.8 million
+// transfers of the 10.7-million-record trace, where it takes 7.9 million
+// elements out of the second and third pass, the fix and the scans (the whole
+// analysis 1,409 -> 1,215 us).
+constexpr uint32_t kFilterT = 1024;
+constexpr uint32_t kFilterBits = 19;
+constexpr uint32_t kFilterMax = 1u << 17;
+constexpr int kFilterHeld = 40;  // elements per thread held in registers between the two steps
+
+__device__ __forceinline__ uint32_t filter_hash(unsigned long long key) {
+  return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> (64 - kFilterBits));
+}
+
+__global__ __launch_bounds__(kFilterT) void sort_filter_kernel(SortJob* job) {
+  SortJob& s = *job;
+  __shared__ uint32_t s_once[1u << (kFilterBits - 5)], s_again[1u << (kFilterBits - 5)];
+  __shared__ uint32_t s_lo, s_len;
+  if (s.npasses < 2) return;
+  const uint32_t t = threadIdx.x;
+  // the range of digit blockIdx.x
+  if (t < 64) {
+    uint32_t before = 0;
+    for (uint32_t d = t; d < blockIdx.x; d += 64) before += s.totals[d];
+    before = (uint32_t)wave_sum(before);
+    if (t == 0) {
+      s_lo = before;
+      s_len = s.totals[blockIdx.x];
+    }
+  }
+  __syncthreads();
+  const uint32_t lo = s_lo, len = s_len;
+  if (len == 0 || len > kFilterMax) return;
+  for (uint32_t x = t; x < (1u << (kFilterBits - 5)); x += kFilterT) s_once[x] = s_again[x] = 0;
+  __syncthreads();
+  const unsigned long long* k = s.keys[1] + lo;
+  uint8_t* cand = s.cand + lo;
+  auto mark = [&](uint32_t h) {
+    const uint32_t bit = 1u << (h & 31);
+    if (atomicOr(&s_once[h >> 5], bit) & bit) atomicOr(&s_again[h >> 5], bit);
+  };
+  uint32_t held[kFilterHeld];
+#pragma unroll
+  for (int u = 0; u < kFilterHeld; ++u) {
+    held[u] = 0;
+    if ((uint32_t)u * kFilterT < len) {
+      const uint32_t j = (uint32_t)u * kFilterT + t;
+      if (j < len) held[u] = filter_hash(k[j]);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kFilterHeld; ++u)
+    if ((uint32_t)u * kFilterT + t < len) mark(held[u]);
+  for (uint32_t j = kFilterHeld * kFilterT + t; j < len; j += kFilterT) mark(filter_hash(k[j]));
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kFilterHeld; ++u) {
+    const uint32_t j = (uint32_t)u * kFilterT + t;
+    if (j < len) cand[j] = (uint8_t)((s_again[held[u] >> 5] >> (held[u] & 31)) & 1);
+  }
+  for (uint32_t j = kFilterHeld * kFilterT + t; j < len; j += kFilterT) {
+    const uint32_t h = filter_hash(k[j]);
+    cand[j] = (uint8_t)((s_again[h >> 5] >> (h & 31)) & 1);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1695,36 +1794,38 @@ __device__ void ddrt_agg_body(const DDArgs& A) {
   uint32_t cf = 0, cb = 0;
   FS<MODE> fv = S::fid();
   BS<MODE> bv = S::bid();
+  if (wb < ns) {  // (the sorted elements may be far fewer than the launch has room for)
 #pragma unroll 1
-  for (int r = ROUNDS - 1; r >= 0; --r) {
-    uint8_t a;
-    bool head, tail;
-    load_round(k, v, A.aux, ns, packed, wb + r * 64 + lane, a, head, tail);
-    uint32_t f = head;
-    FS<MODE> x = S::flift(a);
-    wave_fscan<MODE>(f, x);
-    const uint32_t f63 = (uint32_t)__shfl((int)f, 63, 64);
-    const FS<MODE> x63 = S::shfl(x, 63);
-    fv = S::fop(x63, fv);  // this round, then the later ones
-    if (f63) {
-      cf = 1;
-      break;
+    for (int r = ROUNDS - 1; r >= 0; --r) {
+      uint8_t a;
+      bool head, tail;
+      load_round(k, v, A.aux, ns, packed, wb + r * 64 + lane, a, head, tail);
+      uint32_t f = head;
+      FS<MODE> x = S::flift(a);
+      wave_fscan<MODE>(f, x);
+      const uint32_t f63 = (uint32_t)__shfl((int)f, 63, 64);
+      const FS<MODE> x63 = S::shfl(x, 63);
+      fv = S::fop(x63, fv);  // this round, then the later ones
+      if (f63) {
+        cf = 1;
+        break;
+      }
     }
-  }
 #pragma unroll 1
-  for (int r = 0; r < ROUNDS; ++r) {
-    uint8_t a;
-    bool head, tail;
-    load_round(k, v, A.aux, ns, packed, wb + r * 64 + lane, a, head, tail);
-    uint32_t g = tail;
-    BS<MODE> y = S::blift(a);
-    wave_bscan<MODE>(g, y);
-    const uint32_t g0 = (uint32_t)__shfl((int)g, 0, 64);
-    const BS<MODE> y0 = S::shfl(y, 0);
-    bv = S::bop(bv, y0);
-    if (g0) {
-      cb = 1;
-      break;
+    for (int r = 0; r < ROUNDS; ++r) {
+      uint8_t a;
+      bool head, tail;
+      load_round(k, v, A.aux, ns, packed, wb + r * 64 + lane, a, head, tail);
+      uint32_t g = tail;
+      BS<MODE> y = S::blift(a);
+      wave_bscan<MODE>(g, y);
+      const uint32_t g0 = (uint32_t)__shfl((int)g, 0, 64);
+      const BS<MODE> y0 = S::shfl(y, 0);
+      bv = S::bop(bv, y0);
+      if (g0) {
+        cb = 1;
+        break;
+      }
     }
   }
   if (lane == 0) {
@@ -1860,6 +1961,7 @@ __device__ void ddrt_carry_body(const DDArgs& A, uint32_t nw) {
 }
 
 __global__ __launch_bounds__(kCT) void ddrt_carry_kernel(DDArgs A, uint32_t nw) {
+  nw = min(nw, ceil_div32(dd_len(A), kWaveElems));  // wavefronts that hold sorted elements
   if (A.ctl->max_ep < 4) ddrt_carry_body<0>(A, nw); else ddrt_carry_body<1>(A, nw);
 }
 
@@ -1880,6 +1982,14 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64],
   // per round: value and endpoint code (LDS), start/end flags and forward results (bits)
   uint32_t heads, tails, fres = 0;
   const uint32_t ns = dd_len(A);
+  if (blockIdx.x * (uint32_t)(kT * ROUNDS) >= ns) {  // past the sorted elements
+    if (threadIdx.x == 0) {
+      for (uint32_t k = S_DD_EVENTS; k <= S_ELIM_TX; ++k) *A.parts.at(k) = 0;
+      if (MID)
+        for (uint32_t k = S_UT_EVENTS; k <= S_UT_TIME; ++k) *A.parts.at(k) = 0;
+    }
+    return;
+  }
   load_wave<ROUNDS>(k, v, A.aux, ns, A.n < kPackLimit, wb, s_val[w], s_code[w], heads, tails);
   FS<MODE> carry = S::fid();
   BS<MODE> bcarry = S::bid();
@@ -2842,6 +2952,7 @@ struct Views {
   SortJob* jobs;
   uint8_t* cls;
   uint8_t* aux;
+  uint8_t* cand;
   unsigned long long* bk[2];
   uint32_t* bv[2];
   uint32_t* tile_cnt;
@@ -2916,6 +3027,7 @@ Views views(Workspace* ws) {
   v.jobs = static_cast<SortJob*>(b[B_JOBS].ptr);
   v.cls = static_cast<uint8_t*>(b[B_CLS].ptr);
   v.aux = static_cast<uint8_t*>(b[B_AUX].ptr);
+  v.cand = v.aux + v.cap;
   v.bk[0] = static_cast<unsigned long long*>(b[B_BKEY0].ptr);
   v.bk[1] = static_cast<unsigned long long*>(b[B_BKEY1].ptr);
   v.bv[0] = static_cast<uint32_t*>(b[B_BVAL0].ptr);
@@ -3087,7 +3199,7 @@ int analyze_reserve(Workspace* ws, size_t max_events) {
   int e;
   MidView sized;
   if ((e = b[B_MID].ensure(mid_views(sized, nullptr, cap) + 64)) || (e = b[B_CTL].ensure(sizeof(AnaCtl))) || (e = b[B_JOBS].ensure(sizeof(SortJob) * kNumJobs)) ||
-      (e = b[B_CLS].ensure(cap)) || (e = b[B_AUX].ensure(cap)) || (e = b[B_BKEY0].ensure(cap * 8)) ||
+      (e = b[B_CLS].ensure(cap)) || (e = b[B_AUX].ensure(2 * cap)) || (e = b[B_BKEY0].ensure(cap * 8)) ||
       (e = b[B_BKEY1].ensure(cap * 8)) || (e = b[B_BVAL0].ensure(cap * 4)) || (e = b[B_BVAL1].ensure(cap * 4)) ||
       (e = b[B_TILECNT].ensure((size_t)nt * 4 * (2 + kWaveCnt * (kT / 64)))) ||
       (e = b[B_AD].ensure(cap * (4 + 8 + 8 + 4 + 4 + 4 + 4 + 8 + 1) + 64)) ||
@@ -3872,7 +3984,8 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
     return check_hip(hipGetLastError(), "odp_analyze_trace launch");
   }
   hipLaunchKernelGGL(classify_kernel, dim3(nt), dim3(kT), 0, stream, events, nn, out_flags, v.cls, v.aux, v.bk[0],
-                     v.bv[0], v.wave_cnt, v.wscan.kmax, v.hist + (size_t)kJobBig * 256 * v.ntc, v.ntc, v.parts);
+                     v.bv[0], v.wave_cnt, v.wscan.kmax, v.hist + (size_t)kJobBig * 256 * v.ntc, v.ntc,
+                     alg2_rx ? nullptr : v.cand, v.parts);
   // the classification's counts, digest masks, first rejected record and endpoint range
   hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_AD_DEV_OR), dim3(kT), 0, stream, v.parts, nt, 0u, ctl, out_report);
 
@@ -3919,7 +4032,7 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   // its tiles instead of a block per log tile.
   const uint32_t side_blocks = std::min<uint32_t>(nt, (uint32_t)cus * 2);
   const JobSet Js{v.jobs + kJobAd, kSubsetJobs, side_blocks};
-  hipLaunchKernelGGL(sort_plan_kernel, dim3(1), dim3(64), 0, side, Js, 0u);
+  hipLaunchKernelGGL(sort_plan_kernel, dim3(1), dim3(64), 0, side, Js, 0u, nullptr, nullptr);
   for (uint32_t p = 0; p < 9; ++p) {
     hipLaunchKernelGGL(sort_hist_kernel, dim3(Js.njobs * side_blocks), dim3(kT), 0, side, Js, p);
     hipLaunchKernelGGL(sort_scan_kernel, dim3(256 * Js.njobs), dim3(kT), 0, side, Js, p);
@@ -3986,8 +4099,14 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   // the digest histograms take two tiles per block on long logs (measured a
   // little faster than one: the per-block start-up is amortised)
   const JobSet Jh{v.jobs + kJobBig, 1, nt > 4u * (uint32_t)cus ? (nt + 1) / 2 : nt};
-  hipLaunchKernelGGL(sort_plan_kernel, dim3(1), dim3(64), 0, stream, Jb, kfirst);
+  // (the literal Algorithm 2 pairs a self-transfer with itself, so there the
+  // single digests stay)
+  const bool filter = alg2_rx == nullptr;
+  hipLaunchKernelGGL(sort_plan_kernel, dim3(1), dim3(64), 0, stream, Jb, kfirst, filter ? v.cand : nullptr,
+                     filter ? &ctl->n_cand : nullptr);
   for (uint32_t p = 0; p < 8; ++p) {
+    if (p == 1 && filter)
+      hipLaunchKernelGGL(sort_filter_kernel, dim3(256), dim3(kFilterT), 0, stream, v.jobs + kJobBig);
     if (p == kfirst) hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, p);
     hipLaunchKernelGGL(sort_hist_kernel, dim3(Jh.stride), dim3(kT), 0, stream, Jh, p);
     hipLaunchKernelGGL(sort_scan_kernel, dim3(256), dim3(kT), 0, stream, Jb, p);

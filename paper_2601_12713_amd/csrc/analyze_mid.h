@@ -386,7 +386,10 @@ __global__ __launch_bounds__(kMidT) void mid_scan_kernel(WaveScan S, uint32_t nc
   constexpr uint32_t kSlot[kMidSums] = {S_N_INVALID, S_N_TRANSFERS, S_N_KERNELS, S_FIRST_BAD, S_MAX_EP, S_TMIN, S_TMAX};
   const uint32_t k = blockIdx.x - nchunk * kScanQ;
   reduce_slot<kMidT>(parts, nb, kSlot[k], ctl, rep);
-  if (k == 0 && threadIdx.x == 0) big->npasses = 2;  // the sorted order ends in keys[0], vals[0]
+  if (k == 0 && threadIdx.x == 0) {
+    big->npasses = 2;  // the sorted order ends in keys[0], vals[0], and holds every transfer
+    big->n_after1 = nullptr;
+  }
 }
 
 // One pass of the stable sort by group number: a tile of kMidTile elements per

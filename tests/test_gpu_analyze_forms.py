@@ -147,3 +147,27 @@ def test_sorted_logs(odp, kind):
     if kind == "all ones":
         ev["digest"] = np.where(k % 3 == 0, np.uint64(2**64 - 1), k // np.uint64(4) << np.uint64(8) | np.uint64(255))
     check(odp, ev)
+
+
+@pytest.mark.parametrize("kind", ["all single", "pairs among single", "self transfers", "crowded byte", "long ranges", "one byte varies"])
+def test_single_digests_are_dropped(odp, kind):
+    """Digests that occur once leave the sort after its first pass, by ranges of their lowest byte."""
+    n = 300_001
+    ev = random_log(n, n, devices=10 if kind == "pairs among single" else 3, digests=40, places=2000,
+                    kernels=0.05, allocs=0.05 if kind in ("crowded byte", "long ranges") else 0.25)
+    k = np.arange(n, dtype=np.uint64)
+    digest = k * np.uint64(0x9E3779B97F4A7C15)  # each once
+    if kind in ("pairs among single", "crowded byte", "long ranges"):
+        digest = np.where(k % 5 == 0, digest[n // 2], digest)
+        digest[n // 2:] = np.where(k[n // 2:] % 3 == 0, digest[:n - n // 2], digest[n // 2:])
+    if kind == "crowded byte":  # more than 2^17 transfers in one range
+        digest = digest & ~np.uint64(255) | np.where(k % 10 == 0, k % np.uint64(256), np.uint64(9))
+    if kind == "long ranges":   # 6 ranges around and above the elements held per thread
+        digest = digest & ~np.uint64(255) | np.where(k % 7 == 0, np.uint64(3), k % np.uint64(6))
+    if kind == "self transfers":
+        ev["src_dev"] = ev["dst_dev"] = 1
+        digest = np.where(k % 50 == 0, np.uint64(5), digest)
+    if kind == "one byte varies":
+        digest = k % np.uint64(256)
+    ev["digest"] = digest
+    check(odp, ev)
