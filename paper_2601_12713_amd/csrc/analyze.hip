@@ -11,12 +11,14 @@
 // sorted order:
 //
 //   classify   one read of the 64-byte records: validity, per-record flags,
-//              the digest sort keys, and a 1-byte class / endpoint code
-//   subsets    ordered compaction of ALLOC/DELETE, KERNEL and copy-in (H2D or
-//              D2D into a device) records, each with its device's kernel
-//              count and latest kernel end so far
-//   sorts      transfers by digest (the first pass drops every other record;
-//              low bytes first, then short runs of equal low bytes sorted in
+//              the digest sort keys, a 1-byte class / endpoint code, and
+//              whether a copy-in (H2D or D2D into a device) is unused where
+//              the records right after it tell
+//   subsets    ordered compaction of ALLOC/DELETE, KERNEL and the other
+//              copy-in records, each with its device's kernel count and
+//              latest kernel end so far
+//   sorts      transfers by digest (the first pass drops every other record,
+//              the second the digests that occur once; low bytes first, then short runs of equal low bytes sorted in
 //              place); ALLOC/DELETE by (device, device
 //              address); when needed, KERNELs by (device, start) and by
 //              (device, end) and copy-ins by (endpoints, source address)
@@ -68,8 +70,10 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint32_t kWalkMax = 4096;
 
 // C_COPYIN: a transfer that writes device memory (H2D or D2D, dst_dev >= 0),
-// the records the unused-transfer rule looks at.
-enum : uint8_t { C_INVALID = 0, C_TRANSFER = 1, C_ALLOCDEL = 2, C_KERNEL = 3, C_COPYIN = 4 };
+// the records the unused-transfer rule looks at. Logs of more than kMidMax
+// records decide most of them in the classification: C_SEEN is decided but
+// may be what a copy before it is searching for, C_DECIDED is neither.
+enum : uint8_t { C_INVALID = 0, C_TRANSFER = 1, C_ALLOCDEL = 2, C_KERNEL = 3, C_COPYIN = 4, C_SEEN = 5, C_DECIDED = 6 };
 
 __host__ __device__ inline uint32_t ceil_div32(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 
@@ -87,7 +91,7 @@ struct AnaCtl {
   uint32_t n_ad;        // ALLOC/DELETE records
   uint32_t n_k;         // KERNEL records
   uint32_t n_pairs;     // paired allocations
-  uint32_t n_ut;        // copy-in records
+  uint32_t n_ut;        // copy-in records listed for the unused-transfer rule
   uint32_t first_bad;
   uint32_t max_ep;      // largest endpoint code among valid transfers
   WordMask m_digest, m_ad_dev, m_ad_addr, m_k_start, m_k_end, m_k_dev, m_ut_addr, m_ut_code;
@@ -98,13 +102,15 @@ struct AnaCtl {
   // last user of each resets it), and each quantity's total
   uint32_t scan_tq[kWaveCnt + kEp];
   uint32_t scan_ticket;
+  uint32_t plan_ticket[2];  // reductions whose last block plans a sort: blocks done
   uint64_t scan_tot[kWaveCnt + kEp];
   uint32_t ut_need_sort;              // 1: some copy-in is decided by the sorted path
   uint32_t kern_sort;                 // 1: the kernel lists are sorted (the count form's binary searches)
-  // removable time (Sec. 7.6), in three parts written by different stages:
+  // removable time (Sec. 7.6), in parts written by different stages:
   // transfers flagged DD or RT_RX; pairs flagged RA or UA; transfers flagged
   // UT only
-  uint64_t elim_tx, elim_pairs, elim_ut;
+  uint64_t elim_tx, elim_pairs;
+  uint64_t ud_events, ud_bytes, ud_time;  // unused transfers by the classification's own decisions
   uint32_t wticket;                   // logs analysed by walks: workgroups done
 };
 constexpr int kNumMasks = 8;
@@ -239,6 +245,7 @@ __device__ void block_add(uint64_t* dst64, unsigned long long v) {
 // serialise at one L2 channel).
 enum Slot : uint32_t {
   S_N_INVALID, S_N_TRANSFERS, S_N_KERNELS, S_DIG_OR, S_DIG_AND, S_FIRST_BAD, S_MAX_EP, S_TMIN, S_TMAX,
+  S_UD_EVENTS, S_UD_BYTES, S_UD_TIME,
   S_AD_DEV_OR, S_AD_DEV_AND, S_AD_ADDR_OR, S_AD_ADDR_AND, S_KS_OR, S_KS_AND, S_KE_OR, S_KE_AND, S_KD_OR, S_KD_AND,
   S_UT_ADDR_OR, S_UT_ADDR_AND, S_UT_CODE_OR, S_UT_CODE_AND,
   S_DD_EVENTS, S_DD_GROUPS, S_DD_BYTES, S_DD_TIME, S_RT_PAIRS, S_RT_RX, S_RT_BYTES, S_RT_TIME, S_ELIM_TX,
@@ -284,9 +291,11 @@ __device__ void block_store(unsigned long long* dst, unsigned long long v) {
 // ---------------------------------------------------------------------------
 // 0. Reset of the report and the call's counters.
 // ---------------------------------------------------------------------------
-__global__ void init_kernel(AnaCtl* ctl, odp_report* rep, uint32_t* totals, uint32_t ntotals, uint32_t n) {
-  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  for (uint32_t i = t; i < ntotals; i += gridDim.x * blockDim.x) totals[i] = 0;
+// (thread t of `step`; run by the classification's launch, which reads none of it)
+constexpr uint32_t kTotals = 5 * kMaxPasses * 256;  // digit totals: jobs x passes x digits
+__device__ __forceinline__ void init_body(AnaCtl* ctl, odp_report* rep, uint32_t* totals, uint32_t n, uint32_t t,
+                                          uint32_t step) {
+  for (uint32_t i = t; i < kTotals; i += step) totals[i] = 0;
   if (t == 0) {
     unsigned long long* r = reinterpret_cast<unsigned long long*>(rep);
     for (int i = 0; i < (int)(offsetof(odp_report, predicted_speedup) / 8); ++i) r[i] = 0;
@@ -300,10 +309,10 @@ __global__ void init_kernel(AnaCtl* ctl, odp_report* rep, uint32_t* totals, uint
     ctl->max_ep = 0;
     ctl->t_min = ~0ull;
     ctl->t_max = 0;
-    ctl->elim_tx = ctl->elim_pairs = ctl->elim_ut = 0;
+    ctl->elim_tx = ctl->elim_pairs = 0;
     ctl->ut_need_sort = 0;
     ctl->kern_sort = 0;
-    ctl->scan_ticket = 0;
+    ctl->scan_ticket = ctl->plan_ticket[0] = ctl->plan_ticket[1] = 0;
     for (int q = 0; q < kWaveCnt + kEp; ++q) ctl->scan_tq[q] = 0;
     WordMask* m = &ctl->m_digest;
     for (int i = 0; i < kNumMasks; ++i) {
@@ -317,29 +326,85 @@ __global__ void init_kernel(AnaCtl* ctl, odp_report* rep, uint32_t* totals, uint
   }
 }
 
+// An empty log: the report alone (in front of finalize_kernel).
+__global__ void init_kernel(AnaCtl* ctl, odp_report* rep, uint32_t* totals) {
+  init_body(ctl, rep, totals, 0, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
 // ---------------------------------------------------------------------------
 // 1. Classification: one read of every record.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ bool dev_ok(int d) { return d >= -1 && d <= ODP_MAX_DEVICE; }
 
+// Hash of a key of two words (group tables, places of copies).
+__device__ __forceinline__ uint32_t near_hash(uint64_t a, uint64_t b) {
+  uint64_t h = (a ^ (b << 48) ^ (b >> 16)) * 0x9E3779B97F4A7C15ull;
+  h ^= h >> 32;
+  h *= 0xBF58476D1CE4E5B9ull;
+  return (uint32_t)(h >> 32);
+}
+
+// Unused transfers inside one span of kSpanRecs consecutive records (Def. 4,
+// see section 8 for the rule): most copies into device memory meet their
+// device's next kernel, or the next copy to their place, a few records later,
+// so the classification decides them while it holds the records, and only the
+// rest is listed, gathered and searched for by the later launches. In a
+// chronological log, for a copy c with no kernel still running at its start:
+//   kernel k in the span   used, unless a copy to c's place lies between them
+//                          and starts before k does
+//   no kernel, a copy n    n starts before the span's last record does, and so
+//     to the place           before any later kernel: unused
+// else c is open. A copy that an open one may be looking for is the first of
+// its place in its span and lies before the span's first kernel on its device,
+// or is open itself (it ties with the span's last record): those are listed
+// too. Kernels of earlier wavefronts that still run at c are taken into
+// account at the end (ut_merge_kernel), as are logs with a rejected record,
+// where none of this counts and every copy is listed.
+// Starts are compared by how many records after a record start later than
+// their predecessor (g below): t(a) < t(b) for a before b exactly if g(a) > g(b).
+constexpr int kSpan = 8;                      // rounds of 64 records
+constexpr uint32_t kSpanRecs = kSpan * 64;
+constexpr uint32_t kSpanHeads = 64;
+constexpr uint32_t kNoNode = 0xFFFFFFFFu;
+constexpr uint32_t kHasPred = 1u << 31;
+struct SpanLds {
+  unsigned long long addr[kSpanRecs];  // source address of a copy
+  uint32_t rec[kSpanRecs];             // copies: next in the bucket's chain (itself: the last) | g << 10 | endpoints << 20 | kHasPred
+  uint32_t head[kSpanHeads];           // buckets by place: the node pushed last (later rounds are pushed first)
+  uint32_t nk[kEp];                    // per device code: the next kernel, g << 10 | record of the span; kNoNode if none
+};
+static_assert(kSpanHeads == 64 && kSpan <= 10 && kRounds % kSpan == 0, "a head per lane, three bits per round, ten of a record of the span");
+
 // One block per tile of kTile records; wavefront w takes the 1,024
 // consecutive records [tile*kTile + w*1024, ...) in 16 rounds of 64 and also
-// counts the ALLOC/DELETE, KERNEL and copy-in records it sees (for the
+// counts the ALLOC/DELETE, KERNEL and listed copy-in records it sees (for the
 // compaction). The block also counts its tile's valid transfers by the least
 // significant byte of their digest (hist0, row length ntc): the digest sort's
 // first pass when that byte varies (that pass keeps only the transfers).
-__global__ __launch_bounds__(kT) void classify_kernel(const odp_event* __restrict__ ev, uint32_t n, uint8_t* __restrict__ flags,
+// Bound by the read of the records, 64 bytes each, and, for the search, by the
+// latency of its LDS reads with 20 wavefronts per CU: 249 us for 10.7 million
+// records (194 us without the search, 20 to 40 of the difference for walking
+// the buckets, 12 for reading the unused copies' bytes again). It leaves 3% of
+// the copies to the later launches there, which took 430 us together and take
+// 90: subset compaction 293 -> 69, forward search 107 -> 12, merge 30 -> 10.
+// Spans of 4 rounds: 220 us, but twice the listed copies with several devices
+// (2 million records on 8 devices: 578 us against 503 in all).
+__global__ __launch_bounds__(kT, 5) void classify_kernel(const odp_event* __restrict__ ev, uint32_t n, uint8_t* __restrict__ flags,
                                                       uint8_t* __restrict__ cls, uint8_t* __restrict__ aux,
                                                       unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                      uint32_t* __restrict__ wave_cnt, uint64_t* __restrict__ wave_kmax,
-                                                      uint32_t* __restrict__ hist0, uint32_t ntc, uint8_t* __restrict__ cand,
-                                                      Parts parts) {
+                                                      uint32_t* __restrict__ wave_cnt, uint32_t* __restrict__ wave_copies,
+                                                      uint64_t* __restrict__ wave_kmax, uint32_t* __restrict__ hist0,
+                                                      uint32_t ntc, uint8_t* __restrict__ cand, Parts parts,
+                                                      AnaCtl* ctl, odp_report* rep, uint32_t* totals) {
+  init_body(ctl, rep, totals, n, blockIdx.x * kT + threadIdx.x, gridDim.x * kT);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint32_t wid = blockIdx.x * (kT / 64) + w;
   const uint32_t wb = wid * kWaveElems;
   __shared__ uint32_t s_kdev[kT / 64][kEp];
   __shared__ unsigned long long s_kmax[kT / 64][kEp];
   __shared__ uint32_t s_h0[256];
+  __shared__ SpanLds s_span[kT / 64];
+  SpanLds& L = s_span[w];
   static_assert(kT == 256, "one histogram bin per thread");
   s_h0[threadIdx.x] = 0;
   if (lane < kEp) {
@@ -347,77 +412,189 @@ __global__ __launch_bounds__(kT) void classify_kernel(const odp_event* __restric
     s_kmax[w][lane] = 0;
   }
   __syncthreads();
-  unsigned long long n_inv = 0, n_tx = 0, n_k = 0, kor = 0, kand = ~0ull, tmin = ~0ull, tmax = 0;
-  uint32_t bad = kNone, mep = 0, c_ad = 0, c_k = 0, c_ut = 0;
+  unsigned long long kor = 0, kand = ~0ull, tmin = ~0ull, tmax = 0;
+  unsigned long long ud_b = 0, ud_t = 0;
+  uint32_t n_inv = 0, n_tx = 0, bad = kNone, mep = 0, c_ad = 0, c_k = 0, c_ut = 0, c_all = 0, c_ud = 0;
+  const uint64_t above = ~lanemask_lt() & ~(1ull << lane);  // lanes above this one
   // records of the next round are loaded while this round is classified; the
   // previous record of lane 0 is lane 63 of the round before
   odp_event e;
   bool in = wb + lane < n;
   if (in) e = ev[wb + lane];
   uint64_t last_prev = (lane == 0 && in && wb > 0) ? ev[wb - 1].t_start : 0;
-  for (int r = 0; r < kRounds; ++r) {
-    const uint32_t i = wb + r * 64 + lane;
-    const bool in_next = r + 1 < kRounds && i + 64 < n;
-    odp_event nx;
-    if (in_next) nx = ev[i + 64];
-    const uint64_t ts = in ? e.t_start : 0;
-    uint64_t prev_start = __shfl_up(ts, 1, 64);
-    if (lane == 0) prev_start = last_prev;
-    last_prev = __shfl(ts, 63, 64);
-    if (in) {
-      const bool is_tx = e.op == ODP_H2D || e.op == ODP_D2H || e.op == ODP_D2D;
-      const bool valid = e.op >= ODP_ALLOC && e.op <= ODP_KERNEL && e.t_end >= e.t_start &&
-                         (i == 0 || e.t_start >= prev_start) && dev_ok(e.dst_dev) && (!is_tx || dev_ok(e.src_dev));
+#pragma unroll 1
+  for (int r0 = 0; r0 < kRounds; r0 += kSpan) {
+    // of this lane's record of round r: class in bits 3r.., bit r of the others
+    // whether it starts after its predecessor and what is decided of a copy
+    uint32_t classes = 0, later = 0, used = 0, unused = 0;
+    L.head[lane] = kNoNode;
+    if (lane < kEp) L.nk[lane] = kNoNode;
+#pragma unroll 1
+    for (int r = 0; r < kSpan; ++r) {
+      const uint32_t i = wb + (r0 + r) * 64 + lane;
+      const bool in_next = r0 + r + 1 < kRounds && i + 64 < n;
+      odp_event nx;
+      if (in_next) nx = ev[i + 64];
+      const uint64_t ts = in ? e.t_start : 0;
+      uint64_t prev_start = __shfl_up(ts, 1, 64);
+      if (lane == 0) prev_start = last_prev;
+      last_prev = __shfl(ts, 63, 64);
       uint8_t c = C_INVALID, a = kNotTransfer;
-      unsigned long long key = ~0ull;
-      if (valid) {
-        tmin = min(tmin, (unsigned long long)e.t_start);
-        tmax = max(tmax, (unsigned long long)e.t_end);
-        if (is_tx) {
-          const bool copyin = e.op != ODP_D2H && e.dst_dev >= 0;
-          c = copyin ? C_COPYIN : C_TRANSFER;
-          c_ut += copyin;
-          a = (uint8_t)(((e.src_dev + 1) << 4) | (e.dst_dev + 1));
-          mep = max(mep, (uint32_t)max(e.src_dev + 1, e.dst_dev + 1));
-          key = e.digest;
-          ++n_tx;
-        } else if (e.op == ODP_KERNEL) {
-          c = C_KERNEL;
-          ++n_k;
-          ++c_k;
-          atomicAdd(&s_kdev[w][e.dst_dev + 1], 1u);
-          atomicMax(&s_kmax[w][e.dst_dev + 1], (unsigned long long)e.t_end);
+      uint32_t dc = 0;
+      if (in) {
+        const bool is_tx = e.op == ODP_H2D || e.op == ODP_D2H || e.op == ODP_D2D;
+        const bool valid = e.op >= ODP_ALLOC && e.op <= ODP_KERNEL && e.t_end >= e.t_start &&
+                           (i == 0 || e.t_start >= prev_start) && dev_ok(e.dst_dev) && (!is_tx || dev_ok(e.src_dev));
+        unsigned long long key = ~0ull;
+        if (valid) {
+          tmin = min(tmin, (unsigned long long)e.t_start);
+          tmax = max(tmax, (unsigned long long)e.t_end);
+          dc = (uint32_t)(e.dst_dev + 1);
+          if (is_tx) {
+            c = e.op != ODP_D2H && e.dst_dev >= 0 ? C_COPYIN : C_TRANSFER;
+            a = (uint8_t)(((e.src_dev + 1) << 4) | (e.dst_dev + 1));
+            mep = max(mep, (uint32_t)max(e.src_dev + 1, e.dst_dev + 1));
+            key = e.digest;
+            ++n_tx;
+          } else if (e.op == ODP_KERNEL) {
+            c = C_KERNEL;
+            ++c_k;
+          } else {
+            c = C_ALLOCDEL;
+            ++c_ad;
+          }
         } else {
-          c = C_ALLOCDEL;
-          ++c_ad;
+          ++n_inv;
+          bad = min(bad, i);
         }
-      } else {
-        ++n_inv;
-        bad = min(bad, i);
+        aux[i] = a;
+        if (cand) cand[i] = 1;
+        keys[i] = key;
+        if (c == C_TRANSFER || c == C_COPYIN) atomicAdd(&s_h0[key & 0xFF], 1u);
+        vals[i] = n < kPackLimit ? i | ((uint32_t)a << 24) : i;
+        kor |= key;
+        kand &= key;
       }
-      flags[i] = valid ? 0 : ODP_F_INVALID;
-      cls[i] = c;
-      aux[i] = a;
-      if (cand) cand[i] = 1;
-      keys[i] = key;
-      if (c == C_TRANSFER || c == C_COPYIN) atomicAdd(&s_h0[key & 0xFF], 1u);
-      vals[i] = n < kPackLimit ? i | ((uint32_t)a << 24) : i;
-      kor |= key;
-      kand &= key;
+      const bool copy = c == C_COPYIN;
+      const uint64_t end = in ? e.t_end : 0;
+      // a kernel of this wavefront logged before the copy still runs at its start
+      uint32_t runs = copy && s_kdev[w][dc] != 0 && s_kmax[w][dc] >= ts;
+      const uint64_t kernels = __ballot(c == C_KERNEL);
+      if (kernels) {
+        for (uint64_t m = kernels; m; m &= m - 1) {
+          const int kl = __builtin_ctzll(m);
+          const uint32_t kd = lane32(dc, kl);
+          const uint64_t kend = lane64(end, kl);
+          runs |= copy && lane > kl && dc == kd && kend >= ts;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (c == C_KERNEL) {
+          atomicAdd(&s_kdev[w][dc], 1u);
+          atomicMax(&s_kmax[w][dc], (unsigned long long)end);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      }
+      classes |= (uint32_t)c << (3 * r);
+      later |= (uint32_t)(in && ts > prev_start) << r;
+      used |= runs << r;
+      L.rec[r * 64 + lane] = (copy ? a : dc) << 20;
+      L.addr[r * 64 + lane] = in ? e.src_addr : 0;
+      e = nx;
+      in = in_next;
     }
-    e = nx;
-    in = in_next;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // backwards: a copy joins its place's bucket and searches it
+    uint32_t g_after = 0;
+#pragma unroll 1
+    for (int r = kSpan - 1; r >= 0; --r) {
+      const uint32_t node = r * 64 + lane, c = (classes >> (3 * r)) & 7;
+      const uint32_t code = L.rec[node] >> 20, dc = code & 15;
+      const bool copy = c == C_COPYIN;
+      const uint64_t lm = __ballot((later >> r) & 1);
+      const uint32_t g = g_after + (uint32_t)__popcll(lm & above);
+      // the next kernel on the receiving device
+      uint32_t nk = copy ? L.nk[dc] : kNoNode;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      for (uint64_t m = __ballot(c == C_KERNEL); m;) {
+        const int kl = 63 - __builtin_clzll(m);
+        m &= ~(1ull << kl);
+        const uint32_t kd = lane32(dc, kl), kk = lane32(g, kl) << 10 | (uint32_t)(r * 64 + kl);
+        if (copy && dc == kd && lane < kl) nk = kk;
+        if (lane == 0) L.nk[kd] = kk;
+      }
+      const unsigned long long addr = L.addr[node];
+      const uint32_t bucket = near_hash(addr, code) % kSpanHeads;
+      if (copy) {
+        const uint32_t old = atomicExch(&L.head[bucket], node);
+        L.rec[node] = (old == kNoNode ? node : old) | g << 10 | code << 20;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      // the first copy to the place after this one and before that kernel. Nodes
+      // of a round come in any order, rounds in order; results stay integers.
+      const uint32_t limit = nk == kNoNode ? kSpanRecs : nk & 1023;
+      const bool open = copy && !((used >> r) & 1);
+      uint32_t best = limit, best_g = 0, cur = open ? L.head[bucket] : kNoNode;
+      while (__ballot(cur != kNoNode)) {
+        if (cur != kNoNode) {
+          const uint32_t x = L.rec[cur];
+          const uint32_t hit = (uint32_t)(L.addr[cur] == addr) & (((x >> 20) & 0xFF) == code) & (cur > node) & (cur < best);
+          best = hit ? cur : best;
+          best_g = hit ? (x >> 10) & 1023 : best_g;
+          const uint32_t nx = x & 1023;
+          cur = nx == cur || (nx >> 6) > (best >> 6) ? kNoNode : nx;
+        }
+      }
+      if (open) {
+        const bool found = best != limit;
+        if (found) atomicOr(&L.rec[best], kHasPred);
+        const bool no = nk != kNoNode ? found && best_g > (nk >> 10) : found && best_g > 0;
+        unused |= (uint32_t)no << r;
+        used |= (uint32_t)(nk != kNoNode && !no) << r;
+      }
+      g_after += (uint32_t)__popcll(lm);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // classes and flags; the unused copies' bytes and durations, read again
+#pragma unroll 4
+    for (int r = 0; r < kSpan; ++r) {
+      const uint32_t node = r * 64 + lane, i = wb + r0 * 64 + node;
+      if (i < n) {
+        uint8_t c = (classes >> (3 * r)) & 7;
+        uint8_t f = c == C_INVALID ? ODP_F_INVALID : 0;
+        if (c == C_COPYIN) {
+          ++c_all;
+          if (((used | unused) >> r) & 1) {
+            const uint32_t x = L.rec[node], first = L.nk[(x >> 20) & 15];
+            const bool seen = (first == kNoNode || node < (first & 1023)) && !(x & kHasPred);
+            c = seen ? C_SEEN : C_DECIDED;
+          }
+          c_ut += c != C_DECIDED;
+        }
+        if ((unused >> r) & 1) {
+          f = ODP_F_UT;
+          ++c_ud;
+          ud_b += ev[i].bytes;
+          ud_t += ev[i].t_end - ev[i].t_start;
+        }
+        flags[i] = f;
+        cls[i] = c;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
+  const uint32_t n_k = c_k;
   // per-wavefront subset counts
   for (int o = 32; o >= 1; o >>= 1) {
     c_ad += __shfl_xor(c_ad, o, 64);
     c_k += __shfl_xor(c_k, o, 64);
     c_ut += __shfl_xor(c_ut, o, 64);
+    c_all += __shfl_xor(c_all, o, 64);
   }
   if (lane == 0) {
     wave_cnt[kWaveCnt * wid] = c_ad;
     wave_cnt[kWaveCnt * wid + 1] = c_k;
     wave_cnt[kWaveCnt * wid + 2] = c_ut;
+    wave_copies[wid] = c_all;
   }
   __syncthreads();
   hist0[(size_t)threadIdx.x * ntc + blockIdx.x] = s_h0[threadIdx.x];
@@ -434,6 +611,9 @@ __global__ __launch_bounds__(kT) void classify_kernel(const odp_event* __restric
   block_store<R_MAX>(parts.at(S_MAX_EP), mep);
   block_store<R_MIN>(parts.at(S_TMIN), tmin);
   block_store<R_MAX>(parts.at(S_TMAX), tmax);
+  block_store<R_ADD>(parts.at(S_UD_EVENTS), c_ud);
+  block_store<R_ADD>(parts.at(S_UD_BYTES), ud_b);
+  block_store<R_ADD>(parts.at(S_UD_TIME), ud_t);
 }
 
 // ---------------------------------------------------------------------------
@@ -496,6 +676,9 @@ struct WaveScan {
   uint32_t* ccnt;  // [nchunk][kWaveCnt]: chunk totals, then their exclusive prefixes
   uint64_t* cmax;  // [nchunk][kEp]
   uint32_t nw;
+  // [nw], or null: all copy-ins of the wavefronts, counted instead of the
+  // listed ones (cnt[..][2]) in a log with a rejected record
+  const uint32_t* copies;
 };
 constexpr uint32_t kScanChunk = 1024;
 
@@ -538,15 +721,15 @@ __device__ __forceinline__ T block_xscan(T x, T* wt, T& total) {
 }
 
 // Scans quantity q (element i at base[stride * i]) over [c * kScanChunk, ...)
-// in place; then the quantity's chunk totals (ct[stride * c]) by its last
+// in place (from the values instead[i] when given); then the quantity's chunk totals (ct[stride * c]) by its last
 // block. Returns true in the block that finished the quantity last overall.
 template <typename T, bool MAX>
 __device__ bool scan_quantity(T* base, T* ct, uint32_t stride, uint32_t nw, uint32_t nchunk, uint32_t c, uint32_t q,
-                              AnaCtl* ctl, T* wt, uint32_t* flag) {
+                              AnaCtl* ctl, T* wt, uint32_t* flag, const T* instead = nullptr) {
   const uint32_t i = c * kScanChunk + threadIdx.x;
   const bool in = i < nw;
   T total;
-  const T x = block_xscan<T, MAX>(in ? base[(size_t)stride * i] : (T)0, wt, total);
+  const T x = block_xscan<T, MAX>(in ? instead ? instead[i] : base[(size_t)stride * i] : (T)0, wt, total);
   if (in) base[(size_t)stride * i] = x;
   // the chunk total reaches the device-coherent level before the ticket:
   // an agent-scope store and a wait for its completion, not a fence (an
@@ -585,7 +768,8 @@ __device__ void wave_scan_body(const WaveScan& S, uint32_t nchunk, AnaCtl* ctl) 
   const bool last =
       q < kWaveCnt
           ? scan_quantity<uint32_t, false>(S.cnt + q, S.ccnt + q, kWaveCnt, S.nw, nchunk, c, q, ctl,
-                                           reinterpret_cast<uint32_t*>(wt), &flag)
+                                           reinterpret_cast<uint32_t*>(wt), &flag,
+                                           q == 2 && S.copies && ctl->first_bad != kNone ? S.copies : nullptr)
           : scan_quantity<unsigned long long, true>(reinterpret_cast<unsigned long long*>(S.kmax) + (q - kWaveCnt),
                                                     reinterpret_cast<unsigned long long*>(S.cmax) + (q - kWaveCnt), kEp,
                                                     S.nw, nchunk, c, q, ctl, wt, &flag);
@@ -609,14 +793,16 @@ __global__ __launch_bounds__(1024) void wave_scan_kernel(WaveScan S, uint32_t nc
   wave_scan_body(S, nchunk, ctl);
 }
 
+constexpr uint8_t kUtSeen = 4;
 struct SubsetOut {
-  uint32_t* ut_idx;     // copy-ins: record index
+  uint32_t* ut_idx;     // listed copy-ins: record index
   uint64_t* ut_w_addr;  // source address
   uint64_t* ut_w_code;  // endpoint code (src_dev + 1) << 4 | (dst_dev + 1)
   uint64_t* ut_ts;      // t_start
   uint32_t* ut_vals;
   uint32_t* ut_kc;      // KERNEL records on the receiving device logged before the copy
   uint64_t* ut_km;      // the latest end among those (0 when there is none)
+  uint8_t* ut_hit;      // kUtSeen for a copy that is decided already (C_SEEN)
   uint32_t* ad_kc;      // ALLOC/DELETE: KERNEL records on its device logged before it
   uint64_t* ad_km;      // ... and the latest end among them
   uint64_t* kd_ts;      // KERNEL records per device code in log order (from kd_base[code]): start
@@ -636,17 +822,12 @@ struct SubsetOut {
   uint32_t* k_vals_e;
 };
 
-// Hash of a key of two words (group tables, places of copies).
-__device__ __forceinline__ uint32_t near_hash(uint64_t a, uint64_t b) {
-  uint64_t h = (a ^ (b << 48) ^ (b >> 16)) * 0x9E3779B97F4A7C15ull;
-  h ^= h >> 32;
-  h *= 0xBF58476D1CE4E5B9ull;
-  return (uint32_t)(h >> 32);
-}
-
 // Ordered compaction of the ALLOC/DELETE, KERNEL and copy-in records. Wavefront w
-// takes its 1,024 records in 16 coalesced rounds of 64 (lane l: record
-// wb + 64r + l); a ballot per round gives each matching lane its rank, so the
+// takes 1,024 records: it first gathers which of them are listed (of the copy-ins
+// those the classification left open, or all in a log with a rejected record)
+// in record order, then reads those, 64 at a time (one record in eight in the
+// trace workload; by 16 rounds of all records: 170 us instead of 69 for 10.7
+// million). A ballot per round gives each matching lane its rank, so the
 // entries land in record order at the wavefront's scanned offsets, and the
 // records of a round are read together. Each copy-in also gets the number of
 // KERNEL records on its receiving device logged before it: the device's count
@@ -667,6 +848,21 @@ __device__ void subset_scatter_body(const odp_event* __restrict__ ev, const uint
     const uint32_t i = wb + r * 64 + lane;
     c[r] = i < n ? cls[i] : C_INVALID;
   }
+  const uint64_t lt = lanemask_lt();
+  const uint8_t last_ut = !MID && S.ctl->first_bad != kNone ? C_DECIDED : C_SEEN;
+  // the listed records of the wavefront: class << 10 | record
+  __shared__ uint16_t s_list[MID ? 1 : kT / 64][MID ? 1 : ROUNDS * 64];
+  uint32_t rounds = ROUNDS, listed = 0;
+  if constexpr (!MID) {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const bool take = c[r] >= C_ALLOCDEL && c[r] <= last_ut;
+      const uint64_t m = __ballot(take);
+      if (take) s_list[w][listed + (uint32_t)__popcll(m & lt)] = (uint16_t)((uint32_t)c[r] << 10 | (uint32_t)(r * 64 + lane));
+      listed += (uint32_t)__popcll(m);
+    }
+    rounds = ceil_div32(listed, 64);
+  }
   // offsets: the wavefront's prefix within its chunk plus the chunk's prefix
   const uint32_t* wo = W.cnt + (size_t)kWaveCnt * wid;
   const uint32_t* co = W.ccnt + (size_t)kWaveCnt * (wid / kScanChunk);
@@ -681,12 +877,19 @@ __device__ void subset_scatter_body(const odp_event* __restrict__ ev, const uint
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   unsigned long long o_dev = 0, a_dev = ~0ull, o_addr = 0, a_addr = ~0ull, o_ks = 0, a_ks = ~0ull, o_ke = 0,
                      a_ke = ~0ull, o_kd = 0, a_kd = ~0ull, o_ua = 0, a_ua = ~0ull, o_uc = 0, a_uc = ~0ull;
-  const uint64_t lt = lanemask_lt();
-  constexpr int kUnroll = ROUNDS < 4 ? ROUNDS : 4;
+  constexpr int kUnroll = MID ? ROUNDS : 2;
 #pragma unroll kUnroll
-  for (int r = 0; r < ROUNDS; ++r) {
-    const uint32_t i = wb + r * 64 + lane;
-    const bool is_ad = c[r] == C_ALLOCDEL, is_k = c[r] == C_KERNEL, is_ut = c[r] == C_COPYIN;
+  for (uint32_t r = 0; r < rounds; ++r) {
+    uint32_t i = wb + r * 64 + lane, cr = C_INVALID;
+    if constexpr (MID) {
+      cr = c[r];
+    } else if (r * 64 + lane < listed) {
+      const uint32_t x = s_list[w][r * 64 + lane];
+      i = wb + (x & 1023);
+      cr = x >> 10;
+    }
+    const bool is_ad = cr == C_ALLOCDEL, is_k = cr == C_KERNEL;
+    const bool is_ut = cr >= C_COPYIN && cr <= last_ut;
     const uint64_t bad = __ballot(is_ad), bk = __ballot(is_k), bu = __ballot(is_ut);
     // the whole record, once, for the records this kernel lists
     odp_event e{};
@@ -697,30 +900,18 @@ __device__ void subset_scatter_body(const odp_event* __restrict__ ev, const uint
     uint32_t kc = (is_ut || is_k || is_ad) ? s_kc[w][dc] : 0u;
     unsigned long long km = (is_ut || is_ad) ? s_km[w][dc] : 0ull;
     if (bk) {
-      uint32_t devs = is_k ? 1u << dc : 0u;
-      for (int o = 32; o >= 1; o >>= 1) devs |= __shfl_xor(devs, o, 64);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      while (devs) {
-        const uint32_t d = (uint32_t)__builtin_ctz(devs);
-        devs &= devs - 1;
-        const uint64_t kd = __ballot(is_k && dc == d);
-        // latest end among this device's kernels in lower lanes (exclusive max scan)
-        unsigned long long x = (is_k && dc == d) ? kend : 0ull;
-        for (int o = 1; o < 64; o <<= 1) {
-          const unsigned long long y = __shfl_up(x, o, 64);
-          if (lane >= o) x = max(x, y);
-        }
-        unsigned long long ex = __shfl_up(x, 1, 64);
-        if (lane == 0) ex = 0;
-        const unsigned long long all = __shfl(x, 63, 64);
-        if ((is_ut || is_k || is_ad) && dc == d) {
-          kc += (uint32_t)__popcll(kd & lt);
-          km = max(km, ex);
-        }
-        if (lane == 0) {
-          s_kc[w][d] += (uint32_t)__popcll(kd);
-          s_km[w][d] = max(s_km[w][d], all);
-        }
+      for (uint64_t m = bk; m; m &= m - 1) {  // this round's kernels, one after another
+        const int kl = __builtin_ctzll(m);
+        const uint32_t d = lane32(dc, kl);
+        const unsigned long long te = lane64(kend, kl);
+        const uint32_t on = dc == d && lane > kl;
+        kc += on;
+        km = on ? max(km, te) : km;
+      }
+      if (is_k) {
+        atomicAdd(&s_kc[w][dc], 1u);
+        atomicMax(&s_km[w][dc], kend);
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
@@ -734,6 +925,7 @@ __device__ void subset_scatter_body(const odp_event* __restrict__ ev, const uint
       S.ut_vals[q] = MID ? near_hash(sa, code) : q;  // MID: a hash of the place
       S.ut_kc[q] = kc;
       S.ut_km[q] = km;
+      if constexpr (!MID) S.ut_hit[q] = cr == C_SEEN ? kUtSeen : 0;
       o_ua |= sa;
       a_ua &= sa;
       o_uc |= code;
@@ -808,6 +1000,18 @@ __global__ __launch_bounds__(kT) void subset_scatter_kernel(const odp_event* ev,
   subset_scatter_body<kRounds, false>(ev, cls, n, W, S, parts, nullptr, nullptr, nullptr);
 }
 
+// A store that another block of the same launch may read (all_read) once it
+// has seen the ticket drawn after it: at agent scope, since the XCDs' L2s do
+// not see each other's stores.
+template <typename T>
+__device__ __forceinline__ void to_all(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T all_read(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // One block per slot: reduces the blocks' partials of slots [first, first +
 // gridDim.x) into the control block and the report.
 template <int NT>
@@ -848,27 +1052,30 @@ __device__ void reduce_slot(const Parts& parts, uint32_t nb, uint32_t slot, AnaC
       ctl->n_tx = (uint32_t)v;
       break;
     case S_N_KERNELS: rep->n_kernels = v; break;
-    case S_DIG_OR: ctl->m_digest.vor = v; break;
-    case S_DIG_AND: ctl->m_digest.vand = v; break;
-    case S_FIRST_BAD: ctl->first_bad = (uint32_t)min(v, (unsigned long long)kNone); break;
+    case S_DIG_OR: to_all(&ctl->m_digest.vor, v); break;
+    case S_DIG_AND: to_all(&ctl->m_digest.vand, v); break;
+    case S_FIRST_BAD: to_all(&ctl->first_bad, (uint32_t)min(v, (unsigned long long)kNone)); break;
     case S_MAX_EP: ctl->max_ep = (uint32_t)v; break;
     case S_TMIN: ctl->t_min = v; break;
     case S_TMAX: ctl->t_max = v; break;
-    case S_UT_ADDR_OR: ctl->m_ut_addr.vor = v; break;
-    case S_UT_ADDR_AND: ctl->m_ut_addr.vand = v; break;
-    case S_UT_CODE_OR: ctl->m_ut_code.vor = v; break;
-    case S_UT_CODE_AND: ctl->m_ut_code.vand = v; break;
+    case S_UD_EVENTS: ctl->ud_events = v; break;
+    case S_UD_BYTES: ctl->ud_bytes = v; break;
+    case S_UD_TIME: ctl->ud_time = v; break;
+    case S_UT_ADDR_OR: to_all(&ctl->m_ut_addr.vor, v); break;
+    case S_UT_ADDR_AND: to_all(&ctl->m_ut_addr.vand, v); break;
+    case S_UT_CODE_OR: to_all(&ctl->m_ut_code.vor, v); break;
+    case S_UT_CODE_AND: to_all(&ctl->m_ut_code.vand, v); break;
     case S_ELIM_TX: ctl->elim_tx = v; break;
-    case S_AD_DEV_OR: ctl->m_ad_dev.vor = v; break;
-    case S_AD_DEV_AND: ctl->m_ad_dev.vand = v; break;
-    case S_AD_ADDR_OR: ctl->m_ad_addr.vor = v; break;
-    case S_AD_ADDR_AND: ctl->m_ad_addr.vand = v; break;
-    case S_KS_OR: ctl->m_k_start.vor = v; break;
-    case S_KS_AND: ctl->m_k_start.vand = v; break;
-    case S_KE_OR: ctl->m_k_end.vor = v; break;
-    case S_KE_AND: ctl->m_k_end.vand = v; break;
-    case S_KD_OR: ctl->m_k_dev.vor = v; break;
-    case S_KD_AND: ctl->m_k_dev.vand = v; break;
+    case S_AD_DEV_OR: to_all(&ctl->m_ad_dev.vor, v); break;
+    case S_AD_DEV_AND: to_all(&ctl->m_ad_dev.vand, v); break;
+    case S_AD_ADDR_OR: to_all(&ctl->m_ad_addr.vor, v); break;
+    case S_AD_ADDR_AND: to_all(&ctl->m_ad_addr.vand, v); break;
+    case S_KS_OR: to_all(&ctl->m_k_start.vor, v); break;
+    case S_KS_AND: to_all(&ctl->m_k_start.vand, v); break;
+    case S_KE_OR: to_all(&ctl->m_k_end.vor, v); break;
+    case S_KE_AND: to_all(&ctl->m_k_end.vand, v); break;
+    case S_KD_OR: to_all(&ctl->m_k_dev.vor, v); break;
+    case S_KD_AND: to_all(&ctl->m_k_dev.vand, v); break;
     case S_DD_EVENTS: rep->dd_events = v; break;
     case S_DD_GROUPS: rep->dd_groups = v; break;
     case S_DD_BYTES: rep->dd_bytes = v; break;
@@ -885,38 +1092,35 @@ __device__ void reduce_slot(const Parts& parts, uint32_t nb, uint32_t slot, AnaC
     case S_UA_BYTES: rep->ua_bytes = v; break;
     case S_UA_TIME: rep->ua_time_ns = v; break;
     case S_ELIM_PAIRS: ctl->elim_pairs = v; break;
-    case S_UT_EVENTS: rep->ut_events = v; break;
-    case S_UT_BYTES: rep->ut_bytes = v; break;
-    case S_UT_TIME: rep->ut_time_ns = v; break;
-    case S_ELIM_UT: ctl->elim_ut = v; break;
     default: break;
   }
-}
-
-__global__ __launch_bounds__(kT) void reduce_parts_kernel(Parts parts, uint32_t nb, uint32_t first, AnaCtl* ctl,
-                                                          odp_report* rep) {
-  reduce_slot<kT>(parts, nb, first + blockIdx.x, ctl, rep);
 }
 
 // ---------------------------------------------------------------------------
 // 3. LSD radix sort, 8-bit digits, several independent jobs per launch.
 // ---------------------------------------------------------------------------
-// first_passes: when nonzero, the passes after that many are deferred to the
-// local fix (digest job only).
+// What a reduction's last block plans: the jobs' passes, from the masks that the
+// reduction has just written (njobs 0: nothing). first_passes: when nonzero, the
+// passes after that many are deferred to the local fix (digest job only).
 // cand, n_after1: the filter's arrays for the job, or null to run without it.
-__global__ void sort_plan_kernel(JobSet J, uint32_t first_passes, uint8_t* cand, uint32_t* n_after1) {
-  const uint32_t j = threadIdx.x;
-  if (j >= J.njobs) return;
-  SortJob& s = J.jobs[j];
-  s.cand = cand;
-  s.n_after1 = n_after1;
+struct PlanArgs {
+  JobSet J;
+  uint32_t first_passes;
+  uint8_t* cand;
+  uint32_t* n_after1;
+  uint32_t* ticket;
+};
+
+__device__ void sort_plan(SortJob& s, const PlanArgs& P) {
+  s.cand = P.cand;
+  s.n_after1 = P.n_after1;
   uint32_t np = 0;
-  const uint32_t skip = (s.first_bad && *s.first_bad == kNone) ? s.mono_word : kNoWord;
+  const uint32_t skip = (s.first_bad && all_read(s.first_bad) == kNone) ? s.mono_word : kNoWord;
   const uint32_t nwords = (s.run_flag && *s.run_flag == 0) ? 0u : s.nwords;
   for (uint32_t w = 0; w < nwords; ++w) {
     if (w == skip) continue;
     // bits that are 1 in some key and 0 in another (0 when there are no keys)
-    const unsigned long long var = s.masks[w]->vor & ~s.masks[w]->vand;
+    const unsigned long long var = all_read(&s.masks[w]->vor) & ~all_read(&s.masks[w]->vand);
     bool first = true;
     for (uint32_t b = 0; b < s.word_bytes[w]; ++b)
       if ((var >> (8 * b)) & 0xFF) {
@@ -928,8 +1132,21 @@ __global__ void sort_plan_kernel(JobSet J, uint32_t first_passes, uint8_t* cand,
       }
   }
   s.np_full = np;
-  s.np_first = first_passes ? min(np, first_passes) : np;
+  s.np_first = P.first_passes ? min(np, P.first_passes) : np;
   s.npasses = s.np_first;
+}
+
+__global__ __launch_bounds__(kT) void reduce_parts_kernel(Parts parts, uint32_t nb, uint32_t first, AnaCtl* ctl,
+                                                          odp_report* rep, PlanArgs P) {
+  reduce_slot<kT>(parts, nb, first + blockIdx.x, ctl, rep);
+  if (P.J.njobs == 0) return;
+  __shared__ uint32_t s_last;
+  if (threadIdx.x == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    s_last = __hip_atomic_fetch_add(P.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (s_last && threadIdx.x < P.J.njobs) sort_plan(P.J.jobs[threadIdx.x], P);
 }
 
 // Local fix of the digest job, launched before the first deferred pass
@@ -2072,8 +2289,8 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64],
       c_dd += (res & ODP_F_DD) != 0;
       c_tx += (res & ODP_F_RT_TX) != 0;
       c_rx += (res & ODP_F_RT_RX) != 0;
-      // classification stored 0 for every valid record: only set flags are written
-      if (res) A.flags[s_val[w][r * 64 + lane]] = res;
+      // the classification stored the other records' flags (MID: 0 for every valid record)
+      if (MID && res) A.flags[s_val[w][r * 64 + lane]] = res;
       s_code[w][r * 64 + lane] = res;  // the code is not read again
     } else {
       s_code[w][r * 64 + lane] = 0;
@@ -2082,17 +2299,22 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64],
     const BS<MODE> y0 = S::shfl(y, 0);
     bcarry = g0 ? y0 : S::bop(y0, bcarry);
   }
-  // bytes and durations of the flagged records, four rounds of gathers in flight at a time
+  // bytes and durations of the flagged records, four rounds of gathers in flight at a time.
+  // What the classification decided of a flagged record stays (in a chronological log).
+  const uint8_t keep_ut = A.ctl->first_bad == kNone ? ODP_F_UT : 0;
   constexpr int kG = ROUNDS < 4 ? ROUNDS : 4;
   wave_lds_fence();
 #pragma unroll 1
   for (int r0 = 0; r0 < ROUNDS; r0 += kG) {
     uint64_t eb[kG], ed[kG];
-    uint8_t rs[kG];
+    uint8_t rs[kG], ut[kG];
 #pragma unroll
     for (int q = 0; q < kG; ++q) {
       rs[q] = s_code[w][(r0 + q) * 64 + lane];
       eb[q] = ed[q] = 0;
+      ut[q] = 0;
+      if constexpr (!MID)
+        if (rs[q]) ut[q] = A.flags[s_val[w][(r0 + q) * 64 + lane]] & keep_ut;
       if (rs[q] & (ODP_F_DD | ODP_F_RT_RX | (MID ? ODP_F_UT : 0))) {
         const odp_event& e = A.ev[s_val[w][(r0 + q) * 64 + lane]];
         eb[q] = e.bytes;
@@ -2101,7 +2323,8 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64],
     }
 #pragma unroll
     for (int q = 0; q < kG; ++q) {
-      t_el += ed[q];  // removable once, whether DD, RT_RX or both
+      if (!MID && rs[q]) A.flags[s_val[w][(r0 + q) * 64 + lane]] = rs[q] | ut[q];
+      if (!ut[q]) t_el += ed[q];  // removable once, whether DD, RT_RX or both (UT: counted with those)
       if (rs[q] & ODP_F_DD) {
         b_dd += eb[q];
         t_dd += ed[q];
@@ -2493,6 +2716,9 @@ __global__ __launch_bounds__(kT) void ra_ua_kernel(RaArgs R) {
 // ---------------------------------------------------------------------------
 struct UtArgs {
   const odp_event* ev;
+  uint32_t n;          // records
+  const uint8_t* cls;
+  WaveScan W;          // scanned
   const SortJob* ut_job;
   const uint32_t* n_ut;
   const uint32_t* ut_idx;
@@ -2522,10 +2748,14 @@ struct UtArgs {
 //   logged before k: if it starts before k does, c is overwritten unread
 //   (unused); if it starts when k does, or there is none before k, k can
 //   read c (used).
-// The forward search stops after kUtWindow copies; a copy still undecided
+// Only the listed copies are searched and searched for (see the classification).
+// The forward search stops after kUtWindow of them; a copy still undecided
 // then, or any copy of a log with a rejected record, is left to the sorted
 // path below, which the device then switches on.
-constexpr uint32_t kUtWindow = 64;
+// (512: with 8 devices a device's next kernel is often hundreds of copies away,
+// and the sorted path costs more than the wider staging does: 2 million records
+// 623 -> 495 us against a window of 64, one device unchanged.)
+constexpr uint32_t kUtWindow = 512;
 
 // A block takes kT consecutive copy-ins (one per thread) and stages the
 // fields of the copies its searches can reach (the next kT + kUtWindow) in
@@ -2558,7 +2788,7 @@ __global__ __launch_bounds__(kT) void ut_scan_kernel(UtArgs U) {
     }
     __syncthreads();
     const uint32_t q = b0 + threadIdx.x;
-    if (q < n) {
+    if (q < n && U.ut_hit[q] != kUtSeen) {
       const uint64_t code = U.ut_w_code[q];
       const uint32_t d = (uint32_t)(code & 15);
       const uint64_t ts = U.ut_ts[q];
@@ -2674,19 +2904,25 @@ __global__ __launch_bounds__(kT) void ut_eval_kernel(UtArgs U) {
   }
 }
 
-// After the join: ORs F_UT into the flags (copy-ins in log order, so the
-// writes advance through the flag array), sums the unused copies' bytes and
-// time, and adds the removable time of those no other flag already made
-// removable.
-// Sets ODP_F_UT and adds up the unused transfers, after the join (the
-// transfers' other flags are final then; a record flagged DD or RT_RX too
-// has its time counted as eliminable there already). Four copy-ins per
-// thread and step, their loads issued together: each is a chain of dependent
-// loads (result, record index, then flag and record).
+// After the join, when the transfers' other flags are final.
+// First the listed copy-ins: sets ODP_F_UT and adds up those their search
+// found unused, and the removable time of those no other flag made removable
+// (a record flagged DD or RT_RX too has its time counted there already). Four
+// copy-ins per thread and step, their loads issued together: each is a chain
+// of dependent loads (result, record index, then flag and record). In a log
+// with a rejected record all copies are listed, and what the classification
+// decided of them is overwritten.
+// Then the kernels that the classification could not see: a copy it found
+// unused is used if a kernel of an earlier wavefront on its device still runs
+// at its start. A wavefront takes the 1,024 records of one of the
+// classification's and reads on while records start before the latest of
+// those ends (a copy flagged DD or RT_RX as well stays removable).
 __global__ __launch_bounds__(kT) void ut_merge_kernel(UtArgs U) {
   constexpr uint32_t kU = 4;
   const uint32_t n = *U.n_ut;
   const uint32_t stride = gridDim.x * kT;
+  const uint32_t n_bad = U.ctl->first_bad;
+  const uint8_t stale = n_bad == kNone ? 0 : ODP_F_UT;
   unsigned long long c_ut = 0, b_ut = 0, t_ut = 0, t_el = 0;
   for (uint32_t q0 = blockIdx.x * kT + threadIdx.x; q0 < n; q0 += kU * stride) {
     bool hit[kU];
@@ -2697,25 +2933,66 @@ __global__ __launch_bounds__(kT) void ut_merge_kernel(UtArgs U) {
       hit[u] = q < n && U.ut_hit[q] == 1;
     }
 #pragma unroll
-    for (uint32_t u = 0; u < kU; ++u) idx[u] = hit[u] ? U.ut_idx[q0 + u * stride] : 0u;
+    for (uint32_t u = 0; u < kU; ++u) idx[u] = hit[u] || (stale && q0 + u * stride < n) ? U.ut_idx[q0 + u * stride] : kNone;
     uint8_t f[kU];
     uint64_t ts[kU], te[kU], by[kU];
 #pragma unroll
     for (uint32_t u = 0; u < kU; ++u) {
-      f[u] = hit[u] ? U.flags[idx[u]] : 0;
+      f[u] = idx[u] != kNone ? U.flags[idx[u]] : 0;
       ts[u] = hit[u] ? U.ev[idx[u]].t_start : 0;
       te[u] = hit[u] ? U.ev[idx[u]].t_end : 0;
       by[u] = hit[u] ? U.ev[idx[u]].bytes : 0;
     }
 #pragma unroll
     for (uint32_t u = 0; u < kU; ++u) {
-      if (!hit[u]) continue;
+      if (!hit[u]) {
+        if (f[u] & stale) U.flags[idx[u]] = f[u] & ~stale;
+        continue;
+      }
       U.flags[idx[u]] = f[u] | ODP_F_UT;
       const uint64_t d = te[u] - ts[u];
       ++c_ut;
       b_ut += by[u];
       t_ut += d;
       if (!(f[u] & (ODP_F_DD | ODP_F_RT_RX))) t_el += d;
+    }
+  }
+  const uint32_t lane = threadIdx.x & 63;
+  if (!stale) {
+    for (uint32_t wid = (blockIdx.x * kT + threadIdx.x) / 64; wid < U.W.nw; wid += stride / 64) {
+      const uint32_t wb = wid * kWaveElems;
+      if (wb >= U.n) break;
+      // the latest end of an earlier wavefront's kernel, per device code (lane)
+      unsigned long long last = 0;
+      uint32_t some = 0;
+      if (lane < kEp) {
+        const uint32_t chunk = wid / kScanChunk;
+        last = max(U.W.kmax[(size_t)kEp * wid + lane], U.W.cmax[(size_t)kEp * chunk + lane]);
+        some = (U.W.cnt[(size_t)kWaveCnt * wid + 3 + lane] + U.W.ccnt[(size_t)kWaveCnt * chunk + 3 + lane]) != 0;
+      }
+      if (!__ballot(some && last >= U.ev[wb].t_start)) continue;
+      unsigned long long most = last;
+      for (int o = 8; o >= 1; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+      most = __shfl(most, 0, 64);
+      for (uint32_t r = 0; r < (uint32_t)kRounds; ++r) {
+        const uint32_t i = wb + r * 64 + lane;
+        const bool in = i < U.n;
+        const uint64_t ts = in ? U.ev[i].t_start : ~0ull;
+        const bool mine = in && U.cls[i] >= C_SEEN;
+        const uint8_t f = mine ? U.flags[i] : 0;
+        const uint32_t d = f & ODP_F_UT ? (uint32_t)(U.ev[i].dst_dev + 1) : 0u;
+        const unsigned long long end = __shfl(last, (int)d, 64);
+        const uint32_t any = (uint32_t)__shfl((int)some, (int)d, 64);
+        if ((f & ODP_F_UT) && any && end >= ts) {
+          U.flags[i] = f & ~ODP_F_UT;
+          const uint64_t dur = U.ev[i].t_end - ts;
+          --c_ut;
+          b_ut -= U.ev[i].bytes;
+          t_ut -= dur;
+          if (!(f & (ODP_F_DD | ODP_F_RT_RX))) t_el -= dur;
+        }
+        if (lane64(ts, 63) > most) break;
+      }
     }
   }
   block_store<R_ADD>(U.parts.at(S_UT_EVENTS), c_ut);
@@ -2733,16 +3010,34 @@ __device__ void write_estimate(odp_report* rep, bool any_valid, uint64_t t_min, 
   rep->predicted_speedup = span == 0 ? 1.0 : elim >= span ? (double)INFINITY : (double)span / (double)(span - elim);
 }
 
-__global__ void finalize_kernel(AnaCtl* ctl, odp_report* rep) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// The last reduction (nb partials of the unused transfers' sums) and the rest of
+// the report, in one block of kT threads.
+__global__ __launch_bounds__(kT) void finalize_kernel(Parts parts, uint32_t nb, AnaCtl* ctl, odp_report* rep) {
+  unsigned long long sum[4] = {};
+  for (uint32_t b = threadIdx.x; b < nb; b += kT)
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) sum[k] += parts.p[(size_t)(S_UT_EVENTS + k) * parts.stride + b];
+  __shared__ unsigned long long s_sum[4];
+#pragma unroll
+  for (uint32_t k = 0; k < 4; ++k) block_store<R_ADD>(&s_sum[k], sum[k]);
+  if (threadIdx.x != 0) return;
   rep->n_alloc_pairs = ctl->n_pairs;
   rep->n_unpaired_delete = (ctl->n_ad - rep->n_unpaired_alloc - 2ull * ctl->n_pairs);
   rep->dd_members = rep->dd_events + rep->dd_groups;
   rep->ra_members = rep->ra_events + rep->ra_groups;
   rep->first_bad_event = ctl->first_bad;
   rep->status = ctl->first_bad != kNone ? 1 : 0;
+  uint64_t ud_time = 0;  // what the classification decided counts in a chronological log
+  rep->ut_events = s_sum[0];
+  rep->ut_bytes = s_sum[1];
+  rep->ut_time_ns = s_sum[2];
+  if (rep->n_events && ctl->first_bad == kNone) {
+    rep->ut_events += ctl->ud_events;
+    rep->ut_bytes += ctl->ud_bytes;
+    rep->ut_time_ns += ud_time = ctl->ud_time;
+  }
   write_estimate(rep, rep->n_events > rep->n_invalid, ctl->t_min, ctl->t_max,
-                 ctl->elim_tx + ctl->elim_pairs + ctl->elim_ut);
+                 ctl->elim_tx + ctl->elim_pairs + s_sum[3] + ud_time);
 }
 
 // ---------------------------------------------------------------------------
@@ -2935,6 +3230,7 @@ enum Buf {
 // Jobs 1..4 (the subsets) are sorted together in the same launches.
 constexpr int kJobBig = 0, kJobAd = 1, kJobKs = 2, kJobKe = 3, kJobUt = 4, kNumJobs = 5;
 constexpr int kSubsetJobs = 4;
+static_assert(kTotals == kNumJobs * kMaxPasses * 256, "digit totals of every job");
 
 template <typename T>
 T* carve(char*& p, size_t count) {
@@ -2957,6 +3253,7 @@ struct Views {
   uint32_t* bv[2];
   uint32_t* tile_cnt;
   uint32_t* wave_cnt;
+  uint32_t* wave_copies;
   SubsetOut S;
   uint32_t* ad_vals1;
   uint32_t* k_vals_s1;
@@ -3012,6 +3309,7 @@ size_t mid_views(MidView& m, char* base, size_t cap) {
   m.wscan.ccnt = carve<uint32_t>(p, nchunk * kWaveCnt);
   m.wscan.cmax = carve<uint64_t>(p, nchunk * kEp);
   m.wscan.nw = 0;
+  m.wscan.copies = nullptr;
   m.agg = carve<WaveAgg>(p, waves);
   m.parts.p = carve<unsigned long long>(p, kSlots * blocks);
   m.parts.stride = (uint32_t)blocks;
@@ -3034,6 +3332,7 @@ Views views(Workspace* ws) {
   v.bv[1] = static_cast<uint32_t*>(b[B_BVAL1].ptr);
   v.tile_cnt = static_cast<uint32_t*>(b[B_TILECNT].ptr);
   v.wave_cnt = v.tile_cnt + 2 * (size_t)v.ntc;  // kWaveCnt counters per wavefront
+  v.wave_copies = v.wave_cnt + (size_t)kWaveCnt * v.ntc * (kT / 64);  // one per wavefront
   const size_t cap = v.cap;
   char* pa = static_cast<char*>(b[B_AD].ptr);
   v.S.ad_idx = carve<uint32_t>(pa, cap);
@@ -3070,6 +3369,7 @@ Views views(Workspace* ws) {
   v.ut_vals1 = carve<uint32_t>(pu, cap);
   v.next_q = carve<uint32_t>(pu, cap);
   v.ut_hit = carve<uint8_t>(pu, cap);
+  v.S.ut_hit = v.ut_hit;
   char* pw = static_cast<char*>(b[B_WSCAN].ptr);
   const uint32_t nw = v.ntc * (kT / 64), nchunk = ceil_div32(nw, kScanChunk);
   v.wscan.cnt = v.wave_cnt;
@@ -3077,6 +3377,7 @@ Views views(Workspace* ws) {
   v.wscan.ccnt = carve<uint32_t>(pw, (size_t)nchunk * kWaveCnt);
   v.wscan.cmax = carve<uint64_t>(pw, (size_t)nchunk * kEp);
   v.wscan.nw = nw;
+  v.wscan.copies = nullptr;
   char* pp = static_cast<char*>(b[B_PR].ptr);
   v.pr_alloc = carve<uint32_t>(pp, cap);
   v.pr_del = carve<uint32_t>(pp, cap);
@@ -3201,7 +3502,7 @@ int analyze_reserve(Workspace* ws, size_t max_events) {
   if ((e = b[B_MID].ensure(mid_views(sized, nullptr, cap) + 64)) || (e = b[B_CTL].ensure(sizeof(AnaCtl))) || (e = b[B_JOBS].ensure(sizeof(SortJob) * kNumJobs)) ||
       (e = b[B_CLS].ensure(cap)) || (e = b[B_AUX].ensure(2 * cap)) || (e = b[B_BKEY0].ensure(cap * 8)) ||
       (e = b[B_BKEY1].ensure(cap * 8)) || (e = b[B_BVAL0].ensure(cap * 4)) || (e = b[B_BVAL1].ensure(cap * 4)) ||
-      (e = b[B_TILECNT].ensure((size_t)nt * 4 * (2 + kWaveCnt * (kT / 64)))) ||
+      (e = b[B_TILECNT].ensure((size_t)nt * 4 * (2 + (kWaveCnt + 1) * (kT / 64)))) ||
       (e = b[B_AD].ensure(cap * (4 + 8 + 8 + 4 + 4 + 4 + 4 + 8 + 1) + 64)) ||
       (e = b[B_K].ensure(cap * (4 + 8 + 8 + 8 + 4 * 4 + 8 + 8 + 8 + 4) + 64)) ||
       (e = b[B_UT].ensure(cap * (4 + 8 + 8 + 8 + 4 + 4 + 8 + 4 + 4 + 1) + 64)) ||
@@ -3975,19 +4276,25 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   const uint32_t grid_rec = n ? ceil_div32(n, kT) : 1, grid_pair = ceil_div32(n / 2 + 1, kT);
   AnaCtl* ctl = v.ctl;
 
-  hipLaunchKernelGGL(init_kernel, dim3(64), dim3(kT), 0, stream, ctl, out_report, v.totals,
-                     (uint32_t)(kNumJobs * kMaxPasses * 256), nn);
   if (alg2_rx)
     hipLaunchKernelGGL(alg2_fill_kernel, dim3(n ? ceil_div32(n, kT) : 1), dim3(kT), 0, stream, alg2_rx, nn, alg2_np);
   if (n == 0) {
-    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64), 0, stream, ctl, out_report);
+    hipLaunchKernelGGL(init_kernel, dim3(64), dim3(kT), 0, stream, ctl, out_report, v.totals);
+    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kT), 0, stream, v.parts, 0u, ctl, out_report);
     return check_hip(hipGetLastError(), "odp_analyze_trace launch");
   }
   hipLaunchKernelGGL(classify_kernel, dim3(nt), dim3(kT), 0, stream, events, nn, out_flags, v.cls, v.aux, v.bk[0],
-                     v.bv[0], v.wave_cnt, v.wscan.kmax, v.hist + (size_t)kJobBig * 256 * v.ntc, v.ntc,
-                     alg2_rx ? nullptr : v.cand, v.parts);
+                     v.bv[0], v.wave_cnt, v.wave_copies, v.wscan.kmax, v.hist + (size_t)kJobBig * 256 * v.ntc, v.ntc,
+                     alg2_rx ? nullptr : v.cand, v.parts, ctl, out_report, v.totals);
   // the classification's counts, digest masks, first rejected record and endpoint range
-  hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_AD_DEV_OR), dim3(kT), 0, stream, v.parts, nt, 0u, ctl, out_report);
+  // (the digest sort is planned from them; the literal Algorithm 2 pairs a
+  // self-transfer with itself, so there the single digests stay)
+  const JobSet Jb{v.jobs + kJobBig, 1, nt};
+  const uint32_t kfirst = first_digest_passes(n);
+  const bool filter = alg2_rx == nullptr;
+  const PlanArgs plan_none{};
+  const PlanArgs plan_big{Jb, kfirst, filter ? v.cand : nullptr, filter ? &ctl->n_cand : nullptr, &ctl->plan_ticket[0]};
+  hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_AD_DEV_OR), dim3(kT), 0, stream, v.parts, nt, 0u, ctl, out_report, plan_big);
 
   // Fork: the allocation path (subsets, their sorts, pairing, RA/UA) runs on
   // the workspace's side stream while the digest groups are sorted and
@@ -4000,12 +4307,16 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   // for the classification), then the digest path on the caller's stream.
   WaveScan WS = v.wscan;
   WS.nw = nt * (kT / 64);
+  WS.copies = v.wave_copies;
   const uint32_t nchunk = ceil_div32(WS.nw, kScanChunk);
   hipLaunchKernelGGL(wave_scan_kernel, dim3(nchunk * kScanQ), dim3(1024), 0, side, WS, nchunk, ctl);
   hipLaunchKernelGGL(subset_scatter_kernel, dim3(nt), dim3(kT), 0, side, events, v.cls, nn, WS, v.S, v.parts);
   // Unused transfers (their flags are merged after the join).
   UtArgs U;
   U.ev = events;
+  U.n = nn;
+  U.cls = v.cls;
+  U.W = WS;
   U.ut_job = v.jobs + kJobUt;
   U.n_ut = &ctl->n_ut;
   U.ut_idx = v.S.ut_idx;
@@ -4024,15 +4335,15 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   U.flags = out_flags;
   U.parts = v.parts;
   hipLaunchKernelGGL(ut_scan_kernel, dim3(grid_rec), dim3(kT), 0, side, U);
-  hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_DD_EVENTS - S_AD_DEV_OR), dim3(kT), 0, side, v.parts, nt,
-                     (uint32_t)S_AD_DEV_OR, ctl, out_report);
   // ALLOC/DELETE by (device, address), kernels by (device, start) and (device,
   // end), copy-ins by (endpoints, source address). The subsets are usually
   // far smaller than the log: a capped number of blocks per job loops over
   // its tiles instead of a block per log tile.
   const uint32_t side_blocks = std::min<uint32_t>(nt, (uint32_t)cus * 2);
   const JobSet Js{v.jobs + kJobAd, kSubsetJobs, side_blocks};
-  hipLaunchKernelGGL(sort_plan_kernel, dim3(1), dim3(64), 0, side, Js, 0u, nullptr, nullptr);
+  const PlanArgs plan_side{Js, 0u, nullptr, nullptr, &ctl->plan_ticket[1]};
+  hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_DD_EVENTS - S_AD_DEV_OR), dim3(kT), 0, side, v.parts, nt,
+                     (uint32_t)S_AD_DEV_OR, ctl, out_report, plan_side);
   for (uint32_t p = 0; p < 9; ++p) {
     hipLaunchKernelGGL(sort_hist_kernel, dim3(Js.njobs * side_blocks), dim3(kT), 0, side, Js, p);
     hipLaunchKernelGGL(sort_scan_kernel, dim3(256 * Js.njobs), dim3(kT), 0, side, Js, p);
@@ -4090,20 +4401,13 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   R.parts = v.parts;
   hipLaunchKernelGGL(ra_ua_kernel, dim3(grid_sum), dim3(kT), 0, side, R);
   hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_ELIM_PAIRS + 1 - S_RA_EVENTS), dim3(kT), 0, side, v.parts, grid_sum,
-                     (uint32_t)S_RA_EVENTS, ctl, out_report);
+                     (uint32_t)S_RA_EVENTS, ctl, out_report, plan_none);
   // Records by digest (up to 8 passes), then duplicates and round trips, on
   // the caller's stream.
-  const JobSet Jb{v.jobs + kJobBig, 1, nt};
-  const uint32_t kfirst = first_digest_passes(n);
   const uint32_t nft = (uint32_t)((n + kFixTile - 1) / kFixTile);  // tiles of the local fix
   // the digest histograms take two tiles per block on long logs (measured a
   // little faster than one: the per-block start-up is amortised)
   const JobSet Jh{v.jobs + kJobBig, 1, nt > 4u * (uint32_t)cus ? (nt + 1) / 2 : nt};
-  // (the literal Algorithm 2 pairs a self-transfer with itself, so there the
-  // single digests stay)
-  const bool filter = alg2_rx == nullptr;
-  hipLaunchKernelGGL(sort_plan_kernel, dim3(1), dim3(64), 0, stream, Jb, kfirst, filter ? v.cand : nullptr,
-                     filter ? &ctl->n_cand : nullptr);
   for (uint32_t p = 0; p < 8; ++p) {
     if (p == 1 && filter)
       hipLaunchKernelGGL(sort_filter_kernel, dim3(256), dim3(kFilterT), 0, stream, v.jobs + kJobBig);
@@ -4129,7 +4433,7 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   hipLaunchKernelGGL(ddrt_carry_kernel, dim3(1), dim3(kCT), 0, stream, D, nt * (kT / 64));
   hipLaunchKernelGGL((ddrt_final_kernel<kRounds, false>), dim3(nt), dim3(kT), 0, stream, D);
   hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_ELIM_TX + 1 - S_DD_EVENTS), dim3(kT), 0, stream, v.parts, nt,
-                     (uint32_t)S_DD_EVENTS, ctl, out_report);
+                     (uint32_t)S_DD_EVENTS, ctl, out_report, plan_none);
   if (alg2_rx) {
     Alg2Args G;
     G.job = v.jobs + kJobBig;
@@ -4144,9 +4448,7 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
 
   ODP_HIP(hipStreamWaitEvent(stream, ws->a_join, 0));
   hipLaunchKernelGGL(ut_merge_kernel, dim3(grid_sum), dim3(kT), 0, stream, U);
-  hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_ELIM_UT + 1 - S_UT_EVENTS), dim3(kT), 0, stream, v.parts, grid_sum,
-                     (uint32_t)S_UT_EVENTS, ctl, out_report);
-  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64), 0, stream, ctl, out_report);
+  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kT), 0, stream, v.parts, grid_sum, ctl, out_report);
   return check_hip(hipGetLastError(), "odp_analyze_trace launch");
 }
 

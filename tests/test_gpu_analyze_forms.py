@@ -171,3 +171,18 @@ def test_single_digests_are_dropped(odp, kind):
         digest = k % np.uint64(256)
     ev["digest"] = digest
     check(odp, ev)
+
+
+@pytest.mark.parametrize("kind", ["one device", "ten devices", "few kernels", "long kernels", "ties", "one place", "kernel every other", "rejected"])
+def test_unused_transfers_by_span(odp, kind):
+    """Copies decided inside their 512 records, and what crosses to the next ones."""
+    n = 262_145 + 513
+    ev = random_log(n, n, devices=10 if kind == "ten devices" else 1, digests=n, places=1 if kind == "one place" else 50,
+                    kernels={"few kernels": 0.0005, "kernel every other": 0.5}.get(kind, 0.02), allocs=0.05,
+                    tie=0.97 if kind == "ties" else 0.3)
+    if kind == "long kernels":
+        k = np.flatnonzero(ev["op"] == W.KERNEL)[::40]
+        ev["t_end"][k] += np.uint64(3000)
+    if kind == "rejected":
+        ev["t_end"][n // 2] = ev["t_start"][n // 2] - np.uint64(1)
+    check(odp, ev)
