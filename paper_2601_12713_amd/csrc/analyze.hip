@@ -56,6 +56,16 @@ constexpr int kMaxWords = 3;
 constexpr int kMaxPasses = 24;
 constexpr int kEp = 11;                 // endpoints: host (0) and devices 0..9 (1..10)
 constexpr uint8_t kNotTransfer = 0xFF;
+// A transfer's byte beside its digest: its endpoints (device + 1 each, 0..10) as
+// source * 11 + destination in the low seven bits and, in the top one, whether
+// the classification found it unused. Unpacked: source << 4 | destination.
+constexpr uint32_t kAuxUnused = 0x80;
+__host__ __device__ inline uint32_t pack_ep(uint32_t src, uint32_t dst) { return src * kEp + dst; }
+__host__ __device__ inline uint8_t unpack_ep(uint32_t a) {
+  const uint32_t c = a & 0x7F, src = (c * 187) >> 11;  // c / 11 for c < 128
+  return a == kNotTransfer ? kNotTransfer : (uint8_t)(src << 4 | (c - src * kEp));
+}
+static_assert(kEp == 11 && kEp * kEp <= 127, "a pair of endpoints in seven bits");
 // Counters per wavefront of the classification, scanned into the subset
 // offsets: ALLOC/DELETE, KERNEL and copy-in records, then KERNEL records per
 // device code (device + 1).
@@ -371,44 +381,50 @@ struct SpanLds {
   unsigned long long addr[kSpanRecs];  // source address of a copy
   uint32_t rec[kSpanRecs];             // copies: next in the bucket's chain (itself: the last) | g << 10 | endpoints << 20 | kHasPred
   uint32_t head[kSpanHeads];           // buckets by place: the node pushed last (later rounds are pushed first)
-  uint32_t nk[kEp];                    // per device code: the next kernel, g << 10 | record of the span; kNoNode if none
+  // per device code: first the kernels counted, then (backwards) the next
+  // kernel, g << 10 | record of the span, kNoNode if none
+  uint32_t dev[kEp];
 };
-static_assert(kSpanHeads == 64 && kSpan <= 10 && kRounds % kSpan == 0, "a head per lane, three bits per round, ten of a record of the span");
+static_assert(kSpanHeads == 64 && kSpan <= 10 && kWaveElems % kSpanRecs == 0, "a head per lane, three bits per round, ten of a record of the span");
 
-// One block per tile of kTile records; wavefront w takes the 1,024
-// consecutive records [tile*kTile + w*1024, ...) in 16 rounds of 64 and also
+// One block per tile of kTile records; wavefront w takes the 512 consecutive
+// records [tile*kTile + w*512, ...), a span, in 8 rounds of 64 and also
 // counts the ALLOC/DELETE, KERNEL and listed copy-in records it sees (for the
 // compaction). The block also counts its tile's valid transfers by the least
 // significant byte of their digest (hist0, row length ntc): the digest sort's
 // first pass when that byte varies (that pass keeps only the transfers).
 // Bound by the read of the records, 64 bytes each, and, for the search, by the
-// latency of its LDS reads with 20 wavefronts per CU: 249 us for 10.7 million
-// records (194 us without the search, 20 to 40 of the difference for walking
-// the buckets, 12 for reading the unused copies' bytes again). It leaves 3% of
-// the copies to the later launches there, which took 430 us together and take
-// 90: subset compaction 293 -> 69, forward search 107 -> 12, merge 30 -> 10.
-// Spans of 4 rounds: 220 us, but twice the listed copies with several devices
-// (2 million records on 8 devices: 578 us against 503 in all).
-__global__ __launch_bounds__(kT, 5) void classify_kernel(const odp_event* __restrict__ ev, uint32_t n, uint8_t* __restrict__ flags,
-                                                      uint8_t* __restrict__ cls, uint8_t* __restrict__ aux,
-                                                      unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                      uint32_t* __restrict__ wave_cnt, uint32_t* __restrict__ wave_copies,
-                                                      uint64_t* __restrict__ wave_kmax, uint32_t* __restrict__ hist0,
-                                                      uint32_t ntc, uint8_t* __restrict__ cand, Parts parts,
-                                                      AnaCtl* ctl, odp_report* rep, uint32_t* totals) {
-  init_body(ctl, rep, totals, n, blockIdx.x * kT + threadIdx.x, gridDim.x * kT);
+// latency of its LDS reads with 24 wavefronts per CU: 229 us for 10.7 million
+// records (194 us without the search; by wavefronts of 16 rounds, two spans, 20
+// per CU: 249, and 75 us instead of 40 at 270,000 records, where the rounds of
+// a wavefront follow each other with little beside them). It leaves 3% of the
+// copies to the later launches there, which took 430 us together and take 90:
+// subset compaction 293 -> 69, forward search 107 -> 12, merge 30 -> 10. Spans
+// of 4 rounds: 220 us, but twice the listed copies with several devices (2
+// million records on 8 devices: 578 us against 503 in all). Whether a copy is
+// unused travels in its sort value: DD/RT keep the flag without reading it (112
+// -> 86 us).
+constexpr int kClassT = kTile / kSpan;  // threads
+__global__ __launch_bounds__(kClassT, 6) void classify_kernel(const odp_event* __restrict__ ev, uint32_t n, uint8_t* __restrict__ flags,
+                                                         uint8_t* __restrict__ cls, uint8_t* __restrict__ aux,
+                                                         unsigned long long* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                         uint32_t* __restrict__ wave_cnt, uint32_t* __restrict__ wave_copies,
+                                                         uint64_t* __restrict__ wave_kmax, uint32_t* __restrict__ hist0,
+                                                         uint32_t ntc, uint8_t* __restrict__ cand, Parts parts,
+                                                         AnaCtl* ctl, odp_report* rep, uint32_t* totals) {
+  init_body(ctl, rep, totals, n, blockIdx.x * kClassT + threadIdx.x, gridDim.x * kClassT);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const uint32_t wid = blockIdx.x * (kT / 64) + w;
-  const uint32_t wb = wid * kWaveElems;
-  __shared__ uint32_t s_kdev[kT / 64][kEp];
-  __shared__ unsigned long long s_kmax[kT / 64][kEp];
+  const uint32_t wid = blockIdx.x * (kClassT / 64) + w;
+  const uint32_t wb = wid * kSpanRecs;
+  __shared__ unsigned long long s_kmax[kClassT / 64][kEp];
   __shared__ uint32_t s_h0[256];
-  __shared__ SpanLds s_span[kT / 64];
+  __shared__ SpanLds s_span[kClassT / 64];
   SpanLds& L = s_span[w];
-  static_assert(kT == 256, "one histogram bin per thread");
-  s_h0[threadIdx.x] = 0;
+  static_assert(kClassT >= 256, "one histogram bin per thread");
+  if (threadIdx.x < 256) s_h0[threadIdx.x] = 0;
+  L.head[lane] = kNoNode;
   if (lane < kEp) {
-    s_kdev[w][lane] = 0;
+    L.dev[lane] = 0;
     s_kmax[w][lane] = 0;
   }
   __syncthreads();
@@ -422,165 +438,172 @@ __global__ __launch_bounds__(kT, 5) void classify_kernel(const odp_event* __rest
   bool in = wb + lane < n;
   if (in) e = ev[wb + lane];
   uint64_t last_prev = (lane == 0 && in && wb > 0) ? ev[wb - 1].t_start : 0;
+  // of this lane's record of round r: class in bits 3r.., bit r of the others
+  // whether it starts after its predecessor and what is decided of a copy
+  uint32_t classes = 0, later = 0, used = 0, unused = 0;
 #pragma unroll 1
-  for (int r0 = 0; r0 < kRounds; r0 += kSpan) {
-    // of this lane's record of round r: class in bits 3r.., bit r of the others
-    // whether it starts after its predecessor and what is decided of a copy
-    uint32_t classes = 0, later = 0, used = 0, unused = 0;
-    L.head[lane] = kNoNode;
-    if (lane < kEp) L.nk[lane] = kNoNode;
-#pragma unroll 1
-    for (int r = 0; r < kSpan; ++r) {
-      const uint32_t i = wb + (r0 + r) * 64 + lane;
-      const bool in_next = r0 + r + 1 < kRounds && i + 64 < n;
-      odp_event nx;
-      if (in_next) nx = ev[i + 64];
-      const uint64_t ts = in ? e.t_start : 0;
-      uint64_t prev_start = __shfl_up(ts, 1, 64);
-      if (lane == 0) prev_start = last_prev;
-      last_prev = __shfl(ts, 63, 64);
-      uint8_t c = C_INVALID, a = kNotTransfer;
-      uint32_t dc = 0;
-      if (in) {
-        const bool is_tx = e.op == ODP_H2D || e.op == ODP_D2H || e.op == ODP_D2D;
-        const bool valid = e.op >= ODP_ALLOC && e.op <= ODP_KERNEL && e.t_end >= e.t_start &&
-                           (i == 0 || e.t_start >= prev_start) && dev_ok(e.dst_dev) && (!is_tx || dev_ok(e.src_dev));
-        unsigned long long key = ~0ull;
-        if (valid) {
-          tmin = min(tmin, (unsigned long long)e.t_start);
-          tmax = max(tmax, (unsigned long long)e.t_end);
-          dc = (uint32_t)(e.dst_dev + 1);
-          if (is_tx) {
-            c = e.op != ODP_D2H && e.dst_dev >= 0 ? C_COPYIN : C_TRANSFER;
-            a = (uint8_t)(((e.src_dev + 1) << 4) | (e.dst_dev + 1));
-            mep = max(mep, (uint32_t)max(e.src_dev + 1, e.dst_dev + 1));
-            key = e.digest;
-            ++n_tx;
-          } else if (e.op == ODP_KERNEL) {
-            c = C_KERNEL;
-            ++c_k;
-          } else {
-            c = C_ALLOCDEL;
-            ++c_ad;
-          }
+  for (int r = 0; r < kSpan; ++r) {
+    const uint32_t i = wb + r * 64 + lane;
+    const bool in_next = r + 1 < kSpan && i + 64 < n;
+    odp_event nx;
+    if (in_next) nx = ev[i + 64];
+    const uint64_t ts = in ? e.t_start : 0;
+    uint64_t prev_start = __shfl_up(ts, 1, 64);
+    if (lane == 0) prev_start = last_prev;
+    last_prev = __shfl(ts, 63, 64);
+    uint8_t c = C_INVALID, a = kNotTransfer;
+    uint32_t dc = 0;
+    if (in) {
+      const bool is_tx = e.op == ODP_H2D || e.op == ODP_D2H || e.op == ODP_D2D;
+      const bool valid = e.op >= ODP_ALLOC && e.op <= ODP_KERNEL && e.t_end >= e.t_start &&
+                         (i == 0 || e.t_start >= prev_start) && dev_ok(e.dst_dev) && (!is_tx || dev_ok(e.src_dev));
+      unsigned long long key = ~0ull;
+      if (valid) {
+        tmin = min(tmin, (unsigned long long)e.t_start);
+        tmax = max(tmax, (unsigned long long)e.t_end);
+        dc = (uint32_t)(e.dst_dev + 1);
+        if (is_tx) {
+          c = e.op != ODP_D2H && e.dst_dev >= 0 ? C_COPYIN : C_TRANSFER;
+          a = (uint8_t)(((e.src_dev + 1) << 4) | (e.dst_dev + 1));
+          mep = max(mep, (uint32_t)max(e.src_dev + 1, e.dst_dev + 1));
+          key = e.digest;
+          ++n_tx;
+        } else if (e.op == ODP_KERNEL) {
+          c = C_KERNEL;
+          ++c_k;
         } else {
-          ++n_inv;
-          bad = min(bad, i);
+          c = C_ALLOCDEL;
+          ++c_ad;
         }
-        aux[i] = a;
-        if (cand) cand[i] = 1;
-        keys[i] = key;
-        if (c == C_TRANSFER || c == C_COPYIN) atomicAdd(&s_h0[key & 0xFF], 1u);
-        vals[i] = n < kPackLimit ? i | ((uint32_t)a << 24) : i;
-        kor |= key;
-        kand &= key;
+      } else {
+        ++n_inv;
+        bad = min(bad, i);
       }
-      const bool copy = c == C_COPYIN;
-      const uint64_t end = in ? e.t_end : 0;
-      // a kernel of this wavefront logged before the copy still runs at its start
-      uint32_t runs = copy && s_kdev[w][dc] != 0 && s_kmax[w][dc] >= ts;
-      const uint64_t kernels = __ballot(c == C_KERNEL);
-      if (kernels) {
-        for (uint64_t m = kernels; m; m &= m - 1) {
-          const int kl = __builtin_ctzll(m);
-          const uint32_t kd = lane32(dc, kl);
-          const uint64_t kend = lane64(end, kl);
-          runs |= copy && lane > kl && dc == kd && kend >= ts;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (c == C_KERNEL) {
-          atomicAdd(&s_kdev[w][dc], 1u);
-          atomicMax(&s_kmax[w][dc], (unsigned long long)end);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      }
-      classes |= (uint32_t)c << (3 * r);
-      later |= (uint32_t)(in && ts > prev_start) << r;
-      used |= runs << r;
-      L.rec[r * 64 + lane] = (copy ? a : dc) << 20;
-      L.addr[r * 64 + lane] = in ? e.src_addr : 0;
-      e = nx;
-      in = in_next;
+      if (cand) cand[i] = 1;
+      keys[i] = key;
+      if (c == C_TRANSFER || c == C_COPYIN) atomicAdd(&s_h0[key & 0xFF], 1u);
+      kor |= key;
+      kand &= key;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // backwards: a copy joins its place's bucket and searches it
-    uint32_t g_after = 0;
+    const bool copy = c == C_COPYIN;
+    const uint64_t end = in ? e.t_end : 0;
+    // a kernel of this wavefront logged before the copy still runs at its start
+    uint32_t runs = copy && L.dev[dc] != 0 && s_kmax[w][dc] >= ts;
+    const uint64_t kernels = __ballot(c == C_KERNEL);
+    if (kernels) {
+      for (uint64_t m = kernels; m; m &= m - 1) {
+        const int kl = __builtin_ctzll(m);
+        const uint32_t kd = lane32(dc, kl);
+        const uint64_t kend = lane64(end, kl);
+        runs |= copy && lane > kl && dc == kd && kend >= ts;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (c == C_KERNEL) {
+        atomicAdd(&L.dev[dc], 1u);
+        atomicMax(&s_kmax[w][dc], (unsigned long long)end);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    classes |= (uint32_t)c << (3 * r);
+    later |= (uint32_t)(in && ts > prev_start) << r;
+    used |= runs << r;
+    L.rec[r * 64 + lane] = (c == C_KERNEL ? dc : a) << 20;
+    L.addr[r * 64 + lane] = in ? e.src_addr : 0;
+    e = nx;
+    in = in_next;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  if (lane < kEp) {
+    wave_cnt[kWaveCnt * wid + 3 + lane] = L.dev[lane];
+    wave_kmax[kEp * wid + lane] = s_kmax[w][lane];
+    L.dev[lane] = kNoNode;  // from here on the next kernel
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  // backwards: a copy joins its place's bucket and searches it
+  uint32_t g_after = 0;
 #pragma unroll 1
-    for (int r = kSpan - 1; r >= 0; --r) {
-      const uint32_t node = r * 64 + lane, c = (classes >> (3 * r)) & 7;
-      const uint32_t code = L.rec[node] >> 20, dc = code & 15;
-      const bool copy = c == C_COPYIN;
-      const uint64_t lm = __ballot((later >> r) & 1);
-      const uint32_t g = g_after + (uint32_t)__popcll(lm & above);
-      // the next kernel on the receiving device
-      uint32_t nk = copy ? L.nk[dc] : kNoNode;
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      for (uint64_t m = __ballot(c == C_KERNEL); m;) {
-        const int kl = 63 - __builtin_clzll(m);
-        m &= ~(1ull << kl);
-        const uint32_t kd = lane32(dc, kl), kk = lane32(g, kl) << 10 | (uint32_t)(r * 64 + kl);
-        if (copy && dc == kd && lane < kl) nk = kk;
-        if (lane == 0) L.nk[kd] = kk;
-      }
-      const unsigned long long addr = L.addr[node];
-      const uint32_t bucket = near_hash(addr, code) % kSpanHeads;
-      if (copy) {
-        const uint32_t old = atomicExch(&L.head[bucket], node);
-        L.rec[node] = (old == kNoNode ? node : old) | g << 10 | code << 20;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      // the first copy to the place after this one and before that kernel. Nodes
-      // of a round come in any order, rounds in order; results stay integers.
-      const uint32_t limit = nk == kNoNode ? kSpanRecs : nk & 1023;
-      const bool open = copy && !((used >> r) & 1);
-      uint32_t best = limit, best_g = 0, cur = open ? L.head[bucket] : kNoNode;
-      while (__ballot(cur != kNoNode)) {
-        if (cur != kNoNode) {
-          const uint32_t x = L.rec[cur];
-          const uint32_t hit = (uint32_t)(L.addr[cur] == addr) & (((x >> 20) & 0xFF) == code) & (cur > node) & (cur < best);
-          best = hit ? cur : best;
-          best_g = hit ? (x >> 10) & 1023 : best_g;
-          const uint32_t nx = x & 1023;
-          cur = nx == cur || (nx >> 6) > (best >> 6) ? kNoNode : nx;
-        }
-      }
-      if (open) {
-        const bool found = best != limit;
-        if (found) atomicOr(&L.rec[best], kHasPred);
-        const bool no = nk != kNoNode ? found && best_g > (nk >> 10) : found && best_g > 0;
-        unused |= (uint32_t)no << r;
-        used |= (uint32_t)(nk != kNoNode && !no) << r;
-      }
-      g_after += (uint32_t)__popcll(lm);
+  for (int r = kSpan - 1; r >= 0; --r) {
+    const uint32_t node = r * 64 + lane, c = (classes >> (3 * r)) & 7;
+    const uint32_t code = L.rec[node] >> 20, dc = code & 15;
+    const bool copy = c == C_COPYIN;
+    const uint64_t lm = __ballot((later >> r) & 1);
+    const uint32_t g = g_after + (uint32_t)__popcll(lm & above);
+    // the next kernel on the receiving device
+    uint32_t nk = copy ? L.dev[dc] : kNoNode;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (uint64_t m = __ballot(c == C_KERNEL); m;) {
+      const int kl = 63 - __builtin_clzll(m);
+      m &= ~(1ull << kl);
+      const uint32_t kd = lane32(dc, kl), kk = lane32(g, kl) << 10 | (uint32_t)(r * 64 + kl);
+      if (copy && dc == kd && lane < kl) nk = kk;
+      if (lane == 0) L.dev[kd] = kk;
+    }
+    const unsigned long long addr = L.addr[node];
+    const uint32_t bucket = near_hash(addr, code) % kSpanHeads;
+    if (copy) {
+      const uint32_t old = atomicExch(&L.head[bucket], node);
+      L.rec[node] = (old == kNoNode ? node : old) | g << 10 | code << 20;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // classes and flags; the unused copies' bytes and durations, read again
+    // the first copy to the place after this one and before that kernel. Nodes
+    // of a round come in any order, rounds in order; results stay integers.
+    const uint32_t limit = nk == kNoNode ? kSpanRecs : nk & 1023;
+    const bool open = copy && !((used >> r) & 1);
+    uint32_t best = limit, best_g = 0, cur = open ? L.head[bucket] : kNoNode;
+    while (__ballot(cur != kNoNode)) {
+      if (cur != kNoNode) {
+        const uint32_t x = L.rec[cur];
+        const uint32_t hit = (uint32_t)(L.addr[cur] == addr) & (((x >> 20) & 0xFF) == code) & (cur > node) & (cur < best);
+        best = hit ? cur : best;
+        best_g = hit ? (x >> 10) & 1023 : best_g;
+        const uint32_t nx = x & 1023;
+        cur = nx == cur || (nx >> 6) > (best >> 6) ? kNoNode : nx;
+      }
+    }
+    if (open) {
+      const bool found = best != limit;
+      if (found) atomicOr(&L.rec[best], kHasPred);
+      const bool no = nk != kNoNode ? found && best_g > (nk >> 10) : found && best_g > 0;
+      unused |= (uint32_t)no << r;
+      used |= (uint32_t)(nk != kNoNode && !no) << r;
+    }
+    g_after += (uint32_t)__popcll(lm);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  // classes and flags; the unused copies' bytes and durations, read again
 #pragma unroll 4
-    for (int r = 0; r < kSpan; ++r) {
-      const uint32_t node = r * 64 + lane, i = wb + r0 * 64 + node;
-      if (i < n) {
-        uint8_t c = (classes >> (3 * r)) & 7;
-        uint8_t f = c == C_INVALID ? ODP_F_INVALID : 0;
-        if (c == C_COPYIN) {
-          ++c_all;
-          if (((used | unused) >> r) & 1) {
-            const uint32_t x = L.rec[node], first = L.nk[(x >> 20) & 15];
-            const bool seen = (first == kNoNode || node < (first & 1023)) && !(x & kHasPred);
-            c = seen ? C_SEEN : C_DECIDED;
-          }
-          c_ut += c != C_DECIDED;
+  for (int r = 0; r < kSpan; ++r) {
+    const uint32_t node = r * 64 + lane, i = wb + node;
+    if (i < n) {
+      uint8_t c = (classes >> (3 * r)) & 7;
+      uint8_t f = c == C_INVALID ? ODP_F_INVALID : 0;
+      const bool is_tx = c == C_TRANSFER || c == C_COPYIN;
+      if (c == C_COPYIN) {
+        ++c_all;
+        if (((used | unused) >> r) & 1) {
+          const uint32_t x = L.rec[node], first = L.dev[(x >> 20) & 15];
+          const bool seen = (first == kNoNode || node < (first & 1023)) && !(x & kHasPred);
+          c = seen ? C_SEEN : C_DECIDED;
         }
-        if ((unused >> r) & 1) {
-          f = ODP_F_UT;
-          ++c_ud;
-          ud_b += ev[i].bytes;
-          ud_t += ev[i].t_end - ev[i].t_start;
-        }
-        flags[i] = f;
-        cls[i] = c;
+        c_ut += c != C_DECIDED;
+      }
+      if ((unused >> r) & 1) {
+        f = ODP_F_UT;
+        ++c_ud;
+        ud_b += ev[i].bytes;
+        ud_t += ev[i].t_end - ev[i].t_start;
+      }
+      flags[i] = f;
+      cls[i] = c;
+      const uint32_t ep = (L.rec[node] >> 20) & 0xFF;
+      const uint32_t a = is_tx ? pack_ep(ep >> 4, ep & 15) | (f & ODP_F_UT ? kAuxUnused : 0u) : kNotTransfer;
+      if (n < kPackLimit) {
+        vals[i] = i | a << 24;
+      } else {
+        vals[i] = i;
+        aux[i] = (uint8_t)a;
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
   const uint32_t n_k = c_k;
   // per-wavefront subset counts
@@ -597,23 +620,19 @@ __global__ __launch_bounds__(kT, 5) void classify_kernel(const odp_event* __rest
     wave_copies[wid] = c_all;
   }
   __syncthreads();
-  hist0[(size_t)threadIdx.x * ntc + blockIdx.x] = s_h0[threadIdx.x];
-  if (lane < kEp) {
-    wave_cnt[kWaveCnt * wid + 3 + lane] = s_kdev[w][lane];
-    wave_kmax[kEp * wid + lane] = s_kmax[w][lane];
-  }
-  block_store<R_ADD>(parts.at(S_N_INVALID), n_inv);
-  block_store<R_ADD>(parts.at(S_N_TRANSFERS), n_tx);
-  block_store<R_ADD>(parts.at(S_N_KERNELS), n_k);
-  block_store<R_OR>(parts.at(S_DIG_OR), kor);
-  block_store<R_AND>(parts.at(S_DIG_AND), kand);
-  block_store<R_MIN>(parts.at(S_FIRST_BAD), bad);
-  block_store<R_MAX>(parts.at(S_MAX_EP), mep);
-  block_store<R_MIN>(parts.at(S_TMIN), tmin);
-  block_store<R_MAX>(parts.at(S_TMAX), tmax);
-  block_store<R_ADD>(parts.at(S_UD_EVENTS), c_ud);
-  block_store<R_ADD>(parts.at(S_UD_BYTES), ud_b);
-  block_store<R_ADD>(parts.at(S_UD_TIME), ud_t);
+  if (threadIdx.x < 256) hist0[(size_t)threadIdx.x * ntc + blockIdx.x] = s_h0[threadIdx.x];
+  block_store<R_ADD, kClassT>(parts.at(S_N_INVALID), n_inv);
+  block_store<R_ADD, kClassT>(parts.at(S_N_TRANSFERS), n_tx);
+  block_store<R_ADD, kClassT>(parts.at(S_N_KERNELS), n_k);
+  block_store<R_OR, kClassT>(parts.at(S_DIG_OR), kor);
+  block_store<R_AND, kClassT>(parts.at(S_DIG_AND), kand);
+  block_store<R_MIN, kClassT>(parts.at(S_FIRST_BAD), bad);
+  block_store<R_MAX, kClassT>(parts.at(S_MAX_EP), mep);
+  block_store<R_MIN, kClassT>(parts.at(S_TMIN), tmin);
+  block_store<R_MAX, kClassT>(parts.at(S_TMAX), tmax);
+  block_store<R_ADD, kClassT>(parts.at(S_UD_EVENTS), c_ud);
+  block_store<R_ADD, kClassT>(parts.at(S_UD_BYTES), ud_b);
+  block_store<R_ADD, kClassT>(parts.at(S_UD_TIME), ud_t);
 }
 
 // ---------------------------------------------------------------------------
@@ -864,15 +883,16 @@ __device__ void subset_scatter_body(const odp_event* __restrict__ ev, const uint
     rounds = ceil_div32(listed, 64);
   }
   // offsets: the wavefront's prefix within its chunk plus the chunk's prefix
-  const uint32_t* wo = W.cnt + (size_t)kWaveCnt * wid;
-  const uint32_t* co = W.ccnt + (size_t)kWaveCnt * (wid / kScanChunk);
+  const uint32_t ent = MID ? wid : wb / kSpanRecs;
+  const uint32_t* wo = W.cnt + (size_t)kWaveCnt * ent;
+  const uint32_t* co = W.ccnt + (size_t)kWaveCnt * (ent / kScanChunk);
   uint32_t q0 = wo[0] + co[0], q1 = wo[1] + co[1], q2 = wo[2] + co[2];
   __shared__ uint32_t s_kc[kT / 64][kEp];            // kernels per device code before the current round
   __shared__ unsigned long long s_km[kT / 64][kEp];  // the latest end among them
   if (lane < kEp) {
     s_kc[w][lane] = wo[3 + lane] + co[3 + lane];
-    s_km[w][lane] = max((unsigned long long)W.kmax[(size_t)kEp * wid + lane],
-                        (unsigned long long)W.cmax[(size_t)kEp * (wid / kScanChunk) + lane]);
+    s_km[w][lane] = max((unsigned long long)W.kmax[(size_t)kEp * ent + lane],
+                        (unsigned long long)W.cmax[(size_t)kEp * (ent / kScanChunk) + lane]);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   unsigned long long o_dev = 0, a_dev = ~0ull, o_addr = 0, a_addr = ~0ull, o_ks = 0, a_ks = ~0ull, o_ke = 0,
@@ -1928,12 +1948,13 @@ __device__ __forceinline__ uint32_t dd_len(const DDArgs& A) { return sorted_len(
 // All 16 rounds of a wavefront at once: keys and values (coalesced), then
 // the endpoint codes gathered by value, all loads in flight together. Values
 // and codes go to the wavefront's LDS rows; bit r of heads / tails says
-// whether this lane's element of round r starts / ends its digest group.
+// whether this lane's element of round r starts / ends its digest group, of
+// unused whether the classification found it unused.
 // n: the sorted elements; packed: codes in the values' top byte.
 template <int ROUNDS>
 __device__ __forceinline__ void load_wave(const unsigned long long* k, const uint32_t* v, const uint8_t* aux,
                                           uint32_t n, bool packed, uint32_t wb, uint32_t* s_val, uint8_t* s_code,
-                                          uint32_t& heads, uint32_t& tails) {
+                                          uint32_t& heads, uint32_t& tails, uint32_t& unused) {
   const int lane = threadIdx.x & 63;
   unsigned long long key[ROUNDS];
   uint32_t val[ROUNDS];
@@ -1956,7 +1977,7 @@ __device__ __forceinline__ void load_wave(const unsigned long long* k, const uin
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) a[r] = wb + r * 64 + lane < n ? aux[val[r]] : kNotTransfer;
   }
-  heads = tails = 0;
+  heads = tails = unused = 0;
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t j = wb + r * 64 + lane;
@@ -1970,7 +1991,8 @@ __device__ __forceinline__ void load_wave(const unsigned long long* k, const uin
     heads |= (uint32_t)(in && (j == 0 || prev != key[r])) << r;
     tails |= (uint32_t)(in && (j + 1 == n || next != key[r])) << r;
     s_val[r * 64 + lane] = val[r];
-    s_code[r * 64 + lane] = a[r];
+    s_code[r * 64 + lane] = unpack_ep(a[r]);
+    unused |= (uint32_t)(a[r] != kNotTransfer && (a[r] & kAuxUnused)) << r;
   }
   wave_lds_fence();
 }
@@ -1988,7 +2010,7 @@ __device__ __forceinline__ void load_round(const unsigned long long* k, const ui
   if (lane == 63 && in && j + 1 < n) next = k[j + 1];
   head = in && (j == 0 || prev != key);
   tail = in && (j + 1 == n || next != key);
-  a = !in ? kNotTransfer : packed ? (uint8_t)(v[j] >> 24) : aux[v[j]];
+  a = !in ? kNotTransfer : unpack_ep(packed ? v[j] >> 24 : aux[v[j]]);
 }
 
 // Per-wavefront aggregates. The forward one folds the elements after the
@@ -2207,10 +2229,12 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64],
     }
     return;
   }
-  load_wave<ROUNDS>(k, v, A.aux, ns, A.n < kPackLimit, wb, s_val[w], s_code[w], heads, tails);
+  uint32_t unread;  // bit r: this lane's element of round r is an unused transfer
+  load_wave<ROUNDS>(k, v, A.aux, ns, A.n < kPackLimit, wb, s_val[w], s_code[w], heads, tails, unread);
+  // (what the classification found counts in a chronological log)
+  if (!MID && A.ctl->first_bad != kNone) unread = 0;
   FS<MODE> carry = S::fid();
   BS<MODE> bcarry = S::bid();
-  uint32_t unread = 0;  // bit r: this lane's element of round r is an unused transfer
   if constexpr (MID) {
     for (int r = 0; r < ROUNDS; ++r)
       if (wb + r * 64 + lane < ns) unread |= (uint32_t)A.uth[s_val[w][r * 64 + lane]] << r;
@@ -2284,13 +2308,14 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64],
       if (fres & (1u << (2 * r))) res |= ODP_F_DD;
       if (fres & (2u << (2 * r))) res |= ODP_F_RT_RX;
       if (sr != d && S::tx(ex, sr, d)) res |= ODP_F_RT_TX;
-      if (MID && ((unread >> r) & 1)) res |= ODP_F_UT;
+      const bool found = res != 0;
+      if ((unread >> r) & 1) res |= ODP_F_UT;
       c_grp += !(res & ODP_F_DD) && S::has_dst(ex, d);
       c_dd += (res & ODP_F_DD) != 0;
       c_tx += (res & ODP_F_RT_TX) != 0;
       c_rx += (res & ODP_F_RT_RX) != 0;
       // the classification stored the other records' flags (MID: 0 for every valid record)
-      if (MID && res) A.flags[s_val[w][r * 64 + lane]] = res;
+      if (MID ? res != 0 : found) A.flags[s_val[w][r * 64 + lane]] = res;
       s_code[w][r * 64 + lane] = res;  // the code is not read again
     } else {
       s_code[w][r * 64 + lane] = 0;
@@ -2299,22 +2324,17 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64],
     const BS<MODE> y0 = S::shfl(y, 0);
     bcarry = g0 ? y0 : S::bop(y0, bcarry);
   }
-  // bytes and durations of the flagged records, four rounds of gathers in flight at a time.
-  // What the classification decided of a flagged record stays (in a chronological log).
-  const uint8_t keep_ut = A.ctl->first_bad == kNone ? ODP_F_UT : 0;
+  // bytes and durations of the flagged records, four rounds of gathers in flight at a time
   constexpr int kG = ROUNDS < 4 ? ROUNDS : 4;
   wave_lds_fence();
 #pragma unroll 1
   for (int r0 = 0; r0 < ROUNDS; r0 += kG) {
     uint64_t eb[kG], ed[kG];
-    uint8_t rs[kG], ut[kG];
+    uint8_t rs[kG];
 #pragma unroll
     for (int q = 0; q < kG; ++q) {
       rs[q] = s_code[w][(r0 + q) * 64 + lane];
       eb[q] = ed[q] = 0;
-      ut[q] = 0;
-      if constexpr (!MID)
-        if (rs[q]) ut[q] = A.flags[s_val[w][(r0 + q) * 64 + lane]] & keep_ut;
       if (rs[q] & (ODP_F_DD | ODP_F_RT_RX | (MID ? ODP_F_UT : 0))) {
         const odp_event& e = A.ev[s_val[w][(r0 + q) * 64 + lane]];
         eb[q] = e.bytes;
@@ -2323,8 +2343,7 @@ __device__ void ddrt_final_body(const DDArgs& A, uint32_t (*s_val)[ROUNDS * 64],
     }
 #pragma unroll
     for (int q = 0; q < kG; ++q) {
-      if (!MID && rs[q]) A.flags[s_val[w][(r0 + q) * 64 + lane]] = rs[q] | ut[q];
-      if (!ut[q]) t_el += ed[q];  // removable once, whether DD, RT_RX or both (UT: counted with those)
+      if (MID || !(rs[q] & ODP_F_UT)) t_el += ed[q];  // removable once, whether DD, RT_RX or both (UT: counted with those)
       if (rs[q] & ODP_F_DD) {
         b_dd += eb[q];
         t_dd += ed[q];
@@ -2628,24 +2647,23 @@ struct RaArgs {
 };
 
 
-// Number of entries of the sorted array w within [lo, hi) that are <= x (le) or < x.
-__device__ __forceinline__ uint32_t count_upto(const uint64_t* w, uint32_t lo, uint32_t hi, uint64_t x, bool le) {
-  uint32_t a = lo, b = hi;
-  while (a < b) {
-    const uint32_t m = (a + b) / 2;
-    const uint64_t y = w[m];
-    if (le ? (y <= x) : (y < x)) a = m + 1; else b = m;
-  }
-  return a - lo;
-}
-
 // Kernels on device code `dev` whose closed interval meets [lo, hi] (lo <= hi):
 // those that start by hi, less those that end before lo (an interval that
-// ends before lo also starts before hi).
+// ends before lo also starts before hi). The two binary searches take the same
+// steps, so their loads, a chain of some twenty each, are in flight together.
 __device__ __forceinline__ uint32_t kernels_meeting(const uint64_t* starts, const uint64_t* ends, const AnaCtl* ctl,
                                                     uint32_t dev, uint64_t lo, uint64_t hi) {
-  const uint32_t a = ctl->dev_lo[dev], b = ctl->dev_hi[dev];
-  return count_upto(starts, a, b, hi, true) - count_upto(ends, a, b, lo, false);
+  uint32_t s = ctl->dev_lo[dev], e = s, len = ctl->dev_hi[dev] - s;
+  if (len == 0) return 0;
+  for (; len > 1; len -= len / 2) {
+    const uint32_t half = len / 2;
+    const uint64_t x = starts[s + half - 1], y = ends[e + half - 1];
+    s += x <= hi ? half : 0u;
+    e += y < lo ? half : 0u;
+  }
+  s += starts[s] <= hi;
+  e += ends[e] < lo;
+  return s - e;
 }
 
 // UA in a chronological log, with K and M as for unused transfers: the pair is
@@ -2914,7 +2932,7 @@ __global__ __launch_bounds__(kT) void ut_eval_kernel(UtArgs U) {
 // decided of them is overwritten.
 // Then the kernels that the classification could not see: a copy it found
 // unused is used if a kernel of an earlier wavefront on its device still runs
-// at its start. A wavefront takes the 1,024 records of one of the
+// at its start. A wavefront takes the 512 records of one of the
 // classification's and reads on while records start before the latest of
 // those ends (a copy flagged DD or RT_RX as well stays removable).
 __global__ __launch_bounds__(kT) void ut_merge_kernel(UtArgs U) {
@@ -2960,7 +2978,7 @@ __global__ __launch_bounds__(kT) void ut_merge_kernel(UtArgs U) {
   const uint32_t lane = threadIdx.x & 63;
   if (!stale) {
     for (uint32_t wid = (blockIdx.x * kT + threadIdx.x) / 64; wid < U.W.nw; wid += stride / 64) {
-      const uint32_t wb = wid * kWaveElems;
+      const uint32_t wb = wid * kSpanRecs;
       if (wb >= U.n) break;
       // the latest end of an earlier wavefront's kernel, per device code (lane)
       unsigned long long last = 0;
@@ -2974,7 +2992,7 @@ __global__ __launch_bounds__(kT) void ut_merge_kernel(UtArgs U) {
       unsigned long long most = last;
       for (int o = 8; o >= 1; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
       most = __shfl(most, 0, 64);
-      for (uint32_t r = 0; r < (uint32_t)kRounds; ++r) {
+      for (uint32_t r = 0; r < (uint32_t)kSpan; ++r) {
         const uint32_t i = wb + r * 64 + lane;
         const bool in = i < U.n;
         const uint64_t ts = in ? U.ev[i].t_start : ~0ull;
@@ -3092,7 +3110,7 @@ __device__ __forceinline__ uint64_t pick64(const uint64_t (&arr)[kEp], uint32_t 
 __device__ __forceinline__ void alg2_load(const Alg2Args& A, const uint32_t* v, uint32_t j, bool& x, uint32_t& src,
                                           uint32_t& dst, uint32_t& rec) {
   const uint32_t w = v[j];
-  const uint8_t a = A.n < kPackLimit ? (uint8_t)(w >> 24) : A.aux[w];
+  const uint8_t a = unpack_ep(A.n < kPackLimit ? w >> 24 : A.aux[w]);
   rec = A.n < kPackLimit ? (w & kIdxMask) : w;
   x = a != kNotTransfer;
   src = x ? (uint32_t)(a >> 4) : 0u;
@@ -3332,7 +3350,7 @@ Views views(Workspace* ws) {
   v.bv[1] = static_cast<uint32_t*>(b[B_BVAL1].ptr);
   v.tile_cnt = static_cast<uint32_t*>(b[B_TILECNT].ptr);
   v.wave_cnt = v.tile_cnt + 2 * (size_t)v.ntc;  // kWaveCnt counters per wavefront
-  v.wave_copies = v.wave_cnt + (size_t)kWaveCnt * v.ntc * (kT / 64);  // one per wavefront
+  v.wave_copies = v.wave_cnt + (size_t)kWaveCnt * v.ntc * (kTile / kSpanRecs);  // one per wavefront
   const size_t cap = v.cap;
   char* pa = static_cast<char*>(b[B_AD].ptr);
   v.S.ad_idx = carve<uint32_t>(pa, cap);
@@ -3371,7 +3389,7 @@ Views views(Workspace* ws) {
   v.ut_hit = carve<uint8_t>(pu, cap);
   v.S.ut_hit = v.ut_hit;
   char* pw = static_cast<char*>(b[B_WSCAN].ptr);
-  const uint32_t nw = v.ntc * (kT / 64), nchunk = ceil_div32(nw, kScanChunk);
+  const uint32_t nw = v.ntc * (kTile / kSpanRecs), nchunk = ceil_div32(nw, kScanChunk);
   v.wscan.cnt = v.wave_cnt;
   v.wscan.kmax = carve<uint64_t>(pw, (size_t)nw * kEp);
   v.wscan.ccnt = carve<uint32_t>(pw, (size_t)nchunk * kWaveCnt);
@@ -3502,12 +3520,12 @@ int analyze_reserve(Workspace* ws, size_t max_events) {
   if ((e = b[B_MID].ensure(mid_views(sized, nullptr, cap) + 64)) || (e = b[B_CTL].ensure(sizeof(AnaCtl))) || (e = b[B_JOBS].ensure(sizeof(SortJob) * kNumJobs)) ||
       (e = b[B_CLS].ensure(cap)) || (e = b[B_AUX].ensure(2 * cap)) || (e = b[B_BKEY0].ensure(cap * 8)) ||
       (e = b[B_BKEY1].ensure(cap * 8)) || (e = b[B_BVAL0].ensure(cap * 4)) || (e = b[B_BVAL1].ensure(cap * 4)) ||
-      (e = b[B_TILECNT].ensure((size_t)nt * 4 * (2 + (kWaveCnt + 1) * (kT / 64)))) ||
+      (e = b[B_TILECNT].ensure((size_t)nt * 4 * (2 + (kWaveCnt + 1) * (kTile / kSpanRecs)))) ||
       (e = b[B_AD].ensure(cap * (4 + 8 + 8 + 4 + 4 + 4 + 4 + 8 + 1) + 64)) ||
       (e = b[B_K].ensure(cap * (4 + 8 + 8 + 8 + 4 * 4 + 8 + 8 + 8 + 4) + 64)) ||
       (e = b[B_UT].ensure(cap * (4 + 8 + 8 + 8 + 4 + 4 + 8 + 4 + 4 + 1) + 64)) ||
-      (e = b[B_WSCAN].ensure((size_t)nt * (kT / 64) * kEp * 8 +
-                             (size_t)ceil_div32((size_t)nt * (kT / 64), kScanChunk) * (kWaveCnt * 4 + kEp * 8) + 64)) ||
+      (e = b[B_WSCAN].ensure((size_t)nt * (kTile / kSpanRecs) * kEp * 8 +
+                             (size_t)ceil_div32((size_t)nt * (kTile / kSpanRecs), kScanChunk) * (kWaveCnt * 4 + kEp * 8) + 64)) ||
       (e = b[B_PR].ensure(cap * (4 + 4 + 8 + 8 + 8 + 4) +
                           ((size_t)pair_table_mask((uint32_t)std::min<size_t>(cap / 2, 0x7FFFFFFFu)) + 1) * 12 + 64)) ||
       (e = b[B_HIST].ensure((size_t)kNumJobs * 256 * nt * 4)) ||
@@ -4283,7 +4301,7 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kT), 0, stream, v.parts, 0u, ctl, out_report);
     return check_hip(hipGetLastError(), "odp_analyze_trace launch");
   }
-  hipLaunchKernelGGL(classify_kernel, dim3(nt), dim3(kT), 0, stream, events, nn, out_flags, v.cls, v.aux, v.bk[0],
+  hipLaunchKernelGGL(classify_kernel, dim3(nt), dim3(kClassT), 0, stream, events, nn, out_flags, v.cls, v.aux, v.bk[0],
                      v.bv[0], v.wave_cnt, v.wave_copies, v.wscan.kmax, v.hist + (size_t)kJobBig * 256 * v.ntc, v.ntc,
                      alg2_rx ? nullptr : v.cand, v.parts, ctl, out_report, v.totals);
   // the classification's counts, digest masks, first rejected record and endpoint range
@@ -4306,7 +4324,7 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   // The allocation path on the side stream, enqueued first (it waits only
   // for the classification), then the digest path on the caller's stream.
   WaveScan WS = v.wscan;
-  WS.nw = nt * (kT / 64);
+  WS.nw = nt * (kTile / kSpanRecs);
   WS.copies = v.wave_copies;
   const uint32_t nchunk = ceil_div32(WS.nw, kScanChunk);
   hipLaunchKernelGGL(wave_scan_kernel, dim3(nchunk * kScanQ), dim3(1024), 0, side, WS, nchunk, ctl);
@@ -4349,6 +4367,23 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
     hipLaunchKernelGGL(sort_scan_kernel, dim3(256 * Js.njobs), dim3(kT), 0, side, Js, p);
     hipLaunchKernelGGL(sort_scatter_kernel, dim3(Js.njobs * side_blocks), dim3(kST), 0, side, Js, p);
   }
+  // Meanwhile the records by digest, up to 8 passes, on the caller's stream.
+  // Only the launches after the sorts alternate between the two streams, so that
+  // neither chain waits for the other's to be enqueued (1 million records 386 ->
+  // 355 us). Alternating from the first pass on takes 355 us there and 558
+  // instead of 517 for 2 million records on 8 devices, whose subsets sort longer.
+  const uint32_t nft = (uint32_t)((n + kFixTile - 1) / kFixTile);  // tiles of the local fix
+  // the digest histograms take two tiles per block on long logs (measured a
+  // little faster than one: the per-block start-up is amortised)
+  const JobSet Jh{v.jobs + kJobBig, 1, nt > 4u * (uint32_t)cus ? (nt + 1) / 2 : nt};
+  for (uint32_t p = 0; p < 8; ++p) {
+    if (p == 1 && filter)
+      hipLaunchKernelGGL(sort_filter_kernel, dim3(256), dim3(kFilterT), 0, stream, v.jobs + kJobBig);
+    if (p == kfirst) hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, p);
+    hipLaunchKernelGGL(sort_hist_kernel, dim3(Jh.stride), dim3(kT), 0, stream, Jh, p);
+    hipLaunchKernelGGL(sort_scan_kernel, dim3(256), dim3(kT), 0, stream, Jb, p);
+    hipLaunchKernelGGL(sort_scatter_kernel, dim3(nt), dim3(kST), 0, stream, Jb, p);
+  }
   // Pairing and the pair list.
   PairArgs P;
   P.ev = events;
@@ -4368,10 +4403,29 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   P.flags = out_flags;
   P.ctl = ctl;
   P.rep = out_report;
+  // Beside them the duplicates and round trips, on the caller's stream.
+  DDArgs D;
+  D.ev = events;
+  D.n = nn;
+  D.aux = v.aux;
+  D.job = v.jobs + kJobBig;
+  D.ctl = ctl;
+  D.agg = v.agg;
+  D.carry = v.carry;
+  D.flags = out_flags;
+  D.rep = out_report;
+  D.parts = v.parts;
+  D.uth = nullptr;
+  hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, kFixFinal);
   hipLaunchKernelGGL(pair_kernel, dim3(grid_map), dim3(kT), 0, side, P);
+  hipLaunchKernelGGL(ddrt_agg_kernel<kRounds>, dim3(nt), dim3(kT), 0, stream, D);
   hipLaunchKernelGGL(pair_count_kernel, dim3(nt), dim3(kT), 0, side, P);
+  hipLaunchKernelGGL(ddrt_carry_kernel, dim3(1), dim3(kCT), 0, stream, D, nt * (kT / 64));
   hipLaunchKernelGGL(scan_counts_kernel<2>, dim3(1), dim3(1024), 0, side, v.tile_cnt, nt, &ctl->n_pairs, nullptr);
+  hipLaunchKernelGGL((ddrt_final_kernel<kRounds, false>), dim3(nt), dim3(kT), 0, stream, D);
   hipLaunchKernelGGL(pair_scatter_kernel, dim3(nt), dim3(kT), 0, side, P);
+  hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_ELIM_TX + 1 - S_DD_EVENTS), dim3(kT), 0, stream, v.parts, nt,
+                     (uint32_t)S_DD_EVENTS, ctl, out_report, plan_none);
   const KernRangeArgs K{v.jobs + kJobKs, v.jobs + kJobKe, v.S.k_w_dev, v.S.k_w_start, v.S.k_w_end,
                         &ctl->n_k, v.starts_sorted, v.ends_sorted, ctl};
   hipLaunchKernelGGL(side_misc_kernel, dim3(grid_map), dim3(kT), 0, side, K, U, v.pt, &ctl->n_pairs);
@@ -4402,38 +4456,6 @@ static int enqueue_analysis(Workspace* ws, const odp_event* events, size_t n, ui
   hipLaunchKernelGGL(ra_ua_kernel, dim3(grid_sum), dim3(kT), 0, side, R);
   hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_ELIM_PAIRS + 1 - S_RA_EVENTS), dim3(kT), 0, side, v.parts, grid_sum,
                      (uint32_t)S_RA_EVENTS, ctl, out_report, plan_none);
-  // Records by digest (up to 8 passes), then duplicates and round trips, on
-  // the caller's stream.
-  const uint32_t nft = (uint32_t)((n + kFixTile - 1) / kFixTile);  // tiles of the local fix
-  // the digest histograms take two tiles per block on long logs (measured a
-  // little faster than one: the per-block start-up is amortised)
-  const JobSet Jh{v.jobs + kJobBig, 1, nt > 4u * (uint32_t)cus ? (nt + 1) / 2 : nt};
-  for (uint32_t p = 0; p < 8; ++p) {
-    if (p == 1 && filter)
-      hipLaunchKernelGGL(sort_filter_kernel, dim3(256), dim3(kFilterT), 0, stream, v.jobs + kJobBig);
-    if (p == kfirst) hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, p);
-    hipLaunchKernelGGL(sort_hist_kernel, dim3(Jh.stride), dim3(kT), 0, stream, Jh, p);
-    hipLaunchKernelGGL(sort_scan_kernel, dim3(256), dim3(kT), 0, stream, Jb, p);
-    hipLaunchKernelGGL(sort_scatter_kernel, dim3(nt), dim3(kST), 0, stream, Jb, p);
-  }
-  hipLaunchKernelGGL(sort_fix_kernel, dim3(nft), dim3(kT), 0, stream, v.jobs + kJobBig, kFixFinal);
-  DDArgs D;
-  D.ev = events;
-  D.n = nn;
-  D.aux = v.aux;
-  D.job = v.jobs + kJobBig;
-  D.ctl = ctl;
-  D.agg = v.agg;
-  D.carry = v.carry;
-  D.flags = out_flags;
-  D.rep = out_report;
-  D.parts = v.parts;
-  D.uth = nullptr;
-  hipLaunchKernelGGL(ddrt_agg_kernel<kRounds>, dim3(nt), dim3(kT), 0, stream, D);
-  hipLaunchKernelGGL(ddrt_carry_kernel, dim3(1), dim3(kCT), 0, stream, D, nt * (kT / 64));
-  hipLaunchKernelGGL((ddrt_final_kernel<kRounds, false>), dim3(nt), dim3(kT), 0, stream, D);
-  hipLaunchKernelGGL(reduce_parts_kernel, dim3(S_ELIM_TX + 1 - S_DD_EVENTS), dim3(kT), 0, stream, v.parts, nt,
-                     (uint32_t)S_DD_EVENTS, ctl, out_report, plan_none);
   if (alg2_rx) {
     Alg2Args G;
     G.job = v.jobs + kJobBig;

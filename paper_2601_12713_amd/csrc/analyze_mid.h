@@ -295,7 +295,7 @@ __global__ __launch_bounds__(kClsT) void mid_classify_kernel(MidClassify A) {
         tmax = max(tmax, (unsigned long long)x.t_end);
         if (is_tx) {
           c = x.op != ODP_D2H && x.dst_dev >= 0 ? C_COPYIN : C_TRANSFER;
-          code[r] = (uint32_t)(x.src_dev + 1) << 4 | (uint32_t)(x.dst_dev + 1);
+          code[r] = pack_ep((uint32_t)(x.src_dev + 1), (uint32_t)(x.dst_dev + 1));
           mep = max(mep, (uint32_t)max(x.src_dev + 1, x.dst_dev + 1));
           pr[r] = probe_start(near_hash(x.digest, 0), A.dmask, true);
           ++n_tx;
