@@ -3074,10 +3074,15 @@ __global__ __launch_bounds__(kT) void finalize_kernel(Parts parts, uint32_t nb, 
 // unrecorded, which only grows. A recorded k pairs with the m-th transfer into
 // s, m = the recorded transfers into s before k.
 // One wavefront per 64 sorted positions handles the digest groups that start
-// there: groups of one transfer at once (recorded, with rx = itself, exactly
-// when it is a self-transfer), longer ones one after another in three
-// sweeps: counts per endpoint, then the decisions and each group's transfers
-// listed by destination endpoint (in `lists`), then rx.
+// there. Those that end there too are handled together, a lane per transfer:
+// counts and ranks are bits of the lane's own group in ballots over all 64, and
+// the late transfers of all groups decide side by side. A group that goes on
+// past the 64 is read from its start, and handled in the same way if it fits
+// into 64 lanes, else in three sweeps: counts per endpoint, then the decisions
+// and its transfers listed by destination endpoint (in `lists`), then rx.
+// Bound by the latency of these chains of dependent steps: 53 us for 200,000
+// records of three devices when the groups of a wavefront were taken one after
+// another, 20 us now.
 struct Alg2Args {
   const SortJob* job;        // the digest job (keys/vals in buffer npasses & 1)
   const uint8_t* aux;
@@ -3117,6 +3122,49 @@ __device__ __forceinline__ void alg2_load(const Alg2Args& A, const uint32_t* v, 
   dst = x ? (uint32_t)(a & 15) : 0u;
 }
 
+// The groups of a wavefront's 64 sorted positions from b on: G is the mask of the
+// lanes of this lane's group, or 0 when the lane takes no part. Returns the
+// number of transfers recorded. list: 64 words of LDS of the wavefront.
+__device__ __forceinline__ uint32_t alg2_together(const Alg2Args& A, const uint32_t* v, uint32_t b, uint64_t G, uint32_t* list) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t lt = lanemask_lt();
+  bool x = false;
+  uint32_t src = 0, dst = 0, rec = 0;
+  if (G) alg2_load(A, v, b + lane, x, src, dst, rec);
+  uint64_t into[kEp];
+#pragma unroll
+  for (int e = 0; e < kEp; ++e) into[e] = __ballot(x && dst == (uint32_t)e);
+  const uint64_t isrc = pick64(into, src) & G;
+  const uint32_t before = (uint32_t)__popcll(isrc & lt);
+  // every transfer into its source comes before it: late ones decide in log order
+  uint32_t waits = x && before == (uint32_t)__popcll(isrc), u = 0, F = 0;
+  for (;;) {
+    const uint64_t c = __ballot(waits && !((F >> src) & 1)) & G;
+    if (!__ballot(c != 0)) break;
+    const uint32_t first = c ? (uint32_t)__builtin_ctzll(c) : lane;  // of this lane's group
+    const uint32_t d = (uint32_t)__shfl((int)dst, (int)first, 64);
+    F |= c ? 1u << d : 0u;
+    u |= c && lane == first;
+    waits = c && lane <= first ? 0u : waits;
+  }
+  uint64_t uinto[kEp];
+  uint32_t at = G ? (uint32_t)__builtin_ctzll(G) : 0u, mine = 0, base_src = at;
+#pragma unroll
+  for (int e = 0; e < kEp; ++e) {
+    uinto[e] = __ballot(u && dst == (uint32_t)e);
+    if ((uint32_t)e == dst) mine = at;
+    if ((uint32_t)e == src) base_src = at;
+    at += (uint32_t)__popcll(into[e] & G);
+  }
+  if (x) list[mine + (uint32_t)__popcll(pick64(into, dst) & G & lt)] = rec;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const bool recorded = x && !u;
+  const uint32_t m = before - (uint32_t)__popcll(pick64(uinto, src) & G & lt);
+  if (recorded) A.rx[rec] = list[base_src + m];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return (uint32_t)__popcll(__ballot(recorded));
+}
+
 __global__ __launch_bounds__(kT) void alg2_kernel(Alg2Args A) {
   const SortJob& s = *A.job;
   const unsigned long long* k = s.keys[s.npasses & 1];
@@ -3131,19 +3179,28 @@ __global__ __launch_bounds__(kT) void alg2_kernel(Alg2Args A) {
   const unsigned long long key = in ? k[j] : 0ull;
   const bool head = in && (j == 0 || k[j - 1] != key);
   const bool tail = in && (j + 1 == n || k[j + 1] != key);
-  uint64_t pairs = 0;
-  {  // groups of one record
-    bool x = false;
-    uint32_t src = 0, dst = 0, rec = 0;
-    if (head && tail) alg2_load(A, v, j, x, src, dst, rec);
-    if (x && src == dst) A.rx[rec] = rec;
-    pairs += (uint64_t)__popcll(__ballot(x && src == dst));
+  __shared__ uint32_t s_list[kT / 64][64];
+  uint32_t* list = s_list[threadIdx.x >> 6];
+  const uint64_t heads = __ballot(head), tails = __ballot(tail), le = lt | 1ull << lane;
+  const uint64_t starts = heads & le, ends = tails & ~lt;  // of this lane's group
+  uint64_t G = 0;
+  if (in && starts && ends) {
+    const int from = 63 - __builtin_clzll(starts), to = __builtin_ctzll(ends);
+    G = (to == 63 ? ~0ull : (1ull << (to + 1)) - 1) & ~((1ull << from) - 1);
   }
-  uint64_t heads = __ballot(head && !tail);
-  while (heads) {
-    const uint32_t g0 = c0 + (uint32_t)__builtin_ctzll(heads);
-    heads &= heads - 1;
+  uint64_t pairs = alg2_together(A, v, c0, G, list);
+  // the group that starts here and goes on, if any
+  const int last = heads ? 63 - __builtin_clzll(heads) : -1;
+  if (last >= 0 && (tails >> last) == 0) {
+    const uint32_t g0 = c0 + (uint32_t)last;
     const unsigned long long gkey = k[g0];
+    const bool more = g0 + lane < n && k[g0 + lane] == gkey;
+    const uint64_t members = __ballot(more);
+    if (members != ~0ull || g0 + 64 >= n || k[g0 + 64] != gkey) {
+      pairs += alg2_together(A, v, g0, more ? members : 0ull, list);
+      if (lane == 0 && pairs) atomicAdd(A.npairs, (unsigned long long)pairs);
+      return;
+    }
     // sweep 1: transfers into each endpoint, and the group's end g1
     uint32_t cnt[kEp];
 #pragma unroll

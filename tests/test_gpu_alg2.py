@@ -157,3 +157,20 @@ def test_log_above_packed_index_limit(odp):
     ev["digest"][tx] = rng.integers(0, 50, size=tx.size).astype(np.uint64)
     rx, npairs, rep = check(odp, ev, transfers=tx)
     assert rep["n_transfers"] == tx.size and npairs > 1000
+
+
+@pytest.mark.parametrize("n_devices", [1, 3, 10])
+@pytest.mark.parametrize("sizes", [(1, 2, 3, 5, 8), (62, 63, 64, 65, 66), (1, 127, 2, 128, 129, 1), (31, 33, 64, 1, 1, 700)])
+def test_groups_within_and_across_wavefronts(odp, sizes, n_devices):
+    """Groups up to, of and above 64 transfers, at every offset to the 64 a wavefront takes."""
+    n = 20_000
+    rng = np.random.default_rng(sum(sizes) + n_devices)
+    ev = W.empty_events(n)
+    groups = np.repeat(np.arange(n), np.resize(sizes, n))[:n]
+    ev["digest"] = rng.permutation(groups).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
+    ev["op"] = rng.choice([W.H2D, W.D2H, W.D2D], size=n)
+    ev["src_dev"], ev["dst_dev"] = rng.integers(-1, n_devices, size=n), rng.integers(-1, n_devices, size=n)
+    ev["bytes"] = 64
+    ev["t_start"] = np.arange(n) * 10 + 5
+    ev["t_end"] = ev["t_start"] + np.uint64(3)
+    check(odp, ev)
