@@ -179,17 +179,31 @@ __device__ __forceinline__ uint32_t pass_len(const SortJob& s, uint32_t p) {
 // Elements in the job's sorted order once its passes have run (all of them
 // when none ran).
 __device__ __forceinline__ uint32_t sorted_len(const SortJob& s) { return pass_len(s, s.npasses); }
-// Whether the first pass keeps the element of value val.
-__device__ __forceinline__ bool keep0(const SortJob& s, uint32_t val) {
-  const uint8_t a = *s.n_ptr < kPackLimit ? (uint8_t)(val >> 24) : s.aux[val];
-  return a != kNotTransfer;
-}
-// Whether pass p drops elements, and whether it keeps element j of value val.
-__device__ __forceinline__ bool drops(const SortJob& s, uint32_t p) {
-  return (p == 0 && s.drop0) || (p == 1 && s.cand != nullptr);
-}
-__device__ __forceinline__ bool keep(const SortJob& s, uint32_t p, uint32_t j, uint32_t val) {
-  return p == 0 ? keep0(s, val) : s.cand[j] != 0;
+// Bit r: pass p of job s keeps the thread's element of round r, j0 + r * step of
+// n, whose value is val[r] (used by the first pass only). The loads of all
+// rounds are issued together.
+template <int R>
+__device__ __forceinline__ uint32_t keep_mask(const SortJob& s, uint32_t p, uint32_t j0, uint32_t step, uint32_t n,
+                                              const uint32_t (&val)[R]) {
+  uint32_t mask = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) mask |= (uint32_t)(j0 + r * step < n) << r;
+  const bool packed = *s.n_ptr < kPackLimit;
+  if (p == 0 && s.drop0 && packed) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) mask &= ~((uint32_t)((val[r] >> 24) == kNotTransfer) << r);
+  } else if ((p == 0 && s.drop0) || (p == 1 && s.cand)) {
+    uint8_t a[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t j = min(j0 + r * step, n - 1);
+      a[r] = p == 0 ? s.aux[j0 + r * step < n ? val[r] : 0u] : s.cand[j];
+    }
+    const uint8_t drop = p == 0 ? kNotTransfer : 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) mask &= ~((uint32_t)(a[r] == drop) << r);
+  }
+  return mask;
 }
 constexpr uint32_t kNoWord = 0xFFFFFFFFu;
 
@@ -1339,13 +1353,10 @@ __device__ __forceinline__ bool next_tile(const JobSet& J, const SortJob* s, uin
   return (uint64_t)tile * kTile < n && tile < s->ntiles_max;
 }
 
-// The key of element j for pass p: gathered from the pass's word on the
-// first pass of that word, else carried in keys[src].
-__device__ __forceinline__ unsigned long long key_of(const SortJob& s, uint32_t p, uint32_t src, uint32_t j) {
-  if (s.pg[p]) return s.words[s.pw[p]][s.vals[src][j]];
-  return s.keys[src][j];
-}
-
+// Counts the digits of a tile. All loads of a thread are issued before any is
+// waited for (a load under its element's condition, one after another, took
+// 35 us instead of 22 for the 9.8 million elements of the trace's second pass,
+// and 13 instead of 8 for the 2 million of its third).
 __global__ __launch_bounds__(kT) void sort_hist_kernel(JobSet J, uint32_t p) {
   const SortJob* s;
   uint32_t tile, n;
@@ -1357,18 +1368,26 @@ __global__ __launch_bounds__(kT) void sort_hist_kernel(JobSet J, uint32_t p) {
   __syncthreads();
   const uint32_t src = p & 1;
   const uint32_t b = tile * kTile;
-  uint32_t d[kItems];
   const uint32_t shift = s->ps[p];
-  const bool drop = drops(*s, p);
+  const bool gather = s->pg[p] != 0;  // the keys are read from the pass's word by value, else carried
+  uint32_t val[kItems];
+  unsigned long long key[kItems];
+  if (gather || p == 0) {
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
-    const uint32_t j = b + r * kT + threadIdx.x;
-    const bool in = j < n && (!drop || keep(*s, p, j, p == 0 ? s->vals[src][j] : 0u));
-    d[r] = in ? (uint32_t)(key_of(*s, p, src, j) >> shift) & 0xFF : 256u;
+    for (int r = 0; r < kItems; ++r) val[r] = s->vals[src][min(b + r * kT + threadIdx.x, n - 1)];
   }
+  if (gather) {
+    const uint64_t* word = s->words[s->pw[p]];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) key[r] = word[val[r]];
+  } else {
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) key[r] = s->keys[src][min(b + r * kT + threadIdx.x, n - 1)];
+  }
+  const uint32_t mask = keep_mask(*s, p, b + threadIdx.x, kT, n, val);
 #pragma unroll
   for (int r = 0; r < kItems; ++r)
-    if (d[r] < 256u) atomicAdd(&h[d[r]], 1u);
+    if ((mask >> r) & 1) atomicAdd(&h[(uint32_t)(key[r] >> shift) & 0xFF], 1u);
   __syncthreads();
   s->hist[threadIdx.x * s->ntiles_max + tile] = h[threadIdx.x];
   __syncthreads();
@@ -1436,7 +1455,6 @@ __global__ __launch_bounds__(kST) void sort_scatter_kernel(JobSet J, uint32_t p)
   __shared__ uint32_t ws[4], wt[4];
   __shared__ uint32_t s_kept;       // elements of this tile the pass writes
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const bool drop = drops(*s, p);
   do {
   for (int x = 0; x < 256; x += 64) wcnt[w][x + lane] = 0;
   __syncthreads();
@@ -1463,12 +1481,7 @@ __global__ __launch_bounds__(kST) void sort_scatter_kernel(JobSet J, uint32_t p)
     }
   }
   // bit r: this lane's element of round r is written by the pass
-  uint32_t inmask = 0;
-#pragma unroll
-  for (int r = 0; r < kSRounds; ++r) {
-    const uint32_t j = wb + r * 64 + lane;
-    inmask |= (uint32_t)(j < n && (!drop || keep(*s, p, j, vl[r]))) << r;
-  }
+  const uint32_t inmask = keep_mask(*s, p, wb + lane, 64, n, vl);
 #pragma unroll
   for (int r = 0; r < kSRounds; ++r) {
     const bool in = (inmask >> r) & 1;
