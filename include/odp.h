@@ -238,11 +238,12 @@ typedef struct odp_report {
  * ODP_F_INVALID, take part in no rule, and set report.status.
  * n = 0 writes an empty report. n > 2^32 - 1 returns ODP_ERANGE.
  * Logs of at most 512 records are analysed by one workgroup in one launch and
- * need no workspace. For longer logs the allocation rules run on a side
- * stream of the workspace that is forked from `stream` and joined back before
- * the report is written, so the call remains ordered on `stream` (and
- * capturable as one unit). Capture-safe once odp_reserve covered n (always for
- * n <= 512). */
+ * need no workspace; logs of up to 4,096 records by two launches on `stream`.
+ * For longer logs (grouped by hash tables up to 262,144 records, by sorts
+ * beyond) the allocation rules run on a side stream of the workspace that is
+ * forked from `stream` and joined back before the report is written, so the
+ * call remains ordered on `stream` (and capturable as one unit). Capture-safe
+ * once odp_reserve covered n (always for n <= 512). */
 int odp_analyze_trace(const odp_event* events, size_t n, uint8_t* out_flags, odp_report* out_report,
                       odp_stream_t stream);
 

@@ -67,10 +67,10 @@ __host__ __device__ inline uint8_t unpack_ep(uint32_t a) {
 }
 static_assert(kEp == 11 && kEp * kEp <= 127, "a pair of endpoints in seven bits");
 // Counters per wavefront of the classification, scanned into the subset
-// offsets: ALLOC/DELETE, KERNEL and copy-in records, then KERNEL records per
-// device code (device + 1).
+// offsets: ALLOC/DELETE, KERNEL and listed copy-in records, then KERNEL records
+// per device code (device + 1).
 constexpr int kWaveCnt = 3 + kEp;
-// Logs of fewer than 2^24 records carry each record's endpoint code in the
+// Logs of fewer than 2^24 records carry each record's endpoint byte in the
 // top byte of its digest-sort value (the record index in the low 24 bits), so
 // the scans over the sorted order need no gather of the code by index.
 constexpr uint32_t kPackLimit = 1u << 24;
