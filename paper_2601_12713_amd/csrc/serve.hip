@@ -676,6 +676,8 @@ struct odp_server {
   odp_server_config cfg{};
   uint64_t state_bytes = 0;       // device memory of the server's state and digest workspace
   uint64_t payload_budget = 0;    // budget_bytes - state_bytes
+  uint8_t* arena = nullptr;       // device block of everything below
+  uint8_t* h_arena = nullptr;     // pinned block of the staging
   // device state
   odp_event* log = nullptr;
   uint8_t* known = nullptr;
@@ -702,32 +704,53 @@ static Table* table_at(odp_server* s, int i) {
   return t[i];
 }
 
+// One device block and one pinned block hold all of a server's arrays, and one
+// fill clears what starts at zero, instead of 22 allocations, 8 fills and as
+// many frees (2,000 requests, server created, drained and destroyed: 1,035 ->
+// 982 us).
 static int server_alloc(odp_server* s) {
   const uint64_t cap = s->cfg.max_events;
-  ODP_HIP(hipMalloc(&s->log, cap * sizeof(odp_event)));
-  ODP_HIP(hipMalloc(&s->known, (cap + 8) & ~3ull));
-  ODP_HIP(hipMalloc(&s->link, cap * 4));
-  ODP_HIP(hipMalloc(&s->kc_at, cap * 4));
-  ODP_HIP(hipMalloc(&s->kstart, (uint64_t)kDev * cap * 8));
-  ODP_HIP(hipMalloc(&s->kmaxend, (uint64_t)kDev * cap * 8));
-  for (int b = 0; b < 2; ++b) ODP_HIP(hipMalloc(&s->pend[b], cap * sizeof(Pending)));
   const uint64_t tcap = pow2_at_least(std::max<uint64_t>(1024, 2 * cap));
+  uint64_t size = 0;
+  auto place = [&](uint64_t bytes) {
+    const uint64_t at = size;
+    size += (bytes + 255) & ~255ull;
+    return at;
+  };
+  uint64_t tables[kTables], pend[2], stage[2], dig[2];
+  for (uint64_t& t : tables) t = place(tcap * sizeof(Slot));
+  const uint64_t st = place(sizeof(ServeState)), known = place((cap + 8) & ~3ull), zeroed = size;
+  const uint64_t log = place(cap * sizeof(odp_event)), link = place(cap * 4), kc_at = place(cap * 4);
+  const uint64_t kstart = place((uint64_t)kDev * cap * 8), kmaxend = place((uint64_t)kDev * cap * 8);
+  for (uint64_t& t : pend) t = place(cap * sizeof(Pending));
+  for (uint64_t& t : stage) t = place(kTickMax * kStageBytes);
+  for (uint64_t& t : dig) t = place(kTickMax * 8);
+  ODP_HIP(hipMalloc(&s->arena, size));
+  ODP_HIP(hipMemsetAsync(s->arena, 0, zeroed, s->stream));
   for (int i = 0; i < kTables; ++i) {
     Table* T = table_at(s, i);
-    ODP_HIP(hipMalloc(&T->slots, tcap * sizeof(Slot)));
-    ODP_HIP(hipMemset(T->slots, 0, tcap * sizeof(Slot)));
+    T->slots = reinterpret_cast<Slot*>(s->arena + tables[i]);
     T->mask = tcap - 1;
   }
-  ODP_HIP(hipMalloc(&s->st, sizeof(ServeState)));
-  ODP_HIP(hipMemset(s->st, 0, sizeof(ServeState)));
-  ODP_HIP(hipMemset(s->known, 0, (cap + 8) & ~3ull));
+  s->st = reinterpret_cast<ServeState*>(s->arena + st);
+  s->known = s->arena + known;
+  s->log = reinterpret_cast<odp_event*>(s->arena + log);
+  s->link = reinterpret_cast<uint32_t*>(s->arena + link);
+  s->kc_at = reinterpret_cast<uint32_t*>(s->arena + kc_at);
+  s->kstart = reinterpret_cast<uint64_t*>(s->arena + kstart);
+  s->kmaxend = reinterpret_cast<uint64_t*>(s->arena + kmaxend);
+  constexpr uint64_t kHostStage = (kTickMax * kStageBytes + 255) & ~255ull;
+  ODP_HIP(hipHostMalloc(reinterpret_cast<void**>(&s->h_arena), 2 * kHostStage, hipHostMallocDefault));
   for (int b = 0; b < 2; ++b) {
-    ODP_HIP(hipHostMalloc(reinterpret_cast<void**>(&s->h_stage[b]), kTickMax * kStageBytes, hipHostMallocDefault));
-    ODP_HIP(hipMalloc(&s->d_stage[b], kTickMax * kStageBytes));
-    ODP_HIP(hipMalloc(&s->d_dig[b], kTickMax * 8));
+    s->pend[b] = reinterpret_cast<Pending*>(s->arena + pend[b]);
+    s->d_stage[b] = s->arena + stage[b];
+    s->d_dig[b] = reinterpret_cast<uint64_t*>(s->arena + dig[b]);
+    s->h_stage[b] = s->h_arena + b * kHostStage;
     ODP_HIP(hipEventCreateWithFlags(&s->digested[b], hipEventDisableTiming));
     ODP_HIP(hipEventCreateWithFlags(&s->done[b], hipEventDisableTiming));
   }
+  // the first tick may run on either stream
+  ODP_HIP(hipStreamSynchronize(s->stream));
   return ODP_OK;
 }
 
@@ -738,19 +761,9 @@ static void server_free(odp_server* s) {
     // the digest and analysis workspace the library keeps for this stream
     workspace_drop(s->device, q);
   }
-  (void)hipFree(s->log);
-  (void)hipFree(s->known);
-  (void)hipFree(s->link);
-  (void)hipFree(s->kc_at);
-  (void)hipFree(s->kstart);
-  (void)hipFree(s->kmaxend);
-  for (int b = 0; b < 2; ++b) (void)hipFree(s->pend[b]);
-  for (int i = 0; i < kTables; ++i) (void)hipFree(table_at(s, i)->slots);
-  (void)hipFree(s->st);
+  (void)hipFree(s->arena);
+  (void)hipHostFree(s->h_arena);
   for (int b = 0; b < 2; ++b) {
-    (void)hipHostFree(s->h_stage[b]);
-    (void)hipFree(s->d_stage[b]);
-    (void)hipFree(s->d_dig[b]);
     if (s->digested[b]) (void)hipEventDestroy(s->digested[b]);
     if (s->done[b]) (void)hipEventDestroy(s->done[b]);
   }
@@ -986,9 +999,11 @@ extern "C" int odp_server_drain(odp_server* s, uint8_t* out_known, uint8_t* out_
   if (!s) return set_error(ODP_EINVAL, "odp_server_drain: null server");
   ODP_HIP(hipStreamSynchronize(s->dstream));
   ODP_HIP(hipStreamSynchronize(s->stream));
-  ServeState hs;
-  ODP_HIP(hipMemcpy(&hs, s->st, sizeof(hs), hipMemcpyDeviceToHost));
-  if (hs.overflow) return set_error(ODP_ECAPACITY, "odp_server_drain: a state table ran full");
+  // (both streams are idle, so the pinned staging is free)
+  ServeState* hs = reinterpret_cast<ServeState*>(s->h_stage[0]);
+  ODP_HIP(hipMemcpyAsync(hs, s->st, sizeof(*hs), hipMemcpyDeviceToHost, s->stream));
+  ODP_HIP(hipStreamSynchronize(s->stream));
+  if (hs->overflow) return set_error(ODP_ECAPACITY, "odp_server_drain: a state table ran full");
   const uint64_t n = s->n_logged;
   if (out_known && n) ODP_HIP(hipMemcpyAsync(out_known, s->known, n, hipMemcpyDeviceToDevice, s->stream));
   if (out_flags || out_report) {
