@@ -367,9 +367,10 @@ __device__ __forceinline__ uint64_t hash_wave_rows(const RowDesc* rows, uint8_t*
   } else {
 #pragma unroll 1
     for (uint32_t s0 = 0; s0 < nstripes; s0 += 8) {
+      // (no load under a branch: past the row's last stripe it is read again)
       uint64_t wv[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) wv[j] = s0 + j < nstripes ? load64_any(hrow.base + (s0 + j) * 32 + a * 8) : 0ull;
+      for (int j = 0; j < 8; ++j) wv[j] = load64_any(hrow.base + min(s0 + j, nstripes - 1) * 32 + a * 8);
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         if (s0 + j < nstripes) acc = xx_round(acc, wv[j]);
