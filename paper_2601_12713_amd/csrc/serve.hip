@@ -999,10 +999,12 @@ extern "C" int odp_server_drain(odp_server* s, uint8_t* out_known, uint8_t* out_
   if (!s) return set_error(ODP_EINVAL, "odp_server_drain: null server");
   ODP_HIP(hipStreamSynchronize(s->dstream));
   ODP_HIP(hipStreamSynchronize(s->stream));
-  // (both streams are idle, so the pinned staging is free)
+  // A blocking copy on the default stream: it waits for what the caller has
+  // enqueued there, so an output array that is still being cleared or filled
+  // there is not written over after the results. (The server's own streams do
+  // not wait for the default one; both are idle, so the pinned staging is free.)
   ServeState* hs = reinterpret_cast<ServeState*>(s->h_stage[0]);
-  ODP_HIP(hipMemcpyAsync(hs, s->st, sizeof(*hs), hipMemcpyDeviceToHost, s->stream));
-  ODP_HIP(hipStreamSynchronize(s->stream));
+  ODP_HIP(hipMemcpy(hs, s->st, sizeof(*hs), hipMemcpyDeviceToHost));
   if (hs->overflow) return set_error(ODP_ECAPACITY, "odp_server_drain: a state table ran full");
   const uint64_t n = s->n_logged;
   if (out_known && n) ODP_HIP(hipMemcpyAsync(out_known, s->known, n, hipMemcpyDeviceToDevice, s->stream));

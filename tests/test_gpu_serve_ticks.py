@@ -30,3 +30,28 @@ def test_tick_lengths(odp, max_tick, kind):
     compare(fl, rep, fo, ro)
     check_known(known, fo, ev)
     assert stats["max_tick"] <= max_tick
+
+
+def test_drain_waits_for_the_default_stream(odp):
+    """Output arrays that the default stream is still filling when the drain is
+    called hold the drain's results afterwards, not the fill."""
+    n = 400
+    ev = random_log(5, n, devices=2, digests=50, places=20)
+    srv = odp.Server(max_events=n, budget_bytes=64 << 20)
+    zero = np.zeros(n, dtype=np.uint64)
+    srv.run(ev, zero, zero, zero)
+    known = torch.empty(n, dtype=torch.uint8, device="cuda")
+    flags = torch.empty(n, dtype=torch.uint8, device="cuda")
+    rep = torch.empty(odp.REPORT_BYTES, dtype=torch.uint8, device="cuda")
+    a = torch.ones((4096, 4096), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(20):  # some milliseconds of work in front of the fills
+        a = a @ a
+    for out in (known, flags, rep):
+        out.fill_(0xEE)
+    assert odp.load().odp_server_drain(srv._h, *(t.data_ptr() for t in (known, flags, rep))) == odp.ODP_OK
+    torch.cuda.synchronize()
+    srv.close()
+    fo, ro = oracle.analyze(ev)
+    compare(flags.cpu().numpy(), odp.report_to_dict(rep.cpu().numpy()), fo, ro)
+    check_known(known.cpu().numpy(), fo, ev)
