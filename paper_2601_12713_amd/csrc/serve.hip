@@ -41,30 +41,16 @@
 #include <vector>
 
 #include "internal.h"
+#include "serve_layout.h"
 
 namespace odp {
 namespace {
 
-constexpr int kTickMax = 1024;     // records per tick (one workgroup)
 constexpr uint32_t kPerBufferTick = 3;  // ticks of at most this many requests digest per buffer
-// staged bytes per request: the record, the payload pointer and size, a flag
-constexpr size_t kStageBytes = sizeof(odp_event) + 8 + 8 + 1;
 constexpr uint32_t kEmpty = 0;
 // Set in every second key word: an unwritten (zeroed) slot never matches.
 constexpr uint64_t kMark = 1ull << 63;
-constexpr int kDev = ODP_MAX_DEVICE + 2;  // device codes: host (-1) .. ODP_MAX_DEVICE, shifted by one
 constexpr uint64_t kNone64 = ~0ull;
-
-// Open-addressing table entry; keys are three words, values two. state is
-// kEmpty or the tag of the tick that claimed the slot (never kEmpty), so a
-// thread tells a slot claimed earlier (keys complete and visible) from one
-// another thread of its own tick is still filling in.
-struct Slot {
-  uint32_t state;
-  uint32_t v0;
-  uint64_t k0, k1, k2;
-  uint64_t v1;
-};
 
 struct Table {
   Slot* slots;
@@ -119,29 +105,6 @@ __device__ Slot* tupsert(const Table& T, uint64_t k0, uint64_t k1, uint64_t k2, 
   *inserted = false;
   return nullptr;  // table full: reported through the server status
 }
-
-// A window waiting for its deadline (UA: an ALLOC and its DELETE; UT: a copy
-// and the next copy of its place). The kernels on `dev` that meet
-// [lo, deadline] are those among the first `kc` (logged before the window
-// opened) whose end reaches lo, and those logged later that start by the
-// deadline.
-struct Pending {
-  uint64_t lo, deadline;
-  uint32_t id;    // the record that gets the flag
-  uint32_t kc;    // kernels on dev logged before it
-  uint32_t dev;   // device code (device + 1)
-  uint32_t flag;  // ODP_F_UA or ODP_F_UT
-};
-
-struct ServeState {
-  uint64_t last_t_start;  // t_start of the last logged record
-  uint64_t n_logged;
-  uint32_t overflow;      // a table ran full
-  uint32_t any_invalid;   // some record was rejected: UA/UT wait for the drain
-  uint32_t kcount[kDev];  // valid KERNEL records per device code
-  uint32_t pend_n;        // windows waiting in pend[pend_cur]
-  uint32_t pend_cur;
-};
 
 struct TickArgs {
   const odp_event* tick_ev;     // m records
@@ -645,23 +608,8 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
   }
 }
 
-uint64_t pow2_at_least(uint64_t x) {
-  uint64_t p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
 double now_s() {
   return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
-}
-
-constexpr int kTables = 6;
-
-// Device bytes of a server's state for a log of `cap` records.
-uint64_t state_bytes_for(uint64_t cap) {
-  const uint64_t tcap = pow2_at_least(std::max<uint64_t>(1024, 2 * cap));
-  return cap * (sizeof(odp_event) + 4 + 4) + ((cap + 8) & ~3ull) + 2ull * kDev * cap * 8 + 2 * cap * sizeof(Pending) +
-         kTables * tcap * sizeof(Slot) + sizeof(ServeState) + 2ull * kTickMax * (kStageBytes + 8);
 }
 
 }  // namespace
@@ -709,42 +657,27 @@ static Table* table_at(odp_server* s, int i) {
 // many frees (2,000 requests, server created, drained and destroyed: 1,035 ->
 // 982 us).
 static int server_alloc(odp_server* s) {
-  const uint64_t cap = s->cfg.max_events;
-  const uint64_t tcap = pow2_at_least(std::max<uint64_t>(1024, 2 * cap));
-  uint64_t size = 0;
-  auto place = [&](uint64_t bytes) {
-    const uint64_t at = size;
-    size += (bytes + 255) & ~255ull;
-    return at;
-  };
-  uint64_t tables[kTables], pend[2], stage[2], dig[2];
-  for (uint64_t& t : tables) t = place(tcap * sizeof(Slot));
-  const uint64_t st = place(sizeof(ServeState)), known = place((cap + 8) & ~3ull), zeroed = size;
-  const uint64_t log = place(cap * sizeof(odp_event)), link = place(cap * 4), kc_at = place(cap * 4);
-  const uint64_t kstart = place((uint64_t)kDev * cap * 8), kmaxend = place((uint64_t)kDev * cap * 8);
-  for (uint64_t& t : pend) t = place(cap * sizeof(Pending));
-  for (uint64_t& t : stage) t = place(kTickMax * kStageBytes);
-  for (uint64_t& t : dig) t = place(kTickMax * 8);
-  ODP_HIP(hipMalloc(&s->arena, size));
-  ODP_HIP(hipMemsetAsync(s->arena, 0, zeroed, s->stream));
+  const ServerLayout L = server_layout(s->cfg.max_events);
+  ODP_HIP(hipMalloc(&s->arena, L.bytes));
+  ODP_HIP(hipMemsetAsync(s->arena + L.zeroed, 0, L.bytes - L.zeroed, s->stream));
   for (int i = 0; i < kTables; ++i) {
     Table* T = table_at(s, i);
-    T->slots = reinterpret_cast<Slot*>(s->arena + tables[i]);
-    T->mask = tcap - 1;
+    T->slots = reinterpret_cast<Slot*>(s->arena + L.tables[i]);
+    T->mask = L.table_slots - 1;
   }
-  s->st = reinterpret_cast<ServeState*>(s->arena + st);
-  s->known = s->arena + known;
-  s->log = reinterpret_cast<odp_event*>(s->arena + log);
-  s->link = reinterpret_cast<uint32_t*>(s->arena + link);
-  s->kc_at = reinterpret_cast<uint32_t*>(s->arena + kc_at);
-  s->kstart = reinterpret_cast<uint64_t*>(s->arena + kstart);
-  s->kmaxend = reinterpret_cast<uint64_t*>(s->arena + kmaxend);
-  constexpr uint64_t kHostStage = (kTickMax * kStageBytes + 255) & ~255ull;
+  s->st = reinterpret_cast<ServeState*>(s->arena + L.st);
+  s->known = s->arena + L.known;
+  s->log = reinterpret_cast<odp_event*>(s->arena + L.log);
+  s->link = reinterpret_cast<uint32_t*>(s->arena + L.link);
+  s->kc_at = reinterpret_cast<uint32_t*>(s->arena + L.kc_at);
+  s->kstart = reinterpret_cast<uint64_t*>(s->arena + L.kstart);
+  s->kmaxend = reinterpret_cast<uint64_t*>(s->arena + L.kmaxend);
+  constexpr uint64_t kHostStage = kTickMax * kStageBytes;
   ODP_HIP(hipHostMalloc(reinterpret_cast<void**>(&s->h_arena), 2 * kHostStage, hipHostMallocDefault));
   for (int b = 0; b < 2; ++b) {
-    s->pend[b] = reinterpret_cast<Pending*>(s->arena + pend[b]);
-    s->d_stage[b] = s->arena + stage[b];
-    s->d_dig[b] = reinterpret_cast<uint64_t*>(s->arena + dig[b]);
+    s->pend[b] = reinterpret_cast<Pending*>(s->arena + L.pend[b]);
+    s->d_stage[b] = s->arena + L.stage[b];
+    s->d_dig[b] = reinterpret_cast<uint64_t*>(s->arena + L.dig[b]);
     s->h_stage[b] = s->h_arena + b * kHostStage;
     ODP_HIP(hipEventCreateWithFlags(&s->digested[b], hipEventDisableTiming));
     ODP_HIP(hipEventCreateWithFlags(&s->done[b], hipEventDisableTiming));
@@ -783,7 +716,7 @@ extern "C" int odp_server_create(const odp_server_config* cfg, odp_server** out)
   // The budget covers the server's state, its digest workspace and the
   // payload bytes of the requests in flight. The workspace is sized for
   // payload batches of at most the whole budget, so it is known up front.
-  const uint64_t fixed = state_bytes_for(cfg->max_events) +
+  const uint64_t fixed = server_layout(cfg->max_events).bytes +
                          digest_workspace_bytes(kTickMax, cfg->budget_bytes + (uint64_t)kTickMax * kNodeBytes) +
                          digest_plain_workspace_bytes(cfg->budget_bytes);
   if (cfg->budget_bytes <= fixed)
