@@ -186,3 +186,13 @@ def test_unused_transfers_by_span(odp, kind):
     if kind == "rejected":
         ev["t_end"][n // 2] = ev["t_start"][n // 2] - np.uint64(1)
     check(odp, ev)
+
+
+@pytest.mark.parametrize("n", [4097, 4097 + 63, 20000])
+@pytest.mark.parametrize("hot", [1, 2, 9, 300])
+def test_table_logs_of_hot_digests(odp, n, hot):
+    """A wavefront's lanes want the same few empty slots at once, beside fresh digests."""
+    ev = random_log(n + hot, n, digests=n, kernels=0.02, allocs=0.05)
+    k = np.arange(n, dtype=np.uint64)
+    ev["digest"] = np.where(k % 7 == 3, ev["digest"], (k % np.uint64(hot)) * np.uint64(0xC2B2AE3D27D4EB4F))
+    check(odp, ev)
