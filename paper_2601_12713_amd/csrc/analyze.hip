@@ -3387,9 +3387,8 @@ size_t mid_views(MidView& m, char* base, size_t cap) {
     t->owner = carve<uint32_t>(p, slots);
     t->bits = carve<unsigned long long>(p, slots * kChunkWords);
     t->ckey = carve<uint32_t>(p, slots);
-    t->cfirst = carve<uint32_t>(p, slots);
     t->clast = carve<uint32_t>(p, slots);
-    t->gid = carve<uint32_t>(p, c + 8) + 4;
+    t->link = carve<uint32_t>(p, c);
   }
   const size_t nchunk = waves / kScanChunk + 1;
   m.wscan.cnt = carve<uint32_t>(p, waves * kWaveCnt);

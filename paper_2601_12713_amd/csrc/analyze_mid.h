@@ -17,8 +17,8 @@
 //             group aggregates, DD/RT (carries looked up, not scanned)
 //   other path: subsets; unused transfers and the groups of ALLOC/DELETE
 //             records; pairing and RA table; RA/UA. The nearest record of a
-//             group comes from the group's table entries per chunk of 2,048
-//             records (NearTable) instead of a sort
+//             group comes from its chunk of the list, grouped in LDS, and the
+//             group's table entries per chunk (NearTable) instead of a sort
 //   finish    all sums into the report
 #pragma once
 
@@ -27,28 +27,45 @@ constexpr int kMidT = 1024, kMidRounds = 2;
 constexpr uint32_t kMidTile = kMidT * kMidRounds;           // records (elements) per workgroup
 constexpr uint32_t kMidWave = 64 * kMidRounds;              // ... per wavefront
 constexpr uint32_t kMidDigits = 1024;                       // at most, per pass
-constexpr uint32_t kChunkBits = 11;                         // positions per chunk of a NearTable: 2,048
-constexpr uint32_t kChunkWords = (kMidMax >> kChunkBits) / 64;
-static_assert((kMidMax >> kChunkBits) % 64 == 0 && kChunkWords == 2, "a chunk is one bit of two words");
+constexpr uint32_t kChunkWords = 4;                         // 64 chunks of a NearTable each
+constexpr uint32_t kChunkMax = 1024;                        // positions per chunk, at most
+static_assert(kChunkWords * 64 * kChunkMax >= kMidMax, "a chunk is one bit of the words");
 
-// Groups of equal keys over a list of positions (0 .. m - 1, m <= kMidMax),
-// and the nearest earlier or later position of a group. A position's group is
-// the slot of its key in an open-addressing table. Per group, a bit for each
-// chunk of positions that holds it; per (group, chunk), the first and the last
-// such position. Within a chunk the neighbour is searched from the position
-// itself, only when the chunk's first (last) says that there is one.
+// Groups of equal keys over a list of positions (0 .. m - 1, m <= kMidMax), and
+// the nearest earlier position of a group (REV: of the list read backwards, so
+// the nearest later one). A workgroup enters a chunk of the list at a time
+// (near_enter): it groups the chunk's positions in LDS, which gives each one's
+// neighbour inside the chunk, and then touches the tables once per group and
+// chunk only: a position's group is the slot of its key in an open-addressing
+// table; per group, a bit for each chunk that holds it; per (group, chunk), the
+// last such position. A position whose neighbour lies in an earlier chunk finds
+// it by those (near_prev). No step depends on how far apart a group's
+// positions are or how many share it. (Entering position by position, with a
+// search through the list inside a chunk of 2,048, took 411 us for 262,144
+// ALLOC/DELETE records of 10 addresses, all updates going to few words, and
+// 454 us when each array is freed 2,000 records after its allocation; by
+// chunks 137 and 165 us. 100,000 records of the trace, few of them such: 111
+// and 107 us.)
 struct NearTable {
   uint32_t* owner;           // group table (below)
   unsigned long long* bits;  // [slots][kChunkWords]
-  uint32_t *ckey, *cfirst, *clast;  // 0 empty, else (group << 7 | chunk) + 1; complement of the first; last + 1
-  uint32_t* gid;             // per position; four words of padding before and after
+  uint32_t *ckey, *clast;    // 0 empty, else (group << 8 | chunk) + 1; the last position
+  uint32_t* link;            // per position: the neighbour in its chunk, else kFar | group
 };
+constexpr uint32_t kFar = 0x80000000u;
+// Positions per chunk: the list in at most kChunkWords * 64 of them, and not
+// fewer than a workgroup has threads.
+__device__ __forceinline__ uint32_t near_chunk_bits(uint32_t m) {
+  uint32_t b = 8;
+  while (m > (kChunkWords * 64) << b) ++b;
+  return b;
+}
 
 // (grid-stride over the workgroups of the launch)
 __device__ __forceinline__ void near_clear(const NearTable& T, uint32_t m, uint32_t start, uint32_t step) {
   const uint32_t slots = pair_table_mask(m) + 1;
   for (uint32_t i = start; i < slots; i += step) {
-    T.owner[i] = T.ckey[i] = T.cfirst[i] = T.clast[i] = 0;
+    T.owner[i] = T.ckey[i] = 0;
 #pragma unroll
     for (uint32_t w = 0; w < kChunkWords; ++w) T.bits[(size_t)i * kChunkWords + w] = 0;
   }
@@ -167,7 +184,7 @@ __device__ __forceinline__ uint32_t near_group(const NearTable& T, uint32_t mask
 }
 
 __device__ __forceinline__ uint32_t near_slot(const NearTable& T, uint32_t mask, uint32_t g, uint32_t chunk, bool insert) {
-  const uint32_t key = (g << 7 | chunk) + 1;
+  const uint32_t key = (g << 8 | chunk) + 1;
   uint32_t h = near_hash(key, 0) & mask;
   for (;;) {
     uint32_t o = T.ckey[h];
@@ -178,64 +195,135 @@ __device__ __forceinline__ uint32_t near_slot(const NearTable& T, uint32_t mask,
   return h;
 }
 
-// Enters 64 consecutive positions q (one per lane, from a multiple of 64;
-// lanes with in == false take no part). A position followed (preceded) by its
-// group within four lanes leaves the last (first) to that one: hot groups would
-// otherwise send every lane's update to one word.
-__device__ __forceinline__ void near_insert(const NearTable& T, uint32_t m, uint32_t q, bool in, const uint64_t* a,
-                                            const uint64_t* b) {
-  const uint32_t mask = pair_table_mask(m), lane = threadIdx.x & 63;
-  const uint32_t gq = near_group(T, mask, q, in, a, b), g = in ? gq : kNone;
-  if (in) T.gid[q] = g;
-  bool first = in, last = in;
+struct NearLds {
+  uint64_t a[kChunkMax];
+  alignas(8) uint16_t slot[kChunkMax];  // per position: its key's slot below, kNoGroup16 past the list
+  uint32_t owner[2 * kChunkMax];    // a position of the key; then the key's group
+  uint32_t rounds[2 * kChunkMax];   // which stretches of 64 positions hold the key
+  uint8_t b[kChunkMax];
+};
+constexpr uint32_t kNoGroup16 = 0xFFFF;
+static_assert(kChunkMax <= 32 * 64, "a bit per stretch of 64");
+
+// Enters the chunks first, first + step, ... of the list, by a workgroup of kT
+// threads: keys a (64 bits) and b (below 256) of every position. In LDS an exact
+// hash table of the chunk's keys; ballots over its slot numbers give the
+// neighbours inside 64 positions, a bit per stretch of 64 the others. Bound by
+// the latency of its LDS and table accesses.
+template <bool REV>
+__device__ void near_enter(const NearTable& T, uint32_t m, const uint64_t* a, const uint64_t* b, NearLds& L, uint32_t first,
+                           uint32_t step) {
+  constexpr uint32_t kFree = 0xFFFFFFFFu, kSlots = 2 * kChunkMax;
+  constexpr int kR = kChunkMax / kT;
+  const uint32_t mask = pair_table_mask(m), cb = near_chunk_bits(m), size = 1u << cb;
+  const uint32_t t = threadIdx.x, lane = t & 63;
+  const uint64_t lt = lanemask_lt();
+  uint16_t* const slot = L.slot;
+  for (uint32_t c = first; (uint64_t)c << cb < m; c += step) {
+    const uint32_t base = c << cb;
+    __syncthreads();
+    for (uint32_t x = t; x < kSlots; x += kT) {
+      L.owner[x] = kFree;
+      L.rounds[x] = 0;
+    }
+    uint64_t ka[kR], kb[kR];
 #pragma unroll
-  for (int o = 1; o <= 4; ++o) {
-    const uint32_t up = (uint32_t)__shfl_up((int)g, o, 64), dn = (uint32_t)__shfl_down((int)g, o, 64);
-    if ((int)lane >= o && up == g) first = false;
-    if ((int)lane + o < 64 && dn == g) last = false;
+    for (int r = 0; r < kR; ++r) {
+      const uint32_t i = r * kT + t, p = base + i;
+      ka[r] = kb[r] = 0;
+      if (i < size && p < m) {
+        ka[r] = a[REV ? m - 1 - p : p];
+        kb[r] = b[REV ? m - 1 - p : p];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      L.a[r * kT + t] = ka[r];
+      L.b[r * kT + t] = (uint8_t)kb[r];
+    }
+    __syncthreads();
+    for (uint32_t i = t; i < size; i += kT) {
+      uint32_t s = kNoGroup16;
+      if (base + i < m) {
+        const uint64_t x = L.a[i];
+        const uint8_t y = L.b[i];
+        s = (near_hash(x, y) >> 8) % kSlots;
+        for (;;) {
+          uint32_t o = L.owner[s];
+          if (o == kFree) o = atomicCAS(&L.owner[s], kFree, i);
+          if (o == kFree || (L.a[o] == x && L.b[o] == y)) break;
+          s = (s + 1) % kSlots;
+        }
+      }
+      slot[i] = (uint16_t)s;
+    }
+    __syncthreads();
+    // bit r: of this thread's position r * kT + t, whether it owns its slot and
+    // whether it is the key's first or last in its 64 positions
+    uint32_t owns = 0, firsts = 0, lasts = 0;
+    for (uint32_t i = t, r = 0; i < size; i += kT, ++r) {
+      const uint32_t s = slot[i], in = s != kNoGroup16;
+      uint64_t peers = __ballot(in);
+#pragma unroll
+      for (int k = 0; k < 11; ++k) {
+        const bool bit = (s >> k) & 1;
+        const uint64_t x = __ballot(bit);
+        peers &= bit ? x : ~x;
+      }
+      if (!in) continue;
+      if (peers & lt) {
+        T.link[base + i] = base + i - lane + 63 - (uint32_t)__builtin_clzll(peers & lt);
+      } else {
+        firsts |= 1u << r;
+        atomicOr(&L.rounds[s], 1u << (i >> 6));
+      }
+      if ((peers & ~lt) == 1ull << lane) lasts |= 1u << r;
+      if (L.owner[s] == i) owns |= 1u << r;
+    }
+    __syncthreads();
+    for (uint32_t i = t, r = 0; i < size; i += kT, ++r) {
+      const bool own = (owns >> r) & 1;
+      const uint32_t p = base + i, g = near_group(T, mask, REV ? m - 1 - p : p, own, a, b);
+      if (own) L.owner[slot[i]] = g;
+    }
+    __syncthreads();
+    for (uint32_t i = t, r = 0; i < size; i += kT, ++r) {
+      if (!(((firsts | lasts) >> r) & 1)) continue;
+      const uint32_t s = slot[i], x = i >> 6, rounds = L.rounds[s], g = L.owner[s];
+      if ((firsts >> r) & 1) {
+        const uint32_t earlier = rounds & ((1u << x) - 1);
+        uint32_t v = kFar | g;
+        if (earlier) {  // the last of them in that stretch, four at a time
+          const uint32_t y = 31 - (uint32_t)__builtin_clz(earlier);
+          uint32_t found = kFree;
+          for (uint32_t u = y * 16 + 16; found == kFree;) {
+            uint64_t four;
+            __builtin_memcpy(&four, slot + 4 * --u, 8);
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+              if (((four >> (16 * k)) & 0xFFFF) == s) found = u * 4 + k;
+          }
+          v = base + found;
+        }
+        T.link[base + i] = v;
+      }
+      if (((lasts >> r) & 1) && rounds >> x == 1) {  // its last in the chunk
+        T.clast[near_slot(T, mask, g, c, true)] = base + i;
+        atomicOr(T.bits + (size_t)g * kChunkWords + (c >> 6), 1ull << (c & 63));
+      }
+    }
   }
-  if (!(first || last)) return;
-  const uint32_t c = q >> kChunkBits;
-  unsigned long long* w = T.bits + (size_t)g * kChunkWords + (c >> 6);
-  if (!((*w >> (c & 63)) & 1)) atomicOr(w, 1ull << (c & 63));
-  const uint32_t h = near_slot(T, mask, g, c, true);
-  if (first && T.cfirst[h] < ~q) atomicMax(T.cfirst + h, ~q);
-  if (last && T.clast[h] < q + 1) atomicMax(T.clast + h, q + 1);
 }
 
-// The nearest earlier (later) position of q's group, or kNone.
-__device__ __forceinline__ uint32_t near_prev(const NearTable& T, uint32_t mask, uint32_t q) {
-  const uint32_t g = T.gid[q], c = q >> kChunkBits;
-  if (~T.cfirst[near_slot(T, mask, g, c, false)] < q) {
-    // four at a time (the list is padded by four in front)
-    for (const uint32_t* p = T.gid + q;; p -= 4) {
-      const uint32_t x[4] = {p[-1], p[-2], p[-3], p[-4]};
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (x[k] == g) return (uint32_t)(p - T.gid) - 1 - k;
-    }
-  }
+// The nearest earlier position of p's group, or kNone. (A launch after near_enter's.)
+__device__ __forceinline__ uint32_t near_prev(const NearTable& T, uint32_t m, uint32_t p) {
+  const uint32_t v = T.link[p];
+  if (!(v & kFar)) return v;
+  const uint32_t g = v & ~kFar, c = p >> near_chunk_bits(m);
   for (int w = (int)(c >> 6); w >= 0; --w) {
-    unsigned long long b = T.bits[(size_t)g * kChunkWords + w];
-    if (w == (int)(c >> 6)) b &= (1ull << (c & 63)) - 1;
-    if (b) return T.clast[near_slot(T, mask, g, (uint32_t)w * 64 + 63 - (uint32_t)__builtin_clzll(b), false)] - 1;
-  }
-  return kNone;
-}
-__device__ __forceinline__ uint32_t near_next(const NearTable& T, uint32_t mask, uint32_t q) {
-  const uint32_t g = T.gid[q], c = q >> kChunkBits;
-  if (T.clast[near_slot(T, mask, g, c, false)] - 1 > q) {
-    for (const uint32_t* p = T.gid + q;; p += 4) {  // (and behind)
-      const uint32_t x[4] = {p[1], p[2], p[3], p[4]};
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (x[k] == g) return (uint32_t)(p - T.gid) + 1 + k;
-    }
-  }
-  for (uint32_t w = c >> 6; w < kChunkWords; ++w) {
-    unsigned long long b = T.bits[(size_t)g * kChunkWords + w];
-    if (w == c >> 6) b &= (c & 63) == 63 ? 0ull : ~0ull << ((c & 63) + 1);
-    if (b) return ~T.cfirst[near_slot(T, mask, g, w * 64 + (uint32_t)__builtin_ctzll(b), false)];
+    unsigned long long x = T.bits[(size_t)g * kChunkWords + w];
+    if (w == (int)(c >> 6)) x &= (1ull << (c & 63)) - 1;
+    if (x) return T.clast[near_slot(T, pair_table_mask(m), g, (uint32_t)w * 64 + 63 - (uint32_t)__builtin_clzll(x), false)];
   }
   return kNone;
 }
@@ -579,18 +667,25 @@ __global__ __launch_bounds__(kT) void mid_subset_kernel(MidSide A) {
 // copies then (with 64 copies ahead, 200,000 records on three devices did: the
 // table's insertion and lookups took 340 us).
 constexpr uint32_t kMidWindow = 1024;
-__device__ void mid_ut_scan(const MidSide& A, uint32_t block, uint32_t nblocks) {
+constexpr uint32_t kMidStage = kT + kMidWindow;
+struct UtLds {
+  uint32_t ix[kMidStage], h[kMidStage + 8];  // (read eight at a time)
+};
+union LinkLds {
+  UtLds ut;
+  NearLds near;
+};
+__device__ void mid_ut_scan(const MidSide& A, UtLds& L, uint32_t block, uint32_t nblocks) {
   const UtArgs& U = A.U;
   const uint32_t n = *U.n_ut;
   if (U.ctl->first_bad != kNone) {
     if (n && block == 0 && threadIdx.x == 0) U.ctl->ut_need_sort = 1;
     return;
   }
-  constexpr uint32_t kStage = kT + kMidWindow;
-  __shared__ uint32_t s_ix[kStage], s_h[kStage + 8];  // (read eight at a time)
+  uint32_t *const s_ix = L.ix, *const s_h = L.h;
   for (uint32_t b0 = block * kT; b0 < n; b0 += nblocks * kT) {
     // s_*[x] holds copy-in b0 + 1 + x (index kNone past the last)
-    for (uint32_t x = threadIdx.x; x < kStage; x += kT) {
+    for (uint32_t x = threadIdx.x; x < kMidStage; x += kT) {
       const uint32_t r = b0 + 1 + x;
       s_ix[x] = r < n ? U.ut_idx[r] : kNone;
       s_h[x] = r < n ? A.S.ut_vals[r] : 0u;
@@ -641,14 +736,13 @@ __device__ void mid_ut_scan(const MidSide& A, uint32_t block, uint32_t nblocks) 
 
 // Half of the workgroups each: both are chains of memory round trips.
 __global__ __launch_bounds__(kT) void mid_link_kernel(MidSide A) {
+  __shared__ LinkLds L;
   const uint32_t half = gridDim.x / 2;
   if (blockIdx.x >= half) {
-    mid_ut_scan(A, blockIdx.x - half, half);
+    mid_ut_scan(A, L.ut, blockIdx.x - half, half);
     return;
   }
-  const uint32_t m = A.ctl->n_ad, lane = threadIdx.x & 63;
-  for (uint32_t b = (blockIdx.x * kT + threadIdx.x) / 64 * 64; b < m; b += half * kT)
-    near_insert(A.M.ad, m, b + lane, b + lane < m, A.S.ad_w_addr, A.S.ad_w_dev);
+  near_enter<false>(A.M.ad, A.ctl->n_ad, A.S.ad_w_addr, A.S.ad_w_dev, L.near, blockIdx.x, half);
 }
 
 // Inserts the paired ALLOC at position k into the RA table.
@@ -674,10 +768,10 @@ __device__ __forceinline__ void mid_ra_insert(const MidSide& A, uint32_t tmask, 
 // extremes of the kernel lists.
 __global__ __launch_bounds__(kT) void mid_pair_kernel(MidSide A) {
   const AnaCtl* c = A.ctl;
-  const uint32_t m = c->n_ad, mask = pair_table_mask(m), tmask = pair_table_mask(m / 2);
+  const uint32_t m = c->n_ad, tmask = pair_table_mask(m / 2);
   for (uint32_t q = blockIdx.x * kT + threadIdx.x; q < m; q += gridDim.x * kT) {
     if (A.S.ad_op[q] != ODP_DELETE) continue;
-    const uint32_t p = near_prev(A.M.ad, mask, q);
+    const uint32_t p = near_prev(A.M.ad, m, q);
     if (p == kNone || A.S.ad_op[p] != ODP_ALLOC) continue;
     A.S.ad_alloc_partner[p] = q;
     A.flags[A.S.ad_idx[q]] = ODP_F_PAIRED;
@@ -685,9 +779,8 @@ __global__ __launch_bounds__(kT) void mid_pair_kernel(MidSide A) {
   }
   const uint32_t lane = threadIdx.x & 63;
   if (c->ut_need_sort) {
-    const uint32_t u = c->n_ut;
-    for (uint32_t b = (blockIdx.x * kT + threadIdx.x) / 64 * 64; b < u; b += gridDim.x * kT)
-      near_insert(A.M.ut, u, b + lane, b + lane < u, A.S.ut_w_addr, A.S.ut_w_code);
+    __shared__ NearLds L;
+    near_enter<true>(A.M.ut, c->n_ut, A.S.ut_w_addr, A.S.ut_w_code, L, blockIdx.x, gridDim.x);
   }
   if (c->first_bad != kNone) {
     // a wavefront per 4,096 kernels
@@ -793,10 +886,11 @@ __global__ __launch_bounds__(kT) void mid_ra_ua_kernel(MidSide A) {
     A.flags[ai] = f;
   }
   if (ctl->ut_need_sort) {
-    const uint32_t n = ctl->n_ut, mask = pair_table_mask(n);
+    const uint32_t n = ctl->n_ut;
     for (uint32_t q = blockIdx.x * kT + threadIdx.x; q < n; q += gridDim.x * kT) {
       if (chrono && A.U.ut_hit[q] != 2) continue;
-      const uint32_t dev = (uint32_t)(A.S.ut_w_code[q] & 15), nq = near_next(A.M.ut, mask, q);
+      const uint32_t dev = (uint32_t)(A.S.ut_w_code[q] & 15), np = near_prev(A.M.ut, n, n - 1 - q);
+      const uint32_t nq = np == kNone ? kNone : n - 1 - np;  // (the list was entered backwards)
       const uint64_t ts = A.S.ut_ts[q];
       bool read;
       if (chrono) {

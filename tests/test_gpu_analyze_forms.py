@@ -196,3 +196,54 @@ def test_table_logs_of_hot_digests(odp, n, hot):
     k = np.arange(n, dtype=np.uint64)
     ev["digest"] = np.where(k % 7 == 3, ev["digest"], (k % np.uint64(hot)) * np.uint64(0xC2B2AE3D27D4EB4F))
     check(odp, ev)
+
+
+def lifetimes(n, arrays, devices, gap, seed):
+    """ALLOC/DELETE records of `arrays` addresses per device, each freed `gap` of
+    its own kind later, between other records; some frees come twice."""
+    rng = np.random.default_rng(seed)
+    ev = W.empty_events(n)
+    i = np.arange(n)
+    rec = rng.random(n)
+    ev["op"] = np.where(rec < 0.03, W.KERNEL, np.where(rec < 0.06, W.H2D, np.where((i // gap) % 2 == 0, W.ALLOC, W.DELETE)))
+    slot = i % gap % arrays if seed % 2 else (gap - 1 - i % gap) % arrays
+    slot = np.where(rng.random(n) < 0.02, rng.integers(0, arrays, size=n), slot)
+    ev["src_dev"], ev["dst_dev"] = -1, slot % devices
+    ev["src_addr"] = W.HOST_BASE + 4096 * (slot % 37)
+    ev["dst_addr"] = W.DEV_BASE + 4096 * slot
+    ev["bytes"] = 64 + 64 * (slot % 3)
+    ev["digest"] = rng.integers(0, 1 << 40, size=n)
+    ev["t_start"] = np.cumsum(rng.integers(0, 5, size=n))
+    ev["t_end"] = ev["t_start"] + rng.integers(0, 5, size=n)
+    return ev
+
+
+@pytest.mark.parametrize("n", [4097, 70_000, 262_144])
+@pytest.mark.parametrize("arrays,gap", [(1, 1), (10, 10), (300, 300), (255, 1024), (2000, 2000), (1 << 17, 60_000)])
+def test_table_logs_lifetimes(odp, n, arrays, gap):
+    """Neighbours of a group inside 64 positions, inside a chunk, in the chunk
+    before and far chunks; chunks of 256 to 1,024 positions."""
+    for seed in (1, 2):
+        check(odp, lifetimes(n, arrays, 3, gap, seed))
+
+
+@pytest.mark.parametrize("n", [5000, 66_000, 262_144])
+@pytest.mark.parametrize("places", [1, 40, 3000, 50_000])
+@pytest.mark.parametrize("rejected", [False, True])
+def test_table_logs_far_copies(odp, n, places, rejected):
+    """Copies whose next copy or kernel lies beyond the forward search, in logs
+    with and without a rejected record: the copies' table, read backwards."""
+    rng = np.random.default_rng(n + places)
+    ev = W.empty_events(n)
+    ev["op"] = np.where(np.arange(n) % 3001 == 3000, W.KERNEL, np.where(rng.random(n) < 0.02, W.D2H, W.H2D))
+    ev["src_dev"] = np.where(ev["op"] == W.D2H, 0, -1)
+    ev["dst_dev"] = np.where(ev["op"] == W.D2H, -1, rng.integers(0, 2, size=n))
+    ev["src_addr"] = W.HOST_BASE + 4096 * rng.integers(0, places, size=n)
+    ev["digest"] = rng.integers(0, n, size=n)
+    ev["t_start"] = np.cumsum(rng.integers(0, 2, size=n)) + 10
+    ev["t_end"] = ev["t_start"] + rng.integers(0, 3, size=n)
+    ev["bytes"] = 64
+    if rejected:
+        ev["op"][n // 3] = 9
+    fg, rg = check(odp, ev)
+    assert 0 < rg["ut_events"]
