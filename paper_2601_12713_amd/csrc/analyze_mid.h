@@ -745,21 +745,51 @@ __global__ __launch_bounds__(kT) void mid_link_kernel(MidSide A) {
   near_enter<false>(A.M.ad, A.ctl->n_ad, A.S.ad_w_addr, A.S.ad_w_dev, L.near, blockIdx.x, half);
 }
 
-// Inserts the paired ALLOC at position k into the RA table.
-__device__ __forceinline__ void mid_ra_insert(const MidSide& A, uint32_t tmask, uint32_t k) {
-  const uint64_t ha = A.M.ad_host[k], dv = A.S.ad_w_dev[k], by = A.M.ad_bytes[k];
-  uint32_t t = pair_hash(ha, dv, by) & tmask;
-  for (;; t = (t + 1) & tmask) {
-    uint32_t o = A.T.owner[t];
-    if (o == 0) o = atomicCAS(A.T.owner + t, 0u, k + 1);
-    if (o == 0) break;  // claimed
-    if (same_pair_key(A.M.ad_host, A.S.ad_w_dev, A.M.ad_bytes, o - 1, k)) {  // joined
-      if (A.T.multi[t] == 0) A.T.multi[t] = 1;
-      break;
+// Enters the wavefront's paired ALLOCs (positions k of the lanes with in) in the
+// RA table. Lanes of one key agree on one of them (as probe_step_shared; two
+// keys that meet in a lead word: one of the two goes lane by lane), which
+// enters the smallest position for all: a program that maps one array again and
+// again would send every swap and minimum to the same words (131,072 pairs of
+// one array: the whole analysis 310 us, and 106 so).
+struct RaLds {
+  uint32_t least[64];  // per leading lane: the smallest position of its lanes
+  uint8_t several[64], lead[kLeads];
+};
+__device__ __forceinline__ void mid_ra_insert(const MidSide& A, uint32_t tmask, uint32_t k, bool in, RaLds& L) {
+  if (!__ballot(in)) return;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t ha = in ? A.M.ad_host[k] : 0, dv = in ? A.S.ad_w_dev[k] : 0, by = in ? A.M.ad_bytes[k] : 0;
+  const uint32_t h = pair_hash(ha, dv, by);
+  L.least[lane] = kNone;
+  L.several[lane] = 0;
+  if (in) L.lead[h % kLeads] = (uint8_t)lane;
+  wave_lds_fence();
+  uint32_t l = in ? L.lead[h % kLeads] : lane;
+  const bool same = __shfl(ha, (int)l, 64) == ha && __shfl(dv, (int)l, 64) == dv && __shfl(by, (int)l, 64) == by;
+  if (!same) l = lane;
+  if (in) atomicMin(&L.least[l], k);
+  if (in && l != lane) L.several[l] = 1;
+  wave_lds_fence();
+  uint32_t t = h & tmask;
+  if (in && l == lane) {
+    // what the probe loop's lanes decide is stored inside it: they leave it at different trips
+    for (;; t = (t + 1) & tmask) {
+      uint32_t o = A.T.owner[t];
+      if (o == 0) o = atomicCAS(A.T.owner + t, 0u, k + 1);
+      if (o == 0) {  // claimed
+        if (L.several[lane]) A.T.multi[t] = 1;
+        break;
+      }
+      if (same_pair_key(A.M.ad_host, A.S.ad_w_dev, A.M.ad_bytes, o - 1, k)) {  // joined
+        if (A.T.multi[t] == 0) A.T.multi[t] = 1;
+        break;
+      }
     }
+    if (L.least[lane] < A.T.first[t]) atomicMin(A.T.first + t, L.least[lane]);
   }
-  if (k < A.T.first[t]) atomicMin(A.T.first + t, k);
-  A.T.slot[k] = t;
+  t = (uint32_t)__shfl((int)t, (int)l, 64);
+  if (in) A.T.slot[k] = t;
+  wave_lds_fence();
 }
 
 // Pairing (a DELETE with its predecessor of the same device address, when that
@@ -769,15 +799,19 @@ __device__ __forceinline__ void mid_ra_insert(const MidSide& A, uint32_t tmask, 
 __global__ __launch_bounds__(kT) void mid_pair_kernel(MidSide A) {
   const AnaCtl* c = A.ctl;
   const uint32_t m = c->n_ad, tmask = pair_table_mask(m / 2);
-  for (uint32_t q = blockIdx.x * kT + threadIdx.x; q < m; q += gridDim.x * kT) {
-    if (A.S.ad_op[q] != ODP_DELETE) continue;
-    const uint32_t p = near_prev(A.M.ad, m, q);
-    if (p == kNone || A.S.ad_op[p] != ODP_ALLOC) continue;
-    A.S.ad_alloc_partner[p] = q;
-    A.flags[A.S.ad_idx[q]] = ODP_F_PAIRED;
-    mid_ra_insert(A, tmask, p);
-  }
   const uint32_t lane = threadIdx.x & 63;
+  __shared__ RaLds s_ra[kT / 64];
+  for (uint32_t b = (blockIdx.x * kT + threadIdx.x) / 64 * 64; b < m; b += gridDim.x * kT) {
+    const uint32_t q = b + lane;
+    const bool del = q < m && A.S.ad_op[q] == ODP_DELETE;
+    const uint32_t p = del ? near_prev(A.M.ad, m, q) : kNone;
+    const bool paired = p != kNone && A.S.ad_op[p] == ODP_ALLOC;
+    if (paired) {
+      A.S.ad_alloc_partner[p] = q;
+      A.flags[A.S.ad_idx[q]] = ODP_F_PAIRED;
+    }
+    mid_ra_insert(A, tmask, p, paired, s_ra[threadIdx.x >> 6]);
+  }
   if (c->ut_need_sort) {
     __shared__ NearLds L;
     near_enter<true>(A.M.ut, c->n_ut, A.S.ut_w_addr, A.S.ut_w_code, L, blockIdx.x, gridDim.x);

@@ -247,3 +247,16 @@ def test_table_logs_far_copies(odp, n, places, rejected):
         ev["op"][n // 3] = 9
     fg, rg = check(odp, ev)
     assert 0 < rg["ut_events"]
+
+
+@pytest.mark.parametrize("n", [4097, 20_000, 262_144])
+@pytest.mark.parametrize("hosts", [1, 3, 300])
+def test_table_logs_repeated_allocations(odp, n, hosts):
+    """Few (host address, device, bytes) keys: a wavefront's pairs share one
+    entry of the repeated-allocation table; frees in either order."""
+    for seed in (1, 2):
+        ev = lifetimes(n, 500, 2, 700, seed)
+        slot = ((ev["dst_addr"] - np.uint64(W.DEV_BASE)) // np.uint64(4096)).astype(np.int64)
+        ev["src_addr"] = W.HOST_BASE + 4096 * (slot % hosts)
+        ev["bytes"] = 64
+        check(odp, ev)
