@@ -3380,8 +3380,8 @@ size_t mid_views(MidView& m, char* base, size_t cap) {
   m.ad_host = carve<uint64_t>(p, c);
   m.ad_bytes = carve<uint64_t>(p, c);
   m.kd_te = carve<uint64_t>(p, c);
-  m.node1 = carve<KernNode>(p, c / 64);
-  m.node2 = carve<KernNode>(p, c / 4096 + 1);
+  m.ks = carve<uint64_t>(p, c);
+  m.ke = carve<uint64_t>(p, c);
   for (NearTable* t : {&m.ad, &m.ut}) {
     p = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(p) + 15) & ~uintptr_t(15));  // read four slots at once
     t->owner = carve<uint32_t>(p, slots);

@@ -328,12 +328,6 @@ __device__ __forceinline__ uint32_t near_prev(const NearTable& T, uint32_t m, ui
   return kNone;
 }
 
-// Extremes of the starts and ends of 64 (and of 4,096) consecutive kernels of
-// the per-device lists, for logs that are not chronological.
-struct KernNode {
-  uint64_t smin, smax, emin, emax;
-};
-
 struct MidView {
   uint32_t *gid0, *gid1;   // digest group of each record (kNone: no transfer); of each element after the first pass
   uint32_t* dtab;          // digest table: 1 + the record that claimed the slot
@@ -341,7 +335,7 @@ struct MidView {
   uint8_t* uth;            // per record: 1 for an unused transfer
   uint64_t *ad_host, *ad_bytes;  // per ALLOC/DELETE: host address, bytes
   uint64_t* kd_te;         // per kernel of the per-device lists: end
-  KernNode *node1, *node2; // per 64, per 4,096 of them
+  uint64_t *ks, *ke;       // starts and ends of the lists, each sorted by tiles of kKernTile (not chronological logs)
   NearTable ad, ut;
   WaveScan wscan;
   WaveAgg* agg;
@@ -671,9 +665,11 @@ constexpr uint32_t kMidStage = kT + kMidWindow;
 struct UtLds {
   uint32_t ix[kMidStage], h[kMidStage + 8];  // (read eight at a time)
 };
+constexpr uint32_t kKernTile = 2048;
 union LinkLds {
   UtLds ut;
   NearLds near;
+  uint64_t kern[kKernTile];
 };
 __device__ void mid_ut_scan(const MidSide& A, UtLds& L, uint32_t block, uint32_t nblocks) {
   const UtArgs& U = A.U;
@@ -734,12 +730,47 @@ __device__ void mid_ut_scan(const MidSide& A, UtLds& L, uint32_t block, uint32_t
   }
 }
 
+// In a log that is not chronological: the starts and the ends of each device's
+// kernels, sorted in tiles of kKernTile (a workgroup each, in LDS), for the count
+// form's binary searches (mid_kernels_meeting).
+__device__ void mid_sort_kernels(const MidSide& A, uint64_t* s, uint32_t block, uint32_t nblocks) {
+  uint32_t job = block;  // (device, tile, starts or ends)
+  for (int d = 0; d < kEp; ++d) {
+    const uint32_t total = A.ctl->kd_total[d], jobs = 2 * ((total + kKernTile - 1) / kKernTile);
+    for (; job < jobs; job += nblocks) {
+      const uint32_t at = job / 2 * kKernTile, len = min(kKernTile, total - at);
+      const uint64_t* from = (job & 1 ? A.M.kd_te : A.S.kd_ts) + A.ctl->kd_base[d] + at;
+      uint64_t* to = (job & 1 ? A.M.ke : A.M.ks) + A.ctl->kd_base[d] + at;
+      uint32_t top = 2;
+      while (top < len) top <<= 1;
+      __syncthreads();
+      for (uint32_t x = threadIdx.x; x < top; x += kT) s[x] = x < len ? from[x] : ~0ull;
+      __syncthreads();
+      for (uint32_t k = 2; k <= top; k <<= 1)  // bitonic
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+          for (uint32_t x = threadIdx.x; x < top / 2; x += kT) {
+            const uint32_t i = (x & ~(j - 1)) << 1 | (x & (j - 1)), o = i | j;
+            const uint64_t a = s[i], b = s[o];
+            if ((a > b) == ((i & k) == 0)) {
+              s[i] = b;
+              s[o] = a;
+            }
+          }
+          __syncthreads();
+        }
+      for (uint32_t x = threadIdx.x; x < len; x += kT) to[x] = s[x];
+    }
+    job -= jobs;
+  }
+}
+
 // Half of the workgroups each: both are chains of memory round trips.
 __global__ __launch_bounds__(kT) void mid_link_kernel(MidSide A) {
   __shared__ LinkLds L;
   const uint32_t half = gridDim.x / 2;
   if (blockIdx.x >= half) {
     mid_ut_scan(A, L.ut, blockIdx.x - half, half);
+    if (A.ctl->first_bad != kNone) mid_sort_kernels(A, L.kern, blockIdx.x - half, half);
     return;
   }
   near_enter<false>(A.M.ad, A.ctl->n_ad, A.S.ad_w_addr, A.S.ad_w_dev, L.near, blockIdx.x, half);
@@ -794,8 +825,7 @@ __device__ __forceinline__ void mid_ra_insert(const MidSide& A, uint32_t tmask, 
 
 // Pairing (a DELETE with its predecessor of the same device address, when that
 // is an ALLOC) and the RA table; when the forward search left copies open, the
-// groups of the copies' places; in a log that is not chronological, the
-// extremes of the kernel lists.
+// groups of the copies' places.
 __global__ __launch_bounds__(kT) void mid_pair_kernel(MidSide A) {
   const AnaCtl* c = A.ctl;
   const uint32_t m = c->n_ad, tmask = pair_table_mask(m / 2);
@@ -816,59 +846,35 @@ __global__ __launch_bounds__(kT) void mid_pair_kernel(MidSide A) {
     __shared__ NearLds L;
     near_enter<true>(A.M.ut, c->n_ut, A.S.ut_w_addr, A.S.ut_w_code, L, blockIdx.x, gridDim.x);
   }
-  if (c->first_bad != kNone) {
-    // a wavefront per 4,096 kernels
-    const uint32_t k = c->n_k;
-    for (uint32_t b = (blockIdx.x * kT + threadIdx.x) / 64; b < (k + 4095) / 4096; b += gridDim.x * (kT / 64)) {
-      KernNode all{~0ull, 0, ~0ull, 0};
-      for (uint32_t x = 0; x < 64 && b * 4096 + x * 64 < k; ++x) {
-        const uint32_t q = b * 4096 + x * 64 + lane;
-        KernNode d{q < k ? A.S.kd_ts[q] : ~0ull, q < k ? A.S.kd_ts[q] : 0ull, q < k ? A.M.kd_te[q] : ~0ull,
-                   q < k ? A.M.kd_te[q] : 0ull};
-        for (int o = 32; o >= 1; o >>= 1) {
-          d.smin = min(d.smin, __shfl_xor(d.smin, o, 64));
-          d.smax = max(d.smax, __shfl_xor(d.smax, o, 64));
-          d.emin = min(d.emin, __shfl_xor(d.emin, o, 64));
-          d.emax = max(d.emax, __shfl_xor(d.emax, o, 64));
-        }
-        if (lane == 0) A.M.node1[b * 64 + x] = d;
-        all.smin = min(all.smin, d.smin);
-        all.smax = max(all.smax, d.smax);
-        all.emin = min(all.emin, d.emin);
-        all.emax = max(all.emax, d.emax);
-      }
-      if (lane == 0) A.M.node2[b] = all;
-    }
-  }
 }
 
 // Kernels of device code dev that start by hi, less those that end before lo
-// (modulo 2^32): the count form, in any kernel order. Whole nodes on one side
-// of both bounds count at once.
+// (modulo 2^32): the count form, in any kernel order, tile by tile. A tile on one
+// side of a bound, as most are where only a stretch of the log is out of
+// order, needs no search. (By extremes of 64 and 4,096 kernels in log order
+// instead of sorted tiles, each query went through hundreds of them: 200,000
+// records, 3 of them rejected, 760 us; 192 us so.)
 __device__ __forceinline__ uint32_t mid_kernels_meeting(const MidSide& A, uint32_t dev, uint64_t lo, uint64_t hi) {
-  uint32_t cnt = 0, p = A.ctl->kd_base[dev];
-  const uint32_t end = p + A.ctl->kd_total[dev];
-  while (p < end) {
-    uint32_t len = 1;
-    KernNode d;
-    if ((p & 4095) == 0 && p + 4096 <= end) {
-      d = A.M.node2[p >> 12];
-      len = 4096;
-    }
-    if (len == 1 || !((d.smax <= hi || d.smin > hi) && (d.emax < lo || d.emin >= lo))) {
-      len = 1;
-      if ((p & 63) == 0 && p + 64 <= end) {
-        d = A.M.node1[p >> 6];
-        len = 64;
+  const uint32_t total = A.ctl->kd_total[dev], base = A.ctl->kd_base[dev];
+  uint32_t cnt = 0;
+  for (uint32_t at = 0; at < total; at += kKernTile) {
+    const uint32_t len = min(kKernTile, total - at);
+    const uint64_t *ks = A.M.ks + base + at, *ke = A.M.ke + base + at;
+    const uint64_t s0 = ks[0], s1 = ks[len - 1], e0 = ke[0], e1 = ke[len - 1];
+    uint32_t started = s0 > hi ? 0u : len, ended = e0 >= lo ? 0u : len;
+    if ((started && s1 > hi) || (ended && e1 >= lo)) {
+      // both searches take the same steps, so their loads are in flight together
+      uint32_t a = 0, b = 0, left = len;
+      for (; left > 1; left -= left / 2) {
+        const uint32_t half = left / 2;
+        const uint64_t x = ks[a + half - 1], y = ke[b + half - 1];
+        a += x <= hi ? half : 0u;
+        b += y < lo ? half : 0u;
       }
-      if (len == 1 || !((d.smax <= hi || d.smin > hi) && (d.emax < lo || d.emin >= lo))) {
-        len = 1;
-        d.smax = A.S.kd_ts[p];
-        d.emax = A.M.kd_te[p];
-      }
+      started = a + (ks[a] <= hi);
+      ended = b + (ke[b] < lo);
     }
-    cnt += (d.smax <= hi ? len : 0u) - (d.emax < lo ? len : 0u);
-    p += len;
+    cnt += started - ended;
   }
   return cnt;
 }

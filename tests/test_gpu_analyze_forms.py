@@ -260,3 +260,23 @@ def test_table_logs_repeated_allocations(odp, n, hosts):
         ev["src_addr"] = W.HOST_BASE + 4096 * (slot % hosts)
         ev["bytes"] = 64
         check(odp, ev)
+
+
+@pytest.mark.parametrize("kernels", [1, 2, 2047, 2048, 2049, 4097, 9000])
+def test_table_logs_out_of_order_kernels(odp, kernels):
+    """Logs that are not chronological: the kernels of a device in sorted tiles
+    of 2,048, the last one partly filled; one end at the type's largest value."""
+    n = 6000 + 2 * kernels
+    ev = random_log(kernels, n, devices=2, digests=n, places=200, invalid=0.0, kernels=0.0)
+    at = np.sort(np.random.default_rng(kernels).choice(n, size=kernels + 5, replace=False))
+    ev["op"][at] = W.KERNEL
+    ev["dst_dev"][at] = 0
+    ev["dst_dev"][at[::kernels // 5 + 1]] = 1
+    ev["t_end"][at] += np.random.default_rng(kernels).integers(0, 300, size=at.size).astype(np.uint64)
+    half = n // 2  # the clock jumps back once
+    ev["t_start"][half:] -= ev["t_start"][half] - ev["t_start"][half // 2]
+    ev["t_end"][half:] -= np.minimum(ev["t_end"][half:], ev["t_end"][half] - ev["t_start"][half // 2])
+    ev["t_end"] = np.maximum(ev["t_end"], ev["t_start"])
+    ev["t_end"][at[-1]] = np.uint64(2**64 - 1)
+    fg, rg = check(odp, ev)
+    assert rg["status"] == 1
