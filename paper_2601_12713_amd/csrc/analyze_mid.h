@@ -655,10 +655,8 @@ __global__ __launch_bounds__(kT) void mid_subset_kernel(MidSide A) {
 
 // Unused transfers by the forward search, and the groups of the ALLOC/DELETE
 // records.
-// The forward search of ut_scan_body over a longer stretch: the staged copies
-// are hashes of their places, compared in full when equal. A log whose devices
-// each run a kernel every few hundred copies needs no group table for its
-// copies then (with 64 copies ahead, 200,000 records on three devices did: the
+// The forward search goes over a longer stretch here: a log whose devices each
+// run a kernel every few hundred copies needs no group table for its copies then (with 64 copies ahead, 200,000 records on three devices did: the
 // table's insertion and lookups took 340 us).
 constexpr uint32_t kMidWindow = 1024;
 constexpr uint32_t kMidStage = kT + kMidWindow;
@@ -689,39 +687,7 @@ __device__ void mid_ut_scan(const MidSide& A, UtLds& L, uint32_t block, uint32_t
     __syncthreads();
     const uint32_t q = b0 + threadIdx.x;
     if (q < n) {
-      const uint64_t code = U.ut_w_code[q], ts = U.ut_ts[q];
-      const uint32_t d = (uint32_t)(code & 15), k = U.ut_kc[q], total = U.ctl->kd_total[d];
-      uint8_t hit = 0;  // a kernel is still running
-      if (!(k > 0 && U.ut_km[q] >= ts)) {
-        if (k == total) {
-          hit = 1;  // no kernel follows
-        } else {
-          const uint32_t kp = U.ctl->kd_base[d] + k, kidx = U.kd_idx[kp], h = A.S.ut_vals[q];
-          const uint64_t sk = U.kd_ts[kp], addr = U.ut_w_addr[q];
-          // end: the staged copies logged before the kernel, kMidWindow of them at most
-          uint32_t x = threadIdx.x, end = x, top = x + kMidWindow;
-          while (end < top) {
-            const uint32_t mid = (end + top) / 2;
-            if (s_ix[mid] > kidx) top = mid; else end = mid + 1;
-          }
-          if (end == threadIdx.x + kMidWindow) hit = 2;  // undecided unless the next copy is among them
-          for (; x < end; x += 8) {
-            uint32_t eq = 0;
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k) eq |= (s_h[x + k] == h ? 1u : 0u) << k;
-            if (end - x < 8) eq &= (1u << (end - x)) - 1;
-            while (eq) {
-              const uint32_t c = b0 + 1 + x + (uint32_t)__builtin_ctz(eq);
-              if (U.ut_w_addr[c] == addr && U.ut_w_code[c] == code) {
-                hit = U.ut_ts[c] < sk ? 1 : 0;  // the next copy of the place
-                break;
-              }
-              eq &= eq - 1;
-            }
-            if (eq) break;
-          }
-        }
-      }
+      const uint8_t hit = ut_decide<kMidWindow, kMidWindow>(U, s_ix, s_h, b0, q, A.S.ut_vals[q]);
       U.ut_hit[q] = hit;
       if (hit == 1) A.M.uth[U.ut_idx[q]] = 1;
       if (hit == 2) U.ctl->ut_need_sort = 1;

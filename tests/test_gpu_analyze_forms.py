@@ -280,3 +280,21 @@ def test_table_logs_out_of_order_kernels(odp, kernels):
     ev["t_end"][at[-1]] = np.uint64(2**64 - 1)
     fg, rg = check(odp, ev)
     assert rg["status"] == 1
+
+
+@pytest.mark.parametrize("places", [1, 90, 5000])
+@pytest.mark.parametrize("every", [509, 515, 1023, 4001])
+def test_sorted_logs_far_kernels(odp, every, places):
+    """The sorting pipeline's forward search: a copy's kernel just inside and past
+    its window of listed copies, its next copy before and behind what is searched."""
+    n = 262_145 + 3 * every
+    rng = np.random.default_rng(every * places)
+    ev = W.empty_events(n)
+    ev["op"] = np.where(np.arange(n) % every == every - 1, W.KERNEL, W.H2D)
+    ev["src_dev"], ev["dst_dev"] = -1, 0
+    ev["src_addr"] = W.HOST_BASE + 4096 * rng.integers(0, places, size=n)
+    ev["digest"] = rng.integers(0, n, size=n)
+    ev["t_start"] = np.cumsum(rng.integers(0, 2, size=n)) + 10
+    ev["t_end"] = ev["t_start"] + rng.integers(0, 2, size=n)
+    ev["bytes"] = 64
+    check(odp, ev)
