@@ -38,6 +38,7 @@
 #include <chrono>
 #include <cstring>
 #include <deque>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -156,8 +157,11 @@ __device__ __forceinline__ uint64_t tx_key(int s, int d) { return kMark | ((uint
 // 960 us, almost all of the kernel; the kernel takes 109 now. Groups are the slots of an LDS
 // hash table (exact: a slot's owner has the same key), and two stable 6-bit
 // passes order the records by slot. Ticks of at most kWalkTick records are
-// their own only group: there the walk is shorter than the sort.
-constexpr uint32_t kWalkTick = 64;
+// their own only group, in a kernel of their own: there the walk is shorter than
+// the sort (kernel, median over ticks: 10 records 23.9 against 24.8 us, 12: 25.1
+// and 24.9, 16: 31.1 and 28.0, 64: 77 and 38).
+constexpr uint32_t kWalkTick = 12;
+constexpr uint32_t kWalkThreads = 256;
 constexpr uint32_t kGroupSlots = 2 * kTickMax;
 struct GroupLds {
   uint32_t owner[kGroupSlots];
@@ -174,15 +178,9 @@ struct GroupList {
 // The range [lo, hi) of L.ord that holds the group of record t (key[t], tag;
 // records with active == false are in no group). All threads of the workgroup
 // call it; L is complete after the next barrier.
-__device__ void group_tick(GroupLds& G, GroupList& L, const uint64_t* key, uint32_t tag, bool active, uint32_t m,
-                           uint32_t& lo, uint32_t& hi) {
+__device__ void group_tick(GroupLds& G, GroupList& L, const uint64_t* key, uint32_t tag, bool active, uint32_t& lo,
+                           uint32_t& hi) {
   const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6;
-  if (m <= kWalkTick) {
-    L.ord[t] = (uint16_t)t;
-    lo = 0;
-    hi = m;
-    return;
-  }
   constexpr uint32_t kFree = 0xFFFFFFFFu;
   G.tag[t] = tag;
   G.owner[t] = G.owner[t + kTickMax] = kFree;
@@ -243,23 +241,33 @@ __device__ void group_tick(GroupLds& G, GroupList& L, const uint64_t* key, uint3
   }
 }
 
-__global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
-  __shared__ GroupLds s_group;
-  __shared__ GroupList s_main, s_place;  // transfers by digest, ALLOC/DELETE by device address; copies by place
-  __shared__ uint64_t s_key[kTickMax];
-  __shared__ uint64_t s_kmask[kDev][kTickMax / 64];  // the tick's KERNEL records per device code
-  __shared__ uint64_t s_pmask[kTickMax / 64];        // its DELETEs that pair
-  __shared__ uint64_t s_dig[kTickMax];
-  __shared__ uint64_t s_addr[kTickMax];   // dst_addr (ALLOC/DELETE: device address)
-  __shared__ uint64_t s_saddr[kTickMax];  // src_addr (copies: source; ALLOC: host address)
-  __shared__ uint64_t s_ts[kTickMax];
-  __shared__ uint64_t s_te[kTickMax];
-  __shared__ uint64_t s_pid[kTickMax];    // DELETE: the ALLOC it pairs (arrival index), else none
-  __shared__ uint64_t s_xchg[kTickMax];   // RT_TX list head taken by a key's last element; RA tick minimum
-  __shared__ int16_t s_src[kTickMax], s_dst[kTickMax];
-  __shared__ uint8_t s_kind[kTickMax];
-  __shared__ uint8_t s_op[kTickMax];
-  __shared__ uint8_t s_unmarked[kTickMax];  // transfer not sent back later in this tick
+// GROUPED: a tick of up to kTickMax records by groups, a thread each. Else one of
+// up to kWalkTick: all records in the first wavefront, which keeps what it
+// counts over them in registers, and LDS for them only; the other wavefronts
+// are there for the waiting windows. (One kernel for both took 11.6 to 15.6 us
+// for 1 to 4 records, with the masks, lists and barriers of 1,024 threads.)
+template <bool GROUPED>
+__global__ __launch_bounds__(GROUPED ? kTickMax : kWalkThreads) void serve_tick_kernel(TickArgs A) {
+  constexpr uint32_t NT = GROUPED ? kTickMax : kWalkThreads, MAX = GROUPED ? kTickMax : 64, kWords = MAX / 64;
+  static_assert(kWalkTick <= 64 && kDev <= 64, "records and device codes in one wavefront");
+  struct Unused {};
+  __shared__ std::conditional_t<GROUPED, GroupLds, Unused> s_group;
+  // transfers by digest, ALLOC/DELETE by device address; copies by place
+  __shared__ std::conditional_t<GROUPED, GroupList, Unused> s_main, s_place;
+  __shared__ uint64_t s_key[GROUPED ? kTickMax : 1];
+  __shared__ uint64_t s_kmask[GROUPED ? kDev : 1][kWords];  // the tick's KERNEL records per device code
+  __shared__ uint64_t s_pmask[kWords];        // its DELETEs that pair
+  __shared__ uint64_t s_dig[MAX];
+  __shared__ uint64_t s_addr[MAX];   // dst_addr (ALLOC/DELETE: device address)
+  __shared__ uint64_t s_saddr[MAX];  // src_addr (copies: source; ALLOC: host address)
+  __shared__ uint64_t s_ts[MAX];
+  __shared__ uint64_t s_te[MAX];
+  __shared__ uint64_t s_pid[MAX];    // DELETE: the ALLOC it pairs (arrival index), else none
+  __shared__ uint64_t s_xchg[MAX];   // RT_TX list head taken by a key's last element; RA tick minimum
+  __shared__ int16_t s_src[MAX], s_dst[MAX];
+  __shared__ uint8_t s_kind[MAX];
+  __shared__ uint8_t s_op[MAX];
+  __shared__ uint8_t s_unmarked[MAX];  // transfer not sent back later in this tick
   __shared__ uint32_t s_kc0[kDev];          // kernels per device before this tick
   __shared__ uint32_t s_kc1[kDev];          // ... and after it
   __shared__ uint32_t s_pend_n, s_keep;
@@ -305,23 +313,44 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
   // Kernels on my device logged before me (earlier ticks and earlier in this one).
   const uint32_t lane = t & 63, wave = t >> 6;
   const uint64_t lt = lane ? ~0ull >> (64 - lane) : 0ull;
-  for (int dv = 0; dv < kDev; ++dv) {
-    const uint64_t b = __ballot(kind == K_KERNEL && e.dst_dev + 1 == dv);
-    if (lane == 0) s_kmask[dv][wave] = b;
+  uint64_t km_own = 0;   // not GROUPED: the tick's KERNEL records on this lane's device,
+  uint32_t k_code = 0;   // and how many there are on device code `lane`
+  if constexpr (GROUPED) {
+    for (int dv = 0; dv < kDev; ++dv) {
+      const uint64_t b = __ballot(kind == K_KERNEL && e.dst_dev + 1 == dv);
+      if (lane == 0) s_kmask[dv][wave] = b;
+    }
+  } else if (wave == 0) {
+    for (uint64_t b = __ballot(kind == K_KERNEL); b; b &= b - 1) {
+      const int dv = __shfl((int)e.dst_dev, __builtin_ctzll(b), 64);
+      if (e.dst_dev == dv) km_own |= b & (~b + 1);
+      k_code += (int)lane == dv + 1;
+    }
   }
-  // My groups in the tick.
+  // My groups in the tick: the records main_at(q), q in [g0, g1), and place_at(q), q in [p0, p1).
   const bool copyin_me = kind == K_TRANSFER && e.op != ODP_D2H && e.dst_dev >= 0;
-  uint32_t g0, g1, p0, p1;
-  s_key[t] = kind == K_TRANSFER ? e.digest : kind == K_ALLOCDEL ? e.dst_addr : 0ull;
-  group_tick(s_group, s_main, s_key, kind == K_TRANSFER ? 1u : 2u | (uint32_t)(uint16_t)(e.dst_dev + 1) << 8,
-             kind == K_TRANSFER || kind == K_ALLOCDEL, A.m, g0, g1);
-  group_tick(s_group, s_place, s_saddr, (uint32_t)(uint16_t)e.src_dev << 16 | (uint16_t)e.dst_dev, copyin_me, A.m, p0, p1);
+  uint32_t g0 = 0, g1 = A.m, p0 = 0, p1 = A.m;
+  if constexpr (GROUPED) {
+    s_key[t] = kind == K_TRANSFER ? e.digest : kind == K_ALLOCDEL ? e.dst_addr : 0ull;
+    group_tick(s_group, s_main, s_key, kind == K_TRANSFER ? 1u : 2u | (uint32_t)(uint16_t)(e.dst_dev + 1) << 8,
+               kind == K_TRANSFER || kind == K_ALLOCDEL, g0, g1);
+    group_tick(s_group, s_place, s_saddr, (uint32_t)(uint16_t)e.src_dev << 16 | (uint16_t)e.dst_dev, copyin_me, p0, p1);
+  }
+  auto main_at = [&](uint32_t q) -> uint32_t {
+    if constexpr (GROUPED) return s_main.ord[q]; else return q;
+  };
+  auto place_at = [&](uint32_t q) -> uint32_t {
+    if constexpr (GROUPED) return s_place.ord[q]; else return q;
+  };
   __syncthreads();
   uint32_t kc_me = 0;
   if (in && kind != K_INVALID) {
-    const uint64_t* km = s_kmask[e.dst_dev + 1];
-    uint32_t c = (uint32_t)__popcll(km[wave] & lt);
-    for (uint32_t x = 0; x < wave; ++x) c += (uint32_t)__popcll(km[x]);
+    uint32_t c = (uint32_t)__popcll(km_own & lt);
+    if constexpr (GROUPED) {
+      const uint64_t* km = s_kmask[e.dst_dev + 1];
+      c = (uint32_t)__popcll(km[wave] & lt);
+      for (uint32_t x = 0; x < wave; ++x) c += (uint32_t)__popcll(km[x]);
+    }
     kc_me = s_kc0[e.dst_dev + 1] + c;
   }
   // Phase 1: predecessors inside the tick, else the state of earlier ticks.
@@ -341,7 +370,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     is_copyin = copyin_me;
     if (is_copyin) {
       for (uint32_t q = p0; q < p1; ++q) {
-        const uint32_t u = s_place.ord[q];
+        const uint32_t u = place_at(q);
         if (u != t && s_kind[u] == K_TRANSFER && s_op[u] != ODP_D2H && s_dst[u] == d && s_src[u] == s &&
             s_saddr[u] == e.src_addr) {
           if (u < t) ut_prev = (int)u; else seen |= kUtLater;
@@ -349,7 +378,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
       }
     }
     for (uint32_t q = g0; q < g1; ++q) {
-      const uint32_t u = s_main.ord[q];
+      const uint32_t u = main_at(q);
       if (s_kind[u] != K_TRANSFER || s_dig[u] != h) continue;
       const int su = s_src[u], du = s_dst[u];
       const bool same_pair = s != d && su != du && min(su, du) == lo && max(su, du) == hi;
@@ -407,7 +436,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     const uint64_t a = e.dst_addr;
     const int d = e.dst_dev;
     for (uint32_t q = g0; q < g1; ++q) {
-      const uint32_t u = s_main.ord[q];
+      const uint32_t u = main_at(q);
       if (s_kind[u] != K_ALLOCDEL || s_addr[u] != a || s_dst[u] != d) continue;
       if (u < t) ad_pred = (int)u;
       else if (u > t) seen |= kAdLater;
@@ -434,7 +463,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     known_or(A.known, id, f);
     A.kc_at[id] = kc_me;
   }
-  {
+  if (wave < kWords) {
     const uint64_t b = __ballot(kind == K_ALLOCDEL && s_pid[t] != kNone64);
     if (lane == 0) s_pmask[wave] = b;
   }
@@ -462,7 +491,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     if (s != d && !(seen & kTxLater)) {
       int newest = -1;
       for (uint32_t q = g0; q < g1; ++q) {
-        const uint32_t u = s_main.ord[q];
+        const uint32_t u = main_at(q);
         if (u <= t && s_kind[u] == K_TRANSFER && s_unmarked[u] && s_dig[u] == h && s_src[u] == s && s_dst[u] == d)
           newest = (int)u;
       }
@@ -511,7 +540,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
       const uint64_t k0 = a.src_addr, k1 = kMark | (uint64_t)(a.dst_dev + 1), k2 = a.bytes;
       uint32_t earlier = 0;
       uint64_t tick_min = pid;
-      for (uint32_t x = 0; x < kTickMax / 64; ++x) {
+      for (uint32_t x = 0; x < kWords; ++x) {
         for (uint64_t pm = s_pmask[x]; pm; pm &= pm - 1) {
           const uint32_t u = x * 64 + (uint32_t)__builtin_ctzll(pm);
           if (u == t) continue;
@@ -546,7 +575,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     const uint32_t k0 = s_kc0[dv + 1];
     uint64_t mx = k0 ? A.kmaxend[row + k0 - 1] : 0;
     for (uint32_t x = 0; x <= wave; ++x)
-      for (uint64_t km = s_kmask[dv + 1][x] & (x < wave ? ~0ull : lt | 1ull << lane); km; km &= km - 1)
+      for (uint64_t km = (GROUPED ? s_kmask[dv + 1][x] : km_own) & (x < wave ? ~0ull : lt | 1ull << lane); km; km &= km - 1)
         mx = max(mx, s_te[x * 64 + (uint32_t)__builtin_ctzll(km)]);
     A.kstart[row + kc_me] = e.t_start;
     A.kmaxend[row + kc_me] = mx;
@@ -564,7 +593,7 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     const int s = e.src_dev, d = e.dst_dev;
     int older = -1, last = -1;
     for (uint32_t q = g0; q < g1; ++q) {
-      const uint32_t u = s_main.ord[q];
+      const uint32_t u = main_at(q);
       if (!(s_kind[u] == K_TRANSFER && s_dig[u] == h && s_src[u] == s && s_dst[u] == d)) continue;
       if (u < t && s_unmarked[u]) older = (int)u;
       last = (int)u;  // the pair's last transfer of the tick took the old head
@@ -572,8 +601,9 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
     A.link[id] = older >= 0 ? (uint32_t)(A.base_id + older + 1) : (uint32_t)s_xchg[last];
   }
   if (t < kDev) {
-    uint32_t c = 0;
-    for (uint32_t x = 0; x < kTickMax / 64; ++x) c += (uint32_t)__popcll(s_kmask[t][x]);
+    uint32_t c = k_code;
+    if constexpr (GROUPED)
+      for (uint32_t x = 0; x < kWords; ++x) c += (uint32_t)__popcll(s_kmask[t][x]);
     s_kc1[t] = s_kc0[t] + c;
   }
   __syncthreads();
@@ -584,17 +614,26 @@ __global__ __launch_bounds__(kTickMax) void serve_tick_kernel(TickArgs A) {
   const uint32_t cur = st->pend_cur, np = s_pend_n;
   const Pending* P = A.pend[cur];
   Pending* Q = A.pend[cur ^ 1];
+  constexpr uint32_t kU = kTickMax / NT;  // windows per thread and step, read together
   for (uint32_t base = 0; base < np; base += kTickMax) {
-    const uint32_t j = base + t;
-    if (j >= np || !windows_on) continue;  // after a rejected record these bits wait for the drain
-    const Pending p = P[j];
-    if (p.deadline < now_ts) {
-      const uint64_t row = (uint64_t)p.dev * A.cap;
-      const bool before = p.kc > 0 && A.kmaxend[row + p.kc - 1] >= p.lo;
-      const bool after = count_upto(A.kstart + row, s_kc1[p.dev], p.deadline) > p.kc;
-      if (!before && !after) known_or(A.known, p.id, p.flag);
-    } else {
-      Q[atomicAdd(&s_keep, 1u)] = p;
+    if (!windows_on) break;  // after a rejected record these bits wait for the drain
+    Pending p[kU];
+#pragma unroll
+    for (uint32_t u = 0; u < kU; ++u) {
+      const uint32_t j = base + u * NT + t;
+      if (j < np) p[u] = P[j];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kU; ++u) {
+      if (base + u * NT + t >= np) break;
+      if (p[u].deadline < now_ts) {
+        const uint64_t row = (uint64_t)p[u].dev * A.cap;
+        const bool before = p[u].kc > 0 && A.kmaxend[row + p[u].kc - 1] >= p[u].lo;
+        const bool after = count_upto(A.kstart + row, s_kc1[p[u].dev], p[u].deadline) > p[u].kc;
+        if (!before && !after) known_or(A.known, p[u].id, p[u].flag);
+      } else {
+        Q[atomicAdd(&s_keep, 1u)] = p[u];
+      }
     }
   }
   __syncthreads();
@@ -824,7 +863,10 @@ static int launch_tick(odp_server* s, int b, uint32_t m, uint64_t bytes, bool id
   A.t_ra = s->t_ra;
   A.t_ut = s->t_ut;
   A.st = s->st;
-  hipLaunchKernelGGL(serve_tick_kernel, dim3(1), dim3(kTickMax), 0, cs, A);
+  if (m <= kWalkTick)
+    hipLaunchKernelGGL(serve_tick_kernel<false>, dim3(1), dim3(kWalkThreads), 0, cs, A);
+  else
+    hipLaunchKernelGGL(serve_tick_kernel<true>, dim3(1), dim3(kTickMax), 0, cs, A);
   ODP_HIP(hipGetLastError());
   ODP_HIP(hipEventRecord(s->done[b], cs));
   s->n_logged += m;
