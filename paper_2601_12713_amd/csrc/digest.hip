@@ -806,15 +806,15 @@ __device__ void finalize_plan(const PlanArgs& A, const uint64_t carry[kQ]) {
   c->tree_total = carry[2];
   c->tk_total = carry[3];
   c->head = 0;
-  c->overflow = plan_overflow(A, carry) ? 1u : 0u;
   // When every item can have a workgroup of its own, nothing is claimed and
   // nothing is carried from item to item: the digest kernel then hashes each
   // node like the per-buffer kernel (more loads in flight, levels above done
   // by the last node's workgroup). Small buffers then go one per wavefront if
   // there are workgroups enough, else 64 per workgroup.
-  c->few = carry[4] || c->overflow ? 0u
-           : carry[0] + ceil_div(carry[1], kWaves) <= A.grid ? (uint32_t)kWaves
-           : carry[0] + ceil_div(carry[1], kRows) <= A.grid  ? (uint32_t)kRows : 0u;
+  c->form = plan_overflow(A, carry) ? kPlanOverflow
+            : carry[4] ? 0u
+            : carry[0] + ceil_div(carry[1], kWaves) <= A.grid ? (uint64_t)kWaves
+            : carry[0] + ceil_div(carry[1], kRows) <= A.grid  ? (uint64_t)kRows : 0u;
 }
 
 __global__ __launch_bounds__(kPlanThreads) void plan_count_kernel(PlanArgs A) {
@@ -898,7 +898,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_write_kernel(PlanArgs A) {
 // rec[k] = the node's address, length and digest destination.
 __global__ __launch_bounds__(kPlanThreads) void plan_items_kernel(PlanArgs A, uint32_t* item_buf) {
   const DigestCtl* c = A.ctl;
-  if (c->overflow) return;
+  if (c->form == kPlanOverflow) return;
   const uint64_t total = c->n_node_items;
   for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (uint64_t)gridDim.x * blockDim.x) {
     uint64_t lo = 0, hi = A.n;  // invariant: node_off[lo] <= k < node_off[hi] (node_off[n] = total)
@@ -1062,8 +1062,11 @@ __device__ __forceinline__ const uint8_t* fast_rows(const uint8_t* base, uint32_
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void digest_batched_kernel(BatchArgs A) {
   __shared__ Smem<kSlabBatch> sm;
   const DigestCtl* c = A.ctl;
-  if (c->few) return;
-  if (c->overflow) {
+  // (read as one word: the two flags read one after the other, and again at the
+  // start of the tree kernel, cost 2 us of 87 for 8,193 buffers of 64 B-16 KiB)
+  const uint64_t form = c->form;
+  if ((uint32_t)form) return;
+  if (form) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < A.n; i += (uint64_t)gridDim.x * blockDim.x)
       A.out[i] = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0 && A.status) *reinterpret_cast<volatile uint32_t*>(A.status) = (uint32_t)(-ODP_ECAPACITY);
@@ -1177,7 +1180,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   }
 }
 
-// A plan with at most one item per workgroup (DigestCtl::few rows per group of
+// A plan with at most one item per workgroup (DigestCtl::form rows per group of
 // small buffers): level-1 nodes as in the per-buffer kernel, upper levels
 // included. It runs in the tree kernel's launch, which such a plan leaves idle:
 // inside the persistent kernel its registers pushed that one's loop into 40
@@ -1186,9 +1189,10 @@ __device__ __forceinline__ void run_few(const BatchArgs& A, Smem<kSlabOne>& sm, 
   const int t = threadIdx.x, w = uniform(t >> 6), lane = t & 63;
   const uint32_t item = blockIdx.x;
   if (item < n_node) {
+    // (in scalar registers: with these words in vector ones the kernel spills)
     const uint32_t i = uniform(A.rec[item].buf);
-    run_node(sm, static_cast<const uint8_t*>(A.ptrs[i]), A.sizes[i], item - A.node_off[i], A.out + i,
-             A.tree + A.tree_off[i], A.tickets + A.tk_off[i]);
+    run_node(sm, uniform_ptr(static_cast<const uint8_t*>(A.ptrs[i])), uniform(A.sizes[i]), item - uniform(A.node_off[i]),
+             A.out + i, A.tree + uniform(A.tree_off[i]), A.tickets + uniform(A.tk_off[i]));
     return;
   }
   const uint64_t q0 = (item - n_node) * few;
@@ -1232,12 +1236,14 @@ __device__ __forceinline__ void run_few(const BatchArgs& A, Smem<kSlabOne>& sm, 
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void digest_tree_kernel(BatchArgs A) {
   __shared__ Smem<kSlabOne> sm;
   const DigestCtl* c = A.ctl;
-  if (c->overflow) return;
-  if (c->few) {
-    run_few(A, sm, c->few, c->n_node_items, c->n_small);
+  const uint64_t form = c->form;
+  uint64_t n_node = c->n_node_items, n_med = c->n_med;
+  asm volatile("" : "+s"(n_node), "+s"(n_med));  // read with the form, not after it
+  if (form == kPlanOverflow) return;
+  if (form) {
+    run_few(A, sm, (uint32_t)form, n_node, c->n_small);
     return;
   }
-  const uint64_t n_node = c->n_node_items;
   const int lane = threadIdx.x & 63;
   const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
   const uint64_t nwaves = (uint64_t)gridDim.x * kWaves;
@@ -1269,7 +1275,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     }
   }
   // a level-2 node whose only child is a buffer's last node, hashed as a medium node
-  const uint64_t n_med = c->n_med;
   const uint64_t mper = min<uint64_t>(64, ceil_div(n_med, nwaves));
   for (uint64_t base = wave * mper; base < n_med; base += nwaves * mper) {
     const uint64_t j = base + lane;

@@ -41,10 +41,13 @@ struct DigestCtl {
   uint64_t tree_total;    // tree scratch slots needed
   uint64_t tk_total;      // ticket slots needed
   uint64_t n_med;         // level-1 nodes small enough for one wavefront
+  // kPlanOverflow when the plan did not fit the workspace; else, for a plan of at
+  // most one item per workgroup, how many small buffers go into a group; else 0
+  // (one word: every launch after the plan waits for it first)
+  uint64_t form;
   uint32_t head;          // work-queue head
-  uint32_t overflow;      // 1 when the plan did not fit the workspace
-  uint32_t few;           // nonzero: an item per workgroup at most, with this many small buffers in a group
 };
+constexpr uint64_t kPlanOverflow = 1ull << 32;
 
 struct Workspace {
   int device = -1;
