@@ -389,6 +389,11 @@ __device__ __forceinline__ uint32_t near_hash(uint64_t a, uint64_t b) {
 constexpr int kSpan = 8;                      // rounds of 64 records
 constexpr uint32_t kSpanRecs = kSpan * 64;
 constexpr uint32_t kSpanHeads = 64;
+// Up to this many kernels in a round of 64 records are taken one after another,
+// more by device (with every second record a kernel, 2 million of them: 394 us
+// one after another, 295 by device; kernels only 441 and 294. A trace with 4 of
+// 64 takes the short way.)
+constexpr int kFewKernels = 8;
 constexpr uint32_t kNoNode = 0xFFFFFFFFu;
 constexpr uint32_t kHasPred = 1u << 31;
 struct SpanLds {
@@ -400,6 +405,19 @@ struct SpanLds {
   uint32_t dev[kEp];
 };
 static_assert(kSpanHeads == 64 && kSpan <= 10 && kWaveElems % kSpanRecs == 0, "a head per lane, three bits per round, ten of a record of the span");
+
+// The maximum over the lanes below this one, 0 in the first.
+__device__ __forceinline__ uint64_t wave_max_below(uint64_t x) {
+  const int lane = threadIdx.x & 63;
+  x = __shfl_up(x, 1, 64);
+  if (lane == 0) x = 0;
+#pragma unroll 1  // (unrolled its callers spill)
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x = max(x, y);
+  }
+  return x;
+}
 
 // One block per tile of kTile records; wavefront w takes the 512 consecutive
 // records [tile*kTile + w*512, ...), a span, in 8 rounds of 64 and also
@@ -505,11 +523,23 @@ __global__ __launch_bounds__(kClassT, 6) void classify_kernel(const odp_event* _
     uint32_t runs = copy && L.dev[dc] != 0 && s_kmax[w][dc] >= ts;
     const uint64_t kernels = __ballot(c == C_KERNEL);
     if (kernels) {
-      for (uint64_t m = kernels; m; m &= m - 1) {
-        const int kl = __builtin_ctzll(m);
-        const uint32_t kd = lane32(dc, kl);
-        const uint64_t kend = lane64(end, kl);
-        runs |= copy && lane > kl && dc == kd && kend >= ts;
+      if (__ballot(copy)) {
+        if (__popcll(kernels) <= kFewKernels) {
+          for (uint64_t m = kernels; m; m &= m - 1) {
+            const int kl = __builtin_ctzll(m);
+            const uint32_t kd = lane32(dc, kl);
+            const uint64_t kend = lane64(end, kl);
+            runs |= copy && lane > kl && dc == kd && kend >= ts;
+          }
+        } else {  // by device
+          for (uint64_t m = kernels; m;) {
+            const uint32_t kd = lane32(dc, __builtin_ctzll(m));
+            const uint64_t on = __ballot(c == C_KERNEL && dc == kd);
+            m &= ~on;
+            const uint64_t latest = wave_max_below((on >> lane) & 1 ? end : 0ull);
+            runs |= copy && dc == kd && (on & ~above & ~(1ull << lane)) != 0 && latest >= ts;
+          }
+        }
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       if (c == C_KERNEL) {
@@ -545,12 +575,16 @@ __global__ __launch_bounds__(kClassT, 6) void classify_kernel(const odp_event* _
     // the next kernel on the receiving device
     uint32_t nk = copy ? L.dev[dc] : kNoNode;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    for (uint64_t m = __ballot(c == C_KERNEL); m;) {
-      const int kl = 63 - __builtin_clzll(m);
-      m &= ~(1ull << kl);
-      const uint32_t kd = lane32(dc, kl), kk = lane32(g, kl) << 10 | (uint32_t)(r * 64 + kl);
-      if (copy && dc == kd && lane < kl) nk = kk;
-      if (lane == 0) L.dev[kd] = kk;
+    for (uint64_t m = __ballot(c == C_KERNEL); m;) {  // by device
+      const int k0 = __builtin_ctzll(m);
+      const uint32_t kd = lane32(dc, k0);
+      const uint64_t on = __ballot(c == C_KERNEL && dc == kd);
+      m &= ~on;
+      if (copy && dc == kd && (on & above)) {
+        const int kl = __builtin_ctzll(on & above);
+        nk = (g_after + (uint32_t)__popcll(lm >> kl >> 1)) << 10 | (uint32_t)(r * 64 + kl);
+      }
+      if (lane == 0) L.dev[kd] = (g_after + (uint32_t)__popcll(lm >> k0 >> 1)) << 10 | (uint32_t)(r * 64 + k0);
     }
     const unsigned long long addr = L.addr[node];
     const uint32_t bucket = near_hash(addr, code) % kSpanHeads;
@@ -935,13 +969,25 @@ __device__ void subset_scatter_body(const odp_event* __restrict__ ev, const uint
     unsigned long long km = (is_ut || is_ad) ? s_km[w][dc] : 0ull;
     if (bk) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      for (uint64_t m = bk; m; m &= m - 1) {  // this round's kernels, one after another
-        const int kl = __builtin_ctzll(m);
-        const uint32_t d = lane32(dc, kl);
-        const unsigned long long te = lane64(kend, kl);
-        const uint32_t on = dc == d && lane > kl;
-        kc += on;
-        km = on ? max(km, te) : km;
+      if (__popcll(bk) <= kFewKernels) {
+        for (uint64_t m = bk; m; m &= m - 1) {  // this round's kernels, one after another
+          const int kl = __builtin_ctzll(m);
+          const uint32_t d = lane32(dc, kl);
+          const unsigned long long te = lane64(kend, kl);
+          const uint32_t on = dc == d && lane > kl;
+          kc += on;
+          km = on ? max(km, te) : km;
+        }
+      } else {  // by device
+        for (uint64_t m = bk; m;) {
+          const uint32_t d = lane32(dc, __builtin_ctzll(m));
+          const uint64_t on = __ballot(is_k && dc == d);
+          m &= ~on;
+          if (dc == d) kc += (uint32_t)__popcll(on & lt);
+          if (!__ballot((is_ut || is_ad) && dc == d)) continue;
+          const unsigned long long latest = wave_max_below((on >> lane) & 1 ? kend : 0ull);
+          if (dc == d) km = max(km, latest);
+        }
       }
       if (is_k) {
         atomicAdd(&s_kc[w][dc], 1u);

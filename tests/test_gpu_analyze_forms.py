@@ -298,3 +298,13 @@ def test_sorted_logs_far_kernels(odp, every, places):
     ev["t_end"] = ev["t_start"] + rng.integers(0, 2, size=n)
     ev["bytes"] = 64
     check(odp, ev)
+
+
+@pytest.mark.parametrize("share", [7, 8, 9, 33, 64])
+@pytest.mark.parametrize("devices", [1, 10])
+def test_sorted_logs_many_kernels(odp, share, devices):
+    """Rounds of 64 records with few and many kernels among the copies, some of
+    them still running at later copies."""
+    n = 262_145 + 700
+    ev = random_log(share, n, devices=devices, digests=n, places=30, kernels=share / 64, allocs=0.1, long_kernels=share == 9)
+    check(odp, ev)
