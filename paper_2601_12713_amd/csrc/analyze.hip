@@ -389,6 +389,7 @@ __device__ __forceinline__ uint32_t near_hash(uint64_t a, uint64_t b) {
 constexpr int kSpan = 8;                      // rounds of 64 records
 constexpr uint32_t kSpanRecs = kSpan * 64;
 constexpr uint32_t kSpanHeads = 64;
+constexpr uint32_t kSpanNear = 2;
 // Up to this many kernels in a round of 64 records are taken one after another,
 // more by device (with every second record a kernel, 2 million of them: 394 us
 // one after another, 295 by device; kernels only 441 and 294. A trace with 4 of
@@ -406,6 +407,13 @@ struct SpanLds {
 };
 static_assert(kSpanHeads == 64 && kSpan <= 10 && kWaveElems % kSpanRecs == 0, "a head per lane, three bits per round, ten of a record of the span");
 
+// The value of the next (previous) lane, 0 in the last (first).
+__device__ __forceinline__ uint32_t wave_shl1(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130, 0xF, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_shr1(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, false);
+}
 // The maximum over the lanes below this one, 0 in the first.
 __device__ __forceinline__ uint64_t wave_max_below(uint64_t x) {
   const int lane = threadIdx.x & 63;
@@ -587,8 +595,23 @@ __global__ __launch_bounds__(kClassT, 6) void classify_kernel(const odp_event* _
       if (lane == 0) L.dev[kd] = (g_after + (uint32_t)__popcll(lm >> k0 >> 1)) << 10 | (uint32_t)(r * 64 + k0);
     }
     const unsigned long long addr = L.addr[node];
-    const uint32_t bucket = near_hash(addr, code) % kSpanHeads;
-    if (copy) {
+    const uint32_t hash = near_hash(addr, code), bucket = hash % kSpanHeads;
+    // The next copy of the place within kSpanNear lanes is found by lane moves, and
+    // a copy that follows one so closely joins no bucket: nobody else is looking
+    // for it. (A place copied to again and again had a chain of all its copies: 2
+    // million copies to one place 411 us, and 279 so; two places 330 and 282. Three
+    // and more take 290 either way; looking 4 lanes far cost the trace 1%.)
+    const uint32_t mark = copy ? hash | 1u : 0u;
+    uint32_t after = mark, before = mark, succ = 0, pred = 0;
+#pragma unroll
+    for (uint32_t d = 1; d <= kSpanNear; ++d) {
+      after = wave_shl1(after);
+      before = wave_shr1(before);
+      if (copy && succ == 0 && after == mark && L.addr[node + d] == addr && L.rec[node + d] >> 20 == code) succ = d;
+      if (copy && pred == 0 && before == mark && L.addr[node - d] == addr && L.rec[node - d] >> 20 == code) pred = d;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (copy && pred == 0) {
       const uint32_t old = atomicExch(&L.head[bucket], node);
       L.rec[node] = (old == kNoNode ? node : old) | g << 10 | code << 20;
     }
@@ -597,7 +620,11 @@ __global__ __launch_bounds__(kClassT, 6) void classify_kernel(const odp_event* _
     // of a round come in any order, rounds in order; results stay integers.
     const uint32_t limit = nk == kNoNode ? kSpanRecs : nk & 1023;
     const bool open = copy && !((used >> r) & 1);
-    uint32_t best = limit, best_g = 0, cur = open ? L.head[bucket] : kNoNode;
+    uint32_t best = limit, best_g = 0, cur = open && succ == 0 ? L.head[bucket] : kNoNode;
+    if (open && succ != 0 && node + succ < limit) {
+      best = node + succ;
+      best_g = g_after + (uint32_t)__popcll(lm >> (lane + succ) >> 1);
+    }
     while (__ballot(cur != kNoNode)) {
       if (cur != kNoNode) {
         const uint32_t x = L.rec[cur];

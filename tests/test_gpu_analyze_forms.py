@@ -308,3 +308,24 @@ def test_sorted_logs_many_kernels(odp, share, devices):
     n = 262_145 + 700
     ev = random_log(share, n, devices=devices, digests=n, places=30, kernels=share / 64, allocs=0.1, long_kernels=share == 9)
     check(odp, ev)
+
+
+@pytest.mark.parametrize("places", [1, 2, 3, 4, 7])
+@pytest.mark.parametrize("kernels", [0.0, 0.05, 0.4])
+def test_sorted_logs_near_copies(odp, places, kernels):
+    """Copies of a few places in turn or at random: the next copy one, two or more
+    lanes on, in the next round, and across the span; places of equal hash bits."""
+    n = 262_145 + 700
+    rng = np.random.default_rng(places)
+    for order in ("turn", "random"):
+        ev = W.empty_events(n)
+        ev["op"] = np.where(rng.random(n) < kernels, W.KERNEL, np.where(rng.random(n) < 0.1, W.D2H, W.H2D))
+        d2h = ev["op"] == W.D2H
+        ev["src_dev"], ev["dst_dev"] = np.where(d2h, 0, -1), np.where(d2h, -1, rng.integers(0, 2, size=n))
+        place = np.arange(n) % places if order == "turn" else rng.integers(0, places, size=n)
+        ev["src_addr"] = W.HOST_BASE + (place.astype(np.uint64) << np.uint64(12))
+        ev["digest"] = np.arange(n)
+        ev["t_start"] = np.cumsum(rng.integers(0, 3, size=n)) + 10
+        ev["t_end"] = ev["t_start"] + rng.integers(0, 6, size=n)
+        ev["bytes"] = 64
+        check(odp, ev)
