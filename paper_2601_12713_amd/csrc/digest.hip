@@ -155,21 +155,26 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_rsrc(const uint8_t* base)
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), (short)0, -1, 0x00020000);
 }
 
+__device__ __forceinline__ bool on_line(const uint8_t* p) { return (reinterpret_cast<uintptr_t>(p) & 127) == 0; }
+
 // Loads of one step. Leaves that start on a 128-byte line are streamed past the
 // caches: no step touches another's lines. Otherwise the last line of each
 // row's step is the first of its next one, and streamed it is fetched from
 // memory twice (1.5 times the bytes with 256-byte steps), so these loads go
 // through the L2. 2,000 sections of fp64 arrays (2.2 GB): 521 us streamed, 437
 // cached; the same buffers on line boundaries: 412 streamed, 444 cached. (Only
-// the second 128 bytes of the step cached: 449.)
-template <int NL>
+// the second 128 bytes of the step cached: 449.) The per-buffer kernel chooses
+// once for a node's rows: chosen at each step, a launch of 64 KiB took 6.8 us
+// instead of 6.6, one of 64 MiB 17.2 instead of 17.0.
+enum Lines { kEither, kOnLine, kOffLine };
+template <int NL, Lines LINES>
 __device__ __forceinline__ void fast_load(u32x4 (&R)[NL], const uint8_t* base, uint32_t step_off) {
   constexpr int kStream = 2;  // nontemporal
   const int lane = threadIdx.x & 63;
   const __amdgpu_buffer_rsrc_t rs = wave_rsrc(base);
   const uint32_t o = (uint32_t)(lane >> 3) * kLeaf + (uint32_t)(lane & 7) * 16;
   auto voff = [&](int k) { return (int)(o + (uint32_t)(8 * (k & 1)) * kLeaf + (uint32_t)(k >> 1) * 128); };
-  if ((reinterpret_cast<uintptr_t>(base) & 127) == 0) {
+  if (LINES == kOnLine || (LINES == kEither && on_line(base))) {
 #pragma unroll
     for (int k = 0; k < NL; ++k)
       R[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff(k), (int)step_off, kStream));
@@ -205,7 +210,7 @@ __device__ __forceinline__ uint64_t fast_fold(uint64_t acc, const uint8_t* slab)
   return acc;
 }
 
-template <int NL>
+template <int NL, Lines LINES>
 __device__ __forceinline__ uint64_t hash_wave_leaves_pipe(const uint8_t* leaf_base, const uint8_t* next, bool& pre,
                                                           u32x4 (&RA)[NL], u32x4 (&RB)[NL], uint8_t* slab) {
   constexpr int kSlab = NL * 64;  // NL 128-bit loads per lane cover one step
@@ -213,20 +218,20 @@ __device__ __forceinline__ uint64_t hash_wave_leaves_pipe(const uint8_t* leaf_ba
   const int lane = threadIdx.x & 63;
   uint64_t acc = xx_acc_init(0, lane & 3);
   if (!pre) {
-    fast_load(RA, leaf_base, 0);
-    fast_load(RB, leaf_base, kSlab);
+    fast_load<NL, LINES>(RA, leaf_base, 0);
+    fast_load<NL, LINES>(RB, leaf_base, kSlab);
   }
 #pragma unroll 1
   for (uint32_t s = 0; s < NS; s += 2) {
     fast_stage(RA, slab);
-    if (s + 2 < NS) fast_load(RA, leaf_base, (s + 2) * kSlab);
-    else if (next) fast_load(RA, next, 0);
+    if (s + 2 < NS) fast_load<NL, LINES>(RA, leaf_base, (s + 2) * kSlab);
+    else if (next) fast_load<NL, LINES>(RA, next, 0);
     wave_fence();
     acc = fast_fold<kSlab>(acc, slab);
     wave_fence();
     fast_stage(RB, slab);
-    if (s + 3 < NS) fast_load(RB, leaf_base, (s + 3) * kSlab);
-    else if (next) fast_load(RB, next, kSlab);
+    if (s + 3 < NS) fast_load<NL, LINES>(RB, leaf_base, (s + 3) * kSlab);
+    else if (next) fast_load<NL, LINES>(RB, next, kSlab);
     wave_fence();
     acc = fast_fold<kSlab>(acc, slab);
     wave_fence();
@@ -568,7 +573,9 @@ __device__ __forceinline__ void run_node(Smem<kSlabOne>& sm, const uint8_t* buf,
     constexpr int NL = kSlabOne / 64;
     u32x4 RA[NL], RB[NL];
     bool pre = false;
-    h = hash_wave_leaves_pipe<NL>(uniform_ptr(buf + wfirst * kLeaf), nullptr, pre, RA, RB, sm.slab[w]);
+    const uint8_t* leaves = uniform_ptr(buf + wfirst * kLeaf);
+    h = on_line(leaves) ? hash_wave_leaves_pipe<NL, kOnLine>(leaves, nullptr, pre, RA, RB, sm.slab[w])
+                        : hash_wave_leaves_pipe<NL, kOffLine>(leaves, nullptr, pre, RA, RB, sm.slab[w]);
   } else {
     RowDesc* rows = sm.rows + w * kRowsPerWave;
     if ((t & 63) < kRowsPerWave) {
@@ -1104,7 +1111,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     uint64_t h;
     if (mine) {
       const uint8_t* next = nxt < n_node ? fast_rows(uniform_ptr(rn.base), uniform(rn.len), w) : nullptr;
-      h = hash_wave_leaves_pipe<NL>(mine, next, pre, RA, RB, sm.slab[w]);
+      h = hash_wave_leaves_pipe<NL, kEither>(mine, next, pre, RA, RB, sm.slab[w]);
     } else {
       // Nothing is in flight for this path (pre is false after it): constant
       // stage registers are rematerialised instead of kept across it.
