@@ -574,8 +574,8 @@ __device__ __forceinline__ void run_node(Smem<kSlabOne>& sm, const uint8_t* buf,
     u32x4 RA[NL], RB[NL];
     bool pre = false;
     const uint8_t* leaves = uniform_ptr(buf + wfirst * kLeaf);
-    h = on_line(leaves) ? hash_wave_leaves_pipe<NL, kOnLine>(leaves, nullptr, pre, RA, RB, sm.slab[w])
-                        : hash_wave_leaves_pipe<NL, kOffLine>(leaves, nullptr, pre, RA, RB, sm.slab[w]);
+    if (__builtin_expect(on_line(leaves), 1)) h = hash_wave_leaves_pipe<NL, kOnLine>(leaves, nullptr, pre, RA, RB, sm.slab[w]);
+    else h = hash_wave_leaves_pipe<NL, kOffLine>(leaves, nullptr, pre, RA, RB, sm.slab[w]);
   } else {
     RowDesc* rows = sm.rows + w * kRowsPerWave;
     if ((t & 63) < kRowsPerWave) {
