@@ -157,10 +157,12 @@ __device__ __forceinline__ uint64_t tx_key(int s, int d) { return kMark | ((uint
 // 960 us, almost all of the kernel; the kernel takes 109 now. Groups are the slots of an LDS
 // hash table (exact: a slot's owner has the same key), and two stable 6-bit
 // passes order the records by slot. Ticks of at most kWalkTick records are
-// their own only group, in a kernel of their own: there the walk is shorter than
-// the sort (kernel, median over ticks: 10 records 23.9 against 24.8 us, 12: 25.1
-// and 24.9, 16: 31.1 and 28.0, 64: 77 and 38).
-constexpr uint32_t kWalkTick = 12;
+// their own only group, in a kernel of their own: the walk is shorter than the
+// sort there, also where one group holds them all and the sort gains nothing
+// (kernel, median over ticks, walked and grouped; digests all different: 12
+// records 24.7 and 24.9 us, 32: 47 and 32; one digest: 16: 24.9 and 32.4, 32: 38
+// and 44.5; longer ticks of one digest gain too, 64: 82 walked and 67 grouped).
+constexpr uint32_t kWalkTick = 32;
 constexpr uint32_t kWalkThreads = 256;
 constexpr uint32_t kGroupSlots = 2 * kTickMax;
 struct GroupLds {

@@ -57,7 +57,7 @@ def test_drain_waits_for_the_default_stream(odp):
     check_known(known.cpu().numpy(), fo, ev)
 
 
-@pytest.mark.parametrize("max_tick", [1, 2, 11, 12, 13])
+@pytest.mark.parametrize("max_tick", [1, 2, 13, 31, 32, 33])
 @pytest.mark.parametrize("kind", ["few keys", "kernels", "rejected", "waiting windows"])
 def test_short_ticks(odp, max_tick, kind):
     """Ticks on both sides of the length up to which one wavefront takes all
