@@ -363,7 +363,9 @@ int odp_version(void);
 /* Text of the calling thread's last error ("" if none). Owned by the library. */
 const char* odp_last_error_string(void);
 
-/* Pre-size the workspace of the current device for `stream`: up to max_buffers
+/* Pre-size the workspace of the current device for `stream` (about 320 bytes
+ * per record of max_events, and up to 65 MB of tables for logs of at most
+ * 262,144 records): up to max_buffers
  * buffers totalling max_total_bytes for odp_digest_buffers, and up to
  * max_events records for odp_analyze_trace (which also creates the
  * workspace's side stream and the two events that fork and join it).
@@ -385,7 +387,9 @@ int odp_device_status(void);
 /* Launch parameters of the batched digest. They change speed, never results. */
 typedef struct odp_tuning {
   uint32_t blocks_per_cu;   /* persistent workgroups per compute unit, 1..8 */
-  uint32_t use_graph;       /* 1: replay the work plan + digest launch as a hipGraph */
+  uint32_t use_graph;       /* 1: a call with the arguments of the one before it replays the
+                               work plan + digest launches as a hipGraph (the second such call
+                               builds it); 0: always launched */
   uint32_t split_bytes;     /* level-1 nodes of at most this many bytes (0 or 4096..65536) are
                                hashed and combined by one wavefront, four per work item;
                                larger nodes take a whole workgroup */

@@ -3734,9 +3734,8 @@ void analyze_release(Workspace* ws) {
 // thread per record, each rule written out as its definition. The records sit
 // in LDS, compacted into per-class lists (transfers, ALLOC/DELETE, kernels);
 // a thread walks the list its rule needs in a loop that is the same for the
-// whole wavefront, so every LDS read is a broadcast. One launch instead of the
-// sort and scan pipeline (two dozen launches on two streams) that longer logs
-// take.
+// whole wavefront, so every LDS read is a broadcast. One launch, where longer
+// logs take 2 (walks), 13 (hash tables) or 76 (sorts).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kTinyMax = 512;
 
@@ -4690,9 +4689,9 @@ extern "C" int odp_analyze_trace(const odp_event* events, size_t n, uint8_t* out
   }
   if (n <= kWalkMax) return enqueue_walks(ws, events, n, out_flags, out_report, stream);
   if (capturing) return enqueue_analysis(ws, events, n, out_flags, out_report, stream);
-  // The sequence is some fifty launches on two streams; a call repeated with
-  // the same arguments replays it as one graph instead (the first repeat
-  // captures it), so the host's launch cost leaves the device's time.
+  // The sequence is 13 or 76 launches on two streams; a call repeated with the
+  // same arguments replays it as one graph instead (the first repeat captures
+  // it), so the host's launch cost leaves the device's time.
   const bool same = ws->ag_ev == events && ws->ag_n == n && ws->ag_flags == out_flags && ws->ag_rep == out_report;
   if (!same) {
     if (ws->a_graph) {

@@ -4,9 +4,13 @@
 // bytes: the 79 launches of the pipeline for longer logs took 290 us for 100,000
 // records, whose bytes take 2. Random accesses to tables that stay in the caches
 // are cheap here (25 G compare-and-swaps a second), so the groups come from hash
-// tables, and 13 launches remain, the longest chain 9: 113 us. (At 10.7 million
-// records the same tables would cost 0.4 ms per access to each record, more
-// than the sort passes; 262,144 records, the last here: 150 us against 330.)
+// tables, and 13 launches remain, the longest chain 9 (11 with Algorithm 2's
+// pairs): 107 us. Where a key is shared by many records, their updates meet in
+// few words, so lanes or chunks of one key go to the tables once.
+// The last length here is what the fields below hold (owners, chunks and groups
+// in 32 bits), not where the sorts become faster: 262,144 records take 130 us
+// here, 262,145 take 282 by sorts. (At 10.7 million records the tables' atomics
+// would cost 0.4 ms per access to each record, more than the sort passes.)
 //
 //   clear     the digest table, the call's counters
 //   classify  as in the pipeline; each transfer also finds its digest's slot in

@@ -1496,8 +1496,12 @@ extern "C" int odp_digest_buffers(const void* const* ptrs, const uint64_t* sizes
   const Tuning& tn = tuning();
   if (!tn.use_graph || capturing) return enqueue_batched(space_of(ws), ptrs, sizes, n, out, stream);
   // A call with other arguments than the last one launches directly; the first
-  // repeat captures the launches and every further one replays them. (Building
-  // a graph for each change cost 120 us a call against 4 launches' 10.)
+  // repeat captures the launches and every further one replays them, as use_graph
+  // asks for. A graph for each change cost about 100 us a call. Replays keep the
+  // host free but are not faster on the device than the launches: 64 buffers
+  // 22.1 us replayed and 18.0 launched, 2,000 large ones 229.6 and 225.5; two
+  // calls with each argument set 60 us a call, for the build. A caller whose
+  // calls do not repeat many times sets use_graph to 0.
   const uint32_t grid = cu_count(ws->device) * tn.blocks_per_cu;
   if (!(ws->g_ptrs == ptrs && ws->g_sizes == sizes && ws->g_out == out && ws->g_n == n && ws->g_grid == grid &&
         ws->g_split == tn.split_bytes && ws->g_chunk == tn.chunk_nodes)) {

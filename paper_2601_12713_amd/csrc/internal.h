@@ -56,7 +56,7 @@ struct Workspace {
   DevBuf node_off, tree_off, tk_off, small_list, blk, ctl, item_buf, item_rec, med_rec, tree, tickets;
   size_t cap_buffers = 0;
   uint64_t cap_items = 0, cap_tree = 0, cap_tk = 0;
-  // plain digest (one buffer at a time)
+  // plain digest (tree slots and tickets of one launch: a buffer, or several)
   DevBuf p_tree, p_tickets;
   uint64_t p_cap_tree = 0, p_cap_tk = 0;
   // analysis: the allocation path runs on a second stream of this workspace,

@@ -830,9 +830,9 @@ static int launch_tick(odp_server* s, int b, uint32_t m, uint64_t bytes, bool id
   ODP_HIP(hipMemcpyAsync(s->d_stage[b], s->h_stage[b], m * kStageBytes, hipMemcpyHostToDevice, ds));
   const StageView hv = stage_view(s->h_stage[b], m), dv = stage_view(s->d_stage[b], m);
   // Tick sizes change every tick: direct launches rather than a captured
-  // graph. A tick of up to kPerBufferTick requests takes per-buffer launches
-  // (one kernel each instead of the plan, the persistent digest and the tree
-  // kernels: fewer launches and a shorter chain on the device).
+  // graph. A tick of up to kPerBufferTick requests takes the form for host
+  // descriptors (one launch for all of them instead of the plan, the persistent
+  // digest and the tree kernels).
   int e = s->cfg.mode == ODP_SERVER_PLAIN || m <= kPerBufferTick
               ? odp_digest_buffers_plain(reinterpret_cast<const void* const*>(hv.ptr), hv.size, m, s->d_dig[b], ds)
               : digest_batched_direct(reinterpret_cast<const void* const*>(dv.ptr), dv.size, m, s->d_dig[b], ds, bytes);
