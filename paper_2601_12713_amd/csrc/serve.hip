@@ -246,8 +246,9 @@ __device__ void group_tick(GroupLds& G, GroupList& L, const uint64_t* key, uint3
 // GROUPED: a tick of up to kTickMax records by groups, a thread each. Else one of
 // up to kWalkTick: all records in the first wavefront, which keeps what it
 // counts over them in registers, and LDS for them only; the other wavefronts
-// are there for the waiting windows. (One kernel for both took 11.6 to 15.6 us
-// for 1 to 4 records, with the masks, lists and barriers of 1,024 threads.)
+// are there for the waiting windows. (One kernel for both, with the masks, lists
+// and barriers of 1,024 threads, took 12.2 us for 1 record and 17.2 for 4; this
+// one takes 10.4 and 15.1.)
 template <bool GROUPED>
 __global__ __launch_bounds__(GROUPED ? kTickMax : kWalkThreads) void serve_tick_kernel(TickArgs A) {
   constexpr uint32_t NT = GROUPED ? kTickMax : kWalkThreads, MAX = GROUPED ? kTickMax : 64, kWords = MAX / 64;
